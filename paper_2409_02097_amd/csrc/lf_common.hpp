@@ -199,7 +199,12 @@ struct Layout {
   long long batch, head;   // strides between batches / heads
   int row;                 // stride between consecutive tokens of one head
   int H;                   // heads per batch
-  LF_DEV long long slice(long long bh) const { return (bh / H) * batch + (bh % H) * head; }
+  // (bh < 2^16 always: divided in 32 bits -- a 64-bit division by a variable is 130 dependent scalar instructions at
+  // the start of every workgroup)
+  LF_DEV long long slice(long long bh) const {
+    const unsigned b = (unsigned)bh / (unsigned)H, h = (unsigned)bh - b * (unsigned)H;
+    return (long long)b * batch + (long long)h * head;
+  }
 };
 
 // Heads [first, first + count) of every batch: grid row y of a per-head kernel works on
