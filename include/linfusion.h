@@ -39,8 +39,8 @@
  *     two before it becomes a 16-bit matrix-core operand.  Operands are rounded once to fp16 for fp16 tensors
  *     (relative 2^-12 each); carried as two bf16 levels (about 16 bits) for bf16 tensors, except in the apply
  *     kernel of the widths above 80, which multiplies bf16 tensors as fp16 operands after scaling every query
- *     row into fp16's range (the factor cancels in Eq. 5's ratio); fp32 tensors never pass through 16-bit
- *     products of fewer than 24 bits.  The result is rounded once, to nearest even, to the tensors' type.
+ *     row into fp16's range (the factor cancels in Eq. 5's ratio); fp32 tensors are multiplied on the fp32
+ *     instruction or as three bf16 terms per value (24 bits, six products).  The result is rounded once, to nearest even, to the tensors' type.
  */
 #ifndef LINFUSION_H_
 #define LINFUSION_H_
@@ -187,14 +187,13 @@ int linfusion_attn_fwd_profile(const void* q, const void* k, const void* v, void
  *                   16-byte aligned; must not overlap dq, dk, dv or `workspace`.
  *   q, k, v, dout   DEVICE pointers, contiguous [B, H, N, d].  fp16, bf16: d in {8, ..., 64 step 8, 80}; fp16 also
  *                   d in {96, 128, 160} (bf16 there -> LINFUSION_ERR_UNSUPPORTED); fp32: d in {8, ..., 64 step 8}.
- *                   fp16 above 80 and fp32 run a pass composed of the forward's kernels with three temporaries of
- *                   the tensors' type in the workspace, sixteen launches: there so that every level of the UNet
- *                   and every type has a gradient, not for speed.
+ *                   fp16 above 80 runs a pass composed of the forward's kernels with three fp16 temporaries in the
+ *                   workspace, sixteen launches: there so that every level of the UNet has a gradient, not for speed.
  *   dq, dk, dv      DEVICE pointers, same shape and type; must not overlap any input or each other.
  *   flags           LINFUSION_FLAG_NONE or LINFUSION_FLAG_UNNORMALIZED (anything else -> ERR_INVALID).
  *   workspace       DEVICE scratch of at least linfusion_attn_bwd_workspace_bytes(...) bytes, 16-byte
  *                   aligned, caller-owned, contents undefined before and after.
- * Enqueues six kernels (four when `state` is given) on `stream`; never allocates, never synchronises.  Results are run-to-run identical.
+ * Enqueues up to six kernels (four when `state` is given; fp16 above 80: see there) on `stream`; never allocates, never synchronises.  Results are run-to-run identical.
  */
 int linfusion_attn_bwd(const void* q, const void* k, const void* v, const void* dout, const float* state,
                        void* dq, void* dk, void* dv,

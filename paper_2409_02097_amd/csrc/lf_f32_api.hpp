@@ -1,5 +1,5 @@
-// Host-side interface to the fp32 kernels of linfusion.hip for the library's other translation units: the state
-// reduction (+ combine) and the apply step by themselves (the fp32 backward pass is composed of them).
+// Host-side interface between the translation units: the fp32 three-kernel path and backward pass (linfusion_f32.hip),
+// the launch plan they take from the forward planner (linfusion.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -11,35 +11,41 @@ namespace lf32 {
 struct Plan32 {
   int splits, blk_reduce, apply_wgs, blk_apply;
 };
-// LINFUSION_OK, or the forward plan's error code; `partial_bytes`: what the partial states take
+// LINFUSION_OK, or the forward plan's error code; `partial_bytes`: what the partial states of one pass take
 int launch_plan32(int B, int H, long long N, int d, Plan32* p, size_t* partial_bytes);
 
-// state[bh] = {S = sum_t phi(k_t)^T v_t, z = sum_t phi(k_t)}, fp32 [d*d + d]
-struct Reduce32Args {
-  const void *k, *v;
-  int B, H;
-  long long N;
+// out = mixer(q, k, v); with out == null only the state.  The head states are left in `state` either way.
+struct Fwd32Args {
+  const void *q, *k, *v;
+  void* out;
+  long long BH, N;
   int d, fm;
-  lf::Layout lk, lv;          // the two tensors may be laid out differently
+  float eps;
+  bool unnorm;
+  lf::Layout lq, lkv, lo;
   float *partials, *state;    // [B*H][splits][d*d + d] and [B*H][d*d + d]
   Plan32 plan;
   hipStream_t st;
+  hipEvent_t* ev;             // null, or four events around the kernels
 };
-// out_t = phi(q_t) S / (phi(q_t) z + eps)   (unnorm: phi(q_t) S)   from a given state
-struct Apply32Args {
-  const void* q;
-  void* out;
+int run_fwd32(const Fwd32Args& a);
+
+// gradients of q, k, v
+struct Bwd32Args {
+  const float* saved_state;   // the forward state of the same q, k, v, or null: recompute it from k, v
+  const void *q, *k, *v, *g;
+  void *dq, *dk, *dv;
   int B, H;
   long long N;
   int d, fm;
   float eps;
   bool unnorm;
-  lf::Layout lq, lo;
-  const float* state;
-  Plan32 plan;
+  lf::Layout lq, lkv, lg, ldq, ldkv;   // q; k and v; dout; dq; dk and dv
+  unsigned char* ws;                   // bwd32_workspace_bytes
   hipStream_t st;
 };
-int run_reduce32(const Reduce32Args& a);
-int run_apply32(const Apply32Args& a);
+bool bwd32_supported(int d);
+size_t bwd32_workspace_bytes(int B, int H, long long N, int d);   // 0 for unsupported shapes
+int run_bwd32(const Bwd32Args& a);
 
 }  // namespace lf32

@@ -15,7 +15,6 @@
 #include <random>
 
 #include "lf_fused.hpp"
-#include "lf_reduce32s.hpp"
 #include "lf_solo_api.hpp"
 #include "lf_host_api.hpp"
 #include "lf_f32_api.hpp"
@@ -615,38 +614,12 @@ int run16(const Args& a) {
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
 
-// fp32 state reduction of the split path: on the 16-bit matrix cores through three bf16 terms per value
-// (state_reduce32_split), or on the fp32 instruction (state_reduce32).  Measured on MI355X, B=1, H=8, whole step:
-// d = 8: 249 against 942 us at 2^20 tokens, d = 16: 393 / 939, d = 24: 306 / 531 at 2^19, d = 32: 738 / 1138 at
-// 2^20, d = 40: 502 / 632 at 2^19, d = 48: 344 / 355 at 2^18; d = 56: 434 / 422 and d = 64: 495 / 459 the other way
-// (its six 16-bit tiles per wave leave one workgroup per CU there); below about 8192 tokens per head the fp32
-// instruction's shorter prologue wins (d = 40, N = 2048: 24.8 / 20.6 us, N = 8192: 36.7 / 37.2).
-template <int D, int FM>
-int launch_reduce32(const lf::f32x4* K, lf::Layout lk, const lf::f32x4* V, lf::Layout lv, float* partials, long long N,
-                    int splits, int blk, long long BH, hipStream_t st) {
-  using namespace lf;
-  const dim3 g1(splits, (unsigned)BH), b(kThreads);
-  const int mode = env_int("LINFUSION_F32_SPLIT", 1);   // 1 = by shape, 2 = never, 3 = always
-  if (mode == 3 || (mode == 1 && D <= 48 && N >= 8192)) {
-    constexpr int lds = reduce32s_lds_bytes<D>();
-    if (!lfh::allow_lds(state_reduce32_split<D, FM>, lds)) return LINFUSION_ERR_HIP;
-    // the plan counts 16-token tiles; this kernel's are 32 tokens
-    const int blk32 = ((blk / 2 + kWavesPerWG - 1) / kWavesPerWG) * kWavesPerWG;
-    state_reduce32_split<D, FM><<<g1, b, lds, st>>>(K, lk, V, lv, partials, N, blk32 < kWavesPerWG ? kWavesPerWG : blk32);
-  } else {
-    constexpr size_t lds = reduce32_lds_bytes<D>() > 1024 ? reduce32_lds_bytes<D>() : 1024;
-    state_reduce32<D, FM><<<g1, b, lds, st>>>(K, lk, V, lv, partials, N, blk);
-  }
-  return LINFUSION_OK;
-}
-
 template <int D>
 int run32(const Args& a) {
   using namespace lf;
   const Plan& p = *a.p;
   float* partials = reinterpret_cast<float*>(a.ws);
   float* state = a.state_out ? a.state_out : reinterpret_cast<float*>(a.ws + p.ws_partials);
-  constexpr int NE = D * D + D;
   const dim3 blk(kThreads);
   const f32x4* K = (const f32x4*)a.k;
   const f32x4* V = (const f32x4*)a.v;
@@ -654,7 +627,6 @@ int run32(const Args& a) {
   f32x4* O = (f32x4*)a.out;
   hipStream_t st = a.st;
   constexpr size_t ldsf = fused32_lds_bytes<D>();
-  constexpr size_t ldsa = apply32_lds_bytes<D>();
   if (p.path == 1 && a.out && !capturing(a.st)) {
     unsigned long long* sync = reinterpret_cast<unsigned long long*>(a.ws + p.ws_partials + p.ws_state);
     unsigned long long* err = sync + a.BH * 2 * p.fsplits;
@@ -675,23 +647,9 @@ int run32(const Args& a) {
       return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
     }
   }
-  if (a.ev) (void)hipEventRecord(a.ev[0], st);
-#define LF_REDUCE(FM)                                                                                              \
-  if (int rc = launch_reduce32<D, FM>(K, a.lkv, V, a.lkv, partials, a.N, p.splits, p.blk_reduce, a.BH, st)) return rc;
-  LF_SWITCH_FM(LF_REDUCE)
-#undef LF_REDUCE
-  if (a.ev) (void)hipEventRecord(a.ev[1], st);
-  combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)a.BH), dim3(kCombineThreads), 0, st>>>(
-      partials, p.splits, NE, state);
-  if (a.ev) (void)hipEventRecord(a.ev[2], st);
-  if (a.out) {
-    const dim3 g2(p.apply_wgs, (unsigned)a.BH);
-#define LF_APPLY(FM, NORM) apply32<D, FM, NORM><<<g2, blk, ldsa, st>>>(Q, a.lq, O, a.lo, state, a.eps, a.N, p.blk_apply);
-    LF_SWITCH_FM_NORM(LF_APPLY)
-#undef LF_APPLY
-  }
-  if (a.ev) (void)hipEventRecord(a.ev[3], st);
-  return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
+  const lf32::Fwd32Args x{a.q, a.k, a.v, a.out, a.BH, a.N, D, a.fm, a.eps, a.unnorm, a.lq, a.lkv, a.lo, partials, state,
+                          lf32::Plan32{p.splits, p.blk_reduce, p.apply_wgs, p.blk_apply}, st, a.ev};
+  return lf32::run_fwd32(x);
 }
 
 int dispatch(int d, int dtype, const Args& a) {
@@ -916,60 +874,6 @@ int launch_plan32(int B, int H, long long N, int d, Plan32* out, size_t* partial
   *out = Plan32{p.splits, p.blk_reduce, p.apply_wgs, p.blk_apply};
   *partial_bytes = p.ws_partials;
   return LINFUSION_OK;
-}
-
-namespace {
-template <int D>
-int reduce32(const Reduce32Args& a) {
-  using namespace lf;
-  constexpr int NE = D * D + D;
-  const long long BH = (long long)a.B * a.H;
-  const f32x4* K = (const f32x4*)a.k;
-  const f32x4* V = (const f32x4*)a.v;
-  int rc;
-  switch (a.fm) {
-    case 0: rc = launch_reduce32<D, 0>(K, a.lk, V, a.lv, a.partials, a.N, a.plan.splits, a.plan.blk_reduce, BH, a.st); break;
-    case 1: rc = launch_reduce32<D, 1>(K, a.lk, V, a.lv, a.partials, a.N, a.plan.splits, a.plan.blk_reduce, BH, a.st); break;
-    default: rc = launch_reduce32<D, 2>(K, a.lk, V, a.lv, a.partials, a.N, a.plan.splits, a.plan.blk_reduce, BH, a.st); break;
-  }
-  if (rc != LINFUSION_OK) return rc;
-  combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)BH), dim3(kCombineThreads), 0, a.st>>>(
-      a.partials, a.plan.splits, NE, a.state);
-  return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
-}
-
-template <int D>
-int apply32(const Apply32Args& a) {
-  using namespace lf;
-  constexpr size_t ldsa = apply32_lds_bytes<D>();
-  const long long BH = (long long)a.B * a.H;
-  const dim3 g2(a.plan.apply_wgs, (unsigned)BH), blk(kThreads);
-  const f32x4* Q = (const f32x4*)a.q;
-  f32x4* O = (f32x4*)a.out;
-#define LF_APPLY(FM, NORM) \
-  lf::apply32<D, FM, NORM><<<g2, blk, ldsa, a.st>>>(Q, a.lq, O, a.lo, a.state, a.eps, a.N, a.plan.blk_apply);
-  LF_SWITCH_FM_NORM(LF_APPLY)
-#undef LF_APPLY
-  return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
-}
-}  // namespace
-
-int run_reduce32(const Reduce32Args& a) {
-  switch (a.d) {
-#define X(DD) case DD: return reduce32<DD>(a);
-    LF_FOR_D(X)
-#undef X
-  }
-  return LINFUSION_ERR_UNSUPPORTED;
-}
-
-int run_apply32(const Apply32Args& a) {
-  switch (a.d) {
-#define X(DD) case DD: return apply32<DD>(a);
-    LF_FOR_D(X)
-#undef X
-  }
-  return LINFUSION_ERR_UNSUPPORTED;
 }
 
 }  // namespace lf32

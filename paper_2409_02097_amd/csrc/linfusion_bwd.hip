@@ -8,6 +8,7 @@
 #include "lf_backward16.hpp"
 #include "lf_backward16_rows.hpp"
 #include "lf_bwdw_api.hpp"
+#include "lf_f32_api.hpp"
 #include "lf_host_api.hpp"
 
 namespace {
@@ -18,7 +19,7 @@ struct BwdPlan {
   int apply1_wgs, blk_apply1;   // launch shape of the gradient kernels of which one workgroup fills a CU
   int gsplits, gblk_reduce;   // the state-gradient reduction's own launch shape
   int most;                   // partial states per head the workspace has room for
-  bool wide;                  // widths above 80: the composed pass of linfusion_bwdw.hip (its own workspace layout)
+  bool wide;                  // fp16 above 80: the composed pass of linfusion_bwdw.hip (its own workspace layout)
   size_t ne, ws_partials, ws_state, ws_scal, ws_pack, ws_total;
   bool kv_packed;             // dK / dV from operands packed once per head, many short-lived workgroups
   int kvp_wgs, kvp_blk;
@@ -36,10 +37,16 @@ bool bwd_supported_d(int d) { return (d >= 8 && d <= 64 && d % 8 == 0) || d == 8
 int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   if (B <= 0 || H <= 0 || N <= 0 || d <= 0) return LINFUSION_ERR_INVALID;
   if ((long long)B * H > 65535) return LINFUSION_ERR_INVALID;
-  p->wide = lfbw::bwd_wide_supported(d, dtype);   // the composed pass: fp16 above 80, fp32
-  if (dtype != LINFUSION_DTYPE_F16 && dtype != LINFUSION_DTYPE_BF16 && !p->wide) return LINFUSION_ERR_UNSUPPORTED;
+  p->wide = lfbw::bwd_wide_supported(d, dtype);   // the composed pass: fp16 above 80
+  const bool f32 = dtype == LINFUSION_DTYPE_F32 && lf32::bwd32_supported(d);
+  if (dtype != LINFUSION_DTYPE_F16 && dtype != LINFUSION_DTYPE_BF16 && !f32) return LINFUSION_ERR_UNSUPPORTED;
   if (!bwd_supported_d(d) && !p->wide) return LINFUSION_ERR_UNSUPPORTED;
   if (N > (1LL << 40) / d) return LINFUSION_ERR_INVALID;
+  if (f32) {
+    p->ne = (size_t)d * d + d;
+    p->ws_total = lf32::bwd32_workspace_bytes(B, H, N, d);
+    return p->ws_total ? LINFUSION_OK : LINFUSION_ERR_UNSUPPORTED;
+  }
   if (p->wide) {
     p->ne = (size_t)d * d + d;
     p->ws_total = lfbw::bwd_wide_workspace_bytes(B, H, N, d, dtype);
@@ -489,6 +496,12 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* dou
   if (rc != LINFUSION_OK) return rc;
   const int per = 16 / (int)esz;   // elements per 16-byte unit
   auto lay = [&](const long long* s) { return lf::Layout{s[0] / per, s[1] / per, (int)(s[2] / per), H}; };   // 16-byte units
+  if (dtype == LINFUSION_DTYPE_F32) {
+    const lf32::Bwd32Args w{state, q, k, v, dout, dq, dk, dv, B, H, N, d, feature_map, eps,
+                            (flags & LINFUSION_FLAG_UNNORMALIZED) != 0, lay(st5[0]), lay(st5[1]), lay(st5[2]),
+                            lay(st5[3]), lay(st5[4]), (unsigned char*)workspace, (hipStream_t)stream};
+    return lf32::run_bwd32(w);
+  }
   if (p.wide) {
     const lfbw::BwdWideArgs w{state, q, k, v, dout, dq, dk, dv, B, H, N, d, dtype, feature_map, eps,
                               (flags & LINFUSION_FLAG_UNNORMALIZED) != 0, (unsigned char*)workspace,
