@@ -330,6 +330,79 @@ struct ApplyDma {
     eps_s = eps * scales[1];
   }
 
+  // The same operands straight from the head's fp32 state, each wave for itself: for kernels of long-lived workgroups,
+  // where some two hundred loads per lane and workgroup cost less than a launch that packs (2 x 8 x 36503 x 40 bf16
+  // token-major: 61.6 -> 57.0 us per call).  The wave's operands hold every element of S, so the maxima that set the
+  // scales come from the loaded registers.  All loads are issued, from clamped and valid places, before the first use.
+  LF_DEV void load_direct(const float* state, float eps) {
+    const int m = lane & 31, hv = (m >> 2) & 1;
+    float raw[MT2][KS][8];
+#pragma unroll
+    for (int t = 0; t < MT2; ++t) {
+      const int slot = 16 * t + 4 * (m >> 3) + (m & 3);
+      const bool isS = slot < HALF;
+      const float* src = isS ? state + hv * HALF + slot : state + D * DV;
+      const int step = isS ? DV : 1;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const int chunk = kg * KS + s;
+        const int ch0 = (chunk < CPR ? chunk : 0) * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) raw[t][s][j] = src[(ch0 + j) * step];
+      }
+    }
+    float mS = 0.0f, mz = 0.0f;
+#pragma unroll
+    for (int t = 0; t < MT2; ++t) {
+      const bool isS = 16 * t + 4 * (m >> 3) + (m & 3) < HALF;
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {   // (a lane past the channels or the rows holds some other element of S or z)
+          const float x = fabsf(raw[t][s][j]);
+          mS = fmaxf(mS, isS ? x : 0.0f);
+          mz = fmaxf(mz, isS ? 0.0f : x);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      mS = fmaxf(mS, __shfl_xor(mS, o));
+      mz = fmaxf(mz, __shfl_xor(mz, o));
+    }
+    const float aS = pow2_scale_for(mS);
+    const float az = NORM ? pow2_scale_for(mz) : 1.0f;
+    c1 = az / aS;
+    eps_s = eps * az;
+#pragma unroll
+    for (int t = 0; t < MT2; ++t) {
+      const int slot = 16 * t + 4 * (m >> 3) + (m & 3);
+      make_operands_of(t, slot < HALF, NORM && slot == HALF, NORM && slot == HALF + 1, aS, az, raw[t]);
+    }
+  }
+
+  // Output tile t's operands from this lane's raw values: of S (isS), of z (isZ) or of what rounding z leaves (zrem)
+  LF_DEV void make_operands_of(int t, bool isS, bool isZ, bool zrem, float aS, float az, const float (&raw)[KS][8]) {
+    const float sc = isS ? aS : az;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bool used = (kg * KS + s < CPR) && (isS || isZ || zrem);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        float hi2[2], lo2[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float x = used ? raw[s][2 * w + q] * sc : 0.0f;
+          float r0, r1;
+          unpack2<T>(pack2<T>(x, 0.0f), r0, r1);   // x rounded once to 16 bits
+          hi2[q] = zrem ? x - r0 : x;
+          lo2[q] = isS ? x - r0 : 0.0f;            // S' remainder -> lo fragment (bf16 only)
+        }
+        A[0][t][s][w] = pack2<T>(hi2[0], hi2[1]);
+        if constexpr (NS == 2) A[1][t][s][w] = pack2<T>(lo2[0], lo2[1]);
+      }
+    }
+  }
+
   // Writes this wave's operands where load_packed finds them (`out`: one head's Pack16 record).
   LF_DEV void save_packed(unsigned char* out, bool header) const {
     u32x4* frag = reinterpret_cast<u32x4*>(out + Pack16<T, D>::kHeaderBytes);
@@ -407,7 +480,6 @@ struct ApplyDma {
         const bool isS = slot < HALF;
         const bool isZ = NORM && slot == HALF, zrem = NORM && slot == HALF + 1;
         const int col = isS ? hv * HALF + slot : 0;
-        const float sc = isS ? aS : az;
         float raw[KS][8];
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
@@ -424,24 +496,7 @@ struct ApplyDma {
             for (int j = 0; j < 4; ++j) { raw[s][j] = lo4[j]; raw[s][4 + j] = hi4[j]; }
           }
         }
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-          const bool used = (kg * KS + s < CPR) && (isS || isZ || zrem);
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            float hi2[2], lo2[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const float x = used ? raw[s][2 * w + q] * sc : 0.0f;
-              float r0, r1;
-              unpack2<T>(pack2<T>(x, 0.0f), r0, r1);   // x rounded once to 16 bits
-              hi2[q] = zrem ? x - r0 : x;
-              lo2[q] = isS ? x - r0 : 0.0f;            // S' remainder -> lo fragment (bf16 only)
-            }
-            A[0][t][s][w] = pack2<T>(hi2[0], hi2[1]);
-            if constexpr (NS == 2) A[1][t][s][w] = pack2<T>(lo2[0], lo2[1]);
-          }
-        }
+        make_operands_of(t, isS, isZ, zrem, aS, az, raw);
       }
     }
     __syncthreads();   // the staged state is dead: the third slot block may be filled from here on
@@ -771,13 +826,15 @@ apply16_packed(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, La
   ap.stream();
 }
 
-// Apply on groups of W (4 or 8) neighbouring heads (see ROWS_W above).  grid = (wgs, B * groups_per_batch),
+// Apply on groups of W (4 or 8) neighbouring heads (see ROWS_W above).  `packed`: the heads' operands (pack_state16), or
+// null: from `state`.  grid = (wgs, B * groups_per_batch),
 // block = 64 W: workgroup (x, y) takes heads W (y % gpb) .. + W - 1 of batch y / gpb.  Heads beyond the last
 // whole group are left to apply16_dma.
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
 apply16_rows(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, int groups_per_batch,
-             const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
+             const unsigned char* __restrict__ packed, const float* __restrict__ state, float eps, long long N,
+             int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long b = blockIdx.y / groups_per_batch;
@@ -785,7 +842,9 @@ apply16_rows(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layo
   ApplyDma<T, D, FM, NORM, W> ap(Q + (b * lq.batch + h0 * lq.head), lq.row, O + (b * lo.batch + h0 * lo.head), lo.row,
                                  N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   ap.prefetch();
-  ap.load_packed(packed + (b * lq.H + h0 + wave) * Pack16<T, D>::kHeadBytes, eps);
+  const long long bh = b * lq.H + h0 + wave;
+  if (packed) ap.load_packed(packed + bh * Pack16<T, D>::kHeadBytes, eps);
+  else ap.load_direct(state + bh * (D * D + D), eps);
   ap.stream();
 }
 

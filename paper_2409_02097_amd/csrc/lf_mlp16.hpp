@@ -324,13 +324,12 @@ constexpr int apply16_mlp_lds_bytes(int waves) {
   return 2 * ApplyDmaCfg<D>::kRing * ApplyDmaCfg<D>::kSlotBytes * waves + waves * 2 * kTile * 8;
 }
 
-// Apply from the branch results of f'.  grid = (wgs, B), block = 64 W, H = W heads; `packed`: the heads'
-// operand-ready states (pack_state16).  a_q and t_q share the token stride `row_q`; out has `row_o`.
+// Apply from the branch results of f'.  grid = (wgs, B), block = 64 W, H = W heads; `state`: the heads' fp32 states.  a_q and t_q share the token stride `row_q`; out has `row_o`.
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
 apply16_mlp(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, long long batch_q, int row_q,
             u32x4* __restrict__ O, long long batch_o, int row_o, const float* __restrict__ gamma,
-            const float* __restrict__ beta, float ln_eps, float slope, const unsigned char* __restrict__ packed,
+            const float* __restrict__ beta, float ln_eps, float slope, const float* __restrict__ state,
             float eps, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -339,7 +338,7 @@ apply16_mlp(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, long lon
                                        gridDim.x, smem);
   ap.set_mlp(Tq + b * batch_q, gamma, beta, ln_eps, slope);
   ap.prefetch();
-  ap.load_packed(packed + (b * W + wave) * Pack16<T, D>::kHeadBytes, eps);
+  ap.load_direct(state + (b * W + wave) * (D * D + D), eps);
   ap.stream();
 }
 
@@ -348,7 +347,7 @@ __global__ void __launch_bounds__(64 * W)
 apply16_mlpg(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, long long batch_q, int row_q,
              u32x4* __restrict__ O, long long batch_o, int row_o, int gpb, const f32x2* __restrict__ stats,
              long long n_pad, const float* __restrict__ gamma, const float* __restrict__ beta, float slope,
-             const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
+             const float* __restrict__ state, float eps, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long b = blockIdx.y / gpb;
@@ -359,7 +358,7 @@ apply16_mlpg(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, long lo
   ap.set_mlp(Tq + b * batch_q + in_row, gamma + grp * (W * D), beta + grp * (W * D), 0.0f, slope);
   ap.set_stats(stats + b * n_pad);
   ap.prefetch();
-  ap.load_packed(packed + ((b * gpb + grp) * W + wave) * Pack16<T, D>::kHeadBytes, eps);
+  ap.load_direct(state + ((b * gpb + grp) * W + wave) * (D * D + D), eps);
   ap.stream();
 }
 

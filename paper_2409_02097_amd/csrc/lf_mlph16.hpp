@@ -91,8 +91,8 @@ state_reduce16_mlph(const u32x4* __restrict__ Ak, const u32x4* __restrict__ Tk, 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long bh = blockIdx.y;
-  const long long b = bh / H;
-  const int h = (int)(bh % H);
+  const int h = (int)((unsigned)bh % (unsigned)H);
+  const long long b = (unsigned)bh / (unsigned)H;
   const long long off = b * batch + (long long)h * CPR;
   const u32x4* Ah = Ak + off;
   const u32x4* Th = Tk + off;
@@ -278,25 +278,25 @@ constexpr int apply16_mlph_lds_bytes() {
 }
 
 // Apply of one head from the branch results of f' and the rows' statistics.  grid = (wgs, B * H), block = 256;
-// `packed`: the heads' operand-ready states (pack_state16); `stats`: this branch's [B][n_pad] pairs, n_pad a
+// `state`: the heads' fp32 states; `stats`: this branch's [B][n_pad] pairs, n_pad a
 // multiple of the tile so that a whole last tile can be read.
 template <typename T, int D, int FM, bool NORM>
 __global__ void __launch_bounds__(kThreads)
 apply16_mlph(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, long long batch_q, int row_q,
              u32x4* __restrict__ O, long long batch_o, int row_o, int H, const f32x2* __restrict__ stats,
              long long n_pad, const float* __restrict__ gamma, const float* __restrict__ beta, float slope,
-             const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
+             const float* __restrict__ state, float eps, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const long long bh = blockIdx.y;
-  const long long b = bh / H;
-  const int h = (int)(bh % H);
+  const int h = (int)((unsigned)bh % (unsigned)H);
+  const long long b = (unsigned)bh / (unsigned)H;
   const long long off_q = b * batch_q + (long long)h * (D / 8);
   ApplyDma<T, D, FM, NORM, 0, true, D, true> ap(Aq + off_q, row_q, O + b * batch_o + (long long)h * (D / 8), row_o, N,
                                                tiles_per_block, blockIdx.x, gridDim.x, smem);
   ap.set_mlp(Tq + off_q, gamma + h * D, beta + h * D, 0.0f, slope);
   ap.set_stats(stats + b * n_pad);
   ap.prefetch();
-  ap.load_packed(packed + bh * Pack16<T, D>::kHeadBytes, eps);
+  ap.load_direct(state + bh * (D * D + D), eps);
   ap.stream();
 }
 

@@ -25,8 +25,8 @@ state_reduce16_wide_mlp(const u32x4* __restrict__ Ak, const u32x4* __restrict__ 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const long long bh = blockIdx.y;
-  const long long b = bh / H;
-  const int h = (int)(bh % H);
+  const int h = (int)((unsigned)bh % (unsigned)H);
+  const long long b = (unsigned)bh / (unsigned)H;
   const long long off = b * batch + (long long)h * CPR;
   const u32x4* Ah = Ak + off;
   const u32x4* Th = Tk + off;
@@ -196,8 +196,8 @@ apply16_wide_mlp(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, lon
                  const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const long long bh = blockIdx.y;
-  const long long b = bh / H;
-  const int h = (int)(bh % H);
+  const int h = (int)((unsigned)bh % (unsigned)H);
+  const long long b = (unsigned)bh / (unsigned)H;
   const long long off_q = b * batch_q + (long long)h * (D / 8);
   ApplyWide<T, D, FM, NORM, W, true> ap(Aq + off_q, row_q, O + b * batch_o + (long long)h * (D / 8), row_o, N,
                                         tiles_per_block, blockIdx.x, gridDim.x, smem);
@@ -217,7 +217,7 @@ apply16_wide_mlp(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, lon
 // B operands (a and t chunks from the slot, {rstd, cn} of its token from the slot's statistics deposit, gamma and
 // beta of its channels from the table), phi applied, rounded to fp16 -- the arithmetic of apply16_wide_mlp's phi pass
 // for fp16 tensors; the formed row of a bf16 tensor is scaled into fp16's range first, as apply16_wave does.
-// Operands from pack_state_wave<D>.
+// Operands from combine_pack_wave<D>.
 // ==========================================================================================
 template <int D> struct ApplyWaveMlpShape {
   using Sw = ApplyWaveShape<D>;
@@ -256,7 +256,7 @@ struct ApplyWaveMlp {
   int rowb, x0;              // byte offset of this lane's token row in a tile image, its swizzle
   TileIter it, ahead;
   u32x4 A[RB][KS];
-  float c1, eps_s;
+  float c1[CB], eps_s;
 
   LF_DEV ApplyWaveMlp(const u32x4* Ah_, const u32x4* Th_, int rs_q_, u32x4* Oh_, int rs_o_, const void* stats,
                       float slope_, long long N_, int tiles_per_block, int wg, int nwg, unsigned char* smem_)
@@ -329,8 +329,9 @@ struct ApplyWaveMlp {
 #pragma unroll
       for (int s = 0; s < KS; ++s) A[b][s] = frag[(b * KS + s) * 64 + lane];
     const float* scales = reinterpret_cast<const float*>(packed);
-    c1 = scales[0];
-    eps_s = eps * scales[1];
+#pragma unroll
+    for (int b = 0; b < CB; ++b) c1[b] = scales[b];
+    eps_s = eps * scales[CB];
   }
 
   LF_DEV void store_tile(long long tile, int slot) {
@@ -445,17 +446,18 @@ struct ApplyWaveMlp {
 #pragma unroll
       for (int b = 0; b < RB; ++b) acc[b] = mfma_16x16x32<TA>(A[b][s], Ba[s], acc[b]);
     }
-    float scale = c1 * post;
+    float scale = post;
     if constexpr (NORM) {
       // rows d and d + 1 (the normalizer and what its rounding left) are rows 0 and 1 of the last block: lanes
       // 0-15 hold them for their tokens
       const float part = acc[RB - 1][0] + acc[RB - 1][1];
       const float den = __shfl(part, lane & 15) + eps_tok;
-      scale = c1 * __builtin_amdgcn_rcpf(den);
+      scale = __builtin_amdgcn_rcpf(den);
     }
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
-      const u32x2 w = {pack2<T>(acc[b][0] * scale, acc[b][1] * scale), pack2<T>(acc[b][2] * scale, acc[b][3] * scale)};
+      const float sc = c1[b] * scale;
+      const u32x2 w = {pack2<T>(acc[b][0] * sc, acc[b][1] * sc), pack2<T>(acc[b][2] * sc, acc[b][3] * sc)};
       // channels 16 b + 4 g .. + 3: chunk 2 b + g / 2, its first or second half
       *reinterpret_cast<u32x2*>(sl + chunk_off(2 * b + (g >> 1)) + 8 * (g & 1)) = w;
     }
@@ -504,8 +506,8 @@ apply16_wave_mlp(const u32x4* __restrict__ Aq, const u32x4* __restrict__ Tq, lon
                  const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const long long bh = blockIdx.y;
-  const long long b = bh / H;
-  const int h = (int)(bh % H);
+  const int h = (int)((unsigned)bh % (unsigned)H);
+  const long long b = (unsigned)bh / (unsigned)H;
   const long long off_q = b * batch_q + (long long)h * (D / 8);
   ApplyWaveMlp<T, D, FM, NORM> ap(Aq + off_q, Tq + off_q, row_q, O + b * batch_o + (long long)h * (D / 8), row_o,
                                stats + b * n_pad, slope, N, tiles_per_block, blockIdx.x, gridDim.x, smem);

@@ -57,10 +57,11 @@ constexpr int kApplyWaveRing = 3;
 template <int D>
 constexpr int apply16_wave_lds_bytes() { return ApplyWaveShape<D>::kWaves * kApplyWaveRing * ApplyWaveShape<D>::kSlotBytes; }
 
-// The operand-ready state of one head for apply16_wave: {c1 = alpha_z / alpha_S, alpha_z} then frag[b][s][lane],
-// 16 bytes each, fp16.  Lane l of fragment (b, s), element j:  output row m = 16 b + l % 16, contraction channel
-// ch = 32 s + 8 (l / 16) + j;  m < d -> S'[ch][m] = alpha_S S[ch][m];  m == d -> z'[ch] = alpha_z z[ch] rounded to
-// fp16;  m == d + 1 -> what that rounding left;  else 0.
+// The operand-ready state of one head for apply16_wave: a header of scales, then frag[b][s][lane], 16 bytes each, fp16.
+// Lane l of fragment (b, s), element j:  output row m = 16 b + l % 16, contraction channel ch = 32 s + 8 (l / 16) + j;
+// m < d -> S'[ch][m] = alpha_b S[ch][m];  m == d -> z'[ch] = alpha_z z[ch] rounded to fp16;  m == d + 1 -> what that
+// rounding left;  else 0.  Every block of 16 output channels has a power of two of its own; header: [b] = alpha_z / alpha_b
+// for b < d / 16, [d / 16] = alpha_z.
 template <int D> struct PackWave {
   using Sw = ApplyWaveShape<D>;
   static constexpr int kHeaderBytes = 256;
@@ -68,84 +69,141 @@ template <int D> struct PackWave {
   static constexpr int kHeadBytes = kHeaderBytes + kFrags * 64 * 16;
 };
 
-// grid = (d / 32, heads), block = 256.  Every workgroup finds the maxima (power-of-two scales, as
-// pack_state_wide); workgroup s writes the fragments of contraction step s, wave w those of row blocks w, w + 4, ..
-template <int D>
-__global__ void __launch_bounds__(kThreads)
-pack_state_wave(const float* __restrict__ state, unsigned char* __restrict__ packed, int normalize) {
+// Sum of the head's partial states and its operands in one launch (two before: combine_state, then a kernel that scanned
+// the whole state for its maxima in every workgroup).  grid = (d / 16 + 1, heads), block = 256 Q: workgroup b sums, scales
+// and packs the 16 value channels of block b (the last one z), which is why every block has a scale of its own.  Q = 4
+// for 5 .. kPackParts partials: a quarter of the threads sums a quarter of the partials in order, the quarters are added
+// 0..3; Q = 1 up to 4.  Either way the bits are combine_state's.
+// Measured (us per call, two launches -> one): 2 x 8 x 256 x 160 fp16 (8 partials) 26.7 -> 24.0; the fp16 training step of 12
+// x 8 x 256 x 160 (four packings of one or few partials) 202 -> 185.
+// src: [heads][parts][D*D + D]; keep: null, or where the summed states go ([heads][D*D + D]).
+// Beyond kPackParts partials a head's eleven workgroups would pull in what combine_state spreads over the whole chip (64
+// partials of 8 heads of 160: 21.9 us against 9.2 + 6.3), so that runs first.
+constexpr int kPackParts = 16;
+template <int D, int Q>
+__global__ void __launch_bounds__(256 * Q)
+combine_pack_wave(const float* __restrict__ src, int parts, float* __restrict__ keep, unsigned char* __restrict__ packed,
+                  int normalize) {
   using Sw = ApplyWaveShape<D>;
-  constexpr int KS = Sw::kKS, RB = Sw::kRB, NE = D * D + D;
-  __shared__ float redmax[2 * kWavesPerWG];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int s = blockIdx.x;
+  constexpr int KS = Sw::kKS, CB = Sw::kCB, NE = D * D + D;
+  constexpr int PER = D / 16;          // elements per thread of the 16 columns' sums
+  constexpr int RS = 17;               // LDS row stride of the [D][16] block
+  constexpr int NT = 256 * Q;
+  __shared__ float quarter[Q > 1 ? Q - 1 : 1][Q > 1 ? D * 16 : 1];
+  __shared__ float tile[D * RS];       // the block's sums, [ch][column]; or z
+  __shared__ float zsum[Q][D];
+  __shared__ float red[2][NT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int q = tid >> 8, t = tid & 255;
+  const int b = blockIdx.x;
   const long long bh = blockIdx.y;
-  const float* st = state + bh * NE;
+  const float* st = src + bh * parts * (long long)NE;
   unsigned char* out = packed + bh * PackWave<D>::kHeadBytes;
+  const int per = (parts + Q - 1) / Q;
+  const int p0 = q * per, p1 = p0 + per < parts ? p0 + per : parts;
+  const bool isZ = b == CB;
 
-  // this wave's row blocks b = wave, wave + 4, ..: their raw values are requested before the maxima are known, so that
-  // the kernel waits for memory once
-  constexpr int NB = (RB + kWavesPerWG - 1) / kWavesPerWG;
-  const int g = lane >> 4;
-  float raw[NB][8];
+  // z (every workgroup: its scale enters all of theirs)
+  if (t < D) {
+    float s = 0.0f;
+#pragma unroll 4
+    for (int p = p0; p < p1; ++p) s += st[(long long)p * NE + D * D + t];
+    zsum[q][t] = s;
+  }
+  float acc[PER];
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = wave + kWavesPerWG * i;
-    const int m = 16 * b + (lane & 15);
+  for (int i = 0; i < PER; ++i) acc[i] = 0.0f;
+  const int ch0 = t >> 4, col = t & 15;
+  if (!isZ) {
+    const float* sp = st + ch0 * D + 16 * b + col;
+#pragma unroll 4
+    for (int p = p0; p < p1; ++p) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int ch = 32 * s + 8 * g + j;
-      int at = ch * D;                                  // (rows past d + 1 and blocks past the end: a valid place, unused)
-      if (m < D) at = ch * D + m;
-      else if (m <= D + 1) at = D * D + ch;
-      raw[i][j] = st[at];
+      for (int i = 0; i < PER; ++i) acc[i] += sp[(long long)p * NE + 16 * i * D];
+    }
+    if (Q > 1 && q > 0) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) quarter[q - 1][(16 * i + ch0) * 16 + col] = acc[i];
     }
   }
-  float mS, mz;
-  state_maxima_share<D, kThreads>(st, tid, mS, mz);
+  __syncthreads();
+  float mz = 0.0f, mS = 0.0f;
+  if (tid < D) {
+    float z = zsum[0][tid];
+#pragma unroll
+    for (int k = 1; k < Q; ++k) z += zsum[k][tid];
+    mz = fabsf(z);
+    if (isZ) {
+      tile[tid] = z;
+      if (keep) keep[bh * NE + D * D + tid] = z;
+    }
+  }
+  if (!isZ && q == 0) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int at = (16 * i + ch0) * 16 + col;
+      float x = acc[i];
+#pragma unroll
+      for (int k = 1; k < Q; ++k) x += quarter[k - 1][at];
+      mS = fmaxf(mS, fabsf(x));
+      tile[(16 * i + ch0) * RS + col] = x;
+      if (keep) keep[bh * NE + (16 * i + ch0) * D + 16 * b + col] = x;
+    }
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     mS = fmaxf(mS, __shfl_xor(mS, o));
     mz = fmaxf(mz, __shfl_xor(mz, o));
   }
-  if (lane == 0) { redmax[wave] = mS; redmax[kWavesPerWG + wave] = mz; }
+  if (lane == 0) { red[0][wave] = mS; red[1][wave] = mz; }
   __syncthreads();
   mS = 0.0f; mz = 0.0f;
 #pragma unroll
-  for (int w = 0; w < kWavesPerWG; ++w) { mS = fmaxf(mS, redmax[w]); mz = fmaxf(mz, redmax[kWavesPerWG + w]); }
+  for (int w = 0; w < NT / 64; ++w) { mS = fmaxf(mS, red[0][w]); mz = fmaxf(mz, red[1][w]); }
   const float aS = pow2_scale_for(mS);
   const float az = normalize ? pow2_scale_for(mz) : 1.0f;
-  if (s == 0 && tid == 0) {
-    float* scales = reinterpret_cast<float*>(out);
-    scales[0] = az / aS;
-    scales[1] = az;
-  }
+  if (tid == 0) reinterpret_cast<float*>(out)[b] = isZ ? az : az / aS;
 
   u32x4* frag = reinterpret_cast<u32x4*>(out + PackWave<D>::kHeaderBytes);
+  for (int f = tid; f < KS * 64; f += NT) {
+    const int s = f >> 6, l = f & 63, ch = 32 * s + 8 * (l >> 4), m = l & 15;
+    u32x4 w4;
 #pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int b = wave + kWavesPerWG * i;
-    if (b < RB) {
-      const int m = 16 * b + (lane & 15);
-      u32x4 w4;
+    for (int w = 0; w < 4; ++w) {
+      float v2[2];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        float v2[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          float x = 0.0f;
-          bool zrem = false;
-          if (m < D) x = raw[i][2 * w + q] * aS;
-          else if (normalize && m == D) x = raw[i][2 * w + q] * az;
-          else if (normalize && m == D + 1) { x = raw[i][2 * w + q] * az; zrem = true; }
+      for (int k = 0; k < 2; ++k) {
+        float x;
+        if (!isZ) {
+          x = tile[(ch + 2 * w + k) * RS + m] * aS;
+        } else {
+          const float y = normalize && m < 2 ? tile[ch + 2 * w + k] * az : 0.0f;
           float r0, r1;
-          unpack2<F16>(pack2<F16>(x, 0.0f), r0, r1);   // x rounded once to fp16
-          v2[q] = zrem ? x - r0 : x;
+          unpack2<F16>(pack2<F16>(y, 0.0f), r0, r1);   // y rounded once to fp16
+          x = m == 1 ? y - r0 : y;
         }
-        w4[w] = pack2<F16>(v2[0], v2[1]);
+        v2[k] = x;
       }
-      frag[(b * KS + s) * 64 + lane] = w4;
+      w4[w] = pack2<F16>(v2[0], v2[1]);
     }
+    frag[(b * KS + s) * 64 + l] = w4;
+  }
+}
+
+// `parts` partials per head at `part`; the sum goes to `state` as well (parts = 1 and state = null: `part` is the state)
+template <int D>
+inline void launch_pack_wave(const float* part, int parts, float* state, unsigned char* packed, bool normalize,
+                             unsigned heads, hipStream_t st) {
+  constexpr int NE = D * D + D;
+  const dim3 grid(ApplyWaveShape<D>::kRB, heads);
+  if (parts > kPackParts) {
+    combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, heads), dim3(kCombineThreads), 0, st>>>(part, parts, NE,
+                                                                                                           state);
+    combine_pack_wave<D, 1><<<grid, dim3(256), 0, st>>>(state, 1, nullptr, packed, normalize ? 1 : 0);
+  } else if (parts > 4) {
+    combine_pack_wave<D, 4><<<grid, dim3(1024), 0, st>>>(part, parts, state, packed, normalize ? 1 : 0);
+  } else {
+    combine_pack_wave<D, 1><<<grid, dim3(256), 0, st>>>(part, parts, state, packed, normalize ? 1 : 0);
   }
 }
 
@@ -170,7 +228,7 @@ struct ApplyWave {
   int rowb[2], x0[2];        // per token block: byte offset of this lane's token row in a slot, its swizzle
   TileIter it, ahead;
   u32x4 A[RB][KS];
-  float c1, eps_s;
+  float c1[CB], eps_s;   // c1: alpha_z / alpha_b of output block b (the same for every lane)
 
   LF_DEV ApplyWave(const u32x4* Qh_, int rs_q_, u32x4* Oh_, int rs_o_, long long N_, int tiles_per_block, int wg,
                    int nwg, unsigned char* smem_)
@@ -225,7 +283,7 @@ struct ApplyWave {
     }
   }
 
-  // `packed`: this head's operands as pack_state_wave wrote them
+  // `packed`: this head's operands as combine_pack_wave wrote them
   LF_DEV void load_packed(const unsigned char* packed, float eps) {
     const u32x4* frag = reinterpret_cast<const u32x4*>(packed + PackWave<D>::kHeaderBytes);
 #pragma unroll
@@ -233,8 +291,9 @@ struct ApplyWave {
 #pragma unroll
       for (int s = 0; s < KS; ++s) A[b][s] = frag[(b * KS + s) * 64 + lane];
     const float* scales = reinterpret_cast<const float*>(packed);
-    c1 = scales[0];
-    eps_s = eps * scales[1];
+#pragma unroll
+    for (int b = 0; b < CB; ++b) c1[b] = scales[b];
+    eps_s = eps * scales[CB];
   }
 
   // the finished tile in `slot` goes out; always NL vector memory instructions for a full tile (only the very
@@ -336,17 +395,18 @@ struct ApplyWave {
 #pragma unroll
       for (int b = 0; b < RB; ++b) acc[b] = mfma_16x16x32<TA>(A[b][s], B[s], acc[b]);
     }
-    float scale = c1 * post;
+    float scale = post;
     if constexpr (NORM) {
       // rows d and d + 1 (the normalizer and what its rounding left) are rows 0 and 1 of the last block: lanes
       // 0-15 hold them for their tokens
       const float part = acc[RB - 1][0] + acc[RB - 1][1];
       const float den = __shfl(part, lane & 15) + eps_tok;
-      scale = c1 * __builtin_amdgcn_rcpf(den);
+      scale = __builtin_amdgcn_rcpf(den);
     }
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
-      const u32x2 w = {pack2<T>(acc[b][0] * scale, acc[b][1] * scale), pack2<T>(acc[b][2] * scale, acc[b][3] * scale)};
+      const float sc = c1[b] * scale;
+      const u32x2 w = {pack2<T>(acc[b][0] * sc, acc[b][1] * sc), pack2<T>(acc[b][2] * sc, acc[b][3] * sc)};
       // channels 16 b + 4 g .. + 3: chunk 2 b + g / 2, its first or second half
       *reinterpret_cast<u32x2*>(sl + chunk_off(tb, 2 * b + (g >> 1)) + 8 * (g & 1)) = w;
     }
@@ -399,7 +459,7 @@ struct ApplyWave {
   }
 };
 
-// grid = (wgs, heads), block = 256 (four waves that share nothing but the workgroup); `packed` from pack_state_wave<D>
+// grid = (wgs, heads), block = 256 (four waves that share nothing but the workgroup); `packed` from combine_pack_wave<D>
 template <typename T, int D, int FM, bool NORM>
 __global__ void __launch_bounds__(kThreads)
 apply16_wave(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, HeadSubset hs,

@@ -86,6 +86,7 @@ struct Plan {
   int gwaves, groups, gsplits, gblk_reduce, gapply_wgs, gblk_apply;
   int apply_waves;      // waves per workgroup of the packed per-head apply (1, 2 or 4)
   bool wave_apply;      // widths above 80: apply16_wave (a wave per tile) instead of apply16_wide
+  bool gapply_packed;   // row-piece apply from operands prepared by pack_state16 (many short-lived workgroups)
   bool apply_packed;    // per-head apply from operands prepared by pack_state16 (many short-lived workgroups)
   long long n_tiles;
   size_t state_floats;  // d*d + d: one partial, and one head's state
@@ -205,7 +206,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     p->gwaves = lf::kWavesPerWG;
     p->groups = p->gsplits = p->gapply_wgs = 0;
     p->gblk_reduce = p->gblk_apply = 1;
-    p->apply_packed = false;
+    p->apply_packed = p->gapply_packed = false;
     p->apply_waves = lf::kWavesPerWG;
     p->path = 0;
     p->solo_g = 0;
@@ -317,12 +318,14 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     long long gwant = 2 * num_cu();
     if (!one_round && p->groups * p->n_tiles / kGroupTilesPerWG * unit > gwant)
       gwant = p->groups * p->n_tiles / kGroupTilesPerWG * unit;
+    p->gapply_packed = gwant > 2 * num_cu();
     if (gwant > (1 << 24)) gwant = 1 << 24;
     p->gapply_wgs = per_group(env_int("LINFUSION_GROUP_APPLY_WGS", (int)gwant) / unit, &share);
     p->gblk_apply = block_tiles(share, "LINFUSION_GROUP_APPLY_BLK", p->gwaves == 8 ? 1 : 2, 1);
   } else {
     p->gsplits = p->gapply_wgs = 0;
     p->gblk_reduce = p->gblk_apply = lf::kWavesPerWG;
+    p->gapply_packed = false;
   }
   // Measured on MI355X: with the apply launch sized to one resident round the three short kernels match
   // or beat the single launch (two in-kernel barriers) nearly everywhere; the single launch still wins
@@ -551,20 +554,24 @@ int run16(const Args& a) {
     const size_t lds2 = apply16_dma_lds_bytes<T, D>();
     if (a.group_apply) {
       const dim3 g2(p.gapply_wgs, (unsigned)p.groups);
-      unsigned char* packed = a.ws + p.ws_partials + p.ws_state + p.ws_sync;
-      static_assert(Pack16<T, D>::kFrags == NSplit<T>::value * ((D / 2 + 2 + 15) / 16) * ((D / 8 + 1) / 2),
-                    "the workspace size formula must match the packed layout");
-      if (!allow_lds(pack_state16<T, D, true>, (int)lds2) || !allow_lds(pack_state16<T, D, false>, (int)lds2))
-        return LINFUSION_ERR_HIP;
-      if (a.unnorm) pack_state16<T, D, false><<<dim3((unsigned)a.BH), blk, lds2, st>>>(state, packed);
-      else pack_state16<T, D, true><<<dim3((unsigned)a.BH), blk, lds2, st>>>(state, packed);
+      // operands packed once per head where the workgroups are many and short-lived; a resident grid builds them itself
+      unsigned char* packed = nullptr;
+      if (p.gapply_packed) {
+        packed = a.ws + p.ws_partials + p.ws_state + p.ws_sync;
+        static_assert(Pack16<T, D>::kFrags == NSplit<T>::value * ((D / 2 + 2 + 15) / 16) * ((D / 8 + 1) / 2),
+                      "the workspace size formula must match the packed layout");
+        if (!allow_lds(pack_state16<T, D, true>, (int)lds2) || !allow_lds(pack_state16<T, D, false>, (int)lds2))
+          return LINFUSION_ERR_HIP;
+        if (a.unnorm) pack_state16<T, D, false><<<dim3((unsigned)a.BH), blk, lds2, st>>>(state, packed);
+        else pack_state16<T, D, true><<<dim3((unsigned)a.BH), blk, lds2, st>>>(state, packed);
+      }
       if (a.ev) (void)hipEventRecord(a.ev[2], st);   // the operand packing counts with the combine
 #define LF_APPLY_W(FM, NORM, WW)                                                                          \
   {                                                                                                       \
     constexpr int ldsa = apply16_dma_lds_bytes<T, D>(WW);                                                 \
     if (!allow_lds(apply16_rows<T, D, FM, NORM, WW>, ldsa)) return LINFUSION_ERR_HIP;                     \
-    apply16_rows<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), ldsa, st>>>(Q, a.lq, O, a.lo, gpb, packed, a.eps, \
-                                                                      a.N, p.gblk_apply);                 \
+    apply16_rows<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), ldsa, st>>>(Q, a.lq, O, a.lo, gpb, packed, state, \
+                                                                      a.eps, a.N, p.gblk_apply);                 \
   }
 #define LF_APPLY(FM, NORM)                                          \
   if constexpr (D <= 64) {                                          \

@@ -180,16 +180,11 @@ int run_mlp(const MlpArgs& a) {
   const long long batch = a.in_batch, batch_o = a.out_batch;
   float* partials = reinterpret_cast<float*>(a.ws);
   float* state = reinterpret_cast<float*>(a.ws + p.ws_partials);
-  unsigned char* packed = a.ws + p.ws_partials + p.ws_state;
   hipStream_t st = a.st;
   constexpr int lds_r = ReduceMlpCfg<T, D, W>::kLdsBytes;
-  constexpr int lds_p = apply16_dma_lds_bytes<T, D>();
   constexpr int lds_a = apply16_mlp_lds_bytes<T, D>(W);
   static_assert(lds_r <= 160 * 1024 && lds_a <= 160 * 1024, "workgroup LDS limit of the device");
-  static_assert(Pack16<T, D>::kFrags == NSplit<T>::value * ((D / 2 + 2 + 15) / 16) * ((D / 8 + 1) / 2),
-                "the workspace size formula must match the packed layout");
-  if (!allow_lds(state_reduce16_mlp<T, D, FM, W>, lds_r) || !allow_lds(pack_state16<T, D, NORM>, lds_p) ||
-      !allow_lds(apply16_mlp<T, D, FM, NORM, W>, lds_a))
+  if (!allow_lds(state_reduce16_mlp<T, D, FM, W>, lds_r) || !allow_lds(apply16_mlp<T, D, FM, NORM, W>, lds_a))
     return LINFUSION_ERR_HIP;
   if (a.ev) (void)hipEventRecord(a.ev[0], st);
   state_reduce16_mlp<T, D, FM, W><<<dim3(p.splits, (unsigned)a.B), dim3(64 * W), lds_r, st>>>(
@@ -198,11 +193,10 @@ int run_mlp(const MlpArgs& a) {
   if (a.ev) (void)hipEventRecord(a.ev[1], st);
   combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)(a.B * W)), dim3(kCombineThreads), 0, st>>>(
       partials, p.splits, NE, state);
-  pack_state16<T, D, NORM><<<dim3((unsigned)(a.B * W)), dim3(kThreads), lds_p, st>>>(state, packed);
   if (a.ev) (void)hipEventRecord(a.ev[2], st);
   apply16_mlp<T, D, FM, NORM, W><<<dim3(p.apply_wgs, (unsigned)a.B), dim3(64 * W), lds_a, st>>>(
       (const u32x4*)a.a_q, (const u32x4*)a.t_q, batch, row, (u32x4*)a.out, batch_o, row_o, a.gamma_q, a.beta_q, a.ln_eps,
-      a.slope, packed, a.eps, a.N, p.blk_apply);
+      a.slope, state, a.eps, a.N, p.blk_apply);
   if (a.ev) (void)hipEventRecord(a.ev[3], st);
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }

@@ -21,13 +21,9 @@ int run_heads_t(const HeadsArgs& a) {
   using namespace lf;
   constexpr int NE = D * D + D;
   constexpr int lds_r = reduce16_mlph_lds_bytes<T, D>();
-  constexpr int lds_p = apply16_dma_lds_bytes<T, D>();
   constexpr int lds_a = apply16_mlph_lds_bytes<T, D>();
   static_assert(lds_r <= 160 * 1024 && lds_a <= 160 * 1024, "workgroup LDS limit of the device");
-  static_assert(Pack16<T, D>::kFrags == NSplit<T>::value * ((D / 2 + 2 + 15) / 16) * ((D / 8 + 1) / 2),
-                "the planner's workspace size formula must match the packed layout");
-  if (!allow_lds(state_reduce16_mlph<T, D, FM>, lds_r) || !allow_lds(pack_state16<T, D, NORM>, lds_p) ||
-      !allow_lds(apply16_mlph<T, D, FM, NORM>, lds_a))
+  if (!allow_lds(state_reduce16_mlph<T, D, FM>, lds_r) || !allow_lds(apply16_mlph<T, D, FM, NORM>, lds_a))
     return LINFUSION_ERR_HIP;
   hipStream_t st = a.st;
   const int row = (int)a.in_row, row_o = (int)a.out_row;
@@ -43,11 +39,10 @@ int run_heads_t(const HeadsArgs& a) {
   if (a.ev) (void)hipEventRecord(a.ev[1], st);
   combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, heads), dim3(kCombineThreads), 0, st>>>(
       a.partials, a.splits, NE, a.state);
-  pack_state16<T, D, NORM><<<dim3(heads), dim3(kThreads), lds_p, st>>>(a.state, a.packed);
   if (a.ev) (void)hipEventRecord(a.ev[2], st);
   apply16_mlph<T, D, FM, NORM><<<dim3(a.apply_wgs, heads), dim3(kThreads), lds_a, st>>>(
       (const u32x4*)a.a_q, (const u32x4*)a.t_q, a.in_batch, row, (u32x4*)a.out, a.out_batch, row_o, a.H, stats_q, a.n_pad,
-      a.gamma_q, a.beta_q, a.slope, a.packed, a.eps, a.N, a.blk_apply);
+      a.gamma_q, a.beta_q, a.slope, a.state, a.eps, a.N, a.blk_apply);
   if (a.ev) (void)hipEventRecord(a.ev[3], st);
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
@@ -74,15 +69,13 @@ int run_wide_t(const HeadsArgs& a) {
       (const u32x4*)a.a_k, (const u32x4*)a.t_k, (const u32x4*)a.v, a.in_batch, row, a.H, stats_k, a.n_pad, a.gamma_k,
       a.beta_k, a.slope, a.partials, a.N, a.blk_reduce);
   if (a.ev) (void)hipEventRecord(a.ev[1], st);
-  combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, heads), dim3(kCombineThreads), 0, st>>>(
-      a.partials, a.splits, NE, a.state);
   // A wave per 16-token tile with the head's whole state in its registers (apply16_wave_mlp), one long-lived
   // workgroup per CU.  (LINFUSION_MLPW_WAVE_APPLY = 2 under tuning: the workgroup-shared kernel instead)
   {
     if (lfh::env_int("LINFUSION_MLPW_WAVE_APPLY", 1) == 1) {
       constexpr int lds_w = ApplyWaveMlpShape<D>::kLdsBytes;
       if (!allow_lds(apply16_wave_mlp<T, D, FM, NORM>, lds_w)) return LINFUSION_ERR_HIP;
-      pack_state_wave<D><<<dim3(ApplyWaveShape<D>::kKS, heads), dim3(kThreads), 0, st>>>(a.state, a.packed, NORM ? 1 : 0);
+      launch_pack_wave<D>(a.partials, a.splits, a.state, a.packed, NORM, heads, st);
       if (a.ev) (void)hipEventRecord(a.ev[2], st);
       const long long tiles = (a.N + ApplyWaveMlpShape<D>::kTok - 1) / ApplyWaveMlpShape<D>::kTok;
       const long long most = (tiles + kWavesPerWG - 1) / kWavesPerWG;   // every wave gets a tile
@@ -95,6 +88,8 @@ int run_wide_t(const HeadsArgs& a) {
       return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
     }
   }
+  combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, heads), dim3(kCombineThreads), 0, st>>>(
+      a.partials, a.splits, NE, a.state);
   pack_state_wide<T, D, WA><<<dim3(ApplyWideShape<D, WA>::kKS, heads), dim3(64 * WA), 0, st>>>(a.state, a.packed,
                                                                                              NORM ? 1 : 0);
   if (a.ev) (void)hipEventRecord(a.ev[2], st);
@@ -120,13 +115,9 @@ int run_groups_t(const HeadsArgs& a) {
   using namespace lf;
   constexpr int NE = D * D + D, W = 4;
   constexpr int lds_r = ReduceMlpCfg<T, D, W>::kLdsBytes;
-  constexpr int lds_p = apply16_dma_lds_bytes<T, D>();
   constexpr int lds_a = apply16_mlpg_lds_bytes<T, D>(W);
   static_assert(lds_r <= 160 * 1024 && lds_a <= 160 * 1024, "workgroup LDS limit of the device");
-  static_assert(Pack16<T, D>::kFrags == NSplit<T>::value * ((D / 2 + 2 + 15) / 16) * ((D / 8 + 1) / 2),
-                "the planner's workspace size formula must match the packed layout");
-  if (!allow_lds(state_reduce16_mlp<T, D, FM, W, true>, lds_r) || !allow_lds(pack_state16<T, D, NORM>, lds_p) ||
-      !allow_lds(apply16_mlpg<T, D, FM, NORM, W>, lds_a))
+  if (!allow_lds(state_reduce16_mlp<T, D, FM, W, true>, lds_r) || !allow_lds(apply16_mlpg<T, D, FM, NORM, W>, lds_a))
     return LINFUSION_ERR_HIP;
   hipStream_t st = a.st;
   const int row = (int)a.in_row, row_o = (int)a.out_row, gpb = a.H / W;
@@ -142,11 +133,10 @@ int run_groups_t(const HeadsArgs& a) {
   if (a.ev) (void)hipEventRecord(a.ev[1], st);
   combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, heads), dim3(kCombineThreads), 0, st>>>(
       a.partials, a.splits, NE, a.state);
-  pack_state16<T, D, NORM><<<dim3(heads), dim3(kThreads), lds_p, st>>>(a.state, a.packed);
   if (a.ev) (void)hipEventRecord(a.ev[2], st);
   apply16_mlpg<T, D, FM, NORM, W><<<dim3(a.apply_wgs, groups), dim3(64 * W), lds_a, st>>>(
       (const u32x4*)a.a_q, (const u32x4*)a.t_q, a.in_batch, row, (u32x4*)a.out, a.out_batch, row_o, gpb, stats_q, a.n_pad,
-      a.gamma_q, a.beta_q, a.slope, a.packed, a.eps, a.N, a.blk_apply);
+      a.gamma_q, a.beta_q, a.slope, a.state, a.eps, a.N, a.blk_apply);
   if (a.ev) (void)hipEventRecord(a.ev[3], st);
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }

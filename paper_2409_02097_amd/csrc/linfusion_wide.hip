@@ -16,8 +16,10 @@ using lfh::allow_lds;
 // (query rows are scaled into fp16's range as they are read): built for every wide width.
 template <typename T, int D> constexpr bool wave_ok() { return true; }
 
+// `combine`: leave the summed state in a.state; otherwise only the partials are left (one of them: the state itself, in
+// a.state)
 template <typename T, int D>
-int reduce(const WideReduceArgs& a, hipEvent_t* ev) {
+int reduce(const WideReduceArgs& a, hipEvent_t* ev, bool combine) {
   using namespace lf;
   constexpr int NE = D * D + D;
   const long long BH = (long long)a.B * a.H;
@@ -44,15 +46,17 @@ int reduce(const WideReduceArgs& a, hipEvent_t* ev) {
   }
 #undef LFW_REDUCE
   if (ev) (void)hipEventRecord(ev[1], st);
-  if (!direct)
+  if (!direct && combine)
     combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)BH), dim3(kCombineThreads), 0, st>>>(
         a.partials, a.plan.splits, NE, a.state);
-  if (ev) (void)hipEventRecord(ev[2], st);
+  if (ev && combine) (void)hipEventRecord(ev[2], st);
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
 
+// `parts`: a.state holds that many partials per head; with `keep` their sum goes there.  `ev`: recorded between packing
+// and apply.
 template <typename T, int D>
-int apply(const WideApplyArgs& a) {
+int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent_t* ev = nullptr) {
   using namespace lf;
   const long long BH = (long long)a.B * a.H;
   const dim3 blk(kThreads);
@@ -74,8 +78,8 @@ int apply(const WideApplyArgs& a) {
   if constexpr (wave_ok<T, D>()) {                                                                          \
     constexpr int lds2 = apply16_wave_lds_bytes<D>();                                                        \
     if (!allow_lds(apply16_wave<T, D, FM, NORM>, lds2)) return LINFUSION_ERR_HIP;                            \
-    pack_state_wave<D><<<dim3(ApplyWaveShape<D>::kKS, (unsigned)BH), blk, 0, st>>>(a.state, a.packed,        \
-                                                                                  NORM ? 1 : 0);             \
+    launch_pack_wave<D>(a.state, parts, keep, a.packed, NORM, (unsigned)BH, st);                             \
+    if (ev) (void)hipEventRecord(*ev, st);                                                                   \
     apply16_wave<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq, O, a.lo, all, a.packed, a.eps, a.N,         \
                                                         a.plan.blk_apply);                                   \
   } else {                                                                                                   \
@@ -98,12 +102,14 @@ int apply(const WideApplyArgs& a) {
 template <typename T, int D>
 int run(const WideArgs& a) {
   const WideReduceArgs r{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.lkv, a.lkv, a.partials, a.state, a.plan, a.st};
-  int rc = reduce<T, D>(r, a.ev);
+  const bool fuse = a.out && a.plan.wave_apply;   // the partials are summed where the operands are packed
+  int rc = reduce<T, D>(r, a.ev, !fuse);
   if (rc != LINFUSION_OK) return rc;
   if (a.out) {
-    const WideApplyArgs p{a.q, a.out, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.eps, a.unnorm, a.lq, a.lo, a.state,
-                          a.packed, a.plan, a.st};
-    rc = apply<T, D>(p);
+    const bool partials = fuse && a.plan.splits > 1;
+    const WideApplyArgs p{a.q, a.out, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.eps, a.unnorm, a.lq, a.lo,
+                          partials ? a.partials : a.state, a.packed, a.plan, a.st};
+    rc = apply<T, D>(p, partials ? a.plan.splits : 1, partials ? a.state : nullptr, fuse && a.ev ? a.ev + 2 : nullptr);
   }
   if (a.ev) (void)hipEventRecord(a.ev[3], a.st);
   return rc;
@@ -155,7 +161,7 @@ size_t wide_packed_bytes(int d, int dtype) {
 int run_wide_reduce(const WideReduceArgs& a) {
   switch (a.d) {
 #define X(DD) \
-  case DD: return a.dtype == LINFUSION_DTYPE_F16 ? reduce<lf::F16, DD>(a, nullptr) : reduce<lf::BF16, DD>(a, nullptr);
+  case DD: return a.dtype == LINFUSION_DTYPE_F16 ? reduce<lf::F16, DD>(a, nullptr, true) : reduce<lf::BF16, DD>(a, nullptr, true);
     LFW_FOR_D(X)
 #undef X
   }

@@ -1,0 +1,57 @@
+"""GPU parity of the routes between the state reduction and the apply step: partial states summed where the wide widths'
+operands are packed (one partial, up to four, up to sixteen, more), and row-piece kernels that build their operands from
+the state themselves."""
+import pytest
+import torch
+
+import paper_2409_02097_amd as lf
+from paper_2409_02097_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+# partials per head with 256 compute units: 1, 2, 4, 5, 12, 32
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,H,N,d", [(2, 8, 64, 160), (12, 16, 70, 160), (8, 16, 200, 96), (4, 16, 300, 128),
+                                     (4, 10, 777, 96), (1, 16, 2001, 160)])
+def test_wide_partials(B, H, N, d, dtype):
+    print(f"wide partials B={B} H={H} N={N} d={d} {dtype}", flush=True)
+    code = wl.DTYPE_CODE[dtype]
+    q, k, v = (t.cuda() for t in wl.make_qkv(B, H, N, d, dtype, idx=130))
+    size = lf.linfusion_attn_workspace_bytes(B, H, N, d, code)
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(q, float("nan"))
+    lf.linfusion_attn_fwd_ex(q, k, v, out, 0, 1e-6, 0, ws)
+    torch.cuda.synchronize()
+    # (every slice of a few heads: the oracle is quadratic in nothing, but these are many heads)
+    pick = slice(0, 1), slice(0, H, max(1, H // 3))
+    parity.check_all(out[pick].contiguous(), *(t[pick].contiguous() for t in (q, k, v)), dtype,
+                     what=f"wide partials {B}x{H}x{N}x{d}")
+    # the state left in the workspace has the bits of the state-only call, which combines in a launch of its own
+    off = lf.linfusion_attn_workspace_state_offset(B, H, N, d, code)
+    left = ws[off:off + B * H * (d * d + d) * 4].view(torch.float32).clone()
+    alone = torch.empty(B * H * (d * d + d), dtype=torch.float32, device="cuda")
+    lf.linfusion_attn_state(k, v, alone, 0, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(left, alone)
+
+
+@pytest.mark.parametrize("B,H,N,d,dtype", [(1, 8, 20001, 40, "f16"), (2, 8, 9000, 48, "bf16"), (1, 4, 33333, 80, "bf16"),
+                                           (1, 12, 20000, 24, "f16"), (1, 16, 70000, 8, "f16")])
+@pytest.mark.parametrize("normalize", [True, False])
+def test_row_pieces_build_their_operands(B, H, N, d, dtype, normalize):
+    print(f"rows direct B={B} H={H} N={N} d={d} {dtype}", flush=True)
+    q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=131, device="cpu")
+    if not normalize:
+        v = v * 0.02            # keeps the un-normalized sums inside fp16's range
+    tm = lambda t: t.permute(0, 2, 1, 3).contiguous().cuda().permute(0, 2, 1, 3)   # [B, N, H, d] in memory
+    qd, kd, vd = (tm(t) for t in (q, k, v))
+    out = torch.full_like(qd, float("nan"))
+    ws = torch.full((lf.linfusion_attn_workspace_bytes(B, H, N, d, wl.DTYPE_CODE[dtype]),), 0xFF, dtype=torch.uint8,
+                    device="cuda")
+    lf.linfusion_attn_fwd_strided(qd, kd, vd, out, 0, 1e-6, 0 if normalize else lf.FLAG_UNNORMALIZED, ws)
+    torch.cuda.synchronize()
+    heads = slice(0, 1), slice(0, H, max(1, H // 3))
+    parity.check_all(out[heads].contiguous(), *(t[heads].contiguous() for t in (q, k, v)), dtype, normalize=normalize,
+                     what=f"rows direct {B}x{H}x{N}x{d}")
