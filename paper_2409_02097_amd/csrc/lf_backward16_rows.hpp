@@ -3,7 +3,7 @@
 // a workgroup of W waves takes a group of W heads, moves every tile as whole row pieces of W*d elements (both
 // tensors, in and out) through a workgroup-wide LDS-DMA ring, and wave w computes head w exactly as the per-head
 // kernel does -- same products, same operands.  bwd_kv16_rows (dK, dV) and bwd_q16_rows (dQ, per-token scalars)
-// give the per-head kernels' bits; bwd_qs16_rows (dQ and the state gradient, fp16) sums a head's partial in one
+// give the per-head kernels' bits; bwd_qs16_rows (dQ and the state gradient) sums a head's partial in one
 // wave instead of four.  The ring, its
 // rotation against bank conflicts and the pipeline with one workgroup barrier per tile are those of ApplyDma's
 // row-piece mode (lf_apply16_dma.hpp), with two tensors per slot.
@@ -12,7 +12,8 @@
 
 namespace lf {
 
-template <int D, int W> struct BwdRowsCfg {
+// RING: slots; two where the operands take the LDS of the third (bwd_qs16_rows, bf16)
+template <int D, int W, int RING = 3> struct BwdRowsCfg {
   using Sh = Shape16<D>;
   static constexpr int kCPR = Sh::kChunksPerRow;
   static constexpr int kPC = W * kCPR;                          // chunks per row piece
@@ -22,8 +23,8 @@ template <int D, int W> struct BwdRowsCfg {
   static constexpr int kRegionBytes = kNL * 1024;
   static constexpr int kTileBytes = W * kRegionBytes;           // one tensor's tile
   static constexpr int kSlotBytes = 2 * kTileBytes;
-  static constexpr int kRing = 3;
-  static constexpr int kStageOffset = (kRing - 1) * kSlotBytes; // third slot: free before the stream loop
+  static constexpr int kRing = RING;
+  static constexpr int kStageOffset = (kRing - 1) * kSlotBytes; // last slot: free before the stream loop
   static constexpr int kStageBytes = (D * D + D) * 4 + 64;
   static constexpr int kG = (kPC % 16 == 0) ? 16 : ((kPC % 8 == 0) ? 8 : 4);
   static_assert(kTile % W == 0 && kPC % 4 == 0 && kRPR * kG >= 16, "rotation classes must fit a region");
@@ -38,22 +39,44 @@ template <int D, int W> struct BwdRowsCfg {
   static __device__ __forceinline__ int rot(int r) { return ((r * kG) >> 4) & (kG - 1); }
 };
 
-template <typename T, int D, int W>
+template <typename T, int D, int W, int RING = 3>
 struct Ring2Rows {
   using Sh = Shape16<D>;
-  using C = BwdRowsCfg<D, W>;
+  using C = BwdRowsCfg<D, W, RING>;
   static constexpr int NS = NSplit<T>::value;
   static constexpr int KS = Sh::kKS, CPR = C::kCPR, PC = C::kPC, RPR = C::kRPR, HALF = Sh::kHalf, MTB = C::kMTB;
   static constexpr int NL = C::kNL, NE = D * D + D, R = C::kRing, TB = C::kTileBytes;
-  static_assert(R == 3, "the wait counts are written for a ring of three slots");
+  static_assert(R == 2 || R == 3, "ring depths the kernels' wait counts are written for");
 
   const u32x4 *Xh, *Yh;   // first token row of the group's row piece in the two tensors
   int rsx, rsy;           // token strides, 16-byte units
   long long N;
   unsigned char* smem;
   int lane, wave, tok, kg, row_byte, tsw;
-  int trow[NL], xoff[NL], yoff[NL];     // copy side: token row and offsets of the chunk this lane brings
-  int trow_o[NL], ooff[NL], soff[NL];   // store side: token row, chunk inside the row piece, byte in the region
+  // With two slots (see bwd_qs16_rows) registers are short: the places below are worked out where they are used.
+  static constexpr bool kLean = RING == 2;
+  static constexpr int NK = kLean ? 1 : NL;
+  int trow[NK], xoff[NK], yoff[NK];     // copy side: token row and offsets of the chunk this lane brings
+  int trow_o[NK], ooff[NK], soff[NK];   // store side: token row, chunk inside the row piece, byte in the region
+  LF_DEV void copy_place(int u, int& row, int& x, int& y) const {
+    const int P = wave * C::kRegionChunks + u * 64 + lane;   // position in the tile of row pieces
+    // lanes past the region's chunks copy what the lane 32 below copies and deposit it in the padding
+    const int Pc = (u * 64 + lane < C::kRegionChunks) ? P : P - 32;
+    row = Pc / PC;
+    int cc = Pc % PC - C::rot(row);
+    if (cc < 0) cc += PC;
+    x = row * rsx + cc;
+    y = row * rsy + cc;
+  }
+  LF_DEV void store_place(int u, int& row, int& o, int& from) const {
+    const int P = wave * C::kRegionChunks + u * 64 + lane;
+    const int cs = P % PC;               // this lane sends chunk cs of the row ...
+    row = P / PC;
+    int pos = cs + C::rot(row);          // ... which sits at this rotated position of the row piece
+    if (pos >= PC) pos -= PC;
+    o = cs;
+    from = ((row % RPR) * PC + pos) * 16;
+  }
   TileIter it, ahead;
   const float* stage;                    // where the state this wave builds its operands from is staged
 
@@ -67,23 +90,12 @@ struct Ring2Rows {
     kg = lane >> 5;
     row_byte = (tok / RPR) * C::kRegionBytes + (tok % RPR) * PC * 16;
     tsw = wave * CPR + C::rot(tok);
+    if constexpr (!kLean) {
 #pragma unroll
-    for (int u = 0; u < NL; ++u) {
-      const int P = wave * C::kRegionChunks + u * 64 + lane;   // position in the tile of row pieces
-      // lanes past the region's chunks copy what the lane 32 below copies and deposit it in the padding
-      const int Pc = (u * 64 + lane < C::kRegionChunks) ? P : P - 32;
-      const int rc = Pc / PC;
-      int cc = Pc % PC - C::rot(rc);
-      if (cc < 0) cc += PC;
-      trow[u] = rc;
-      xoff[u] = rc * rsx + cc;
-      yoff[u] = rc * rsy + cc;
-      const int r = P / PC, cs = P % PC;   // store side: this lane sends chunk cs of row r ...
-      int pos = cs + C::rot(r);            // ... which sits at this rotated position of the row piece
-      if (pos >= PC) pos -= PC;
-      trow_o[u] = r;
-      ooff[u] = cs;
-      soff[u] = ((r % RPR) * PC + pos) * 16;
+      for (int u = 0; u < NL; ++u) {
+        copy_place(u, trow[u], xoff[u], yoff[u]);
+        store_place(u, trow_o[u], ooff[u], soff[u]);
+      }
     }
   }
 
@@ -117,7 +129,10 @@ struct Ring2Rows {
       unsigned char* sl = tile_ptr(slot, which) + wave * C::kRegionBytes;
 #pragma unroll
       for (int u = 0; u < NL; ++u) {
-        const int c = trow[u] < lim ? (which ? yoff[u] : xoff[u]) : 0;   // rows past N re-read chunk 0; never stored
+        int row, x, y;
+        if constexpr (kLean) copy_place(u, row, x, y);
+        else row = trow[u], x = xoff[u], y = yoff[u];
+        const int c = row < lim ? (which ? y : x) : 0;   // rows past N re-read chunk 0; never stored
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gp + c),
                                          (LF_LDS void*)(sl + u * 1024), 16, 0, 2 /* nt */);
       }
@@ -156,8 +171,11 @@ struct Ring2Rows {
     u32x4* op = Oh + tile * kTile * rso;
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(sl + soff[u]);
-      if (u * 64 + lane < C::kRegionChunks && trow_o[u] < lim) st_stream(op + trow_o[u] * rso + ooff[u], w);
+      int row, o, from;
+      if constexpr (kLean) store_place(u, row, o, from);
+      else row = trow_o[u], o = ooff[u], from = soff[u];
+      const u32x4 w = *reinterpret_cast<const u32x4*>(sl + from);
+      if (u * 64 + lane < C::kRegionChunks && row < lim) st_stream(op + row * rso + o, w);
     }
   }
 
@@ -247,12 +265,48 @@ struct Ring2Rows {
       else *reinterpret_cast<u32x2*>(p) = u32x2{w[0], w[1]};
     }
   }
+  // the same as stored / from words already packed (element 2 i in the low half of word i)
+  LF_DEV void read_half_row_words(int slot, int which, uint32_t (&w)[HALF / 2]) const {
+    constexpr int PB = (HALF % 8 == 0) ? 16 : 8;
+#pragma unroll
+    for (int c = 0; c < HALF * 2 / PB; ++c) {
+      const unsigned char* p = byte_ptr(slot, which, kg * HALF * 2 + c * PB);
+      if constexpr (PB == 16) {
+        const u32x4 t = *reinterpret_cast<const u32x4*>(p);
+        w[4 * c] = t[0]; w[4 * c + 1] = t[1]; w[4 * c + 2] = t[2]; w[4 * c + 3] = t[3];
+      } else {
+        const u32x2 t = *reinterpret_cast<const u32x2*>(p);
+        w[2 * c] = t[0]; w[2 * c + 1] = t[1];
+      }
+    }
+  }
+  LF_DEV void write_half_row_words(int slot, int which, const uint32_t (&w)[HALF / 2]) const {
+    constexpr int PB = (HALF % 8 == 0) ? 16 : 8;
+#pragma unroll
+    for (int c = 0; c < HALF * 2 / PB; ++c) {
+      unsigned char* p = byte_ptr(slot, which, kg * HALF * 2 + c * PB);
+      if constexpr (PB == 16) *reinterpret_cast<u32x4*>(p) = u32x4{w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]};
+      else *reinterpret_cast<u32x2*>(p) = u32x2{w[2 * c], w[2 * c + 1]};
+    }
+  }
   LF_DEV void read_B_raw(int slot, int which, u32x4 (&B)[KS]) const {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int chunk = kg * KS + s;
       B[s] = u32x4{0, 0, 0, 0};
       if (chunk < CPR) B[s] = *reinterpret_cast<const u32x4*>(chunk_ptr(slot, which, chunk));
+    }
+  }
+  // products with the low level of this wave's operands in LDS (frag[t][s][lane])
+  LF_DEV void products_lds(const u32x4 (&A)[1][MTB][KS], const u32x4* Al, const u32x4 (&Bh)[KS], f32x16 (&acc)[MTB]) const {
+#pragma unroll
+    for (int t = 0; t < MTB; ++t) {
+      acc[t] = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        acc[t] = mfma_32x32x16<T>(A[0][t][s], Bh[s], acc[t]);
+        acc[t] = mfma_32x32x16<T>(Al[(t * KS + s) * 64 + lane], Bh[s], acc[t]);
+      }
     }
   }
   LF_DEV void products(const u32x4 (&A)[NS][MTB][KS], const u32x4 (&Bh)[KS], const u32x4* Bl, f32x16 (&acc)[MTB]) const {
@@ -396,40 +450,77 @@ bwd_kv16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout l
 }
 
 // ==========================================================================================
-// bwd_qs16_rows (fp16): bwd_qs16 on a group of W neighbouring heads -- dQ, and the group's share of the state
+// bwd_qs16_rows: bwd_qs16 on a group of W neighbouring heads -- dQ, and the group's share of the state
 // gradient.  grid = (wgs, B * gpb), block = 64 W.  Wave w works on head w of the group for every token of the
 // workgroup's tiles, so its accumulators are that head's whole partial: written (divided by beta) without a sum
 // across waves, as [B*H][gridDim.x][D*D + D] for combine_state.  (The order in which tiles enter a partial differs
 // from the per-head kernel's, so dS, dz and what follows from them -- dK, dV -- agree with it up to fp32 summation
-// order, not bit for bit; dQ does not depend on them.)  LDS: BwdRowsCfg<D, W>::lds_bytes() + 64 W.
+// order, not bit for bit; dQ does not depend on them.)
+// bf16 carries phi(q), g beta / den and e beta in two levels as bwd_qs16 does.  Two waves per SIMD leave 256 registers,
+// some fifty too few (a spill reload would wait for every copy of the ring): the low level of the operands of u = S g and
+// z stay in LDS, where the ring leaves room with two slots, phi' is kept as sign bits, chunk places are worked out where
+// they are used, and where d is no multiple of 16 e is a column of g's last block (dz then needs no accumulators).  Before, bf16 took
+// bwd_q16_rows and the per-head bwd_state16, whose 80-byte rows are fragments of cache lines: 28 + 48 us at 12 x 8 x 4096
+// x 40, 44 us now.  LDS: qs_rows_lds_bytes<T, D, W>().
 // ==========================================================================================
+template <typename T, int D> constexpr bool qs_rows_fits() { return NSplit<T>::value == 1 ? D <= 48 : D <= 40; }   // registers
+template <typename T> constexpr int qs_rows_ring() { return NSplit<T>::value == 1 ? 3 : 2; }
+template <typename T, int D, int W> struct QsRowsLds {
+  using C = BwdRowsCfg<D, W, qs_rows_ring<T>()>;
+  static constexpr int kAWave = NSplit<T>::value == 1 ? 0 : C::kMTB * Shape16<D>::kKS * 1024;   // low operands per wave
+  static constexpr int kA = C::lds_bytes();
+  static constexpr int kE = kA + W * kAWave;                      // e column of every wave
+  static constexpr int kZ = kE + 64 * W;                          // z of every wave (bf16)
+  static constexpr int kStage = C::kSlotBytes + W * C::kOwnBytes; // the waves' states behind the first slot
+  static constexpr int kEnd = kZ + (NSplit<T>::value == 1 ? 0 : W * D * 4);
+  static constexpr bool kOwnStage = NSplit<T>::value == 1 ? C::kOwnStage : kStage <= kE;
+};
+template <typename T, int D, int W> constexpr int qs_rows_lds_bytes() { return QsRowsLds<T, D, W>::kEnd; }
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
 bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G, Layout lg, u32x4* __restrict__ dQ,
               Layout ldq, int gpb, const float* __restrict__ state, float* __restrict__ partials, float eps,
               long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  using RG = Ring2Rows<T, D, W>;
+  using RG = Ring2Rows<T, D, W, qs_rows_ring<T>()>;
   using Sh = Shape16<D>;
-  using C = BwdRowsCfg<D, W>;
-  static_assert(NSplit<T>::value == 1, "single-level operands only (fp16)");
-  constexpr int NS = 1, KS = RG::KS, MTB = RG::MTB, HALF = RG::HALF, NL = RG::NL, R = RG::R, CPR = RG::CPR;
+  using L = QsRowsLds<T, D, W>;
+  constexpr int NS = NSplit<T>::value, KS = RG::KS, MTB = RG::MTB, HALF = RG::HALF, NL = RG::NL, R = RG::R, CPR = RG::CPR;
   constexpr int MT = Sh::kMT, NE = D * D + D;
+  constexpr bool kECol = NS == 2 && Sh::kSpareCol;
   const long long b = blockIdx.y / gpb;
   const long long h0 = (long long)(blockIdx.y % gpb) * W;
   RG rg(Q + (b * lq.batch + h0 * lq.head), lq.row, G + (b * lg.batch + h0 * lg.head), lg.row, N, tiles_per_block,
         blockIdx.x, gridDim.x, smem);
   u32x4* dQg = dQ + (b * ldq.batch + h0 * ldq.head);
-  uint16_t* ecol = reinterpret_cast<uint16_t*>(smem + C::lds_bytes()) + rg.wave * 32;
+  uint16_t* ecol = reinterpret_cast<uint16_t*>(smem + L::kE) + rg.wave * 32;
   rg.prefetch_first();
 
   // every wave its own head's operands
-  u32x4 A[NS][MTB][KS];
-  float zo[HALF];
+  u32x4 A[1][MTB][KS], Alow[MTB][KS];   // (bf16: the low level only until it moves to LDS)
+  float zo[NS == 1 ? HALF : 1];
+  u32x4* Al = reinterpret_cast<u32x4*>(smem + L::kA + rg.wave * L::kAWave);
+  float* zlds = reinterpret_cast<float*>(smem + L::kZ) + rg.wave * D;
+  auto zv = [&](int i) -> float {
+    if constexpr (NS == 1) return zo[i];
+    else return zlds[rg.kg * HALF + i];
+  };
   float inv_aS = 1.0f, beta = 1.0f, inv_beta = 1.0f;
   auto build = [&](float aS) {
-    rg.template build_A<false>(aS, A);
-    rg.load_vec(zo);
+    u32x4 A2[NS][MTB][KS];
+    rg.template build_A<false>(aS, A2);
+#pragma unroll
+    for (int t = 0; t < MTB; ++t)
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        A[0][t][s] = A2[0][t][s];
+        Alow[t][s] = A2[NS - 1][t][s];
+      }
+    if constexpr (NS == 1) {
+      rg.load_vec(zo);
+    } else {
+      for (int i = rg.lane; i < D; i += 64) zlds[i] = rg.stage[D * D + i];
+    }
     inv_aS = 1.0f / aS;
     if constexpr (NORM) {   // power of two near the typical denominator (see bwd_state16)
       const float* z = rg.stage + D * D;
@@ -444,17 +535,24 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
       }
     }
   };
-  if constexpr (C::kOwnStage) {
+  if constexpr (L::kOwnStage) {
     build(rg.stage_state_own(state + (b * lq.H + h0 + rg.wave) * NE));
     __syncthreads();   // the staged states are dead: the second slot may be filled
-    rg.prefetch_second();
+    if constexpr (R == 3) rg.prefetch_second();
   } else {
-    rg.prefetch_second();
+    if constexpr (R == 3) rg.prefetch_second();
     for (int h = 0; h < W; ++h) {   // the heads' states pass through the third slot one after the other
       const float aS = rg.stage_state(state + (b * lq.H + h0 + h) * NE);
       if (rg.wave == h) build(aS);
       __syncthreads();
     }
+  }
+
+  if constexpr (NS == 2) {
+#pragma unroll
+    for (int t = 0; t < MTB; ++t)
+#pragma unroll
+      for (int s = 0; s < KS; ++s) Al[(t * KS + s) * 64 + rg.lane] = Alow[t][s];
   }
 
   f32x4 accS[MT][MT], accZ[MT];
@@ -470,7 +568,7 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
   {   // this wave's rows of the first tile: only the second tile's copies were issued after them
     TileIter second = rg.it;
     second.next();
-    if (second.valid()) wait_vmcnt<2 * NL>();
+    if (R == 3 && second.valid()) wait_vmcnt<2 * NL>();
     else wait_vmcnt<0>();
   }
   lds_barrier();
@@ -488,37 +586,75 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
     u32x4 Bg[KS];
     rg.read_B_raw(slot, 1, Bg);
     f32x16 acc[MTB];
-    rg.products(A, Bg, nullptr, acc);
-    float x[HALF], dr[HALF], rr[HALF];
-    rg.read_half_row(slot, 0, x);
-    float denp = 0.0f, rup = 0.0f;
-#pragma unroll
-    for (int i = 0; i < HALF; ++i) {
-      const float r = phi<FM>(x[i]);
-      const float u = acc[i / 16][i % 16] * inv_aS;
-      denp = __builtin_fmaf(r, zo[i], denp);
-      rup = __builtin_fmaf(r, u, rup);
-      dr[i] = u;
-      rr[i] = ok ? r : 0.0f;
-      x[i] = phi_prime_from<FM>(x[i], r);
-    }
+    if constexpr (NS == 1) rg.products(A, Bg, nullptr, acc);
+    else rg.products_lds(A, Al, Bg, acc);
+    // dq and phi(q) leave this block as the 16-bit words that go to LDS (bf16: phi(q) as a rounded value plus the
+    // remainder).  bf16 is short of registers: it keeps phi'(q) as one sign bit per element and takes the value
+    // back from the two levels of phi(q) (16 significant bits; elu + 1 and relu have phi' = 1 where q > 0, else phi
+    // resp. 0, the identity map 1 everywhere).
+    uint32_t dqw[HALF / 2], rw[NS][HALF / 2];
     float gsc = ok ? 1.0f : 0.0f, e = 0.0f;
-    if constexpr (NORM) {
-      const float den = denp + __shfl_xor(denp, 32) + eps;
-      const float ru = rup + __shfl_xor(rup, 32);
-      const float invden = 1.0f / den;
-      const float go = ru * invden;
+    {
+      uint32_t xw[HALF / 2];   // (the row stays in packed words: registers)
+      rg.read_half_row_words(slot, 0, xw);
+      float x[NS == 1 ? HALF : 1], dr[HALF];
+      float denp = 0.0f, rup = 0.0f;
+      uint64_t pos = 0;   // bit i: q at output channel i is positive
 #pragma unroll
-      for (int i = 0; i < HALF; ++i) dr[i] = (dr[i] - go * zo[i]) * invden * x[i];
-      gsc = ok ? invden * beta : 0.0f;
-      e = ok ? -go * invden * beta : 0.0f;
-    } else {
+      for (int i = 0; i < HALF; i += 2) {
+        float r[2], xi[2];
+        unpack2<T>(xw[i / 2], xi[0], xi[1]);
 #pragma unroll
-      for (int i = 0; i < HALF; ++i) dr[i] *= x[i];
+        for (int q = 0; q < 2; ++q) {
+          r[q] = phi<FM>(xi[q]);
+          const float u = acc[(i + q) / 16][(i + q) % 16] * inv_aS;
+          denp = __builtin_fmaf(r[q], zv(i + q), denp);
+          rup = __builtin_fmaf(r[q], u, rup);
+          dr[i + q] = u;
+          if constexpr (NS == 1) x[i + q] = phi_prime_from<FM>(xi[q], r[q]);
+          else pos |= (uint64_t)(xi[q] > 0.0f ? 1u : 0u) << (i + q);
+          r[q] = ok ? r[q] : 0.0f;
+        }
+        if constexpr (NS == 1) rw[0][i / 2] = pack2<T>(r[0], r[1]);
+        else pack2_split<T>(r[0], r[1], rw[0][i / 2], rw[1][i / 2]);
+      }
+      auto phi_prime = [&](int i) -> float {
+        if constexpr (NS == 1) {
+          return x[i];
+        } else if constexpr (FM == kPhiIdentity) {
+          return 1.0f;
+        } else {
+          float h[2], l[2];
+          unpack2<T>(rw[0][i / 2], h[0], h[1]);
+          unpack2<T>(rw[1][i / 2], l[0], l[1]);
+          const float below = FM == kPhiRelu ? 0.0f : h[i & 1] + l[i & 1];
+          return (pos >> i) & 1u ? 1.0f : below;
+        }
+      };
+      if constexpr (NORM) {
+        const float den = denp + __shfl_xor(denp, 32) + eps;
+        const float ru = rup + __shfl_xor(rup, 32);
+        const float invden = 1.0f / den;
+        const float go = ru * invden;
+#pragma unroll
+        for (int i = 0; i < HALF; ++i) dr[i] = (dr[i] - go * zv(i)) * invden * phi_prime(i);
+        gsc = ok ? invden * beta : 0.0f;
+        e = ok ? -go * invden * beta : 0.0f;
+      } else {
+#pragma unroll
+        for (int i = 0; i < HALF; ++i) dr[i] *= phi_prime(i);
+      }
+#pragma unroll
+      for (int i = 0; i < HALF / 2; ++i) dqw[i] = pack2<T>(dr[2 * i], dr[2 * i + 1]);
     }
-    // ---- phi(q), g beta / den and e beta take the places of this head's columns ----------------------
+    // ---- phi(q), g beta / den and e beta take the tiles' places --------------------------------------
+    // bf16 carries each as two 8-bit levels.  The remainders take the same places once the rounded values have
+    // been read into operands (a wave's LDS operations retire in order), so no LDS beyond the ring is needed.
+    u32x4 glo[NS == 2 ? KS : 1];
+    uint32_t elo = 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    rg.write_half_row(slot, 0, rr);
+    rg.write_half_row_words(slot, 0, rw[0]);
+    if constexpr (NS == 2) rg.read_B_raw(slot, 1, Bg);   // (again rather than kept: registers)
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int chunk = rg.kg * KS + s;
@@ -528,42 +664,119 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
         for (int c = 0; c < 4; ++c) {
           float g0, g1;
           unpack2<T>(Bg[s][c], g0, g1);
-          w[c] = pack2<T>(g0 * gsc, g1 * gsc);
+          if constexpr (NS == 1) {
+            w[c] = pack2<T>(g0 * gsc, g1 * gsc);
+          } else {
+            uint32_t h, l;
+            pack2_split<T>(g0 * gsc, g1 * gsc, h, l);
+            w[c] = h;
+            glo[s][c] = l;
+          }
         }
         *reinterpret_cast<u32x4*>(rg.chunk_ptr(slot, 1, chunk)) = w;
       }
     }
-    if (rg.kg == 0) ecol[rg.tok] = (uint16_t)pack2<T>(e, 0.0f);
+    if constexpr (NS == 1) {
+      if (rg.kg == 0) ecol[rg.tok] = (uint16_t)pack2<T>(e, 0.0f);
+    } else {
+      uint32_t eh;
+      pack2_split<T>(e, 0.0f, eh, elo);
+      if (rg.kg == 0) ecol[rg.tok] = (uint16_t)eh;
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // ---- dS, dz: token-major operands by transposing reads --------------------------------------------
-    {
-      u32x4 bfrag[MT], bfe = u32x4{0, 0, 0, 0};
-      if (j16 == 0) bfe = *reinterpret_cast<const u32x4*>(ecol + 8 * g4);
+    auto read_a = [&](int a) {
+      const u32x2 r0 = lds_read_tr16(rg.tr_ptr(slot, 0, tr_row, 16 * a + tr_col));
+      const u32x2 r1 = lds_read_tr16(rg.tr_ptr(slot, 0, tr_row + 4, 16 * a + tr_col));
+      return u32x4{r0[0], r0[1], r1[0], r1[1]};
+    };
+    auto read_b = [&](int b) {
+      const u32x2 r0 = lds_read_tr16(rg.tr_ptr(slot, 1, tr_row, 16 * b + tr_col));
+      const u32x2 r1 = lds_read_tr16(rg.tr_ptr(slot, 1, tr_row + 4, 16 * b + tr_col));
+      return u32x4{r0[0], r0[1], r1[0], r1[1]};
+    };
+    // the lanes of g's last block that lie past d: lane D % 16 takes e
+    auto with_e = [&](u32x4 w) {
+      const u32x4 ev = *reinterpret_cast<const u32x4*>(ecol + 8 * g4);
 #pragma unroll
-      for (int bb = 0; bb < MT; ++bb) {
-        const u32x2 r0 = lds_read_tr16(rg.tr_ptr(slot, 1, tr_row, 16 * bb + tr_col));
-        const u32x2 r1 = lds_read_tr16(rg.tr_ptr(slot, 1, tr_row + 4, 16 * bb + tr_col));
-        bfrag[bb] = u32x4{r0[0], r0[1], r1[0], r1[1]};
+      for (int i = 0; i < 4; ++i) w[i] = j16 == D % 16 ? ev[i] : w[i];
+      return w;
+    };
+    auto read_e = [&]() {
+      u32x4 w = u32x4{0, 0, 0, 0};
+      if (j16 == 0) w = *reinterpret_cast<const u32x4*>(ecol + 8 * g4);
+      return w;
+    };
+    if constexpr (NS == 1) {
+      u32x4 bfrag[MT];
+      const u32x4 bfe = read_e();
+#pragma unroll
+      for (int b = 0; b < MT; ++b) bfrag[b] = read_b(b);
+#pragma unroll
+      for (int a = 0; a < MT; ++a) {
+        const u32x4 afrag = read_a(a);
+#pragma unroll
+        for (int b = 0; b < MT; ++b) accS[a][b] = mfma_16x16x32<T>(afrag, bfrag[b], accS[a][b]);
+        accZ[a] = mfma_16x16x32<T>(afrag, bfe, accZ[a]);
+      }
+    } else {
+      // rounded x rounded, remainder x rounded, rounded x remainder; the remainders' operands live one at a time
+      u32x4 ah[MT], bh[MT];
+      u32x4 beh = u32x4{0, 0, 0, 0};
+      if constexpr (!kECol) beh = read_e();
+#pragma unroll
+      for (int b = 0; b < MT; ++b) bh[b] = read_b(b);
+      if constexpr (kECol) bh[MT - 1] = with_e(bh[MT - 1]);
+#pragma unroll
+      for (int a = 0; a < MT; ++a) ah[a] = read_a(a);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      rg.write_half_row_words(slot, 0, rw[NS - 1]);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const int chunk = rg.kg * KS + s;
+        if (chunk < CPR) *reinterpret_cast<u32x4*>(rg.chunk_ptr(slot, 1, chunk)) = glo[s];
+      }
+      if (rg.kg == 0) ecol[rg.tok] = (uint16_t)elo;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int a = 0; a < MT; ++a) {
+#pragma unroll
+        for (int b = 0; b < MT; ++b) accS[a][b] = mfma_16x16x32<T>(ah[a], bh[b], accS[a][b]);
+        if constexpr (!kECol) accZ[a] = mfma_16x16x32<T>(ah[a], beh, accZ[a]);
       }
 #pragma unroll
       for (int a = 0; a < MT; ++a) {
-        const u32x2 r0 = lds_read_tr16(rg.tr_ptr(slot, 0, tr_row, 16 * a + tr_col));
-        const u32x2 r1 = lds_read_tr16(rg.tr_ptr(slot, 0, tr_row + 4, 16 * a + tr_col));
-        const u32x4 afrag = u32x4{r0[0], r0[1], r1[0], r1[1]};
+        const u32x4 al = read_a(a);
 #pragma unroll
-        for (int bb = 0; bb < MT; ++bb) accS[a][bb] = mfma_16x16x32<T>(afrag, bfrag[bb], accS[a][bb]);
-        accZ[a] = mfma_16x16x32<T>(afrag, bfe, accZ[a]);
+        for (int b = 0; b < MT; ++b) accS[a][b] = mfma_16x16x32<T>(al, bh[b], accS[a][b]);
+        if constexpr (!kECol) accZ[a] = mfma_16x16x32<T>(al, beh, accZ[a]);
+      }
+#pragma unroll
+      for (int b = 0; b < MT; ++b) {
+        u32x4 bl = read_b(b);
+        if constexpr (kECol) {
+          if (b == MT - 1) bl = with_e(bl);
+        }
+#pragma unroll
+        for (int a = 0; a < MT; ++a) accS[a][b] = mfma_16x16x32<T>(ah[a], bl, accS[a][b]);
+      }
+      if constexpr (!kECol) {
+        const u32x4 bel = read_e();
+#pragma unroll
+        for (int a = 0; a < MT; ++a) accZ[a] = mfma_16x16x32<T>(ah[a], bel, accZ[a]);
       }
     }
     // ---- dq takes the place of this head's columns of the Q tile --------------------------------------
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    rg.write_half_row(slot, 0, dr);
+    rg.write_half_row_words(slot, 0, dqw);
 
     rg.it.next();
     rg.ahead.next();
     if (rg.it.valid()) {
       // after the copies of tile j+1 came the stores of tile j-1 (dq only) and the copies of tile j+2
-      if (have_prev && copied) wait_vmcnt<3 * NL>();
+      // (two slots: the copies of tile j+1 are the last that were issued)
+      if (R == 2) wait_vmcnt<0>();
+      else if (have_prev && copied) wait_vmcnt<3 * NL>();
       else if (copied) wait_vmcnt<2 * NL>();
       else if (have_prev) wait_vmcnt<NL>();
       else wait_vmcnt<0>();
@@ -587,8 +800,9 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
         for (int bb = 0; bb < MT; ++bb) {
           const int col = bb * 16 + j16;
           if (col < D) dst[row * D + col] = accS[a][bb][i] * inv_beta;
+          else if (kECol && col == D) dst[D * D + row] = accS[a][bb][i] * inv_beta;
         }
-        if (j16 == 0) dst[D * D + row] = accZ[a][i] * inv_beta;
+        if (!kECol && j16 == 0) dst[D * D + row] = accZ[a][i] * inv_beta;
       }
     }
   }

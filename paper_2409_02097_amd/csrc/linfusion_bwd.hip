@@ -80,6 +80,14 @@ int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   int most = p->splits > p->gsplits ? p->splits : p->gsplits;
   if (p->apply_wgs > most) most = p->apply_wgs;   // the merged dQ + state-gradient kernel writes one partial each
   if (p->apply1_wgs > most) most = p->apply1_wgs;
+  // ... and so does its row-piece form: one workgroup of eight waves per CU (two up to 16 channels), every one of which
+  // serves a whole group of heads.  (With room for the per-head kernels' partials only, 12 x 8 heads left it 60
+  // workgroups: 81 us at 4096 tokens of 40 fp16 channels, 33 us with all of the chip.)
+  if (H % 4 == 0 && d <= 48 && (d * 2) % 128 != 0) {
+    const int w = H % 8 == 0 ? 8 : 4;
+    const long long rows = (long long)lfh::num_cu() * (d <= 16 ? 2 : 1) * (8 / w) / ((long long)B * (H / w));
+    if (rows > most) most = (int)(rows < n_tiles ? rows : n_tiles);
+  }
   p->most = most;
   p->ws_partials = up((size_t)BH * most * p->ne * sizeof(float));
   p->ws_state = up((size_t)BH * p->ne * sizeof(float));
@@ -146,12 +154,12 @@ int launch_kv_rows(const BwdArgs& a, const float* stateD) {
   return LINFUSION_OK;
 }
 
-// dQ and the state gradient in one pass (fp16, d <= 48) on groups of heads: as launch_kv_rows; *wgs_used = partial
+// dQ and the state gradient in one pass (fp16 d <= 48, bf16 d <= 40) on groups of heads: as launch_kv_rows; *wgs_used = partial
 // states per head written for combine_state
 template <typename T, int D, int FM, bool NORM, int W>
 int launch_qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* wgs_used) {
   using namespace lf;
-  constexpr int lds = BwdRowsCfg<D, W>::lds_bytes() + 64 * W;
+  constexpr int lds = qs_rows_lds_bytes<T, D, W>();
   static_assert(lds <= 160 * 1024, "workgroup LDS limit of the device");
   if (!allow_lds(bwd_qs16_rows<T, D, FM, NORM, W>, lds)) return LINFUSION_ERR_HIP;
   const int gpb = a.H / W;
@@ -172,7 +180,7 @@ int launch_qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* 
   return LINFUSION_OK;
 }
 
-// dQ and the per-token scalars (the separate-kernel path: bf16, d > 48) on groups of heads
+// dQ and the per-token scalars (the separate-kernel path: fp16 d > 48, bf16 d > 40) on groups of heads
 template <typename T, int D, int FM, bool NORM, int W>
 int launch_q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal) {
   using namespace lf;
@@ -237,7 +245,7 @@ bool q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal, int* rc) {
 template <typename T, int D, int FM, bool NORM>
 bool qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* wgs_used, int* rc) {
   constexpr int CPR = D / 8;
-  if constexpr ((D * 2) % 128 == 0 || lf::NSplit<T>::value != 1 || D > 48) {
+  if constexpr ((D * 2) % 128 == 0 || !lf::qs_rows_fits<T, D>()) {
     return false;
   } else {
     if (a.lq.head != CPR || a.lg.head != CPR || a.ldq.head != CPR) return false;
@@ -370,10 +378,10 @@ int run_bwd(const BwdArgs& a) {
     if (rcs != LINFUSION_OK) return rcs;
     combine_state<0><<<gc, dim3(kCombineThreads), 0, st>>>(partials, nparts, NE, stateS);
   }
-  // dQ and the state gradient in one pass over Q and dout.  Its row-piece form exists for fp16 up to d = 48; where
+  // dQ and the state gradient in one pass over Q and dout.  Its row-piece form exists for fp16 up to d = 48, bf16 up to 40; where
   // the layout asks for row-piece kernels and that form is missing, the separate row-piece kernels are kept.
   constexpr bool kMerged = !(NSplit<T>::value == 2 && D == 80);   // bf16 at d = 80: measured slower than the separate kernels
-  constexpr bool kQsRows = NSplit<T>::value == 1 && D <= 48;
+  constexpr bool kQsRows = lf::qs_rows_fits<T, D>();
   if constexpr (kMerged) {
     bool merged = lfh::env_int("LINFUSION_BWD_MERGED", 1) == 1;
     if (!kQsRows && q_rows_wanted<D>(a)) merged = false;
