@@ -26,7 +26,7 @@ struct WideReduceArgs {
   hipStream_t st;
 };
 
-// pack + apply:  out_t = phi(q_t) S / (phi(q_t) z + eps)   (unnorm: phi(q_t) S)   from a given fp32 state
+// out_t = phi(q_t) S / (phi(q_t) z + eps)   (unnorm: phi(q_t) S)
 struct WideApplyArgs {
   const void* q;
   void* out;
@@ -58,6 +58,16 @@ struct WideArgs {
   hipEvent_t* ev;             // null, or four events: before reduce, after it, after combine, after apply
 };
 
+// Most state-reduction workgroups per head that pay: each adds a partial of 4 (d^2 + d) bytes per head that is written and
+// read again, about 0.5 us per MB over all heads, and takes its share of about 1.5 us per tile from the others, so the sum
+// is least at sqrt(3 tiles / MB).  (One partial per two tiles, as two workgroups per CU gave, against this, us per call:
+// fp16 12 x 8 x 256 x 160 39.6 -> 33.7 and its training step 131.9 -> 108.2; 2 x 8 x 1024 x 160 35.6 -> 29.5; bf16 4 x 16 x
+// 512 x 128 36.6 -> 30.7.)  Long streams stay at what fills the chip.
+inline long long wide_most_splits(long long heads, long long tiles, int d) {
+  const double mb = (double)heads * ((double)d * d + d) * 4e-6;
+  const double s = __builtin_sqrt(3.0 * (double)tiles / mb) + 0.5;
+  return s < 1.0 ? 1 : (s > 1e6 ? 1000000 : (long long)s);
+}
 // head widths the wide kernels are built for
 bool wide_supported(int d);
 // whether apply16_wave is built for this width and dtype (its state operands must fit one wave's registers)
@@ -69,8 +79,11 @@ int run_wide(const WideArgs& a);
 // the forward plan's launch shape for a wide width (linfusion.hip), and the bytes its partial states take;
 // LINFUSION_ERR_UNSUPPORTED for other widths
 int wide_launch_plan(int B, int H, long long N, int d, int dtype, WidePlan* wp, size_t* partial_bytes);
-// the two halves by themselves (the backward pass for these widths is composed of them)
+// For the backward pass of these widths: the reduction by itself -- the summed state in a.state, or the partials as they
+// are (a single one is the state, in a.state) -- and the apply kernel of one wave per tile on operands that lie packed
+// (PackWave's layout) already; a.state is not read.
 int run_wide_reduce(const WideReduceArgs& a);
-int run_wide_apply(const WideApplyArgs& a);
+int run_wide_reduce_partials(const WideReduceArgs& a);
+int run_wide_apply_packed(const WideApplyArgs& a);
 
 }  // namespace lfw

@@ -1,5 +1,5 @@
-// Translation unit of the library: the composed backward pass (lf_backward_wide.hpp) -- fp16 at head widths above
-// 80 on the forward's wide state reduction and apply kernels -- and its small kernels.
+// Translation unit of the library: the fp16 backward pass at head widths above 80 (lf_backward_wide.hpp), on its own two
+// kernels and the forward's wide state reduction and apply.
 #include "../../include/linfusion.h"
 
 #include "lf_backward_wide.hpp"
@@ -14,100 +14,82 @@ namespace {
 size_t up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Regions {
-  lfw::WidePlan wplan;        // the wide kernels' launch shape
-  int zsplits;
-  size_t ne;
-  size_t partials, state, tstate, dstate, tdstate, packed, aux, dzpart, scal, u, gp, tk, total;   // byte offsets
+  lfw::WidePlan plan;         // the wide kernels' launch shape
+  int wgs;                    // workgroups per head of bwdw_q and bwdw_k: one per CU, every wave a tile
+  size_t partials, state, dstate, packed, packed_t, dzpart, gp, total;   // byte offsets
 };
 
 int make_regions(int B, int H, long long N, int d, int dtype, Regions* r) {
   size_t pbytes = 0;
-  int rc = lfw::wide_launch_plan(B, H, N, d, dtype, &r->wplan, &pbytes);
+  const int rc = lfw::wide_launch_plan(B, H, N, d, dtype, &r->plan, &pbytes);
   if (rc != LINFUSION_OK) return rc;
   const size_t BH = (size_t)B * H;
-  r->ne = (size_t)d * d + d;
-  long long zs = (N + 31) / 32;   // dz partials: at least 32 tokens each
-  r->zsplits = (int)(zs < 1 ? 1 : (zs > 64 ? 64 : zs));
-  const size_t st = up(BH * r->ne * sizeof(float));
-  const size_t tensor = up(BH * (size_t)N * d * 2);
+  const long long tiles = (N + 15) / 16, most = (tiles + lf::kWavesPerWG - 1) / lf::kWavesPerWG;
+  long long wgs = lfh::env_int("LINFUSION_BWDW_WGS", lfh::num_cu()) / (long long)BH;
+  r->wgs = (int)(wgs > most ? most : (wgs < 1 ? 1 : wgs));
+  {   // dv: the forward's one-wave-per-tile apply, whatever the forward plan takes; 32-token tiles
+    const long long t32 = ((N + lf::kTile - 1) / lf::kTile + lf::kWavesPerWG - 1) / lf::kWavesPerWG;
+    r->plan.wave_apply = true;
+    r->plan.apply_wgs = (int)(wgs > t32 ? t32 : (wgs < 1 ? 1 : wgs));
+    r->plan.blk_apply = lf::kWavesPerWG;
+  }
+  const size_t st = up(BH * ((size_t)d * d + d) * sizeof(float));
+  const size_t pk = up(BH * lfw::wide_packed_bytes(d, dtype));
   size_t o = 0;
   r->partials = o; o += up(pbytes);
   r->state = o; o += st;
-  r->tstate = o; o += st;
   r->dstate = o; o += st;
-  r->tdstate = o; o += st;
-  r->packed = o; o += up(BH * lfw::wide_packed_bytes(d, dtype));
-  r->aux = o; o += up(BH * 2 * sizeof(float));
-  r->dzpart = o; o += up(BH * r->zsplits * d * sizeof(float));
-  r->scal = o; o += up(BH * (size_t)N * sizeof(float));
-  r->u = o; o += tensor;
-  r->gp = o; o += tensor;
-  r->tk = o; o += tensor;
+  r->packed = o; o += pk;
+  r->packed_t = o; o += pk;
+  r->dzpart = o; o += up(BH * r->wgs * d * sizeof(float));
+  r->gp = o; o += up(BH * (size_t)N * d * 2);
   r->total = o;
   return LINFUSION_OK;
-}
-
-// the two primitives
-int reduce_to_state(const BwdWideArgs& a, const Regions& r, const void* k, lf::Layout lk, const void* v, lf::Layout lv,
-                    int fm, float* partials, float* state) {
-  const lfw::WideReduceArgs x{k, v, a.B, a.H, a.N, a.d, a.dtype, fm, lk, lv, partials, state, r.wplan, a.st};
-  return lfw::run_wide_reduce(x);
-}
-// out = phi(in) state, no normalizer
-int apply_state(const BwdWideArgs& a, const Regions& r, const void* in, lf::Layout li, void* out, lf::Layout lo, int fm,
-                const float* state) {
-  const lfw::WideApplyArgs x{in, out, a.B, a.H, a.N, a.d, a.dtype, fm, 0.0f, true, li, lo, state, a.ws + r.packed,
-                             r.wplan, a.st};
-  return lfw::run_wide_apply(x);
 }
 
 template <int D, int FM, bool NORM>
 int run(const BwdWideArgs& a, const Regions& r) {
   using namespace lf;
-  constexpr int CPR = D / kBwdPer;
+  constexpr int CPR = D / 8, lds = BwdWaveShape<D>::kLdsBytes;
   const long long BH = (long long)a.B * a.H;
   hipStream_t st = a.st;
   unsigned char* ws = a.ws;
   float* partials = reinterpret_cast<float*>(ws + r.partials);
-  float* raw = reinterpret_cast<float*>(ws + r.state);      // the forward state if computed here; later dS' as reduced
-  float* tstate = reinterpret_cast<float*>(ws + r.tstate);
-  float* dstate = reinterpret_cast<float*>(ws + r.dstate);
-  float* tdstate = reinterpret_cast<float*>(ws + r.tdstate);
-  float* aux = reinterpret_cast<float*>(ws + r.aux);
+  float* whole = reinterpret_cast<float*>(ws + r.state);
+  float* dwhole = reinterpret_cast<float*>(ws + r.dstate);
+  unsigned char *packed = ws + r.packed, *packed_t = ws + r.packed_t;
   float* dzpart = reinterpret_cast<float*>(ws + r.dzpart);
-  float* scal = reinterpret_cast<float*>(ws + r.scal);
-  void* U = ws + r.u;
   void* GP = ws + r.gp;
-  void* TK = ws + r.tk;
-  // dense [B, H, N, D] temporaries, in 16-byte units
-  const Layout dense{(long long)a.H * a.N * CPR, a.N * CPR, CPR, a.H};
-  const dim3 blk(kBwdWideThreads);
-  const dim3 per_token((unsigned)((a.N + 3) / 4), (unsigned)BH);
-  const dim3 strips(D / kBwdStrip, (unsigned)BH);
+  const Layout dense{(long long)a.H * a.N * CPR, a.N * CPR, CPR, a.H};   // [B, H, N, D], in 16-byte units
+  const dim3 blk(kThreads), grid(r.wgs, (unsigned)BH);
+  const int splits = r.plan.splits;
   int rc;
+  if (!lfh::allow_lds(bwdw_q<D, FM, NORM>, lds) || !lfh::allow_lds(bwdw_k<D, FM>, lds)) return LINFUSION_ERR_HIP;
 
   // the forward state, unless the caller kept it
   const float* state = a.saved_state;
   if (!state) {
-    if ((rc = reduce_to_state(a, r, a.k, a.lkv, a.v, a.lkv, FM, partials, raw)) != LINFUSION_OK) return rc;
-    state = raw;
+    const lfw::WideReduceArgs x{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, FM, a.lkv, a.lkv, partials, whole, r.plan, st};
+    if ((rc = lfw::run_wide_reduce(x)) != LINFUSION_OK) return rc;
+    state = whole;
   }
-  bwdw_prep_state<D, NORM><<<strips, blk, 0, st>>>(state, tstate, aux);
-  // u' = S' g
-  if ((rc = apply_state(a, r, a.g, a.lg, U, dense, kPhiIdentity, tstate)) != LINFUSION_OK) return rc;
-  bwdw_q_finish<D, FM, NORM><<<per_token, blk, 0, st>>>((const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg,
-                                                           (const u32x4*)U, tstate, aux, (u32x4*)a.dq, a.ldq,
-                                                           (u32x4*)GP, scal, a.eps, a.N);
-  // dS' = sum phi(q)^T gp;  dz' = sum phi(q) e'
-  if ((rc = reduce_to_state(a, r, a.q, a.lq, GP, dense, FM, partials, raw)) != LINFUSION_OK) return rc;
-  bwdw_dz<D, FM><<<dim3(r.zsplits, (unsigned)BH), blk, 0, st>>>((const uint16_t*)a.q, a.lq, scal, dzpart, a.N);
-  bwdw_finish_state<D><<<strips, blk, 0, st>>>(raw, dstate, tdstate, dzpart, r.zsplits, aux);
+  const float* z = NORM ? state + D * D : nullptr;
+  bwdw_pack<D><<<dim3(D / 16, (unsigned)BH, 1), blk, 0, st>>>(state, 1, z, packed, packed_t, 1);
+  bwdw_q<D, FM, NORM><<<grid, blk, lds, st>>>((const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, (u32x4*)a.dq, a.ldq,
+                                              (u32x4*)GP, packed_t, z, dzpart, a.eps, a.N, kWavesPerWG);
+  // dS' = sum phi(q)^T gp: as partials where the packing sums them (see kPackParts)
+  const bool sum_first = splits > kPackParts;
+  const lfw::WideReduceArgs x{a.q, GP, a.B, a.H, a.N, a.d, a.dtype, FM, a.lq, dense, partials, dwhole, r.plan, st};
+  if ((rc = sum_first ? lfw::run_wide_reduce(x) : lfw::run_wide_reduce_partials(x)) != LINFUSION_OK) return rc;
+  const bool parts = !sum_first && splits > 1;   // (one partial: the reduction wrote the state itself)
+  bwdw_pack<D><<<dim3(D / 16, (unsigned)BH, 2), blk, 0, st>>>(parts ? partials : dwhole, parts ? splits : 1, z, packed,
+                                                              packed_t, 0);
   // dv = dS^T phi(k)
-  if ((rc = apply_state(a, r, a.k, a.lkv, a.dv, a.ldkv, FM, dstate)) != LINFUSION_OK) return rc;
-  // t = dS v;  dk = (t + dz) phi'(k)
-  if ((rc = apply_state(a, r, a.v, a.lkv, TK, dense, kPhiIdentity, tdstate)) != LINFUSION_OK) return rc;
-  bwdw_k_finish<D, FM><<<per_token, blk, 0, st>>>((const u32x4*)a.k, a.lkv, (const u32x4*)TK, dstate,
-                                                     (u32x4*)a.dk, a.ldkv, a.N);
+  const lfw::WideApplyArgs y{a.k, a.dv, a.B, a.H, a.N, a.d, a.dtype, FM, 0.0f, true, a.lkv, a.ldkv, nullptr, packed, r.plan, st};
+  if ((rc = lfw::run_wide_apply_packed(y)) != LINFUSION_OK) return rc;
+  // dk = (dS v + dz) phi'(k)
+  bwdw_k<D, FM><<<grid, blk, lds, st>>>((const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (u32x4*)a.dk, a.ldkv, packed_t, dzpart,
+                                        r.wgs, a.N, kWavesPerWG);
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
 

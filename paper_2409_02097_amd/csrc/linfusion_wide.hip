@@ -53,7 +53,7 @@ int reduce(const WideReduceArgs& a, hipEvent_t* ev, bool combine) {
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
 
-// `parts`: a.state holds that many partials per head; with `keep` their sum goes there.  `ev`: recorded between packing
+// `parts`: a.state holds that many partials per head; with `keep` their sum goes there (0: packed already).  `ev`: recorded between packing
 // and apply.
 template <typename T, int D>
 int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent_t* ev = nullptr) {
@@ -78,7 +78,7 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
   if constexpr (wave_ok<T, D>()) {                                                                          \
     constexpr int lds2 = apply16_wave_lds_bytes<D>();                                                        \
     if (!allow_lds(apply16_wave<T, D, FM, NORM>, lds2)) return LINFUSION_ERR_HIP;                            \
-    launch_pack_wave<D>(a.state, parts, keep, a.packed, NORM, (unsigned)BH, st);                             \
+    if (parts > 0) launch_pack_wave<D>(a.state, parts, keep, a.packed, NORM, (unsigned)BH, st);              \
     if (ev) (void)hipEventRecord(*ev, st);                                                                   \
     apply16_wave<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq, O, a.lo, all, a.packed, a.eps, a.N,         \
                                                         a.plan.blk_apply);                                   \
@@ -168,10 +168,20 @@ int run_wide_reduce(const WideReduceArgs& a) {
   return LINFUSION_ERR_UNSUPPORTED;
 }
 
-int run_wide_apply(const WideApplyArgs& a) {
+int run_wide_reduce_partials(const WideReduceArgs& a) {
   switch (a.d) {
 #define X(DD) \
-  case DD: return a.dtype == LINFUSION_DTYPE_F16 ? apply<lf::F16, DD>(a) : apply<lf::BF16, DD>(a);
+  case DD: return a.dtype == LINFUSION_DTYPE_F16 ? reduce<lf::F16, DD>(a, nullptr, false) : reduce<lf::BF16, DD>(a, nullptr, false);
+    LFW_FOR_D(X)
+#undef X
+  }
+  return LINFUSION_ERR_UNSUPPORTED;
+}
+
+int run_wide_apply_packed(const WideApplyArgs& a) {
+  if (!a.plan.wave_apply || a.dtype != LINFUSION_DTYPE_F16) return LINFUSION_ERR_UNSUPPORTED;
+  switch (a.d) {
+#define X(DD) case DD: return apply<lf::F16, DD>(a, 0);
     LFW_FOR_D(X)
 #undef X
   }
