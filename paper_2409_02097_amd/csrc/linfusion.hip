@@ -177,12 +177,21 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       const double bytes = 4.0 * (double)BH * (double)N * d * 2.0;
       if (d <= 128 && bytes >= 768.0 * 1048576.0) reduce_per_cu = (d <= 96 && dtype == LINFUSION_DTYPE_BF16) ? 4 : 3;
     }
-    p->splits = per_head(env_int("LINFUSION_WIDE_REDUCE_WGS", reduce_per_cu * num_cu()), 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce);
+    const long long most = lfw::wide_most_splits(BH, p->n_tiles, d);
+    int want = reduce_per_cu * num_cu(), room = 0;
+    if (want > most * BH) {
+      // (the entry point with the fixed scratch array keeps asking for what the chip-filling launch needs, so that it
+      // takes and refuses the shapes that it always did)
+      if (compact) room = per_head(want, 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce);
+      want = (int)(most * BH);
+    }
+    p->splits = per_head(env_int("LINFUSION_WIDE_REDUCE_WGS", want), 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce);
     // a head of one or two tiles: one workgroup sums them and writes the state itself (no partials, no combine
     // launch; from four tiles on a workgroup's tiles in sequence cost more than the launch saved)
     if (p->n_tiles <= env_int("LINFUSION_WIDE_ONE_SPLIT_TILES", 2)) {
       p->splits = 1;
       p->blk_reduce = (int)p->n_tiles;
+      room = 0;
     }
     // apply: a wave per tile with the head's whole state in its registers where that fits (one workgroup
     // per CU, long-lived: its prologue loads the (d + 2) x d operands), else the workgroup-shared tiles
@@ -213,7 +222,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     if (flags & (LINFUSION_FLAG_FORCE_FUSED | LINFUSION_FLAG_FORCE_SOLO)) return LINFUSION_ERR_UNSUPPORTED;
     p->state_floats = (size_t)d * d + d;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    p->ws_partials = up((size_t)BH * p->splits * p->state_floats * sizeof(float));
+    p->ws_partials = up((size_t)BH * (room > p->splits ? room : p->splits) * p->state_floats * sizeof(float));
     p->ws_state = up((size_t)BH * p->state_floats * sizeof(float));
     // in place of the single-launch flags: the state as apply operands
     p->ws_sync = up((size_t)BH * lfw::wide_packed_bytes(d, dtype));

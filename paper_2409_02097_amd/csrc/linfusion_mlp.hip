@@ -35,12 +35,6 @@ bool rows_supported(int H, int d) {
   return false;
 }
 
-size_t pack_bytes(int d, int dtype) {
-  const size_t ns = dtype == LINFUSION_DTYPE_BF16 ? 2 : 1;
-  const size_t frags = ns * (size_t)((d / 2 + 2 + 15) / 16) * (size_t)((d / 8 + 1) / 2);   // Pack16<T, D>::kFrags
-  return 256 + frags * 1024;
-}
-
 int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
   if (B <= 0 || H <= 0 || N <= 0 || d <= 0) return LINFUSION_ERR_INVALID;
   if (B > 65535) return LINFUSION_ERR_INVALID;   // grid.y limit
@@ -82,7 +76,7 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     p->stats_wgs = (int)(sw < cap ? sw : cap);
     p->ws_partials = up((size_t)B * H * p->splits * p->ne * sizeof(float));
     p->ws_state = up((size_t)B * H * p->ne * sizeof(float));
-    p->ws_pack = up((size_t)B * H * pack_bytes(d, dtype));
+    p->ws_pack = 0;
     p->ws_stats = up((size_t)2 * B * p->n_pad * 2 * sizeof(float));
     p->ws_total = p->ws_partials + p->ws_state + p->ws_pack + p->ws_stats;
     return LINFUSION_OK;
@@ -110,7 +104,12 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     const int slot = (lf::kTile * d * 2 + 1023) / 1024 * 1024;
     const int lds_apply = (2 * 3 * slot + 3 * 1024) * lf::kWavesPerWG;
     const int resident = (!wide && 160 * 1024 / lds_apply > 0) ? 160 * 1024 / lds_apply : 1;
-    p->splits = per_head(lfh::env_int("LINFUSION_MLPH_REDUCE_WGS", 2 * lfh::num_cu()),
+    long long want = 2 * lfh::num_cu();
+    if (wide) {
+      const long long most = lfw::wide_most_splits(units, n_tiles, d) * units;
+      if (want > most) want = most;
+    }
+    p->splits = per_head(lfh::env_int("LINFUSION_MLPH_REDUCE_WGS", (int)want),
                          lfh::env_int("LINFUSION_MLPH_REDUCE_BLK", wide ? 4 : 8), &p->blk_reduce);
     p->apply_wgs = per_head(lfh::env_int("LINFUSION_MLPH_APPLY_WGS", resident * lfh::num_cu()),
                             lfh::env_int("LINFUSION_MLPH_APPLY_BLK", wide ? 1 : 8), &p->blk_apply);
@@ -119,7 +118,7 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     p->stats_wgs = (int)(sw < cap ? sw : cap);
     p->ws_partials = up((size_t)units * p->splits * p->ne * sizeof(float));
     p->ws_state = up((size_t)units * p->ne * sizeof(float));
-    p->ws_pack = up((size_t)units * (wide ? lfw::wide_packed_bytes(d, dtype) : pack_bytes(d, dtype)));
+    p->ws_pack = wide ? up((size_t)units * lfw::wide_packed_bytes(d, dtype)) : 0;
     p->ws_stats = up((size_t)2 * B * p->n_pad * 2 * sizeof(float));
     p->ws_total = p->ws_partials + p->ws_state + p->ws_pack + p->ws_stats;
     return LINFUSION_OK;
@@ -147,7 +146,7 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
                            lfh::env_int("LINFUSION_MLP_APPLY_BLK", H == 8 ? 1 : 2), &p->blk_apply);
   p->ws_partials = up((size_t)B * H * p->splits * p->ne * sizeof(float));
   p->ws_state = up((size_t)B * H * p->ne * sizeof(float));
-  p->ws_pack = up((size_t)B * H * pack_bytes(d, dtype));
+  p->ws_pack = 0;
   p->ws_total = p->ws_partials + p->ws_state + p->ws_pack;
   return LINFUSION_OK;
 }
