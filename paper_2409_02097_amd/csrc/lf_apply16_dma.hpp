@@ -310,9 +310,10 @@ struct ApplyDma {
   // `state`: this head's [D*D + D] fp32 state.  The staging area (from kStageOffset) must be free.
   // COHERENT: the state was written by other workgroups of the same launch (single-launch kernel) and
   // must be read past this XCD's L2; otherwise an earlier kernel wrote it and plain wide loads do.
+  // parts > 1: `state` holds that many partials, which are summed on the way (and, with `keep`, left there).
   template <bool COHERENT = false>
-  LF_DEV void run(const float* state, float eps) {
-    load_state<COHERENT>(state, eps, true);
+  LF_DEV void run(const float* state, float eps, int parts = 1, float* keep = nullptr) {
+    load_state<COHERENT>(state, eps, true, parts, keep);
     stream();
   }
 
@@ -419,19 +420,20 @@ struct ApplyDma {
     }
   }
 
-  // Whole workgroup: stages one head's state in LDS; the waves with `keep` build their operands from it.
+  // Whole workgroup: stages one head's state in LDS; the waves with `mine` build their operands from it.
   // STAGED: the state already lies in the staging area (the workgroup computed it itself), S row-major as in
   // memory; `state` is not read.  Otherwise S is staged transposed -- st[col * D + ch], then z[ch] -- so that the
   // eight consecutive feature channels of one output column that make up a lane's operand are two 16-byte LDS
   // reads, all of them issued before the first is used (read one by one, row-major, with the slot tests around
   // each read, the operand build took 3-5 us per workgroup: a fifth of a small call).
   template <bool COHERENT = false, bool STAGED = false>
-  LF_DEV void load_state(const float* state, float eps, bool keep) {
+  LF_DEV void load_state(const float* state, float eps, bool mine, int parts = 1, float* keep = nullptr) {
     // ---- prologue: state -> LDS, maxima, power-of-two scales, A fragments -------------------------
     float* st = reinterpret_cast<float*>(smem + kStageOffset);
     float* redmax = st + NE;
     float mS = 0.0f, mz = 0.0f;
     static_assert(NE % 4 == 0 && (D * DV) % 4 == 0 && DV % 4 == 0, "the state is moved four floats of one row at a time");
+#pragma unroll 2
     for (int e = threadIdx.x; e < NE / 4; e += NT) {
       f32x4 x;
       if constexpr (STAGED) {
@@ -440,7 +442,8 @@ struct ApplyDma {
         x = f32x4{ld_agent(state + 4 * e), ld_agent(state + 4 * e + 1), ld_agent(state + 4 * e + 2),
                   ld_agent(state + 4 * e + 3)};
       } else {
-        x = reinterpret_cast<const f32x4*>(state)[e];
+        x = sum_partials(reinterpret_cast<const f32x4*>(state) + e, parts, NE / 4);
+        if (keep) reinterpret_cast<f32x4*>(keep)[e] = x;
       }
       if constexpr (!STAGED) {
         if (e < D * DV / 4) {
@@ -466,7 +469,7 @@ struct ApplyDma {
     for (int w = 0; w < W; ++w) { mS = fmaxf(mS, redmax[w]); mz = fmaxf(mz, redmax[W + w]); }
     const float aS = pow2_scale_for(mS);
     const float az = NORM ? pow2_scale_for(mz) : 1.0f;
-    if (keep) {
+    if (mine) {
       c1 = az / aS;
       eps_s = eps * az;
       c1_az = az;
@@ -797,16 +800,19 @@ struct ApplyDma {
   }
 };
 
+// state: [B*H][parts][D*D + D]; the sum of more than one partial goes to keep ([B*H][D*D + D]) as well.
 template <typename T, int D, int FM, bool NORM>
 __global__ void __launch_bounds__(kThreads)
 apply16_dma(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, HeadSubset hs,
-            const float* __restrict__ state, float eps, long long N, int tiles_per_block) {
+            const float* __restrict__ state, int parts, float* __restrict__ keep, float eps, long long N,
+            int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const long long bh = hs.bh(blockIdx.y, lq.H);
   ApplyDma<T, D, FM, NORM> ap(Q + lq.slice(bh), lq.row, O + lo.slice(bh), lo.row, N, tiles_per_block, blockIdx.x,
                               gridDim.x, smem);
   ap.prefetch();
-  ap.run(state + bh * (D * D + D), eps);
+  constexpr int NE = D * D + D;
+  ap.run(state + bh * parts * NE, eps, parts, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr);
 }
 
 // apply16_dma with the head's operands prepared by pack_state16: a workgroup's start-up is a few coalesced

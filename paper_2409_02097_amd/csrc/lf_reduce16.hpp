@@ -649,6 +649,30 @@ LF_DEV void combine_slice(const float* __restrict__ head_partials, int splits, i
              ((part[el] + part[kCombineElems + el]) + part[2 * kCombineElems + el]) + part[3 * kCombineElems + el]);
 }
 
+// Four neighbouring elements of the sum of `parts` <= kFoldParts partials `stride` vectors apart, in combine_slice's order
+// (the same bits): for kernels that sum the few partials of a small problem where they use them.  All loads are issued
+// before the first addition, from clamped, valid places (as loops over the quarters, one dependent round trip each, two or
+// more partials cost more than the launch they saved).
+constexpr int kFoldParts = 8;
+LF_DEV f32x4 sum_partials(const f32x4* __restrict__ src, int parts, int stride) {
+  if (parts == 1) return *src;
+  const f32x4 none = f32x4{0, 0, 0, 0};
+  if (parts <= 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = src[(p < parts ? p : 0) * stride];
+#pragma unroll
+    for (int p = 1; p < 4; ++p) v[0] += p < parts ? v[p] : none;
+    return v[0];
+  }
+  f32x4 v[kFoldParts];
+#pragma unroll
+  for (int p = 0; p < kFoldParts; ++p) v[p] = src[(p < parts ? p : 0) * stride];
+#pragma unroll
+  for (int p = 4; p < kFoldParts; ++p) v[p] = p < parts ? v[p] : none;
+  return (((v[0] + v[1]) + (v[2] + v[3])) + (v[4] + v[5])) + (v[6] + v[7]);
+}
+
 // grid = (ceil(NE / 64), B*H), block = 256, NE = d*d + d.  (A template only so that the two translation
 // units of the library may both hold it.)
 template <int kUnused>

@@ -26,7 +26,7 @@
 //   column form  lane (m, kq) reads channel 16 i + m of tokens 4 u + kq: the operand whose contraction runs over
 //                tokens (the state's gradient).
 // Chunks of a row are rotated by a row-dependent amount so that both forms are (nearly) free of bank conflicts.
-// They take a state as `parts` partial states and sum them in order while they stage it (parts = 1: a finished
+// They take a state as `parts` partial states and sum them while they stage it (parts = 1: a finished
 // state): where the partials are few that is cheaper than a launch of combine_state in between.
 #pragma once
 #include "lf_common.hpp"
@@ -224,10 +224,7 @@ struct Ring32 {
   LF_DEV const float* stage_state(const float* src, int parts, float* keep) {
     f32x4* st = reinterpret_cast<f32x4*>(smem + kStageOffset);
     for (int e = threadIdx.x; e < NE / 4; e += kThreads) {
-      const f32x4* p = reinterpret_cast<const f32x4*>(src) + e;
-      f32x4 s = p[0];
-#pragma unroll 4
-      for (int i = 1; i < parts; ++i) s += p[(long long)i * (NE / 4)];
+      const f32x4 s = sum_partials(reinterpret_cast<const f32x4*>(src) + e, parts, NE / 4);
       st[e] = s;
       if (keep) reinterpret_cast<f32x4*>(keep)[e] = s;
     }

@@ -556,8 +556,15 @@ int run16(const Args& a) {
 #undef LF_REDUCE
   }
   if (a.ev) (void)hipEventRecord(a.ev[1], st);
-  combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)a.BH), dim3(kCombineThreads), 0, st>>>(
-      partials, a.group_reduce ? p.gsplits : p.splits, NE, state);
+  // Up to eight partials of 64 KB in all are summed by the apply kernel's workgroups themselves, each reading all of its
+  // head's: one launch fewer (us per call: fp16 8 x 40 at 1000 tokens 15.2 -> 12.3, bf16 token-major 32 x 40 at 1000 17.2 ->
+  // 15.0, fp16 64 x 24 at 3000 18.9 -> 18.0; at 120 KB, 80 x 64 at 2000, equal, at 200 KB slower by half).
+  const int parts = a.group_reduce ? p.gsplits : p.splits;
+  const bool fold = a.out && !a.group_apply && !p.apply_packed && parts <= kFoldParts &&
+                    (size_t)parts * NE * sizeof(float) <= (size_t)env_int("LINFUSION_FOLD_KB", 64) * 1024;
+  if (!fold)
+    combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)a.BH), dim3(kCombineThreads), 0, st>>>(
+        partials, parts, NE, state);
   if (a.ev && !(a.out && (a.group_apply || p.apply_packed))) (void)hipEventRecord(a.ev[2], st);
   if (a.out) {
     const size_t lds2 = apply16_dma_lds_bytes<T, D>();
@@ -593,7 +600,7 @@ int run16(const Args& a) {
         const dim3 g2t(p.apply_wgs, (unsigned)(B * rest));
 #define LF_APPLY(FM, NORM)                                                               \
   if (!allow_lds(apply16_dma<T, D, FM, NORM>, (int)lds2)) return LINFUSION_ERR_HIP;      \
-  apply16_dma<T, D, FM, NORM><<<g2t, blk, lds2, st>>>(Q, a.lq, O, a.lo, tail, state, a.eps, a.N, p.blk_apply);
+  apply16_dma<T, D, FM, NORM><<<g2t, blk, lds2, st>>>(Q, a.lq, O, a.lo, tail, state, 1, nullptr, a.eps, a.N, p.blk_apply);
         LF_SWITCH_FM_NORM(LF_APPLY)
 #undef LF_APPLY
       }
@@ -621,7 +628,8 @@ int run16(const Args& a) {
       const dim3 g2(p.apply_wgs, (unsigned)a.BH);
 #define LF_APPLY(FM, NORM)                                                               \
   if (!allow_lds(apply16_dma<T, D, FM, NORM>, (int)lds2)) return LINFUSION_ERR_HIP;      \
-  apply16_dma<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq, O, a.lo, all, state, a.eps, a.N, p.blk_apply);
+  apply16_dma<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq, O, a.lo, all, fold ? partials : state, fold ? parts : 1, \
+                                                      fold ? state : nullptr, a.eps, a.N, p.blk_apply);
       LF_SWITCH_FM_NORM(LF_APPLY)
 #undef LF_APPLY
     }
