@@ -2,7 +2,7 @@
 // SD-v1.5 UNet have d = 80 and d = 160).  Same mathematics as the narrow kernels (Prop. 2's g'(X)^T X state,
 // Eq. 5's normalizer), other work split: the d x d fp32 state no longer fits one wave's accumulators, so
 // the four waves of a workgroup share every 32-token tile and split the state between them --
-//   state_reduce16_wide  by columns (value channels): wave w accumulates the 16-column blocks b = w mod 4;
+//   state_reduce16_wide  by quarters: wave w accumulates half of the rows (feature channels) of half of the columns;
 //   apply16_wide         by output channels: wave w produces channels [w d/4, (w+1) d/4) of every token.
 // Both move tiles as whole workgroups (coalesced over full token rows) and synchronise with workgroup
 // barriers; both address memory through Layout, so every layout of the strided entry point works.
@@ -56,10 +56,16 @@ constexpr int apply16_wide_lds_bytes() {
 // State reduction.  grid = (splits, heads), block = 256.  Workgroup x walks blocks of tiles_per_block
 // consecutive tiles (x, x + splits, ...; every wave visits every tile).  Per tile: all threads load K and V
 // rows (coalesced), apply phi to K, write 16-bit operands into the LDS tiles of the current buffer; barrier;
-// every wave reads all phi(K) operand blocks (transposing LDS reads) and the V blocks of its own columns
-// and accumulates S[:, its columns]; z rows a = w mod 4 through a ones operand.  Two LDS buffers: the next
-// tile is written while slower waves still multiply the previous one, one barrier per tile.
-// Partial: S as [D][D] row-major then z, fp32; each wave writes its own columns.
+// every wave reads the phi(K) and V operand blocks of its quarter of S (transposing LDS reads) and accumulates it; z rows
+// through a ones operand, those of a half shared by its two waves.  Two LDS buffers: the next tile is written while slower
+// waves still multiply the previous one, one barrier per tile.
+// Partial: S as [D][D] row-major then z, fp32; each wave writes its own quarter.
+// What bounds it is issue: conversion, LDS operands and matrix steps of a tile follow one another in each of a SIMD's two
+// waves (in a form of eight waves, loads two to four tiles ahead changed nothing, and leaving the matrix steps out 0.4 of the time).  Quarters need
+// 15 operand blocks per 50 matrix steps at d = 160 in bf16, and as many in each wave; all rows of every fourth column
+// needed 23 per 60 in two waves and per 40 in the others.  Whole tiles test no rows.  Together, 8 heads x 131072 tokens on
+// MI355X, us (TB/s): bf16 d = 160 228 (2.9) -> 195 (3.4), fp16 161 (4.2) -> 143 (4.7), bf16 d = 96 140 (2.9) -> 111 (3.6);
+// eight waves of eighths 200 / 142 / 106.
 // ==========================================================================================
 template <typename T, int D, int FM>
 __global__ void __launch_bounds__(kThreads, 2)   // two workgroups per CU: one multiplies while the other loads
@@ -67,11 +73,14 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
                     float* __restrict__ partials, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using Sw = ShapeWide<D>;
-  constexpr int NS = NSplit<T>::value, RS = Sw::kRS, NL = Sw::kNLR, CPR = Sw::kCPR, MT = Sw::kMT, NBW = Sw::kNBW;
+  constexpr int NS = NSplit<T>::value, RS = Sw::kRS, NL = Sw::kNLR, CPR = Sw::kCPR, MT = Sw::kMT;
+  constexpr int MH = MT / 2, NZ = (MH + 1) / 2;   // blocks of a half; normalizer blocks of one of its two waves
+  static_assert(MT % 2 == 0, "quarters of whole blocks");
   constexpr int TE = Sw::kTileElems, BUF = (NS + 1) * TE;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wave & 1, a0 = (wave >> 1) * MH, b0 = wc * MH;
   const long long bh = hs.bh(blockIdx.y, kl.H);
   const u32x4* Kh = K + kl.slice(bh);
   const u32x4* Vh = V + vl.slice(bh);
@@ -83,7 +92,7 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
   for (int u = 0; u < NL; ++u) {
     const int p = u * kThreads + tid;
     const int r = p / CPR, c = p % CPR;
-    const bool in = p < Sw::kChunks;
+    const bool in = p < Sw::kChunks;       // (the same for all lanes of a wave: 64 divides the chunks of a tile)
     trow[u] = in ? r : kTile;              // kTile: never below the row limit
     goff[u] = r * rs + c;
     goffv[u] = r * rsv + c;
@@ -94,24 +103,38 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
 
   const long long n_tiles = (N + kTile - 1) / kTile;
 
-  f32x4 acc[MT][NBW];
-  f32x4 accz[NBW];
+  f32x4 acc[MH][MH];
+  f32x4 accz[NZ];
   const uint32_t one2 = (uint32_t)OneBits<T>::value * 0x10001u;
   const u32x4 ones = {one2, one2, one2, one2};
 
+  static_assert(Sw::kChunks % 64 == 0, "a wave has all or none of a round's chunks");
+  auto mine = [&](int u) { return (u + 1) * kThreads <= Sw::kChunks || u * kThreads + wave * 64 < Sw::kChunks; };
+  // rows past the end: a key that phi maps to 0 (the identity map: 0 itself), and no value
+  constexpr uint32_t kPad = kPhiKillsLowest<FM> ? LowestBits<T>::value : 0u;
   u32x4 kr[NL], vr[NL];
   auto issue_loads = [&](long long tile) {
     long long rem = N - tile * kTile;
     int lim = rem < kTile ? (int)rem : kTile;
     const u32x4* kp = Kh + tile * kTile * rs;
     const u32x4* vp = Vh + tile * kTile * rsv;
+    if (lim == kTile) {
+#pragma unroll
+      for (int u = 0; u < NL; ++u) {
+        if (mine(u)) {
+          kr[u] = ld_stream(kp + goff[u]);
+          vr[u] = ld_stream(vp + goffv[u]);
+        }
+      }
+      return lim;
+    }
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
       if (trow[u] < lim) {
         kr[u] = ld_stream(kp + goff[u]);
         vr[u] = ld_stream(vp + goffv[u]);
       } else {
-        kr[u] = u32x4{LowestBits<T>::value, LowestBits<T>::value, LowestBits<T>::value, LowestBits<T>::value};   // phi maps it to 0
+        kr[u] = u32x4{kPad, kPad, kPad, kPad};
         vr[u] = u32x4{0, 0, 0, 0};
       }
     }
@@ -132,11 +155,11 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
   for (int pass = 0;; ++pass) {
   TileIter it(blockIdx.x, gridDim.x, 0, tiles_per_block, n_tiles, 1);
 #pragma unroll
-  for (int i = 0; i < NBW; ++i) {
-    accz[i] = f32x4{0, 0, 0, 0};
+  for (int i = 0; i < NZ; ++i) accz[i] = f32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int a = 0; a < MT; ++a) acc[a][i] = f32x4{0, 0, 0, 0};
-  }
+  for (int i = 0; i < MH; ++i)
+#pragma unroll
+    for (int a = 0; a < MH; ++a) acc[a][i] = f32x4{0, 0, 0, 0};
   long long tokens = 0;
   int lim = 0;
   if (it.valid()) lim = issue_loads(it.t);
@@ -150,8 +173,7 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
     uint16_t* bufp = lds + buf * BUF;
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
-      if (u * kThreads + tid < Sw::kChunks) {
-        const bool ok = trow[u] < lim;
+      if (mine(u)) {
         u32x4 ph, pl;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -161,11 +183,7 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
           }
           float x0, x1;
           unpack2<T>(kr[u][w], x0, x1);
-          float p0 = phi<FM>(x0), p1 = phi<FM>(x1);
-          if constexpr (!kPhiKillsLowest<FM>) {
-            p0 = ok ? p0 : 0.0f;
-            p1 = ok ? p1 : 0.0f;
-          }
+          const float p0 = phi<FM>(x0), p1 = phi<FM>(x1);
           if constexpr (NS == 1) {
             ph[w] = pack2<T>(p0, p1);
           } else {
@@ -186,28 +204,23 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
     lds_barrier();   // the tile is complete in this buffer; the other buffer is free to be rewritten
 
     const uint16_t* ldsV = bufp + NS * TE;
-    u32x4 bfrag[NBW];
+    u32x4 bfrag[MH];
 #pragma unroll
-    for (int i = 0; i < NBW; ++i) {
-      const int b = wave + kWavesPerWG * i;
-      bfrag[i] = u32x4{0, 0, 0, 0};
-      if (b < MT) {
-        u32x2 r0 = lds_read_tr16(ldsV + tr_base + 16 * b);
-        u32x2 r1 = lds_read_tr16(ldsV + tr_base + 4 * RS + 16 * b);
-        bfrag[i] = u32x4{r0[0], r0[1], r1[0], r1[1]};
-      }
+    for (int i = 0; i < MH; ++i) {
+      u32x2 r0 = lds_read_tr16(ldsV + tr_base + 16 * (b0 + i));
+      u32x2 r1 = lds_read_tr16(ldsV + tr_base + 4 * RS + 16 * (b0 + i));
+      bfrag[i] = u32x4{r0[0], r0[1], r1[0], r1[1]};
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
 #pragma unroll
-      for (int a = 0; a < MT; ++a) {
-        u32x2 r0 = lds_read_tr16(bufp + s * TE + tr_base + 16 * a);
-        u32x2 r1 = lds_read_tr16(bufp + s * TE + tr_base + 4 * RS + 16 * a);
+      for (int a = 0; a < MH; ++a) {
+        u32x2 r0 = lds_read_tr16(bufp + s * TE + tr_base + 16 * (a0 + a));
+        u32x2 r1 = lds_read_tr16(bufp + s * TE + tr_base + 4 * RS + 16 * (a0 + a));
         u32x4 afrag = u32x4{r0[0], r0[1], r1[0], r1[1]};
 #pragma unroll
-        for (int i = 0; i < NBW; ++i)
-          if (wave + kWavesPerWG * i < MT) acc[a][i] = mfma_16x16x32<T>(afrag, bfrag[i], acc[a][i]);
-        if (a % kWavesPerWG == wave) accz[a / kWavesPerWG] = mfma_16x16x32<T>(afrag, ones, accz[a / kWavesPerWG]);
+        for (int i = 0; i < MH; ++i) acc[a][i] = mfma_16x16x32<T>(afrag, bfrag[i], acc[a][i]);
+        if (a % 2 == wc) accz[a / 2] = mfma_16x16x32<T>(afrag, ones, accz[a / 2]);
       }
     }
     buf ^= 1;
@@ -219,17 +232,17 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
     if (pass == 1) {
       const float back = __builtin_amdgcn_exp2f(-kc);      // the rescanned sums carry 2^kc
 #pragma unroll
-      for (int i = 0; i < NBW; ++i) {
-        accz[i] *= back;
+      for (int i = 0; i < NZ; ++i) accz[i] *= back;
 #pragma unroll
-        for (int a = 0; a < MT; ++a) acc[a][i] *= back;
-      }
+      for (int i = 0; i < MH; ++i)
+#pragma unroll
+        for (int a = 0; a < MH; ++a) acc[a][i] *= back;
       break;
     }
-    // largest normalizer sum of the workgroup (accz: z of rows a = wave mod 4, every column holds it)
+    // largest normalizer sum of the workgroup (accz: z of rows of the wave's half, every column holds it)
     float zm = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NBW; ++i)
+    for (int i = 0; i < NZ; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) zm = fmaxf(zm, accz[i][e]);
 #pragma unroll
@@ -249,6 +262,7 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
         (void)issue_loads(jt.t);
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
+          if (!mine(u)) continue;
 #pragma unroll
           for (int w = 0; w < 4; ++w) {
             const uint32_t word = kr[u][w];
@@ -273,19 +287,16 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
   }
   }
 
-  // ---- each wave writes its columns of the partial (lane: rows 4 (l / 16) + i, column l % 16 of a block) ----
+  // ---- each wave writes its quarter of the partial (lane: rows 4 (l / 16) + i, column l % 16 of a block) ----
   float* dst = partials + (bh * gridDim.x + blockIdx.x) * (long long)(D * D + D);
 #pragma unroll
-  for (int a = 0; a < MT; ++a) {
+  for (int a = 0; a < MH; ++a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int row = a * 16 + 4 * g4 + i;
+      const int row = (a0 + a) * 16 + 4 * g4 + i;
 #pragma unroll
-      for (int c = 0; c < NBW; ++c) {
-        const int b = wave + kWavesPerWG * c;
-        if (b < MT) st_agent(dst + row * D + b * 16 + j16, acc[a][c][i]);
-      }
-      if (a % kWavesPerWG == wave && j16 == 0) st_agent(dst + D * D + row, accz[a / kWavesPerWG][i]);
+      for (int c = 0; c < MH; ++c) st_agent(dst + row * D + (b0 + c) * 16 + j16, acc[a][c][i]);
+      if (a % 2 == wc && j16 == 0) st_agent(dst + D * D + row, accz[a / 2][i]);
     }
   }
 }
