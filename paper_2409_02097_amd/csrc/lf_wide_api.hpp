@@ -58,15 +58,21 @@ struct WideArgs {
   hipEvent_t* ev;             // null, or four events: before reduce, after it, after combine, after apply
 };
 
-// Most state-reduction workgroups per head that pay: each adds a partial of 4 (d^2 + d) bytes per head that is written and
-// read again, about 0.5 us per MB over all heads, and takes its share of about 1.5 us per tile from the others, so the sum
-// is least at sqrt(3 tiles / MB).  (One partial per two tiles, as two workgroups per CU gave, against this, us per call:
-// fp16 12 x 8 x 256 x 160 39.6 -> 33.7 and its training step 131.9 -> 108.2; 2 x 8 x 1024 x 160 35.6 -> 29.5; bf16 4 x 16 x
-// 512 x 128 36.6 -> 30.7.)  Long streams stay at what fills the chip.
-inline long long wide_most_splits(long long heads, long long tiles, int d) {
+// State-reduction workgroups of a problem, given what fills the chip.  Each adds a partial of 4 (d^2 + d) bytes per head that
+// is written and read again, about 0.5 us per MB over all heads, and takes its share of about 1.5 us per tile from the
+// others, so the sum is least at sqrt(3 tiles / MB) per head.  (One partial per two tiles, as two workgroups per CU gave,
+// against this, us per call: fp16 12 x 8 x 256 x 160 39.6 -> 33.7; 2 x 8 x 1024 x 160 35.6 -> 29.5; bf16 4 x 16 x 512 x 128
+// 36.6 -> 30.7.)  From three quarters of a workgroup per CU on, whole rounds: with 1.1 to 1.7 per CU some CUs have two and
+// the others wait (us at the least of the sum -> one per CU: fp16 4 x 8 x 4096 x 160 70.6 -> 62.4, 12 x 8 x 1024 x 160
+// 62.4 -> 56.4, bf16 2 x 8 x 4096 x 160 52.8 -> 46.3, 4 x 16 x 2048 x 128 60.9 -> 56.2; near two per CU -> two: 2 x 8 x
+// 16384 x 160 108 -> 98 to 105).  Long streams stay at what fills the chip.
+inline int wide_reduce_wgs(long long heads, long long tiles, int d, int fill, int cus) {
   const double mb = (double)heads * ((double)d * d + d) * 4e-6;
   const double s = __builtin_sqrt(3.0 * (double)tiles / mb) + 0.5;
-  return s < 1.0 ? 1 : (s > 1e6 ? 1000000 : (long long)s);
+  const long long want = (s < 1.0 ? 1 : (s > 1e6 ? 1000000 : (long long)s)) * heads;
+  if (want >= fill) return fill;
+  if (4 * want >= 7 * (long long)cus) return want > 2 * cus ? (int)want : 2 * cus;   // (`fill` is two per CU or more)
+  return 4 * want >= 3 * (long long)cus ? cus : (int)want;
 }
 // head widths the wide kernels are built for
 bool wide_supported(int d);

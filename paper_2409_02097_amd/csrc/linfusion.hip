@@ -177,14 +177,10 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       const double bytes = 4.0 * (double)BH * (double)N * d * 2.0;
       if (d <= 128 && bytes >= 768.0 * 1048576.0) reduce_per_cu = (d <= 96 && dtype == LINFUSION_DTYPE_BF16) ? 4 : 3;
     }
-    const long long most = lfw::wide_most_splits(BH, p->n_tiles, d);
-    int want = reduce_per_cu * num_cu(), room = 0;
-    if (want > most * BH) {
-      // (the entry point with the fixed scratch array keeps asking for what the chip-filling launch needs, so that it
-      // takes and refuses the shapes that it always did)
-      if (compact) room = per_head(want, 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce);
-      want = (int)(most * BH);
-    }
+    const int fill = reduce_per_cu * num_cu(), want = lfw::wide_reduce_wgs(BH, p->n_tiles, d, fill, num_cu());
+    // (the entry point with the fixed scratch array keeps asking for what the chip-filling launch needs, so that it
+    // takes and refuses the shapes that it always did)
+    int room = want < fill && compact ? per_head(fill, 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce) : 0;
     p->splits = per_head(env_int("LINFUSION_WIDE_REDUCE_WGS", want), 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce);
     // a head of one or two tiles: one workgroup sums them and writes the state itself (no partials, no combine
     // launch; from four tiles on a workgroup's tiles in sequence cost more than the launch saved)

@@ -104,12 +104,9 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     const int slot = (lf::kTile * d * 2 + 1023) / 1024 * 1024;
     const int lds_apply = (2 * 3 * slot + 3 * 1024) * lf::kWavesPerWG;
     const int resident = (!wide && 160 * 1024 / lds_apply > 0) ? 160 * 1024 / lds_apply : 1;
-    long long want = 2 * lfh::num_cu();
-    if (wide) {
-      const long long most = lfw::wide_most_splits(units, n_tiles, d) * units;
-      if (want > most) want = most;
-    }
-    p->splits = per_head(lfh::env_int("LINFUSION_MLPH_REDUCE_WGS", (int)want),
+    int want = 2 * lfh::num_cu();
+    if (wide) want = lfw::wide_reduce_wgs(units, n_tiles, d, want, lfh::num_cu());
+    p->splits = per_head(lfh::env_int("LINFUSION_MLPH_REDUCE_WGS", want),
                          lfh::env_int("LINFUSION_MLPH_REDUCE_BLK", wide ? 4 : 8), &p->blk_reduce);
     p->apply_wgs = per_head(lfh::env_int("LINFUSION_MLPH_APPLY_WGS", resident * lfh::num_cu()),
                             lfh::env_int("LINFUSION_MLPH_APPLY_BLK", wide ? 1 : 8), &p->blk_apply);
