@@ -1,7 +1,7 @@
-// fp32 kernels.  fp32 inputs never pass through 16-bit operands: the d x d contractions use the
-// fp32 matrix-core instruction (16x16x4), whose operand layout holds one contraction index per
-// lane, so no transposition and no LDS staging is needed anywhere.
-//   state_reduce32  S_p, z_p over a workgroup's tiles          (Prop. 2: g'(X)^T X; Eq. 5: Z)
+// fp32 on the fp32 matrix-core instruction (16x16x4), whose operand layout holds one contraction index per
+// lane, so no transposition and no LDS staging is needed: the phases of the single-launch kernels, and the apply kernel of
+// the narrow heads (wider ones and all three-launch reductions: lf_ring32.hpp).
+//   reduce32_phase  S_p, z_p over a workgroup's tiles          (Prop. 2: g'(X)^T X; Eq. 5: Z)
 //   combine_state   (lf_reduce16.hpp) fixed-order sum of the partials
 //   apply32         out_i = phi(q_i) S / (phi(q_i).z + eps)
 #pragma once
@@ -147,18 +147,6 @@ LF_DEV void reduce32_phase(const f32x4* __restrict__ Kh, const f32x4* __restrict
     if constexpr (TO_LDS) dst[i] = v;
     else st_agent(dst + i, v);
   }
-}
-
-// grid = (splits, B*H), block = 256
-template <int D, int FM>
-__global__ void __launch_bounds__(kThreads)
-state_reduce32(const f32x4* __restrict__ K, Layout kl, const f32x4* __restrict__ V, Layout vl,
-               float* __restrict__ partials, long long N, int tiles_per_block) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const long long bh = blockIdx.y;
-  float* dst = partials + (bh * gridDim.x + blockIdx.x) * (long long)(D * D + D);
-  reduce32_phase<D, FM>(K + kl.slice(bh), V + vl.slice(bh), kl.row, vl.row, dst, N, tiles_per_block, blockIdx.x,
-                        gridDim.x, smem);
 }
 
 // ------------------------------------------------------------------------------------------
