@@ -187,13 +187,13 @@ int linfusion_attn_fwd_profile(const void* q, const void* k, const void* v, void
  *                   16-byte aligned; must not overlap dq, dk, dv or `workspace`.
  *   q, k, v, dout   DEVICE pointers, contiguous [B, H, N, d].  fp16, bf16: d in {8, ..., 64 step 8, 80}; fp16 also
  *                   d in {96, 128, 160} (bf16 there -> LINFUSION_ERR_UNSUPPORTED); fp32: d in {8, ..., 64 step 8}.
- *                   fp16 above 80 runs a pass composed of the forward's kernels with three fp16 temporaries in the
- *                   workspace, sixteen launches: there so that every level of the UNet has a gradient, not for speed.
+ *                   fp16 above 80: a query-side and a key-side kernel between the state reduction, two packings of
+ *                   the states as matrix operands and the apply kernel, with one fp16 temporary in the workspace.
  *   dq, dk, dv      DEVICE pointers, same shape and type; must not overlap any input or each other.
  *   flags           LINFUSION_FLAG_NONE or LINFUSION_FLAG_UNNORMALIZED (anything else -> ERR_INVALID).
  *   workspace       DEVICE scratch of at least linfusion_attn_bwd_workspace_bytes(...) bytes, 16-byte
  *                   aligned, caller-owned, contents undefined before and after.
- * Enqueues up to six kernels (four when `state` is given; fp16 above 80: see there) on `stream`; never allocates, never synchronises.  Results are run-to-run identical.
+ * Enqueues up to six kernels (four when `state` is given; fp16 above 80 up to eight, six) on `stream`; never allocates, never synchronises.  Results are run-to-run identical.
  */
 int linfusion_attn_bwd(const void* q, const void* k, const void* v, const void* dout, const float* state,
                        void* dq, void* dk, void* dv,
@@ -212,8 +212,8 @@ int linfusion_attn_bwd(const void* q, const void* k, const void* v, const void* 
  * row is no whole number of 128-byte lines (d * 2 % 128 != 0: d = 40, 80, ...), H is a multiple of 4 and a tensor
  * has 24 MB or more, the gradients come from kernels that move whole row pieces of four or eight neighbouring
  * heads: the forward state (when not handed in), dQ, dK and dV for every width up to 56 and 80, the state gradient
- * too for fp16 up to d = 48 (token-major 8 x 40 at 2 M tokens: fp16 2.2 ms, against 7.0 ms on the per-head kernels
- * and 2.3 ms contiguous; bf16 3.5 against 8.2 and 3.2 ms).  These kernels sum the state and its gradient over the tiles in another order
+ * in the same kernel as dQ for fp16 up to d = 48 and bf16 up to d = 40 (forward and backward of 12 x 8 x 4096 x 40
+ * token-major: bf16 167 us with a state-gradient kernel of its own, 133 so).  These kernels sum the state and its gradient over the tiles in another order
  * than the per-head kernels, so the gradients may differ from the contiguous call's in the last bit; they stay
  * run-to-run identical.  Head counts that are no multiple of 4 run the per-head kernels on partial lines, at a
  * fraction of the contiguous speed; d = 64 token-major does not suffer.
@@ -261,7 +261,7 @@ size_t linfusion_attn_bwd_workspace_bytes(int B, int H, long long N, int d, int 
  *   events                  NULL, or four hipEvent_t created by the caller (passed as void*), recorded on
  *                           `stream` before the first kernel, after the state reduction, after combine +
  *                           operand packing, and after apply.
- * Enqueues four kernels (five with the statistics pass) on `stream`; never allocates, never synchronises; run-to-run identical results.
+ * Enqueues three kernels, four where more than a few partial states are summed first (one more with the statistics pass), on `stream`; never allocates, never synchronises; run-to-run identical results.
  * Errors as linfusion_attn_fwd_ex (first failing check wins; nothing is enqueued on an error).
  */
 int linfusion_attn_fwd_mlp(const void* a_q, const void* t_q, const void* a_k, const void* t_k, const void* v,
