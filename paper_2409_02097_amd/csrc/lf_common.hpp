@@ -195,6 +195,7 @@ template <int D> struct Shape16 {
 // All in units of one vector access (16 bytes): [B, H, N, d] contiguous has row = d * s / 16,
 // head = N * row, batch = H * head; the token-major [B, N, H * d] layout of the UNet has
 // row = H * d * s / 16, head = d * s / 16, batch = N * row.  Inside a row the d channels are contiguous.
+constexpr long long kMaxRowStride = 1LL << 24;   // token strides stay below this: 32 rows in units of 16 bytes fit an int
 struct Layout {
   long long batch, head;   // strides between batches / heads
   int row;                 // stride between consecutive tokens of one head

@@ -380,14 +380,16 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
     const long long rem = N - tile * TOK;
     return rem < TOK ? (int)rem : TOK;
   };
+  // (an offset is 63 rows of floats at most: unsigned, since it may exceed an int)
+  static_assert((TOK - 1) * 4 * (kMaxRowStride - 1) + D <= 0xffffffffLL, "row offsets of a tile fit 32 bits");
   auto issue_loads = [&](long long tile, int lim) {   // rows past N: the tile's first row instead
     const float* kp = Kh + tile * TOK * rsk;
     const float* vp = Vh + tile * TOK * rsv;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int r = t0 + kStep * j < lim ? t0 + kStep * j : 0;
-      load_row(kp + (r * rsk + c0), kr[j]);
-      load_row(vp + (r * rsv + c0), vr[j]);
+      const unsigned r = t0 + kStep * j < lim ? t0 + kStep * j : 0;
+      load_row(kp + (r * (unsigned)rsk + c0), kr[j]);
+      load_row(vp + (r * (unsigned)rsv + c0), vr[j]);
     }
   };
 

@@ -765,7 +765,7 @@ int check_strides(const Strides& s, int B, int H, long long N, int d, size_t esz
   const long long vec = (long long)(16 / esz);
   if (s.b < 0 || s.h < 0 || s.n < 0) return LINFUSION_ERR_INVALID;
   if (s.b % vec || s.h % vec || s.n % vec) return LINFUSION_ERR_MISALIGNED;
-  if (s.n / vec >= (1LL << 24)) return LINFUSION_ERR_INVALID;           // 32 rows * stride stays in int
+  if (s.n / vec >= lf::kMaxRowStride) return LINFUSION_ERR_INVALID;
   const long double span = (long double)(B - 1) * s.b + (long double)(H - 1) * s.h + (long double)(N - 1) * s.n + d;
   if (span * esz >= (long double)(1LL << 46)) return LINFUSION_ERR_INVALID;
   if (written) {

@@ -270,7 +270,7 @@ static int mlp_impl(const void* a_q, const void* t_q, const void* a_k, const voi
   for (const long long* st2 : {si, so}) {
     if (st2[0] < 0 || st2[1] < 0) return LINFUSION_ERR_INVALID;
     if (st2[0] % 8 || st2[1] % 8) return LINFUSION_ERR_MISALIGNED;          // 16-byte aligned rows
-    if (st2[1] / 8 >= (1LL << 24)) return LINFUSION_ERR_INVALID;            // 32 rows * stride stays in int
+    if (st2[1] / 8 >= lf::kMaxRowStride) return LINFUSION_ERR_INVALID;
     if ((long double)(B - 1) * st2[0] + (long double)(N - 1) * st2[1] + C >= (long double)(1LL << 45))
       return LINFUSION_ERR_INVALID;
   }

@@ -71,3 +71,19 @@ def test_other_feature_maps(d, fm, normalize):
     lf.linfusion_attn_fwd_ex(q.cuda(), k.cuda(), v.cuda(), out, fm, 1e-6, 0 if normalize else lf.FLAG_UNNORMALIZED, ws)
     torch.cuda.synchronize()
     parity.check_all(out, q, k, v, "f32", fm, 1e-6, normalize, what=f"f32 fm={fm} norm={normalize} d={d}")
+
+
+# the largest token stride that is accepted: 64-token tiles (d = 8 and 24) reach 63 * 2^26 floats behind their first row
+@pytest.mark.parametrize("d", [8, 24, 40])
+def test_rows_as_far_apart_as_accepted(d):
+    N, row = 67, 4 * (2 ** 24 - 1)                 # 16.5 GiB from the first to the last token, of which 67 rows are used
+    print(f"f32 rows {row} floats apart, d={d}", flush=True)
+    q, k, v = wl.make_qkv(1, 1, N, d, "f32", idx=122, device="cpu")
+    store = torch.empty((N - 1) * row + 2 * d, dtype=torch.float32, device="cuda")
+    kd, vd = (store.as_strided((1, 1, N, d), (N * row, N * row, row, 1), at) for at in (0, d))
+    kd.copy_(k)
+    vd.copy_(v)
+    out = torch.full((1, 1, N, d), float("nan"), device="cuda")
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(1, 1, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
+    _forward(q.cuda(), kd, vd, out, ws)
+    parity.check_all(out, q, k, v, "f32", what=f"f32 far rows d={d}")
