@@ -4,9 +4,17 @@
 // of them takes 233 ns, eight phi 181 ns, both together 419 ns -- the times add up, also with two waves per SIMD, and at
 // d = 64 the products alone are two thirds of the time the bytes need.  The bf16 instructions run beside the vector
 // unit.  Every fp32 value is therefore split into three bf16 terms, x = x1 + x2 + x3 (each the bf16 rounding of what the
-// terms before it left: 24 bits, nothing of an fp32 number is lost), and a product is the sum of the six partial products
+// terms before it left: 24 bits), and a product is the sum of the six partial products
 // whose weight is 2^-16 of the leading one or more (a1 b1, a1 b2, a2 b1, a2 b2, a1 b3, a3 b1; the three dropped ones are
 // below 2^-24, fp32's own rounding), accumulated in fp32, smallest first.
+//
+// The three terms hold 0 and every value from 2^-110 up to below 2^127 exactly.  Smaller ones lose bits, since the third term
+// runs into bf16's subnormals (phi of a key below -76 is such a value), and just above 2^127 the first term may round to
+// infinity; an infinity leaves NaN as its second term.  A tile with such a value, or a head whose state has one, is
+// therefore multiplied on the fp32 instruction, from the same registers: the operands and results of both instructions lie
+// alike in the lanes; the state reduction goes on with it from the first such tile of a wave.  The test costs one instruction
+// per value (Span): 20 heads of 64 channels and 16384 tokens 83.1 -> 85.9 us per call, forward and backward of 96 heads of 40 and
+// 4096 tokens 183 -> 192.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
 //
 //   state_reduce32s  S, z partials        reads K, V                       (Prop. 2: g'(X)^T X; Eq. 5: Z)
 //   apply32s         out                  reads Q, writes out
@@ -79,6 +87,72 @@ LF_DEV f32x4 mfma_split(const Split4& a, const Split4& b, f32x4 c) {
   c = mfma_16x16x16_bf16(a.t[0], b.t[1], c);
   return mfma_16x16x16_bf16(a.t[0], b.t[0], c);
 }
+
+// The same products on the fp32 instruction, for operands that three terms do not hold: lane (m, kq) gives one value of the
+// contraction's index kq at a time, so any order in which both operands' values are taken does.
+LF_DEV f32x4 mfma_f32(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+LF_DEV f32x4 mfma_f32(f32x4 a, f32x4 b, f32x4 c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = mfma_f32(a[e], b[e], c);
+  return c;
+}
+// x, for a path that is hardly ever taken: the empty statement keeps the compiler from working out ahead of the branch, or of
+// the loop around it, what only that path needs (d = 64: the state's fp32 values, 96 registers)
+template <typename X> LF_DEV X rarely(X x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// x1 + x2 + x3 of what join put together: exact where the terms hold the value
+LF_DEV f32x4 joined(const Split8& a, int half) {
+  f32x4 x;
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    float h0, h1, m0, m1, l0, l1;
+    unpack2<BF16>(rarely(a.t[0][2 * half + w]), h0, h1);
+    unpack2<BF16>(rarely(a.t[1][2 * half + w]), m0, m1);
+    unpack2<BF16>(rarely(a.t[2][2 * half + w]), l0, l1);
+    x[2 * w] = h0 + (m0 + l0);
+    x[2 * w + 1] = h1 + (m1 + l1);
+  }
+  return x;
+}
+
+// Whether three bf16 terms hold every value that a wave is about to split.
+constexpr float kSplitLow = 0x1p-110f, kSplitHigh = 0x1p127f;
+LF_DEV bool splits_exactly(float x) {   // (a NaN does as well as any: either instruction gives NaN)
+  const float a = fabsf(x);
+  return !((a < kSplitLow) & (a > 0.0f)) & !(a >= kSplitHigh);
+}
+LF_DEV bool all_lanes(bool x) { return __builtin_amdgcn_ballot_w64(!x) == 0; }
+// smallest and largest magnitude seen: passes only where none is 0; splits_exactly decides where this does not
+struct Span {
+  float lo = 1.0f, hi = 1.0f;
+  // (written out: left to itself the compiler quiets every operand of a minimum or maximum first)
+  LF_DEV void add(float a, float b) {
+    asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(lo) : "v"(a), "v"(b));
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(a), "v"(b));
+  }
+  LF_DEV void add(f32x4 x) {
+    add(x[0], x[1]);
+    add(x[2], x[3]);
+  }
+  LF_DEV bool passes() const { return all_lanes(lo >= kSplitLow && hi < kSplitHigh); }
+};
+// the same for phi of the values that are given: elu + 1 is e^x below 0, and e^-76 above 2^-110
+template <int FM> struct PhiSpan : Span {
+  LF_DEV void add(float a, float b) {
+    if constexpr (FM == kPhiEluPlusOne) {
+      asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lo) : "v"(a), "v"(b));
+      asm("v_max3_f32 %0, %1, %2, %0" : "+v"(hi) : "v"(a), "v"(b));
+    } else {
+      Span::add(a, b);
+    }
+  }
+  LF_DEV bool passes() const {
+    if constexpr (FM == kPhiEluPlusOne) return all_lanes(lo >= -76.0f && hi < 0.5f * kSplitHigh);
+    else return Span::passes();
+  }
+};
 
 template <int D> struct Tile32 {
   static constexpr int kCH = D / 4;                        // 16-byte chunks per token row
@@ -202,7 +276,7 @@ struct Ring32 {
   LF_DEV void read_rows(int slot, int which, f32x4 (&x)[MT]) const {
 #pragma unroll
     for (int T = 0; T < MT; ++T) {
-      x[T] = f32x4{0, 0, 0, 0};
+      x[T] = f32x4{1, 1, 1, 1};   // (past d: multiplied by zeros of the state, and no 0 that Span would stop at)
       if (has(T)) x[T] = *reinterpret_cast<const f32x4*>(tile_ptr(slot, which) + TC::place(m, 4 * T + kq));
     }
   }
@@ -232,16 +306,18 @@ struct Ring32 {
     return reinterpret_cast<const float*>(st);
   }
   // operands of  out[o] = sum_c M'[o][c] x[c]:  element M[o][c], or (TRANSPOSED) M[c][o], at output channel
-  // 16 t + m and input channels 16 T + 4 kq + e, T = 2 s and 2 s + 1; zero outside d
+  // 16 t + m and input channels 16 T + 4 kq + e, T = 2 s and 2 s + 1; zero outside d.  Returns whether three terms do not
+  // hold the state (the same answer in every wave, each of which has all of it): then A keeps the fp32 values as they are,
+  // those of T = 2 s in t[0] and of 2 s + 1 in t[1].
   template <bool TRANSPOSED>
-  LF_DEV void build_A(const float* st, Split8 (&A)[MT][KS]) const {
+  LF_DEV bool build_A(const float* st, Split8 (&A)[MT][KS]) const {
+    bool exact = true;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       const int o = 16 * t + m;
       const bool ok_o = kWhole || 16 * t + 15 < D || o < D;
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        Split4 half[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int T = 2 * s + h;
@@ -253,13 +329,20 @@ struct Ring32 {
             for (int e = 0; e < 4; ++e) {
               const float y = TRANSPOSED ? st[(cc + e) * D + oo] : st[oo * D + cc + e];
               x[e] = ok ? y : 0.0f;
+              exact &= splits_exactly(x[e]);
             }
           }
-          half[h] = split3(x);
+          A[t][s].t[h] = __builtin_bit_cast(u32x4, x);
         }
-        A[t][s] = join(half[0], half[1]);
       }
     }
+    if (!all_lanes(exact)) return true;
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        A[t][s] = join(split3(__builtin_bit_cast(f32x4, A[t][s].t[0])), split3(__builtin_bit_cast(f32x4, A[t][s].t[1])));
+    return false;
   }
   LF_DEV void load_vec(const float* st, f32x4 (&z)[MT]) const {
 #pragma unroll
@@ -268,11 +351,39 @@ struct Ring32 {
       if (has(T)) z[T] = *reinterpret_cast<const f32x4*>(st + D * D + 16 * T + 4 * kq);
     }
   }
-  // x in row form (zero past d)
-  LF_DEV void products(const Split8 (&A)[MT][KS], const f32x4 (&x)[MT], f32x4 (&acc)[MT]) const {
+  static LF_DEV Span span(const f32x4 (&x)[MT]) {
+    Span sp;
+#pragma unroll
+    for (int T = 0; T < MT; ++T) sp.add(x[T]);
+    return sp;
+  }
+  static LF_DEV bool exact(const f32x4 (&x)[MT]) {   // of this lane's values
+    bool ok = true;
+#pragma unroll
+    for (int T = 0; T < MT; ++T)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ok &= splits_exactly(rarely(x[T][e]));
+    return ok;
+  }
+  // x in row form, finite past d; sp = span(x); A and raw from build_A
+  LF_DEV void products(const Split8 (&A)[MT][KS], bool raw, const f32x4 (&x)[MT], const Span& sp, f32x4 (&acc)[MT]) const {
     const f32x4 none = f32x4{0, 0, 0, 0};
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[t] = none;
+    if (raw) {
+#pragma unroll
+      for (int T = 0; T < MT; ++T)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(__builtin_bit_cast(f32x4, A[t][T / 2].t[T % 2]), x[T], acc[t]);
+      return;
+    }
+    if (!sp.passes() && !all_lanes(exact(x))) {
+#pragma unroll
+      for (int T = 0; T < MT; ++T)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(joined(A[t][T / 2], T % 2), x[T], acc[t]);
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const Split8 b = join(split3(x[2 * s]), 2 * s + 1 < MT ? split3(x[2 * s + 1 < MT ? 2 * s + 1 : 0]) : Split4{});
@@ -401,13 +512,7 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
 #pragma unroll
     for (int j = 0; j < CPL; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
   }
-  int lim = 0;
-  if (it.valid()) {
-    lim = lim_of(it.t);
-    issue_loads(it.t, lim);
-  }
-  while (it.valid()) {
-    float k[8][CPL], v[8][CPL];
+  auto take = [&](float (&k)[8][CPL], float (&v)[8][CPL], int lim) {   // the tile that has been loaded
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -425,10 +530,46 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
           v[j][i] = ok ? v[j][i] : 0.0f;
         }
     }
+  };
+  auto phi_of = [&](int i, const float (&k)[8][CPL], float (&p)[8]) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = phi<FM, true>(k[j][i]);
+    z[i] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+  };
+  int lim = 0;
+  if (it.valid()) {
+    lim = lim_of(it.t);
+    issue_loads(it.t, lim);
+  }
+  while (it.valid()) {
+    float k[8][CPL], v[8][CPL];
+    take(k, v, lim);
+    const TileIter cur = it;
     it.next();
     if (it.valid()) {
       lim = lim_of(it.t);
       issue_loads(it.t, lim);
+    }
+    Span vs;
+    PhiSpan<FM> ks;
+#pragma unroll
+    for (int j = 0; j < 8; j += 2)
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        ks.add(k[j][i], k[j + 1][i]);
+        vs.add(v[j][i], v[j + 1][i]);
+      }
+    if (!(ks.passes() && vs.passes())) {
+      bool exact = true;
+#pragma unroll
+      for (int i = 0; i < CPL; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          exact &= splits_exactly(phi<FM, true>(rarely(k[j][i]))) & splits_exactly(rarely(v[j][i]));
+      if (!all_lanes(exact)) {
+        it = cur;
+        break;
+      }
     }
     Split8 b[CPL];
 #pragma unroll
@@ -437,13 +578,28 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
       float p[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) p[j] = phi<FM, true>(k[j][i]);
-      z[i] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      phi_of(i, k, p);
       const Split8 a = join(split3(f32x4{p[0], p[1], p[2], p[3]}), split3(f32x4{p[4], p[5], p[6], p[7]}));
 #pragma unroll
       for (int j = 0; j < CPL; ++j) acc[i][j] = mfma_split(a, b[j], acc[i][j]);
     }
+  }
+  // from the first tile on that three terms do not hold: the fp32 instruction (a loop of its own for the registers' sake)
+  while (it.valid()) {
+    lim = lim_of(it.t);
+    issue_loads(it.t, lim);
+    float k[8][CPL], v[8][CPL];
+    take(k, v, lim);
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      float p[8];
+      phi_of(i, k, p);
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) acc[i][j] = mfma_f32(p[t], v[t][j], acc[i][j]);
+    }
+    it.next();
   }
 #pragma unroll
   for (int i = 0; i < CPL; ++i) {
@@ -500,7 +656,7 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
   rg.prefetch();
   const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr);
   Split8 A[MT][RG::KS];
-  rg.template build_A<true>(st, A);
+  const bool raw = rg.template build_A<true>(st, A);
   f32x4 z[MT];
   if constexpr (NORM) rg.load_vec(st, z);
   __syncthreads();   // the staged state is dead
@@ -520,10 +676,10 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
     for (int T = 0; T < MT; ++T)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        r[T][e] = rg.has(T) ? phi<FM, true>(r[T][e]) : 0.0f;
+        r[T][e] = phi<FM, true>(r[T][e]);
         if constexpr (NORM) den = __builtin_fmaf(r[T][e], z[T][e], den);
       }
-    rg.products(A, r, acc);
+    rg.products(A, raw, r, RG::span(r), acc);
     if constexpr (NORM) {
       const float scale = 1.0f / (RG::token_sum(den) + eps);
 #pragma unroll
@@ -558,7 +714,7 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
   rg.prefetch();
   const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, nullptr);
   Split8 A[MT][RG::KS];
-  rg.template build_A<false>(st, A);       // u = S g
+  const bool raw = rg.template build_A<false>(st, A);       // u = S g
   f32x4 z[MT];
   if constexpr (NORM) rg.load_vec(st, z);
   __syncthreads();                          // the staged state is dead
@@ -582,7 +738,8 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     f32x4 x[MT], g[MT], u[MT];
     rg.read_rows(slot, 1, g);
     rg.read_rows(slot, 0, x);
-    rg.products(A, g, u);
+    const Span gs = RG::span(g);
+    rg.products(A, raw, g, gs, u);
     f32x4 r[MT];
     float den = 0.0f, ru = 0.0f;
 #pragma unroll
@@ -615,6 +772,13 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
         g[T][e] = on ? g[T][e] * invden : 0.0f;
         if constexpr (NORM) dz[T][e] = __builtin_fmaf(r[T][e], e_i, dz[T][e]);
       }
+    // (g / den lies within what its tile's extremes divided by den span, so those need not be sought again)
+    Span rs = RG::span(r);
+    if (on) {
+      rs.lo = fminf(rs.lo, gs.lo * fabsf(invden));
+      rs.hi = fmaxf(rs.hi, gs.hi * fabsf(invden));
+    }
+    const bool split = rs.passes() || all_lanes(RG::exact(r) & RG::exact(g));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     rg.write_rows(slot, 0, r);
     rg.write_rows(slot, 1, g);
@@ -632,14 +796,23 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     rg.store_tile(tile, slot, 0, dQh, ldq.row);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    Split4 b[MT];
+    if (split) {
+      Split4 b[MT];
 #pragma unroll
-    for (int j = 0; j < MT; ++j) b[j] = split3(f32x4{gc[0][j], gc[1][j], gc[2][j], gc[3][j]});
+      for (int j = 0; j < MT; ++j) b[j] = split3(f32x4{gc[0][j], gc[1][j], gc[2][j], gc[3][j]});
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const Split4 a = split3(f32x4{pc[0][i], pc[1][i], pc[2][i], pc[3][i]});
+      for (int i = 0; i < MT; ++i) {
+        const Split4 a = split3(f32x4{pc[0][i], pc[1][i], pc[2][i], pc[3][i]});
 #pragma unroll
-      for (int j = 0; j < MT; ++j) acc[i][j] = mfma_split(a, b[j], acc[i][j]);
+        for (int j = 0; j < MT; ++j) acc[i][j] = mfma_split(a, b[j], acc[i][j]);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+          acc[i][j] = mfma_f32(f32x4{pc[0][i], pc[1][i], pc[2][i], pc[3][i]}, f32x4{gc[0][j], gc[1][j], gc[2][j], gc[3][j]},
+                               acc[i][j]);
     }
     rg.it.next();
     rg.ahead.next();
@@ -694,8 +867,8 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
   rg.prefetch();
   const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, nullptr);
   Split8 A[MT][RG::KS], At[MT][RG::KS];
-  rg.template build_A<false>(st, A);       // dS v
-  rg.template build_A<true>(st, At);       // dS^T p
+  const bool raw = rg.template build_A<false>(st, A);       // dS v
+  (void)rg.template build_A<true>(st, At);                  // dS^T p: the same state, the same answer
   f32x4 dz[MT];
   rg.load_vec(st, dz);
   __syncthreads();                          // the staged state is dead
@@ -711,17 +884,17 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
     f32x4 k[MT], v[MT], t[MT], dv[MT], p[MT];
     rg.read_rows(slot, 1, v);
     rg.read_rows(slot, 0, k);
-    rg.products(A, v, t);
+    rg.products(A, raw, v, RG::span(v), t);
 #pragma unroll
     for (int T = 0; T < MT; ++T)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        p[T][e] = rg.has(T) ? phi<FM, true>(k[T][e]) : 0.0f;
+        p[T][e] = phi<FM, true>(k[T][e]);
         if constexpr (FM == kPhiEluPlusOne) k[T][e] = k[T][e] > 0.0f ? 1.0f : p[T][e];     // phi'(k)
         else if constexpr (FM == kPhiRelu) k[T][e] = k[T][e] > 0.0f ? 1.0f : 0.0f;
         else k[T][e] = 1.0f;
       }
-    rg.products(At, p, dv);
+    rg.products(At, raw, p, RG::span(p), dv);
 #pragma unroll
     for (int T = 0; T < MT; ++T) k[T] *= t[T] + dz[T];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -1,10 +1,12 @@
 """GPU parity of the fp32 kernels at the sizes where their tiles and launches change: tiles of 16 tokens (apply and
 gradients), of 32 (state reduction) and of 64 (its two token groups at d = 8 and 24), the apply kernel that changes
 above d = 24, and partial states summed by their consumers or by a launch of their own."""
+import numpy as np
 import pytest
 import torch
 
 import paper_2409_02097_amd as lf
+from oracle import linattn_oracle as orc
 from paper_2409_02097_amd import workloads as wl
 from tests import parity
 
@@ -87,3 +89,112 @@ def test_rows_as_far_apart_as_accepted(d):
     ws = torch.empty(lf.linfusion_attn_workspace_bytes(1, 1, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
     _forward(q.cuda(), kd, vd, out, ws)
     parity.check_all(out, q, k, v, "f32", what=f"f32 far rows d={d}")
+
+
+# Values that the three bf16 terms of the matrix products do not hold (below 2^-110, from 2^127 on, infinities) are
+# multiplied on the fp32 instruction: the same 1e-5 at both ends of the type's range, in every kernel that splits.  Keys (or
+# queries) that are all alike leave the mean of v, with no averaging of what a tiny phi(k) loses.
+ENDS = ["keys -85", "queries -85", "values 1e-36", "values 3.4e38", "one token's values 3.4e38", "state 3.1e38",
+        "one key -84", "relu zeros"]
+
+
+def _ends(what, N, d):
+    q, k, v = wl.make_qkv(1, 2, N, d, "f32", idx=123, device="cpu")
+    fm = 0
+    if what == "keys -85":
+        k.fill_(-85.02)
+    elif what == "queries -85":
+        q.fill_(-85.02)
+    elif what == "values 1e-36":
+        v.mul_(1e-36)
+    elif what == "values 3.4e38":                    # (sums of phi(k) v and of phi(q) S stay finite)
+        v.clamp_(-1, 1).mul_(3.4e38)
+        v[0, 0, 0, 0] = v[0, 1, N - 1, d - 1] = 3.4e38
+        k.sub_(12)
+        q.sub_(12)
+    elif what == "one token's values 3.4e38":
+        v[:, :, N // 2] = 3.4e38
+        k.sub_(12)
+        q.sub_(12)
+    elif what == "state 3.1e38":
+        k[:, :, 1:] = -80.0
+        k[:, :, 0] = -0.1
+        v[:, :, 0] = 3.4e38
+        q.sub_(12)
+    elif what == "one key -84":
+        k[:, :, N - 1] = -84.0
+    else:
+        fm = 1
+        q, k = q.clamp_(min=0), k.clamp_(min=0)
+        q[..., 0] = k[..., 0] = 1.0
+    return q, k, v, fm
+
+
+@pytest.mark.parametrize("d", [8, 24, 40, 64])
+@pytest.mark.parametrize("what", ENDS)
+@pytest.mark.parametrize("N", [3, 300])
+def test_both_ends_of_the_range(what, N, d):
+    print(f"f32 {what}, N={N} d={d}", flush=True)
+    q, k, v, fm = _ends(what, N, d)
+    dev = [t.cuda() for t in (q, k, v)]
+    out = torch.full_like(dev[0], float("nan"))
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(1, 2, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
+    lf.linfusion_attn_fwd_ex(*dev, out, fm, 0.0, 0, ws)
+    state = torch.full((2, d * d + d), float("nan"), device="cuda")
+    lf.linfusion_attn_state(dev[1], dev[2], state, fm, ws)
+    torch.cuda.synchronize()
+    parity.check_all(out, q, k, v, "f32", fm, 0.0, True, f"f32 {what} N={N} d={d}")
+    for h in range(2):
+        S, z = orc.state(k[0, h].double().numpy(), v[0, h].double().numpy(), fm)
+        got = parity.to_f64(state[h])
+        for name, a, b in (("S", got[:d * d].reshape(d, d), S), ("z", got[d * d:], z)):
+            scale = (np.abs(orc.phi(k[0, h].double().numpy(), fm)).T @ np.abs(v[0, h].double().numpy())).max() if name == "S" else z.max()
+            assert np.abs(a - b).max() <= 1e-5 * scale, f"{what} N={N} d={d} h={h}: {name}"
+
+
+@pytest.mark.parametrize("d", [8, 24, 40, 64])
+def test_an_infinite_value_stays_in_its_channel(d):
+    N = 100
+    q, k, v = wl.make_qkv(1, 2, N, d, "f32", idx=124, device="cpu")
+    v[0, 0, 41, 3] = float("inf")
+    v[0, 1, 97, 5] = float("-inf")
+    out = torch.empty_like(q).cuda()
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(1, 2, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
+    lf.linfusion_attn_fwd_ex(q.cuda(), k.cuda(), v.cuda(), out, 0, 1e-6, 0, ws)
+    torch.cuda.synchronize()
+    assert (out[0, 0, :, 3] == float("inf")).all() and (out[0, 1, :, 5] == float("-inf")).all()
+    out[0, 0, :, 3] = out[0, 1, :, 5] = 0.0
+    v[0, 0, :, 3] = v[0, 1, :, 5] = 0.0
+    parity.check_all(out, q, k, v, "f32", 0, 1e-6, True, f"f32 infinite value d={d}")
+
+
+# gradients: (tokens, what) -- the products with g, with phi(q) and g / den, with v and with phi(k)
+@pytest.mark.parametrize("d", [8, 24, 40, 64])
+@pytest.mark.parametrize("what", ["keys -83", "queries -83", "dout 1e-34", "values 1e-36", "one key -83", "relu zeros"])
+@pytest.mark.parametrize("N", [3, 300])
+def test_gradients_at_both_ends_of_the_range(what, N, d):
+    print(f"f32 gradients, {what}, N={N} d={d}", flush=True)
+    q, k, v = wl.make_qkv(1, 2, N, d, "f32", idx=125, device="cpu")
+    g = wl.draw((1, 2, N, d), wl.BASE_SEED + 125777, "f32", "cpu")
+    fm = 0
+    if what == "keys -83":                           # (dv: phi(k) dS with dS of order g / den = 1e33)
+        k.fill_(-83.01)
+    elif what == "queries -83":
+        q.fill_(-83.01)
+    elif what == "dout 1e-34":
+        g.mul_(1e-34)
+    elif what == "values 1e-36":
+        v.mul_(1e-36)
+    elif what == "one key -83":
+        k[:, :, N - 1] = -83.0
+    else:
+        fm = 1
+        q, k = q.clamp_(min=0), k.clamp_(min=0)
+        q[..., 0] = k[..., 0] = 1.0
+    outs = [torch.full_like(q, float("nan")).cuda() for _ in range(3)]
+    ws = torch.empty(lf.linfusion_attn_bwd_workspace_bytes(1, 2, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
+    lf.linfusion_attn_bwd(*(t.cuda() for t in (q, k, v, g)), *outs, fm, 0.0, 0, ws)
+    torch.cuda.synchronize()
+    for h in range(2):
+        ins = [t[0, h].double().numpy() for t in (q, k, v, g)]
+        parity.check_gradients([parity.to_f64(t[0, h]) for t in outs], *ins, "f32", fm, 0.0, True, f"{what} N={N} d={d}")
