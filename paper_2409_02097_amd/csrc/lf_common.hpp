@@ -31,18 +31,25 @@ struct BF16 {};  // tag: bfloat16 storage
 // ---- feature map -------------------------------------------------------------------------
 // elu(x)+1 = x+1 for x > 0, exp(x) otherwise.  exp(x) = 2^(x*log2 e) on the hardware exp2
 // unit; `Precise` adds the rounding error of the product back as a first-order correction
-// (used on the fp32 path, whose tolerance is 1e-5).
-template <int FM, bool Precise = false>
+// (used on the fp32 path, whose tolerance is 1e-5).  `Masked`: so that keys masked with the type's lowest value or
+// -infinity give 0; without it a Precise x must not lie below about -1e4 (the correction would become infinite, and 0
+// times it NaN).
+template <int FM, bool Precise = false, bool Masked = Precise>
 LF_DEV float phi(float x) {
   if constexpr (FM == kPhiEluPlusOne) {
     constexpr float kLog2e = 1.44269504088896340736f;
-    float t = x * kLog2e;
-    float e = __builtin_amdgcn_exp2f(t);
     if constexpr (Precise) {
-      // t_err = x*log2e - t (exactly, via fma) plus the part of log2e that fp32 drops.
-      float terr = __builtin_fmaf(x, kLog2e, -t) + x * 1.92596299112661746e-8f;
-      e = __builtin_fmaf(e, terr * 0.69314718055994530942f, e);
+      // from -200 on, where exp(x) is 0 already; the branch above 0 does not use it
+      const float y = Masked ? __builtin_amdgcn_fmed3f(x, -200.0f, 0.0f) : x;
+      const float t = y * kLog2e;
+      const float e = __builtin_amdgcn_exp2f(t);
+      // t_err = y*log2e - t (exactly, via fma) plus the part of log2e that fp32 drops.
+      const float terr = __builtin_fmaf(y, kLog2e, -t) + y * 1.92596299112661746e-8f;
+      const float ex = __builtin_fmaf(e, terr * 0.69314718055994530942f, e);
+      if constexpr (Masked) return x <= 0.0f ? ex : x + 1.0f;   // (a NaN stays one)
+      return x > 0.0f ? x + 1.0f : ex;
     }
+    const float e = __builtin_amdgcn_exp2f(x * kLog2e);
     return x > 0.0f ? x + 1.0f : e;
   } else if constexpr (FM == kPhiRelu) {
     return x > 0.0f ? x : 0.0f;   // NaN maps to 0 like fmax(x, 0)

@@ -153,6 +153,10 @@ template <int FM> struct PhiSpan : Span {
     else return Span::passes();
   }
 };
+// A value that did not pass, for phi below: elu + 1 of anything from -200 down is 0.  (A NaN stays one.)
+template <int FM> LF_DEV float unmasked(float x) { return FM == kPhiEluPlusOne && x < -200.0f ? -200.0f : x; }
+// phi of a value that passed or has been unmasked
+template <int FM> LF_DEV float phi32(float x) { return phi<FM, true, false>(x); }
 
 template <int D> struct Tile32 {
   static constexpr int kCH = D / 4;                        // 16-byte chunks per token row
@@ -357,6 +361,24 @@ struct Ring32 {
     for (int T = 0; T < MT; ++T) sp.add(x[T]);
     return sp;
   }
+  // whether phi of every value of the wave passes; the values are fit for phi32 afterwards
+  template <int FM>
+  static LF_DEV bool phi_passes(f32x4 (&x)[MT]) {
+    PhiSpan<FM> sp;
+#pragma unroll
+    for (int T = 0; T < MT; ++T) {
+      sp.add(x[T][0], x[T][1]);
+      sp.add(x[T][2], x[T][3]);
+    }
+    const bool pass = sp.passes();
+    if (FM == kPhiEluPlusOne && !pass) {
+#pragma unroll
+      for (int T = 0; T < MT; ++T)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[T][e] = unmasked<FM>(x[T][e]);
+    }
+    return pass;
+  }
   static LF_DEV bool exact(const f32x4 (&x)[MT]) {   // of this lane's values
     bool ok = true;
 #pragma unroll
@@ -365,8 +387,8 @@ struct Ring32 {
       for (int e = 0; e < 4; ++e) ok &= splits_exactly(rarely(x[T][e]));
     return ok;
   }
-  // x in row form, finite past d; sp = span(x); A and raw from build_A
-  LF_DEV void products(const Split8 (&A)[MT][KS], bool raw, const f32x4 (&x)[MT], const Span& sp, f32x4 (&acc)[MT]) const {
+  // x in row form, finite past d; pass: whether the wave's values are known to split exactly; A and raw from build_A
+  LF_DEV void products(const Split8 (&A)[MT][KS], bool raw, const f32x4 (&x)[MT], bool pass, f32x4 (&acc)[MT]) const {
     const f32x4 none = f32x4{0, 0, 0, 0};
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[t] = none;
@@ -377,7 +399,7 @@ struct Ring32 {
         for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(__builtin_bit_cast(f32x4, A[t][T / 2].t[T % 2]), x[T], acc[t]);
       return;
     }
-    if (!sp.passes() && !all_lanes(exact(x))) {
+    if (!pass && !all_lanes(exact(x))) {
 #pragma unroll
       for (int T = 0; T < MT; ++T)
 #pragma unroll
@@ -533,7 +555,7 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
   };
   auto phi_of = [&](int i, const float (&k)[8][CPL], float (&p)[8]) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) p[j] = phi<FM, true>(k[j][i]);
+    for (int j = 0; j < 8; ++j) p[j] = phi32<FM>(k[j][i]);
     z[i] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
   };
   int lim = 0;
@@ -564,8 +586,10 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
 #pragma unroll
       for (int i = 0; i < CPL; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          exact &= splits_exactly(phi<FM, true>(rarely(k[j][i]))) & splits_exactly(rarely(v[j][i]));
+        for (int j = 0; j < 8; ++j) {
+          k[j][i] = unmasked<FM>(k[j][i]);
+          exact &= splits_exactly(phi32<FM>(rarely(k[j][i]))) & splits_exactly(rarely(v[j][i]));
+        }
       if (!all_lanes(exact)) {
         it = cur;
         break;
@@ -592,6 +616,8 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
     take(k, v, lim);
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) k[j][i] = unmasked<FM>(k[j][i]);
       float p[8];
       phi_of(i, k, p);
 #pragma unroll
@@ -671,15 +697,16 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
     iter = iter < 2 ? iter + 1 : 2;
     f32x4 r[MT], acc[MT];
     rg.read_rows(slot, 0, r);
+    const bool pass = RG::template phi_passes<FM>(r);
     float den = 0.0f;
 #pragma unroll
     for (int T = 0; T < MT; ++T)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        r[T][e] = phi<FM, true>(r[T][e]);
+        r[T][e] = phi32<FM>(r[T][e]);
         if constexpr (NORM) den = __builtin_fmaf(r[T][e], z[T][e], den);
       }
-    rg.products(A, raw, r, RG::span(r), acc);
+    rg.products(A, raw, r, pass, acc);
     if constexpr (NORM) {
       const float scale = 1.0f / (RG::token_sum(den) + eps);
 #pragma unroll
@@ -739,14 +766,15 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     rg.read_rows(slot, 1, g);
     rg.read_rows(slot, 0, x);
     const Span gs = RG::span(g);
-    rg.products(A, raw, g, gs, u);
+    rg.products(A, raw, g, gs.passes(), u);
+    const bool pass = RG::template phi_passes<FM>(x);
     f32x4 r[MT];
     float den = 0.0f, ru = 0.0f;
 #pragma unroll
     for (int T = 0; T < MT; ++T)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        r[T][e] = phi<FM, true>(x[T][e]);
+        r[T][e] = phi32<FM>(x[T][e]);
         if constexpr (NORM) {
           den = __builtin_fmaf(r[T][e], z[T][e], den);   // z and u are zero past d
           ru = __builtin_fmaf(r[T][e], u[T][e], ru);
@@ -773,12 +801,9 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
         if constexpr (NORM) dz[T][e] = __builtin_fmaf(r[T][e], e_i, dz[T][e]);
       }
     // (g / den lies within what its tile's extremes divided by den span, so those need not be sought again)
-    Span rs = RG::span(r);
-    if (on) {
-      rs.lo = fminf(rs.lo, gs.lo * fabsf(invden));
-      rs.hi = fmaxf(rs.hi, gs.hi * fabsf(invden));
-    }
-    const bool split = rs.passes() || all_lanes(RG::exact(r) & RG::exact(g));
+    const float by = fabsf(invden);
+    const bool split = (pass && all_lanes(!on || (gs.lo * by >= kSplitLow && gs.hi * by < kSplitHigh))) ||
+                       all_lanes(RG::exact(r) & RG::exact(g));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     rg.write_rows(slot, 0, r);
     rg.write_rows(slot, 1, g);
@@ -884,17 +909,18 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
     f32x4 k[MT], v[MT], t[MT], dv[MT], p[MT];
     rg.read_rows(slot, 1, v);
     rg.read_rows(slot, 0, k);
-    rg.products(A, raw, v, RG::span(v), t);
+    rg.products(A, raw, v, RG::span(v).passes(), t);
+    const bool pass = RG::template phi_passes<FM>(k);
 #pragma unroll
     for (int T = 0; T < MT; ++T)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        p[T][e] = phi<FM, true>(k[T][e]);
+        p[T][e] = phi32<FM>(k[T][e]);
         if constexpr (FM == kPhiEluPlusOne) k[T][e] = k[T][e] > 0.0f ? 1.0f : p[T][e];     // phi'(k)
         else if constexpr (FM == kPhiRelu) k[T][e] = k[T][e] > 0.0f ? 1.0f : 0.0f;
         else k[T][e] = 1.0f;
       }
-    rg.products(At, raw, p, RG::span(p), dv);
+    rg.products(At, raw, p, pass, dv);
 #pragma unroll
     for (int T = 0; T < MT; ++T) k[T] *= t[T] + dz[T];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -95,7 +95,7 @@ def test_rows_as_far_apart_as_accepted(d):
 # multiplied on the fp32 instruction: the same 1e-5 at both ends of the type's range, in every kernel that splits.  Keys (or
 # queries) that are all alike leave the mean of v, with no averaging of what a tiny phi(k) loses.
 ENDS = ["keys -85", "queries -85", "values 1e-36", "values 3.4e38", "one token's values 3.4e38", "state 3.1e38",
-        "one key -84", "relu zeros"]
+        "one key -84", "masked keys", "relu zeros"]
 
 
 def _ends(what, N, d):
@@ -123,6 +123,8 @@ def _ends(what, N, d):
         q.sub_(12)
     elif what == "one key -84":
         k[:, :, N - 1] = -84.0
+    elif what == "masked keys":
+        k[:, :, ::3] = torch.finfo(torch.float32).min
     else:
         fm = 1
         q, k = q.clamp_(min=0), k.clamp_(min=0)
@@ -198,3 +200,25 @@ def test_gradients_at_both_ends_of_the_range(what, N, d):
     for h in range(2):
         ins = [t[0, h].double().numpy() for t in (q, k, v, g)]
         parity.check_gradients([parity.to_f64(t[0, h]) for t in outs], *ins, "f32", fm, 0.0, True, f"{what} N={N} d={d}")
+
+
+# keys masked with the type's lowest value or -infinity count as nothing (phi = 0) on every fp32 route, a NaN as NaN
+@pytest.mark.parametrize("flags", [lf.FLAG_FORCE_SPLIT, lf.FLAG_FORCE_FUSED, lf.FLAG_FORCE_SOLO])
+@pytest.mark.parametrize("mask", [torch.finfo(torch.float32).min, float("-inf")])
+@pytest.mark.parametrize("d", [8, 40, 64])
+def test_masked_keys_count_as_nothing(mask, d, flags):
+    B, H, N = 1, 2, 200
+    q, k, v = wl.make_qkv(B, H, N, d, "f32", idx=126, device="cpu")
+    k[:, :, 150:] = mask
+    out = torch.full_like(q, float("nan")).cuda()
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(B, H, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
+    dev = [t.cuda() for t in (q, k, v)]
+    lf.linfusion_attn_fwd_ex(*dev, out, 0, 1e-6, flags, ws)
+    torch.cuda.synchronize()
+    parity.check_all(out, q, torch.where(k == mask, torch.full_like(k, -1e4), k), v, "f32", 0, 1e-6, True,
+                     f"f32 masked keys d={d} flags={flags}")
+    dev[0][0, 0, 7, 1] = dev[1][0, 1, 3, 2] = float("nan")    # a query of head 0, a key of head 1
+    lf.linfusion_attn_fwd_ex(*dev, out, 0, 1e-6, flags, ws)
+    torch.cuda.synchronize()
+    bad = torch.isnan(out).all(dim=3)
+    assert bad[0, 0].nonzero().flatten().tolist() == [7] and bad[0, 1].all() and torch.isfinite(out[0, 0, :7]).all()
