@@ -458,7 +458,7 @@ bwd_kv16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout l
 // order, not bit for bit; dQ does not depend on them.)
 // bf16 carries phi(q), g beta / den and e beta in two levels as bwd_qs16 does.  Two waves per SIMD leave 256 registers,
 // some fifty too few (a spill reload would wait for every copy of the ring): the low level of the operands of u = S g and
-// z stay in LDS, where the ring leaves room with two slots, phi' is kept as sign bits, chunk places are worked out where
+// z stay in LDS, where the ring leaves room with two slots, q is read again for phi', chunk places are worked out where
 // they are used, and where d is no multiple of 16 e is a column of g's last block (dz then needs no accumulators).  Before, bf16 took
 // bwd_q16_rows and the per-head bwd_state16, whose 80-byte rows are fragments of cache lines: 28 + 48 us at 12 x 8 x 4096
 // x 40, 44 us now.  LDS: qs_rows_lds_bytes<T, D, W>().
@@ -589,9 +589,8 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
     if constexpr (NS == 1) rg.products(A, Bg, nullptr, acc);
     else rg.products_lds(A, Al, Bg, acc);
     // dq and phi(q) leave this block as the 16-bit words that go to LDS (bf16: phi(q) as a rounded value plus the
-    // remainder).  bf16 is short of registers: it keeps phi'(q) as one sign bit per element and takes the value
-    // back from the two levels of phi(q) (16 significant bits; elu + 1 and relu have phi' = 1 where q > 0, else phi
-    // resp. 0, the identity map 1 everywhere).
+    // remainder).  bf16 is short of registers: it reads q again for phi'(q) rather than keep it (in fp32 it comes from q
+    // or phi(q) as bwd_q16_rows takes it; from the two levels of phi(q) it would have 16 bits).
     uint32_t dqw[HALF / 2], rw[NS][HALF / 2];
     float gsc = ok ? 1.0f : 0.0f, e = 0.0f;
     {
@@ -599,7 +598,6 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
       rg.read_half_row_words(slot, 0, xw);
       float x[NS == 1 ? HALF : 1], dr[HALF];
       float denp = 0.0f, rup = 0.0f;
-      uint64_t pos = 0;   // bit i: q at output channel i is positive
 #pragma unroll
       for (int i = 0; i < HALF; i += 2) {
         float r[2], xi[2];
@@ -612,7 +610,6 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
           rup = __builtin_fmaf(r[q], u, rup);
           dr[i + q] = u;
           if constexpr (NS == 1) x[i + q] = phi_prime_from<FM>(xi[q], r[q]);
-          else pos |= (uint64_t)(xi[q] > 0.0f ? 1u : 0u) << (i + q);
           r[q] = ok ? r[q] : 0.0f;
         }
         if constexpr (NS == 1) rw[0][i / 2] = pack2<T>(r[0], r[1]);
@@ -621,14 +618,10 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
       auto phi_prime = [&](int i) -> float {
         if constexpr (NS == 1) {
           return x[i];
-        } else if constexpr (FM == kPhiIdentity) {
-          return 1.0f;
         } else {
-          float h[2], l[2];
-          unpack2<T>(rw[0][i / 2], h[0], h[1]);
-          unpack2<T>(rw[1][i / 2], l[0], l[1]);
-          const float below = FM == kPhiRelu ? 0.0f : h[i & 1] + l[i & 1];
-          return (pos >> i) & 1u ? 1.0f : below;
+          float xi[2];
+          unpack2<T>(xw[i / 2], xi[0], xi[1]);
+          return phi_prime_from<FM>(xi[i & 1], phi<FM>(xi[i & 1]));
         }
       };
       if constexpr (NORM) {
@@ -636,6 +629,10 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
         const float ru = rup + __shfl_xor(rup, 32);
         const float invden = 1.0f / den;
         const float go = ru * invden;
+        if constexpr (NS == 2) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (read again, not kept)
+          rg.read_half_row_words(slot, 0, xw);
+        }
 #pragma unroll
         for (int i = 0; i < HALF; ++i) dr[i] = (dr[i] - go * zv(i)) * invden * phi_prime(i);
         gsc = ok ? invden * beta : 0.0f;

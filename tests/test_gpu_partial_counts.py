@@ -87,3 +87,27 @@ def test_row_piece_backward_of_many_heads(B, H, N, d, dtype, monkeypatch, tuning
     torch.cuda.synchronize()
     assert all(torch.isfinite(o).all() for o in outs)
     _gradients_match([o.contiguous() for o in outs], (q, k, v, g), dtype, "row-piece backward")
+
+
+# phi'(q) in fp32 in the merged row-piece kernel as in the separate one: the same dq to the bit (both W, every map)
+@pytest.mark.parametrize("H,d,fm", [(8, 40, 0), (4, 40, 0), (8, 32, 0), (8, 24, 0), (12, 16, 0), (8, 8, 0), (8, 40, 1), (8, 40, 2)])
+@pytest.mark.parametrize("flags", [0, lf.FLAG_UNNORMALIZED])
+def test_row_piece_dq_is_the_separate_kernels(H, d, fm, flags, monkeypatch, tuning):
+    B, N, dtype = 2, 1500, "bf16"
+    print(f"row-piece dq H={H} d={d} fm={fm} flags={flags}", flush=True)
+    q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=143, device="cpu")
+    if fm == 2:
+        q, k = q.abs() + 0.1, k.abs() + 0.1
+    g = wl.draw((B, H, N, d), wl.BASE_SEED + 14343, dtype, "cpu")
+    tm = lambda t: t.permute(0, 2, 1, 3).contiguous().cuda().permute(0, 2, 1, 3)
+    dev = [tm(t) for t in (q, k, v, g)]
+    ws = _scratch(lf.linfusion_attn_bwd_workspace_bytes(B, H, N, d, wl.DTYPE_CODE[dtype]))
+    monkeypatch.setenv("LINFUSION_BWD_ROWS", "3")
+    got = []
+    for merged in ("1", "2"):
+        monkeypatch.setenv("LINFUSION_BWD_MERGED", merged)
+        outs = [torch.full_like(dev[0], float("nan")) for _ in range(3)]
+        lf.linfusion_attn_bwd_strided(*dev, *outs, fm, 1e-6, flags, ws)
+        torch.cuda.synchronize()
+        got.append(outs[0].contiguous().view(torch.int16))
+    assert torch.equal(got[0], got[1]), f"{(got[0] != got[1]).sum().item()} of {got[0].numel()} values differ"
