@@ -142,10 +142,23 @@ def _current_stream() -> int:
         import torch
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         device = getattr(torch._C, "_cuda_getDevice", None)
-        if raw is None or device is None:
+        try:                                  # (names of torch's own: taken only where they answer as the public call does)
+            same = raw(device()) == handle
+        except Exception:
+            same = False
+        if not same:
             return handle
         _raw_device, _raw_stream = device, raw   # (in this order: another thread looks at the second)
     return _raw_stream(_raw_device())
+
+
+def _forget_stream_lookup():
+    global _raw_stream
+    _raw_stream = None
+
+
+# A forked child cannot use its parent's GPU runtime; torch says so on the next public lookup, the raw one does not ask.
+os.register_at_fork(after_in_child=_forget_stream_lookup)
 
 
 def _stream_ptr(stream) -> int:

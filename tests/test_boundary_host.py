@@ -113,6 +113,43 @@ def _call(q=4096, k=1 << 20, v=2 << 20, out=3 << 20, B=1, H=2, N=64, d=40, dtype
     return lf.library().linfusion_attn_fwd_ex(q, k, v, out, B, H, N, d, dtype, fm, eps, flags, ws, ws_bytes, None)
 
 
+def test_a_forked_child_asks_torch_for_its_stream_again(monkeypatch):
+    """A child cannot use the runtime that its parent initialised: torch's public lookup raises there, and so must a call
+    of this binding, also where the parent has made calls before."""
+    from paper_2409_02097_amd import binding
+
+    def refuse():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+
+    monkeypatch.setattr(binding, "_raw_device", lambda: 0)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 5)
+    monkeypatch.setattr(binding, "_torch_current_stream", refuse)
+    assert binding._current_stream() == 5
+    pid = os.fork()
+    if pid == 0:
+        try:
+            binding._current_stream()
+        except RuntimeError:
+            os._exit(0)
+        os._exit(1)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0, "the child used its parent's lookup"
+    assert binding._current_stream() == 5
+
+
+def test_the_raw_stream_lookup_has_to_agree_with_the_public_one(monkeypatch):
+    import torch
+    from paper_2409_02097_amd import binding
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(binding, "_torch_current_stream", lambda: 7)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 8, raising=False)
+    assert binding._current_stream() == 7 and binding._raw_stream is None
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda: 7, raising=False)   # another signature
+    assert binding._current_stream() == 7 and binding._raw_stream is None
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 7, raising=False)
+    assert binding._current_stream() == 7 and binding._raw_stream is not None
+
+
 @fake_addresses
 def test_argument_validation_happens_on_the_host():
     assert _call(q=None) == -1 and _call(k=None) == -1 and _call(v=None) == -1 and _call(out=None) == -1
