@@ -556,7 +556,8 @@ int run16(const Args& a) {
   // head's: one launch fewer (us per call: fp16 8 x 40 at 1000 tokens 15.2 -> 12.3, bf16 token-major 32 x 40 at 1000 17.2 ->
   // 15.0, fp16 64 x 24 at 3000 18.9 -> 18.0; at 120 KB, 80 x 64 at 2000, equal, at 200 KB slower by half).
   const int parts = a.group_reduce ? p.gsplits : p.splits;
-  const bool fold = a.out && !a.group_apply && !p.apply_packed && parts <= kFoldParts &&
+  // (LINFUSION_FOLD = 2 under tuning: never)
+  const bool fold = a.out && !a.group_apply && !p.apply_packed && parts <= kFoldParts && env_int("LINFUSION_FOLD", 1) == 1 &&
                     (size_t)parts * NE * sizeof(float) <= (size_t)env_int("LINFUSION_FOLD_KB", 64) * 1024;
   if (!fold)
     combine_state<0><<<dim3((NE + kCombineElems - 1) / kCombineElems, (unsigned)a.BH), dim3(kCombineThreads), 0, st>>>(

@@ -20,8 +20,10 @@ constexpr bool narrow_apply(int d) { return d <= 24; }
 // Whether the consumers of a state sum its partials themselves (see lf_ring32.hpp): every workgroup then reads
 // parts * (d^2 + d) floats, which up to 64 KB is cheaper than the launch it saves (96 heads of 40 channels, five partials
 // each: training step 200.7 -> 197.7 us), beyond that not (20 heads of 64, 25 partials of 16 KB: 83 -> 90 us).
+// (LINFUSION_FOLD = 2 under tuning: never)
 bool fold(int parts, int d) {
-  return parts <= lf::kFoldParts && (long long)parts * ne_of(d) * 4 <= (long long)lfh::env_int("LINFUSION_F32_FOLD_KB", 64) * 1024;
+  return parts <= lf::kFoldParts && lfh::env_int("LINFUSION_FOLD", 1) == 1 &&
+         (long long)parts * ne_of(d) * 4 <= (long long)lfh::env_int("LINFUSION_F32_FOLD_KB", 64) * 1024;
 }
 // the forward state's partials: the same answer in the forward and in the backward pass, so that the state (and with it
 // every result) has the same bits whether it is handed over or computed again

@@ -1,6 +1,8 @@
 """GPU parity where the number of partial states per head decides the route: the narrow heads' apply kernel sums up to
 eight partials itself, the backward pass above width 80 packs its operands from one partial, a few or many, and the
 backward pass on row pieces takes as many workgroups as there is room for partials."""
+import ctypes
+
 import pytest
 import torch
 
@@ -26,6 +28,17 @@ def _gradients_match(outs, ins, dtype, what):
         parity.check_gradients([parity.to_f64(t[b, h]) for t in outs], *w, dtype, 0, 1e-6, True, f"{what} b={b} h={h}")
 
 
+def _launches(call):
+    """How many nodes the call records into a graph: its launches."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)   # the one torch runs on
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    count = ctypes.c_size_t(0)
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
 # 64 to 20001 tokens: one partial, two to eight, more
 @pytest.mark.parametrize("dtype,d", [("f16", 40), ("bf16", 64), ("f16", 8), ("bf16", 80), ("f32", 40), ("f32", 64)])
 @pytest.mark.parametrize("N", [64, 129, 300, 700, 1000, 2100, 20001])
@@ -36,16 +49,18 @@ def test_narrow_partials_summed_by_the_apply_kernel(N, d, dtype, monkeypatch, tu
     q, k, v = (t.cuda() for t in wl.make_qkv(B, H, N, d, dtype, idx=140))
     ws = _scratch(lf.linfusion_attn_workspace_bytes(B, H, N, d, code))
     off = lf.linfusion_attn_workspace_state_offset(B, H, N, d, code)
+    parts = lf.linfusion_attn_plan(B, H, N, d, code, lf.FLAG_FORCE_SPLIT)["reduce_wgs_per_head"]
+    folded = parts <= 8 and parts * (d * d + d) * 4 <= 65536
     res = []
-    for kb in (None, "0"):                      # "0": a launch of its own sums them, whatever their number
-        if kb is not None:
-            monkeypatch.setenv("LINFUSION_FOLD_KB", kb)
-            monkeypatch.setenv("LINFUSION_F32_FOLD_KB", kb)
+    for fold in ("1", "2"):                     # "2": a launch of its own sums them, whatever their number
+        monkeypatch.setenv("LINFUSION_FOLD", fold)
         ws.fill_(0xFF)
         out = torch.full_like(q, float("nan"))
-        lf.linfusion_attn_fwd_ex(q, k, v, out, 0, 1e-6, lf.FLAG_FORCE_SPLIT, ws)
+        call = lambda: lf.linfusion_attn_fwd_ex(q, k, v, out, 0, 1e-6, lf.FLAG_FORCE_SPLIT, ws)
+        call()
         torch.cuda.synchronize()
         res.append((out, ws[off:off + B * H * (d * d + d) * 4].clone()))
+        assert _launches(call) == (2 if folded and fold == "1" else 3)
     parity.check_all(res[0][0], q, k, v, dtype, what=f"narrow partials {N}x{d}")
     # the same order of additions: the same bits, in the output and in the state left in the workspace
     assert torch.equal(res[0][0].view(torch.uint8), res[1][0].view(torch.uint8))
