@@ -66,9 +66,15 @@ struct WideArgs {
 // the others wait (us at the least of the sum -> one per CU: fp16 4 x 8 x 4096 x 160 70.6 -> 62.4, 12 x 8 x 1024 x 160
 // 62.4 -> 56.4, bf16 2 x 8 x 4096 x 160 52.8 -> 46.3, 4 x 16 x 2048 x 128 60.9 -> 56.2; near two per CU -> two: 2 x 8 x
 // 16384 x 160 108 -> 98 to 105).  Long streams stay at what fills the chip.
-inline int wide_reduce_wgs(long long heads, long long tiles, int d, int fill, int cus) {
+// `ratio`: a tile's time over that of a partial's MB, 3 for the mixer alone.  The MLP-fed reduction's tiles have a third
+// stream and the branch sum to form, and it has to reach two workgroups per CU sooner: with 3 it lost to the two per CU that
+// it always had before at bf16 4 x 8 x 4096 x 160 (112.7 -> 121.7 us per call), 1 x 8 x 16384 x 160 (104.5 -> 117.0), fp16 1 x 10
+// x 4096 x 128 (47.9 -> 53.2); kMlpTileRatio gives those their two and keeps what fewer gain (4 x 8 x 256 x 160 44.8 -> 43.1,
+// 2 x 8 x 1024 x 160 47.9 -> 45.3, 4 x 8 x 1024 x 160 64.4 -> 59.2, 4 x 16 x 512 x 128 51.2 -> 46.2).
+constexpr double kMlpTileRatio = 11.0;
+inline int wide_reduce_wgs(long long heads, long long tiles, int d, int fill, int cus, double ratio = 3.0) {
   const double mb = (double)heads * ((double)d * d + d) * 4e-6;
-  const double s = __builtin_sqrt(3.0 * (double)tiles / mb) + 0.5;
+  const double s = __builtin_sqrt(ratio * (double)tiles / mb) + 0.5;
   const long long want = (s < 1.0 ? 1 : (s > 1e6 ? 1000000 : (long long)s)) * heads;
   if (want >= fill) return fill;
   if (4 * want >= 7 * (long long)cus) return want > 2 * cus ? (int)want : 2 * cus;   // (`fill` is two per CU or more)

@@ -105,7 +105,7 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     const int lds_apply = (2 * 3 * slot + 3 * 1024) * lf::kWavesPerWG;
     const int resident = (!wide && 160 * 1024 / lds_apply > 0) ? 160 * 1024 / lds_apply : 1;
     int want = 2 * lfh::num_cu();
-    if (wide) want = lfw::wide_reduce_wgs(units, n_tiles, d, want, lfh::num_cu());
+    if (wide) want = lfw::wide_reduce_wgs(units, n_tiles, d, want, lfh::num_cu(), lfw::kMlpTileRatio);
     p->splits = per_head(lfh::env_int("LINFUSION_MLPH_REDUCE_WGS", want),
                          lfh::env_int("LINFUSION_MLPH_REDUCE_BLK", wide ? 4 : 8), &p->blk_reduce);
     p->apply_wgs = per_head(lfh::env_int("LINFUSION_MLPH_APPLY_WGS", resident * lfh::num_cu()),

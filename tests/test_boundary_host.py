@@ -113,6 +113,16 @@ def _call(q=4096, k=1 << 20, v=2 << 20, out=3 << 20, B=1, H=2, N=64, d=40, dtype
     return lf.library().linfusion_attn_fwd_ex(q, k, v, out, B, H, N, d, dtype, fm, eps, flags, ws, ws_bytes, None)
 
 
+@pytest.mark.parametrize("B,H,N,d,wgs", [(4, 8, 4096, 160, 512), (2, 8, 4096, 160, 512), (1, 8, 16384, 160, 512),
+                                         (1, 10, 4096, 128, 512), (2, 8, 1024, 160, 256), (4, 8, 1024, 160, 256),
+                                         (4, 16, 512, 128, 256), (4, 8, 256, 160, 128)])
+def test_reduction_workgroups_of_the_wide_mlp_fed_call(B, H, N, d, wgs, monkeypatch, tuning):
+    """How many were measured best on 256 compute units (lf_wide_api.hpp), read off the scratch that their partials take."""
+    chosen = lf.linfusion_attn_mlp_workspace_bytes(B, H, N, d, lf.DTYPE_BF16)
+    monkeypatch.setenv("LINFUSION_MLPH_REDUCE_WGS", str(wgs))
+    assert chosen == lf.linfusion_attn_mlp_workspace_bytes(B, H, N, d, lf.DTYPE_BF16)
+
+
 def test_a_forked_child_asks_torch_for_its_stream_again(monkeypatch):
     """A child cannot use the runtime that its parent initialised: torch's public lookup raises there, and so must a call
     of this binding, also where the parent has made calls before."""
