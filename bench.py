@@ -353,7 +353,7 @@ def main():
     evs.close()
     kms = [a / max(args.profile_steps, 1) for a in acc]
     tag = {"f16": "<F16", "bf16": "<BF16", "f32": ""}[dtype]
-    rname = ("state_reduce32" if dtype == "f32" else "state_reduce16") + tag
+    rname = ("state_reduce32s" if dtype == "f32" else "state_reduce16") + tag
     aname = lf.linfusion_attn_apply_kernel(B, H, N, d, code, args.flags) + tag
     mid = "combine_state + pack_state16" if aname.startswith("apply16_packed") else "combine_state"
     if d > 80:

@@ -29,6 +29,7 @@ struct Fwd32Args {
   hipEvent_t* ev;             // null, or four events around the kernels
 };
 int run_fwd32(const Fwd32Args& a);
+const char* apply32_name(int d);   // the kernel that its apply step takes
 
 // gradients of q, k, v
 struct Bwd32Args {

@@ -1094,7 +1094,7 @@ const char* linfusion_attn_apply_kernel(int B, int H, long long N, int d, int dt
   if (is_wide(d)) return p.wave_apply ? "apply16_wave" : "apply16_wide";
   if (p.path == 2) return dtype == LINFUSION_DTYPE_F32 ? "solo32" : "solo16";
   if (p.path == 1) return dtype == LINFUSION_DTYPE_F32 ? "fused32" : "fused16";
-  if (dtype == LINFUSION_DTYPE_F32) return "apply32";
+  if (dtype == LINFUSION_DTYPE_F32) return lf32::apply32_name(d);
   return p.apply_packed ? "apply16_packed" : "apply16_dma";
 }
 

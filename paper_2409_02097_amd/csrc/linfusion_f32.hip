@@ -150,6 +150,8 @@ int bwd_fm(const Bwd32Args& a, const Regions& r) {
 
 }  // namespace
 
+const char* apply32_name(int d) { return narrow_apply(d) ? "apply32" : "apply32s"; }
+
 int run_fwd32(const Fwd32Args& a) {
   switch (a.d) {
 #define X(DD) case DD: return fwd_fm<DD>(a);

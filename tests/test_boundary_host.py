@@ -113,6 +113,13 @@ def _call(q=4096, k=1 << 20, v=2 << 20, out=3 << 20, B=1, H=2, N=64, d=40, dtype
     return lf.library().linfusion_attn_fwd_ex(q, k, v, out, B, H, N, d, dtype, fm, eps, flags, ws, ws_bytes, None)
 
 
+def test_apply_kernel_names_of_fp32():
+    """fp32 applies on the fp32 instruction up to 24 channels and on three bf16 terms above."""
+    for d, name in ((8, "apply32"), (24, "apply32"), (32, "apply32s"), (64, "apply32s")):
+        assert lf.linfusion_attn_apply_kernel(1, 8, 4096, d, lf.DTYPE_F32) == name
+    assert lf.linfusion_attn_apply_kernel(1, 8, 4096, 64, lf.DTYPE_F32, lf.FLAG_FORCE_FUSED) == "fused32"
+
+
 @pytest.mark.parametrize("B,H,N,d,wgs", [(4, 8, 4096, 160, 512), (2, 8, 4096, 160, 512), (1, 8, 16384, 160, 512),
                                          (1, 10, 4096, 128, 512), (2, 8, 1024, 160, 256), (4, 8, 1024, 160, 256),
                                          (4, 16, 512, 128, 256), (4, 8, 256, 160, 128)])
