@@ -12,9 +12,9 @@
 // runs into bf16's subnormals (phi of a key below -76 is such a value), and just above 2^127 the first term may round to
 // infinity; an infinity leaves NaN as its second term.  A tile with such a value, or a head whose state has one, is
 // therefore multiplied on the fp32 instruction, from the same registers: the operands and results of both instructions lie
-// alike in the lanes; the state reduction goes on with it from the first such tile of a wave.  The test costs one instruction
-// per value (Span): 20 heads of 64 channels and 16384 tokens 83.1 -> 85.9 us per call, forward and backward of 96 heads of 40 and
-// 4096 tokens 183 -> 192.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
+// alike in the lanes; the state reduction goes on with it from the first such tile of a wave.  The test (Low) costs half an
+// instruction per value, one in bwd_qs32: 20 heads of 64 channels and 16384 tokens 83.1 -> 85.9 us per call, forward and backward
+// of 96 heads of 40 and 4096 tokens 183 -> 192.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
 //
 //   state_reduce32s  S, z partials        reads K, V                       (Prop. 2: g'(X)^T X; Eq. 5: Z)
 //   apply32s         out                  reads Q, writes out
@@ -124,34 +124,34 @@ LF_DEV bool splits_exactly(float x) {   // (a NaN does as well as any: either in
   return !((a < kSplitLow) & (a > 0.0f)) & !(a >= kSplitHigh);
 }
 LF_DEV bool all_lanes(bool x) { return __builtin_amdgcn_ballot_w64(!x) == 0; }
-// smallest and largest magnitude seen: passes only where none is 0; splits_exactly decides where this does not
-struct Span {
-  float lo = 1.0f, hi = 1.0f;
-  // (written out: left to itself the compiler quiets every operand of a minimum or maximum first)
-  LF_DEV void add(float a, float b) {
-    asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(lo) : "v"(a), "v"(b));
-    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(a), "v"(b));
-  }
-  LF_DEV void add(f32x4 x) {
-    add(x[0], x[1]);
-    add(x[2], x[3]);
-  }
-  LF_DEV bool passes() const { return all_lanes(lo >= kSplitLow && hi < kSplitHigh); }
+// What a wave tests before it splits: the smallest magnitude.  (The three terms of an infinity, or of a value that the first
+// term rounds to one, end in a NaN, which every product with them shows afterwards: nothing has to look for those first.)
+// Passes only where no value is 0; splits_exactly decides where this does not.
+struct Low {
+  float lo = 1.0f;
+  // (written out: left to itself the compiler quiets every operand of a minimum first)
+  LF_DEV void add(float a, float b) { asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(lo) : "v"(a), "v"(b)); }
+  LF_DEV bool passes() const { return all_lanes(lo >= kSplitLow); }
 };
 // the same for phi of the values that are given: elu + 1 is e^x below 0, and e^-76 above 2^-110
-template <int FM> struct PhiSpan : Span {
+template <int FM> struct PhiLow : Low {
   LF_DEV void add(float a, float b) {
-    if constexpr (FM == kPhiEluPlusOne) {
-      asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lo) : "v"(a), "v"(b));
-      asm("v_max3_f32 %0, %1, %2, %0" : "+v"(hi) : "v"(a), "v"(b));
-    } else {
-      Span::add(a, b);
-    }
+    if constexpr (FM == kPhiEluPlusOne) asm("v_min3_f32 %0, %1, %2, %0" : "+v"(lo) : "v"(a), "v"(b));
+    else Low::add(a, b);
   }
   LF_DEV bool passes() const {
-    if constexpr (FM == kPhiEluPlusOne) return all_lanes(lo >= -76.0f && hi < 0.5f * kSplitHigh);
-    else return Span::passes();
+    if constexpr (FM == kPhiEluPlusOne) return all_lanes(lo >= -76.0f);
+    else return Low::passes();
   }
+};
+// with the largest magnitude too, where nothing is looked at afterwards
+template <typename L> struct Both : L {
+  float hi = 1.0f;
+  LF_DEV void add(float a, float b) {
+    L::add(a, b);
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(a), "v"(b));
+  }
+  LF_DEV bool passes() const { return L::passes() && all_lanes(hi < 0.5f * kSplitHigh); }   // (half: x + 1 may round up)
 };
 // A value that did not pass, for phi below: elu + 1 of anything from -200 down is 0.  (A NaN stays one.)
 template <int FM> LF_DEV float unmasked(float x) { return FM == kPhiEluPlusOne && x < -200.0f ? -200.0f : x; }
@@ -280,7 +280,7 @@ struct Ring32 {
   LF_DEV void read_rows(int slot, int which, f32x4 (&x)[MT]) const {
 #pragma unroll
     for (int T = 0; T < MT; ++T) {
-      x[T] = f32x4{1, 1, 1, 1};   // (past d: multiplied by zeros of the state, and no 0 that Span would stop at)
+      x[T] = f32x4{1, 1, 1, 1};   // (past d: multiplied by zeros of the state, and no 0 that would not pass)
       if (has(T)) x[T] = *reinterpret_cast<const f32x4*>(tile_ptr(slot, which) + TC::place(m, 4 * T + kq));
     }
   }
@@ -355,22 +355,20 @@ struct Ring32 {
       if (has(T)) z[T] = *reinterpret_cast<const f32x4*>(st + D * D + 16 * T + 4 * kq);
     }
   }
-  static LF_DEV Span span(const f32x4 (&x)[MT]) {
-    Span sp;
-#pragma unroll
-    for (int T = 0; T < MT; ++T) sp.add(x[T]);
-    return sp;
-  }
-  // whether phi of every value of the wave passes; the values are fit for phi32 afterwards
-  template <int FM>
-  static LF_DEV bool phi_passes(f32x4 (&x)[MT]) {
-    PhiSpan<FM> sp;
+  template <typename L>
+  static LF_DEV L seen(const f32x4 (&x)[MT]) {
+    L sp;
 #pragma unroll
     for (int T = 0; T < MT; ++T) {
       sp.add(x[T][0], x[T][1]);
       sp.add(x[T][2], x[T][3]);
     }
-    const bool pass = sp.passes();
+    return sp;
+  }
+  // whether phi of every value of the wave passes (L: PhiLow<FM>, or Both of it); the values are fit for phi32 afterwards
+  template <int FM, typename L>
+  static LF_DEV bool phi_passes(f32x4 (&x)[MT]) {
+    const bool pass = seen<L>(x).passes();
     if (FM == kPhiEluPlusOne && !pass) {
 #pragma unroll
       for (int T = 0; T < MT; ++T)
@@ -387,30 +385,35 @@ struct Ring32 {
       for (int e = 0; e < 4; ++e) ok &= splits_exactly(rarely(x[T][e]));
     return ok;
   }
-  // x in row form, finite past d; pass: whether the wave's values are known to split exactly; A and raw from build_A
+  // x in row form, finite past d; pass: whether the wave's values are known not to be too small; A and raw from build_A
   LF_DEV void products(const Split8 (&A)[MT][KS], bool raw, const f32x4 (&x)[MT], bool pass, f32x4 (&acc)[MT]) const {
     const f32x4 none = f32x4{0, 0, 0, 0};
+    bool f32 = raw || (!pass && !all_lanes(exact(x)));
+    if (!f32) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) acc[t] = none;
-    if (raw) {
+      for (int t = 0; t < MT; ++t) acc[t] = none;
 #pragma unroll
-      for (int T = 0; T < MT; ++T)
+      for (int s = 0; s < KS; ++s) {
+        const Split8 b = join(split3(x[2 * s]), 2 * s + 1 < MT ? split3(x[2 * s + 1 < MT ? 2 * s + 1 : 0]) : Split4{});
 #pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(__builtin_bit_cast(f32x4, A[t][T / 2].t[T % 2]), x[T], acc[t]);
-      return;
+        for (int t = 0; t < MT; ++t) acc[t] = mfma_split(A[t][s], b, acc[t]);
+      }
+      f32 = !all_lanes(acc[0][0] == acc[0][0]);   // (a NaN among a token's terms is in all of its results)
     }
-    if (!pass && !all_lanes(exact(x))) {
+    if (f32) {
 #pragma unroll
-      for (int T = 0; T < MT; ++T)
+      for (int t = 0; t < MT; ++t) acc[t] = none;
+      if (raw) {
 #pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(joined(A[t][T / 2], T % 2), x[T], acc[t]);
-      return;
-    }
+        for (int T = 0; T < MT; ++T)
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const Split8 b = join(split3(x[2 * s]), 2 * s + 1 < MT ? split3(x[2 * s + 1 < MT ? 2 * s + 1 : 0]) : Split4{});
+          for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(__builtin_bit_cast(f32x4, A[t][T / 2].t[T % 2]), x[T], acc[t]);
+      } else {
 #pragma unroll
-      for (int t = 0; t < MT; ++t) acc[t] = mfma_split(A[t][s], b, acc[t]);
+        for (int T = 0; T < MT; ++T)
+#pragma unroll
+          for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(joined(A[t][T / 2], T % 2), x[T], acc[t]);
+      }
     }
   }
   // over the four lanes that share a token
@@ -558,6 +561,7 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
     for (int j = 0; j < 8; ++j) p[j] = phi32<FM>(k[j][i]);
     z[i] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
   };
+  const TileIter first = it;
   int lim = 0;
   if (it.valid()) {
     lim = lim_of(it.t);
@@ -572,8 +576,8 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
       lim = lim_of(it.t);
       issue_loads(it.t, lim);
     }
-    Span vs;
-    PhiSpan<FM> ks;
+    Low vs;
+    PhiLow<FM> ks;
 #pragma unroll
     for (int j = 0; j < 8; j += 2)
 #pragma unroll
@@ -606,6 +610,24 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
       const Split8 a = join(split3(f32x4{p[0], p[1], p[2], p[3]}), split3(f32x4{p[4], p[5], p[6], p[7]}));
 #pragma unroll
       for (int j = 0; j < CPL; ++j) acc[i][j] = mfma_split(a, b[j], acc[i][j]);
+    }
+  }
+  {   // a NaN among a row's or a column's terms is in every sum of that row or column: all tiles again
+    bool sound = true;
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      sound &= acc[0][i][0] == acc[0][i][0];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sound &= acc[i][0][r] == acc[i][0][r];
+    }
+    if (!all_lanes(sound)) {
+      it = first;
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        z[i] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
+      }
     }
   }
   // from the first tile on that three terms do not hold: the fp32 instruction (a loop of its own for the registers' sake)
@@ -697,7 +719,7 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
     iter = iter < 2 ? iter + 1 : 2;
     f32x4 r[MT], acc[MT];
     rg.read_rows(slot, 0, r);
-    const bool pass = RG::template phi_passes<FM>(r);
+    const bool pass = RG::template phi_passes<FM, PhiLow<FM>>(r);
     float den = 0.0f;
 #pragma unroll
     for (int T = 0; T < MT; ++T)
@@ -765,9 +787,9 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     f32x4 x[MT], g[MT], u[MT];
     rg.read_rows(slot, 1, g);
     rg.read_rows(slot, 0, x);
-    const Span gs = RG::span(g);
+    const auto gs = RG::template seen<Both<Low>>(g);
     rg.products(A, raw, g, gs.passes(), u);
-    const bool pass = RG::template phi_passes<FM>(x);
+    const bool pass = RG::template phi_passes<FM, Both<PhiLow<FM>>>(x);
     f32x4 r[MT];
     float den = 0.0f, ru = 0.0f;
 #pragma unroll
@@ -909,8 +931,8 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
     f32x4 k[MT], v[MT], t[MT], dv[MT], p[MT];
     rg.read_rows(slot, 1, v);
     rg.read_rows(slot, 0, k);
-    rg.products(A, raw, v, RG::span(v).passes(), t);
-    const bool pass = RG::template phi_passes<FM>(k);
+    rg.products(A, raw, v, RG::template seen<Low>(v).passes(), t);
+    const bool pass = RG::template phi_passes<FM, PhiLow<FM>>(k);
 #pragma unroll
     for (int T = 0; T < MT; ++T)
 #pragma unroll
