@@ -13,8 +13,8 @@
 // infinity; an infinity leaves NaN as its second term.  A tile with such a value, or a head whose state has one, is
 // therefore multiplied on the fp32 instruction, from the same registers: the operands and results of both instructions lie
 // alike in the lanes; the state reduction goes on with it from the first such tile of a wave.  The test (Low) costs half an
-// instruction per value, one in bwd_qs32: 20 heads of 64 channels and 16384 tokens 83.1 -> 85.9 us per call, forward and backward
-// of 96 heads of 40 and 4096 tokens 183 -> 192.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
+// instruction per value, one in bwd_qs32: 20 heads of 64 channels and 16384 tokens 82.7 -> 85.1 us per call, forward and backward
+// of 96 heads of 40 and 4096 tokens 181 -> 191.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
 //
 //   state_reduce32s  S, z partials        reads K, V                       (Prop. 2: g'(X)^T X; Eq. 5: Z)
 //   apply32s         out                  reads Q, writes out
@@ -365,17 +365,12 @@ struct Ring32 {
     }
     return sp;
   }
-  // whether phi of every value of the wave passes (L: PhiLow<FM>, or Both of it); the values are fit for phi32 afterwards
-  template <int FM, typename L>
-  static LF_DEV bool phi_passes(f32x4 (&x)[MT]) {
-    const bool pass = seen<L>(x).passes();
-    if (FM == kPhiEluPlusOne && !pass) {
+  template <int FM>
+  static LF_DEV void unmask(f32x4 (&x)[MT]) {
 #pragma unroll
-      for (int T = 0; T < MT; ++T)
+    for (int T = 0; T < MT; ++T)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[T][e] = unmasked<FM>(x[T][e]);
-    }
-    return pass;
+      for (int e = 0; e < 4; ++e) x[T][e] = unmasked<FM>(x[T][e]);
   }
   static LF_DEV bool exact(const f32x4 (&x)[MT]) {   // of this lane's values
     bool ok = true;
@@ -385,35 +380,36 @@ struct Ring32 {
       for (int e = 0; e < 4; ++e) ok &= splits_exactly(rarely(x[T][e]));
     return ok;
   }
-  // x in row form, finite past d; pass: whether the wave's values are known not to be too small; A and raw from build_A
-  LF_DEV void products(const Split8 (&A)[MT][KS], bool raw, const f32x4 (&x)[MT], bool pass, f32x4 (&acc)[MT]) const {
-    const f32x4 none = f32x4{0, 0, 0, 0};
-    bool f32 = raw || (!pass && !all_lanes(exact(x)));
-    if (!f32) {
+  // x in row form, finite past d; A from build_A.  A NaN among a token's terms is in all of its results.
+  LF_DEV void products(const Split8 (&A)[MT][KS], const f32x4 (&x)[MT], f32x4 (&acc)[MT]) const {
 #pragma unroll
-      for (int t = 0; t < MT; ++t) acc[t] = none;
+    for (int t = 0; t < MT; ++t) acc[t] = f32x4{0, 0, 0, 0};
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const Split8 b = join(split3(x[2 * s]), 2 * s + 1 < MT ? split3(x[2 * s + 1 < MT ? 2 * s + 1 : 0]) : Split4{});
+    for (int s = 0; s < KS; ++s) {
+      const Split8 b = join(split3(x[2 * s]), 2 * s + 1 < MT ? split3(x[2 * s + 1 < MT ? 2 * s + 1 : 0]) : Split4{});
 #pragma unroll
-        for (int t = 0; t < MT; ++t) acc[t] = mfma_split(A[t][s], b, acc[t]);
-      }
-      f32 = !all_lanes(acc[0][0] == acc[0][0]);   // (a NaN among a token's terms is in all of its results)
+      for (int t = 0; t < MT; ++t) acc[t] = mfma_split(A[t][s], b, acc[t]);
     }
-    if (f32) {
+  }
+  static LF_DEV bool sound(const f32x4 (&acc)[MT]) { return acc[0][0] == acc[0][0]; }
+  // the same whatever the state and the values: A and raw from build_A
+  LF_DEV void products_any(const Split8 (&A)[MT][KS], bool raw, const f32x4 (&x)[MT], f32x4 (&acc)[MT]) const {
+    if (!raw && all_lanes(exact(x))) {
+      products(A, x, acc);
+      return;
+    }
 #pragma unroll
-      for (int t = 0; t < MT; ++t) acc[t] = none;
-      if (raw) {
+    for (int t = 0; t < MT; ++t) acc[t] = f32x4{0, 0, 0, 0};
+    if (raw) {
 #pragma unroll
-        for (int T = 0; T < MT; ++T)
+      for (int T = 0; T < MT; ++T)
 #pragma unroll
-          for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(__builtin_bit_cast(f32x4, A[t][T / 2].t[T % 2]), x[T], acc[t]);
-      } else {
+        for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(__builtin_bit_cast(f32x4, A[t][T / 2].t[T % 2]), x[T], acc[t]);
+    } else {
 #pragma unroll
-        for (int T = 0; T < MT; ++T)
+      for (int T = 0; T < MT; ++T)
 #pragma unroll
-          for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(joined(A[t][T / 2], T % 2), x[T], acc[t]);
-      }
+        for (int t = 0; t < MT; ++t) acc[t] = mfma_f32(joined(A[t][T / 2], T % 2), x[T], acc[t]);
     }
   }
   // over the four lanes that share a token
@@ -719,16 +715,30 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
     iter = iter < 2 ? iter + 1 : 2;
     f32x4 r[MT], acc[MT];
     rg.read_rows(slot, 0, r);
-    const bool pass = RG::template phi_passes<FM, PhiLow<FM>>(r);
     float den = 0.0f;
+    auto form = [&] {
 #pragma unroll
-    for (int T = 0; T < MT; ++T)
+      for (int T = 0; T < MT; ++T)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        r[T][e] = phi32<FM>(r[T][e]);
-        if constexpr (NORM) den = __builtin_fmaf(r[T][e], z[T][e], den);
-      }
-    rg.products(A, raw, r, pass, acc);
+        for (int e = 0; e < 4; ++e) {
+          r[T][e] = phi32<FM>(r[T][e]);
+          if constexpr (NORM) den = __builtin_fmaf(r[T][e], z[T][e], den);
+        }
+    };
+    bool split = !raw && RG::template seen<PhiLow<FM>>(r).passes();
+    if (split) {   // (one straight piece: phi beside the matrix steps)
+      form();
+      rg.products(A, r, acc);
+      split = all_lanes(RG::sound(acc));
+    }
+    if (!split) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (read again, not kept)
+      rg.read_rows(slot, 0, r);
+      RG::template unmask<FM>(r);
+      den = 0.0f;
+      form();
+      rg.products_any(A, raw, r, acc);
+    }
     if constexpr (NORM) {
       const float scale = 1.0f / (RG::token_sum(den) + eps);
 #pragma unroll
@@ -788,23 +798,29 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     rg.read_rows(slot, 1, g);
     rg.read_rows(slot, 0, x);
     const auto gs = RG::template seen<Both<Low>>(g);
-    rg.products(A, raw, g, gs.passes(), u);
-    const bool pass = RG::template phi_passes<FM, Both<PhiLow<FM>>>(x);
     f32x4 r[MT];
     float den = 0.0f, ru = 0.0f;
+    auto form = [&] {
 #pragma unroll
-    for (int T = 0; T < MT; ++T)
+      for (int T = 0; T < MT; ++T)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        r[T][e] = phi32<FM>(x[T][e]);
-        if constexpr (NORM) {
-          den = __builtin_fmaf(r[T][e], z[T][e], den);   // z and u are zero past d
-          ru = __builtin_fmaf(r[T][e], u[T][e], ru);
+        for (int e = 0; e < 4; ++e) {
+          r[T][e] = phi32<FM>(x[T][e]);
+          if constexpr (NORM) {
+            den = __builtin_fmaf(r[T][e], z[T][e], den);   // z and u are zero past d
+            ru = __builtin_fmaf(r[T][e], u[T][e], ru);
+          }
+          if constexpr (FM == kPhiEluPlusOne) x[T][e] = x[T][e] > 0.0f ? 1.0f : r[T][e];     // phi'(q)
+          else if constexpr (FM == kPhiRelu) x[T][e] = x[T][e] > 0.0f ? 1.0f : 0.0f;
+          else x[T][e] = 1.0f;
         }
-        if constexpr (FM == kPhiEluPlusOne) x[T][e] = x[T][e] > 0.0f ? 1.0f : r[T][e];     // phi'(q)
-        else if constexpr (FM == kPhiRelu) x[T][e] = x[T][e] > 0.0f ? 1.0f : 0.0f;
-        else x[T][e] = 1.0f;
-      }
+    };
+    // (in three pieces, unlike the other two kernels: in one it takes some ten registers more than there are)
+    if (!raw && gs.passes()) rg.products(A, g, u);
+    else rg.products_any(A, raw, g, u);
+    const bool pass = RG::template seen<Both<PhiLow<FM>>>(x).passes();
+    if (!pass) RG::template unmask<FM>(x);
+    form();
     float invden = 1.0f, go = 0.0f;
     if constexpr (NORM) {
       invden = 1.0f / (RG::token_sum(den) + eps);
@@ -931,18 +947,33 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
     f32x4 k[MT], v[MT], t[MT], dv[MT], p[MT];
     rg.read_rows(slot, 1, v);
     rg.read_rows(slot, 0, k);
-    rg.products(A, raw, v, RG::template seen<Low>(v).passes(), t);
-    const bool pass = RG::template phi_passes<FM, PhiLow<FM>>(k);
+    auto form = [&] {
 #pragma unroll
-    for (int T = 0; T < MT; ++T)
+      for (int T = 0; T < MT; ++T)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        p[T][e] = phi32<FM>(k[T][e]);
-        if constexpr (FM == kPhiEluPlusOne) k[T][e] = k[T][e] > 0.0f ? 1.0f : p[T][e];     // phi'(k)
-        else if constexpr (FM == kPhiRelu) k[T][e] = k[T][e] > 0.0f ? 1.0f : 0.0f;
-        else k[T][e] = 1.0f;
-      }
-    rg.products(At, raw, p, pass, dv);
+        for (int e = 0; e < 4; ++e) {
+          p[T][e] = phi32<FM>(k[T][e]);
+          if constexpr (FM == kPhiEluPlusOne) k[T][e] = k[T][e] > 0.0f ? 1.0f : p[T][e];     // phi'(k)
+          else if constexpr (FM == kPhiRelu) k[T][e] = k[T][e] > 0.0f ? 1.0f : 0.0f;
+          else k[T][e] = 1.0f;
+        }
+    };
+    bool split = !raw && RG::template seen<Low>(v).passes() && RG::template seen<PhiLow<FM>>(k).passes();
+    if (split) {
+      rg.products(A, v, t);
+      form();
+      rg.products(At, p, dv);
+      split = all_lanes(RG::sound(t) && RG::sound(dv));
+    }
+    if (!split) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (read again, not kept)
+      rg.read_rows(slot, 1, v);
+      rg.read_rows(slot, 0, k);
+      RG::template unmask<FM>(k);
+      rg.products_any(A, raw, v, t);
+      form();
+      rg.products_any(At, raw, p, dv);
+    }
 #pragma unroll
     for (int T = 0; T < MT; ++T) k[T] *= t[T] + dz[T];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
