@@ -531,7 +531,7 @@ def main():
             "kernels": [
                 {"name": rname, "ms": mk[0], "alg_bytes": rpasses * tensor_bytes,
                  "gbps": rpasses * tensor_bytes / (mk[0] * 1e-3) / 1e9 if mk[0] > 0 else None},
-                {"name": "combine_state + pack_state16", "ms": mk[1], "alg_bytes": 0, "gbps": 0.0},
+                {"name": "combine_state + operand packing" if d > 80 else "combine_state", "ms": mk[1], "alg_bytes": 0, "gbps": 0.0},
                 {"name": aname, "ms": mk[2], "alg_bytes": 3 * tensor_bytes,
                  "gbps": 3 * tensor_bytes / (mk[2] * 1e-3) / 1e9 if mk[2] > 0 else None}],
             "unfused_ms_per_step": udt * 1e3,

@@ -12,8 +12,8 @@
 //     bwd_qs16 + combine_state          reads Q, g: writes dQ, and dS, dz as split partials
 //     bwd_kv16                          reads K, V: writes dK, dV    (large fp16 problems: bwd_pack_kv16 +
 //                                                                      bwd_kv16_packed, short-lived workgroups)
-// The merged bwd_qs16 has no row-piece form for bf16 and d > 48; token-major tensors whose head rows are no whole
-// cache lines take two kernels in its place there (and bf16 at d = 80 everywhere, where that measured faster):
+// The merged bwd_qs16 has no row-piece form for fp16 above 48 and bf16 above 40 channels; token-major tensors whose head
+// rows are no whole cache lines take two kernels in its place there (and bf16 at d = 80 everywhere, where that measured faster):
 //     bwd_q16                           reads Q, g: writes dQ and per token {1 / den_i, e_i}
 //     bwd_state16 + combine_state       reads Q, g and those scalars: dS, dz
 // The two apply-shaped kernels use the LDS-DMA ring of apply16_dma with two tensors per slot; the

@@ -19,7 +19,7 @@ struct BwdPlan {
   int apply1_wgs, blk_apply1;   // launch shape of the gradient kernels of which one workgroup fills a CU
   int gsplits, gblk_reduce;   // the state-gradient reduction's own launch shape
   int most;                   // partial states per head the workspace has room for
-  bool wide;                  // fp16 above 80: the composed pass of linfusion_bwdw.hip (its own workspace layout)
+  bool wide;                  // fp16 above 80: the pass of linfusion_bwdw.hip (its own workspace layout)
   size_t ne, ws_partials, ws_state, ws_scal, ws_pack, ws_total;
   bool kv_packed;             // dK / dV from operands packed once per head, many short-lived workgroups
   int kvp_wgs, kvp_blk;
@@ -37,7 +37,7 @@ bool bwd_supported_d(int d) { return (d >= 8 && d <= 64 && d % 8 == 0) || d == 8
 int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   if (B <= 0 || H <= 0 || N <= 0 || d <= 0) return LINFUSION_ERR_INVALID;
   if ((long long)B * H > 65535) return LINFUSION_ERR_INVALID;
-  p->wide = lfbw::bwd_wide_supported(d, dtype);   // the composed pass: fp16 above 80
+  p->wide = lfbw::bwd_wide_supported(d, dtype);   // fp16 above 80
   const bool f32 = dtype == LINFUSION_DTYPE_F32 && lf32::bwd32_supported(d);
   if (dtype != LINFUSION_DTYPE_F16 && dtype != LINFUSION_DTYPE_BF16 && !f32) return LINFUSION_ERR_UNSUPPORTED;
   if (!bwd_supported_d(d) && !p->wide) return LINFUSION_ERR_UNSUPPORTED;
@@ -202,8 +202,8 @@ int launch_q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal) {
   return LINFUSION_OK;
 }
 
-// whether q_rows below takes the dQ launch (bf16 has no row-piece form of the merged kernel and keeps the separate
-// row-piece kernels wherever they would be picked)
+// whether q_rows below would take the dQ launch (the widths at which the merged kernel has no row-piece form, see
+// qs_rows_fits, keep the separate row-piece kernels wherever they would be picked)
 template <int D>
 bool q_rows_wanted(const BwdArgs& a) {
   constexpr int CPR = D / 8;

@@ -114,7 +114,7 @@ size_t bwd_wide_workspace_bytes(int B, int H, long long N, int d, int dtype) {
 
 int run_bwd_wide(const BwdWideArgs& a) {
   if (!bwd_wide_supported(a.d, a.dtype)) return LINFUSION_ERR_UNSUPPORTED;
-  if ((a.N + 3) / 4 > 0x7fffffffLL) return LINFUSION_ERR_INVALID;
+  if ((a.N + 3) / 4 > 0x7fffffffLL) return LINFUSION_ERR_INVALID;   // (what has always been refused; no launch needs it)
   Regions r;
   const int rc = make_regions(a.B, a.H, a.N, a.d, a.dtype, &r);
   if (rc != LINFUSION_OK) return rc;

@@ -227,7 +227,7 @@ def test_backward_argument_validation_happens_on_the_host():
         return lib.linfusion_attn_bwd(q, k, v, g, state, dq, dk, dv, 1, 2, 64, d, dtype, fm, eps, flags, ws, ws_bytes, None)
     assert call(g=None) == -1 and call(dk=None) == -1 and call(eps=-1.0) == -1 and call(flags=2) == -1
     assert call(d=160, dtype=2) == -2 and call(d=12) == -2 and call(fm=3) == -2 and call(d=80, dtype=0) == -2
-    # fp16 at the wide widths and fp32 are supported (the composed pass): validation goes on to the workspace size
+    # fp16 at the wide widths and fp32 are supported: validation goes on to the workspace size
     # (-4) and, past it, to the device check (-6: there is none here)
     assert call(d=160, dtype=1) == -6 and call(dtype=0) == -6 and call(dtype=0, ws_bytes=1 << 10) == -4
     assert call(dq=(4 << 20) + 8) == -3 and call(ws=(64 << 20) + 4) == -3

@@ -1,6 +1,6 @@
-"""GPU parity of the composed backward pass -- fp16 at head widths above 80 (the d = 160 level of the SD-v1.5 UNet
-and the other widths of the wide kernels) and fp32 at every width -- against the fp64 oracle's gradients, rule of
-tests/parity.py: check_gradients."""
+"""GPU parity of the backward pass of fp16 at head widths above 80 (the d = 160 level of the SD-v1.5 UNet and the other
+widths of the wide kernels) and of fp32 at every width, against the fp64 oracle's gradients, rule of tests/parity.py:
+check_gradients."""
 import pytest
 import torch
 
