@@ -13,8 +13,8 @@
 // infinity; an infinity leaves NaN as its second term.  A tile with such a value, or a head whose state has one, is
 // therefore multiplied on the fp32 instruction, from the same registers: the operands and results of both instructions lie
 // alike in the lanes; the state reduction goes on with it from the first such tile of a wave.  The test (Low) costs half an
-// instruction per value, one in bwd_qs32: 20 heads of 64 channels and 16384 tokens 82.7 -> 85.1 us per call, forward and backward
-// of 96 heads of 40 and 4096 tokens 181 -> 191.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
+// instruction per value, one in bwd_qs32: 20 heads of 64 channels and 16384 tokens 83.3 -> 84.4 us per call, forward and backward
+// of 96 heads of 40 and 4096 tokens 187.8 -> 193.7 (one box).  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
 //
 //   state_reduce32s  S, z partials        reads K, V                       (Prop. 2: g'(X)^T X; Eq. 5: Z)
 //   apply32s         out                  reads Q, writes out
@@ -298,55 +298,61 @@ struct Ring32 {
   }
 
   // ---- the head's state ------------------------------------------------------------------------------------
-  // sum of `parts` partial states -> LDS (and, by one workgroup of the head, -> `keep`)
-  LF_DEV const float* stage_state(const float* src, int parts, float* keep) {
+  static constexpr int kStageBytes = NE * 4 + kWavesPerWG * 4;   // the state, and a word per wave
+  // sum of `parts` partial states -> LDS (and, by one workgroup of the head, -> `keep`); raw: three terms do not hold S
+  LF_DEV const float* stage_state(const float* src, int parts, float* keep, bool& raw) {
     f32x4* st = reinterpret_cast<f32x4*>(smem + kStageOffset);
+    int* flags = reinterpret_cast<int*>(smem + kStageOffset + NE * 4);
+    bool ok = true;
     for (int e = threadIdx.x; e < NE / 4; e += kThreads) {
       const f32x4 s = sum_partials(reinterpret_cast<const f32x4*>(src) + e, parts, NE / 4);
       st[e] = s;
       if (keep) reinterpret_cast<f32x4*>(keep)[e] = s;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ok &= splits_exactly(s[i]) | (4 * e >= D * D);
     }
+    const bool exact = all_lanes(ok);
+    if (lane == 0) flags[wave] = !exact;
     __syncthreads();
+    raw = __builtin_amdgcn_readfirstlane((flags[0] | flags[1]) | (flags[2] | flags[3])) != 0;
     return reinterpret_cast<const float*>(st);
   }
   // operands of  out[o] = sum_c M'[o][c] x[c]:  element M[o][c], or (TRANSPOSED) M[c][o], at output channel
-  // 16 t + m and input channels 16 T + 4 kq + e, T = 2 s and 2 s + 1; zero outside d.  Returns whether three terms do not
-  // hold the state (the same answer in every wave, each of which has all of it): then A keeps the fp32 values as they are,
-  // those of T = 2 s in t[0] and of 2 s + 1 in t[1].
+  // 16 t + m and input channels 16 T + 4 kq + e, T = 2 s and 2 s + 1; zero outside d.  raw (stage_state): A keeps the fp32
+  // values as they are, those of T = 2 s in t[0] and of 2 s + 1 in t[1].
   template <bool TRANSPOSED>
-  LF_DEV bool build_A(const float* st, Split8 (&A)[MT][KS]) const {
-    bool exact = true;
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
+  LF_DEV f32x4 state_values(const float* st, int t, int T) const {
+    f32x4 x = f32x4{0, 0, 0, 0};
+    if (T < MT) {
       const int o = 16 * t + m;
-      const bool ok_o = kWhole || 16 * t + 15 < D || o < D;
+      const bool ok = (kWhole || 16 * t + 15 < D || o < D) && has(T);
+      const int oo = ok ? o : 0, cc = ok ? 16 * T + 4 * kq : 0;
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int T = 2 * s + h;
-          f32x4 x = f32x4{0, 0, 0, 0};
-          if (T < MT) {
-            const bool ok = ok_o && has(T);
-            const int oo = ok ? o : 0, cc = ok ? 16 * T + 4 * kq : 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float y = TRANSPOSED ? st[(cc + e) * D + oo] : st[oo * D + cc + e];
-              x[e] = ok ? y : 0.0f;
-              exact &= splits_exactly(x[e]);
-            }
-          }
-          A[t][s].t[h] = __builtin_bit_cast(u32x4, x);
-        }
+      for (int e = 0; e < 4; ++e) {
+        const float y = TRANSPOSED ? st[(cc + e) * D + oo] : st[oo * D + cc + e];
+        x[e] = ok ? y : 0.0f;
       }
     }
-    if (!all_lanes(exact)) return true;
+    return x;
+  }
+  template <bool TRANSPOSED>
+  LF_DEV void build_A(const float* st, bool raw, Split8 (&A)[MT][KS]) const {
+    if (__builtin_expect(raw, 0)) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          A[t][s].t[0] = __builtin_bit_cast(u32x4, state_values<TRANSPOSED>(st, t, 2 * s));
+          A[t][s].t[1] = __builtin_bit_cast(u32x4, state_values<TRANSPOSED>(st, t, 2 * s + 1));
+          A[t][s].t[2] = u32x4{0, 0, 0, 0};
+        }
+      return;
+    }
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
       for (int s = 0; s < KS; ++s)
-        A[t][s] = join(split3(__builtin_bit_cast(f32x4, A[t][s].t[0])), split3(__builtin_bit_cast(f32x4, A[t][s].t[1])));
-    return false;
+        A[t][s] = join(split3(state_values<TRANSPOSED>(st, t, 2 * s)), split3(state_values<TRANSPOSED>(st, t, 2 * s + 1)));
   }
   LF_DEV void load_vec(const float* st, f32x4 (&z)[MT]) const {
 #pragma unroll
@@ -454,13 +460,13 @@ template <int D, int NT> using Ring32For = Ring32<D, NT, ring32_depth<D, NT>()>;
 constexpr int max32(int a, int b) { return a > b ? a : b; }
 template <int D, int NT> constexpr int consume32_lds_bytes() {
   using RG = Ring32For<D, NT>;
-  return max32(RG::kRingBytes, RG::kStageOffset + RG::NE * 4);
+  return max32(RG::kRingBytes, RG::kStageOffset + RG::kStageBytes);
 }
 // bwd_qs32 at 56 and 64 channels: 280-300 registers, so one workgroup per CU and the deeper ring
 template <int D> using RingQs32 = Ring32<D, 2, 3>;
 template <int D> constexpr int qs32_lds_bytes() {
   using RG = RingQs32<D>;
-  return max32(max32(RG::kRingBytes, RG::kStageOffset + RG::NE * 4), Sum32<D>::kBytes);
+  return max32(max32(RG::kRingBytes, RG::kStageOffset + RG::kStageBytes), Sum32<D>::kBytes);
 }
 
 // grid = (splits, B*H), block = 256, dynamic LDS Sum32<D>::kBytes.  partials: [B*H][splits][D*D + D].
@@ -533,7 +539,21 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
 #pragma unroll
     for (int j = 0; j < CPL; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
   }
-  auto take = [&](float (&k)[8][CPL], float (&v)[8][CPL], int lim) {   // the tile that has been loaded
+  auto test = [&](const float (&k)[8][CPL], const float (&v)[8][CPL]) __attribute__((always_inline)) {
+    Low vs;
+    PhiLow<FM> ks;
+#pragma unroll
+    for (int j = 0; j < 8; j += 2)
+#pragma unroll
+      for (int i = 0; i < CPL; ++i) {
+        ks.add(k[j][i], k[j + 1][i]);
+        vs.add(v[j][i], v[j + 1][i]);
+      }
+    return ks.passes() && vs.passes();
+  };
+  // the tile that has been loaded.  True: it passes the test, though what stands for rows past the end would not.
+  auto take = [&](float (&k)[8][CPL], float (&v)[8][CPL], int lim) {
+    bool passes = false;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -541,7 +561,8 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
         k[j][i] = kr[j][i];
         v[j][i] = vr[j][i];
       }
-    if (lim < TOK) {   // rows past the end add nothing
+    if (lim < TOK) {   // rows past the end (the tile's first so far) add nothing
+      passes = test(k, v);
 #pragma unroll
       for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -551,6 +572,7 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
           v[j][i] = ok ? v[j][i] : 0.0f;
         }
     }
+    return passes;
   };
   auto phi_of = [&](int i, const float (&k)[8][CPL], float (&p)[8]) {
 #pragma unroll
@@ -565,23 +587,14 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
   }
   while (it.valid()) {
     float k[8][CPL], v[8][CPL];
-    take(k, v, lim);
+    const bool passes = take(k, v, lim);
     const TileIter cur = it;
     it.next();
     if (it.valid()) {
       lim = lim_of(it.t);
       issue_loads(it.t, lim);
     }
-    Low vs;
-    PhiLow<FM> ks;
-#pragma unroll
-    for (int j = 0; j < 8; j += 2)
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        ks.add(k[j][i], k[j + 1][i]);
-        vs.add(v[j][i], v[j + 1][i]);
-      }
-    if (!(ks.passes() && vs.passes())) {
+    if (__builtin_expect(!(test(k, v) || passes), 0)) {
       bool exact = true;
 #pragma unroll
       for (int i = 0; i < CPL; ++i)
@@ -616,7 +629,7 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
 #pragma unroll
       for (int r = 0; r < 4; ++r) sound &= acc[i][0][r] == acc[i][0][r];
     }
-    if (!all_lanes(sound)) {
+    if (__builtin_expect(!all_lanes(sound), 0)) {
       it = first;
 #pragma unroll
       for (int i = 0; i < CPL; ++i) {
@@ -631,7 +644,7 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
     lim = lim_of(it.t);
     issue_loads(it.t, lim);
     float k[8][CPL], v[8][CPL];
-    take(k, v, lim);
+    (void)take(k, v, lim);
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
 #pragma unroll
@@ -698,9 +711,10 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   f32x4* Oh = O + lo.slice(bh);
   rg.prefetch();
-  const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr);
+  bool raw;
+  const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr, raw);
   Split8 A[MT][RG::KS];
-  const bool raw = rg.template build_A<true>(st, A);
+  rg.template build_A<true>(st, raw, A);
   f32x4 z[MT];
   if constexpr (NORM) rg.load_vec(st, z);
   __syncthreads();   // the staged state is dead
@@ -716,7 +730,7 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
     f32x4 r[MT], acc[MT];
     rg.read_rows(slot, 0, r);
     float den = 0.0f;
-    auto form = [&] {
+    auto form = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int T = 0; T < MT; ++T)
 #pragma unroll
@@ -731,7 +745,7 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
       rg.products(A, r, acc);
       split = all_lanes(RG::sound(acc));
     }
-    if (!split) {
+    if (__builtin_expect(!split, 0)) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (read again, not kept)
       rg.read_rows(slot, 0, r);
       RG::template unmask<FM>(r);
@@ -771,9 +785,10 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   f32x4* dQh = dQ + ldq.slice(bh);
   rg.prefetch();
-  const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, nullptr);
+  bool raw;
+  const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, nullptr, raw);
   Split8 A[MT][RG::KS];
-  const bool raw = rg.template build_A<false>(st, A);       // u = S g
+  rg.template build_A<false>(st, raw, A);       // u = S g
   f32x4 z[MT];
   if constexpr (NORM) rg.load_vec(st, z);
   __syncthreads();                          // the staged state is dead
@@ -800,7 +815,7 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     const auto gs = RG::template seen<Both<Low>>(g);
     f32x4 r[MT];
     float den = 0.0f, ru = 0.0f;
-    auto form = [&] {
+    auto form = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int T = 0; T < MT; ++T)
 #pragma unroll
@@ -816,10 +831,10 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
         }
     };
     // (in three pieces, unlike the other two kernels: in one it takes some ten registers more than there are)
-    if (!raw && gs.passes()) rg.products(A, g, u);
+    if (__builtin_expect(!raw && gs.passes(), 1)) rg.products(A, g, u);
     else rg.products_any(A, raw, g, u);
     const bool pass = RG::template seen<Both<PhiLow<FM>>>(x).passes();
-    if (!pass) RG::template unmask<FM>(x);
+    if (__builtin_expect(!pass, 0)) RG::template unmask<FM>(x);
     form();
     float invden = 1.0f, go = 0.0f;
     if constexpr (NORM) {
@@ -859,7 +874,7 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     rg.store_tile(tile, slot, 0, dQh, ldq.row);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (split) {
+    if (__builtin_expect(split, 1)) {
       Split4 b[MT];
 #pragma unroll
       for (int j = 0; j < MT; ++j) b[j] = split3(f32x4{gc[0][j], gc[1][j], gc[2][j], gc[3][j]});
@@ -928,10 +943,11 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   f32x4 *dKh = dK + ldkv.slice(bh), *dVh = dV + ldkv.slice(bh);
   rg.prefetch();
-  const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, nullptr);
+  bool raw;
+  const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, nullptr, raw);
   Split8 A[MT][RG::KS], At[MT][RG::KS];
-  const bool raw = rg.template build_A<false>(st, A);       // dS v
-  (void)rg.template build_A<true>(st, At);                  // dS^T p: the same state, the same answer
+  rg.template build_A<false>(st, raw, A);       // dS v
+  rg.template build_A<true>(st, raw, At);       // dS^T p
   f32x4 dz[MT];
   rg.load_vec(st, dz);
   __syncthreads();                          // the staged state is dead
@@ -947,7 +963,7 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
     f32x4 k[MT], v[MT], t[MT], dv[MT], p[MT];
     rg.read_rows(slot, 1, v);
     rg.read_rows(slot, 0, k);
-    auto form = [&] {
+    auto form = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int T = 0; T < MT; ++T)
 #pragma unroll
@@ -965,7 +981,7 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
       rg.products(At, p, dv);
       split = all_lanes(RG::sound(t) && RG::sound(dv));
     }
-    if (!split) {
+    if (__builtin_expect(!split, 0)) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (read again, not kept)
       rg.read_rows(slot, 1, v);
       rg.read_rows(slot, 0, k);
