@@ -14,7 +14,7 @@
 // therefore multiplied on the fp32 instruction, from the same registers: the operands and results of both instructions lie
 // alike in the lanes; the state reduction goes on with it from the first such tile of a wave.  The test (Low) costs half an
 // instruction per value, one in bwd_qs32: 20 heads of 64 channels and 16384 tokens 83.3 -> 84.4 us per call, forward and backward
-// of 96 heads of 40 and 4096 tokens 187.8 -> 193.7 (one box).  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
+// of 96 heads of 40 and 4096 tokens 187.8 -> 193.7.  (The matrix instructions keep subnormal operands, products and sums: measured on MI355X.)
 //
 //   state_reduce32s  S, z partials        reads K, V                       (Prop. 2: g'(X)^T X; Eq. 5: Z)
 //   apply32s         out                  reads Q, writes out
