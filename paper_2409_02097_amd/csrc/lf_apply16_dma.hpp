@@ -59,7 +59,11 @@ template <int D, int DV = D> struct ApplyDmaCfg {
   static constexpr int kSlotBytes = (kNL > kNLO ? kNL : kNLO) * 1024;   // whole 1 KiB deposits; >= either tile's bytes
   static constexpr int kRing = 3;
   static constexpr int kStageOffset = (kRing - 1) * kWavesPerWG * kSlotBytes;
-  static constexpr int kStageBytes = (D * DV + D) * 4 + 256;   // the state and two maxima per wave
+  // Channels of one output column lie kStageStride floats after those of the column before: without the four floats of
+  // padding the lanes of an operand read (one column each) met in one to eight of the sixteen 16-byte bank groups
+  // (at d = 64 all in one; fp16 2 x 5 x 9216 x 64 27.2 -> 23.8 us per call, bf16 2 x 10 x 16384 x 64 52.9 -> 50.5).
+  static constexpr int kStageStride = D + 4;
+  static constexpr int kStageBytes = (DV * kStageStride + D) * 4 + 256;   // the state and two maxima per wave
   // XOR swizzle of the chunk position with the row index where rows are 64 or 128 bytes
   static constexpr int kSwzMask = (kCPR == 8) ? 7 : (kCPR == 4 ? 3 : 0);
   static constexpr int kSwzShift = (kCPR == 4) ? 2 : 0;
@@ -422,15 +426,17 @@ struct ApplyDma {
 
   // Whole workgroup: stages one head's state in LDS; the waves with `mine` build their operands from it.
   // STAGED: the state already lies in the staging area (the workgroup computed it itself), S row-major as in
-  // memory; `state` is not read.  Otherwise S is staged transposed -- st[col * D + ch], then z[ch] -- so that the
+  // memory; `state` is not read.  Otherwise S is staged transposed -- st[col * kStageStride + ch], then z[ch] -- so that the
   // eight consecutive feature channels of one output column that make up a lane's operand are two 16-byte LDS
   // reads, all of them issued before the first is used (read one by one, row-major, with the slot tests around
   // each read, the operand build took 3-5 us per workgroup: a fifth of a small call).
   template <bool COHERENT = false, bool STAGED = false>
   LF_DEV void load_state(const float* state, float eps, bool mine, int parts = 1, float* keep = nullptr) {
     // ---- prologue: state -> LDS, maxima, power-of-two scales, A fragments -------------------------
+    constexpr int SS = Cfg::kStageStride;
     float* st = reinterpret_cast<float*>(smem + kStageOffset);
-    float* redmax = st + NE;
+    float* stz = st + (STAGED ? D * DV : DV * SS);
+    float* redmax = stz + D;
     float mS = 0.0f, mz = 0.0f;
     static_assert(NE % 4 == 0 && (D * DV) % 4 == 0 && DV % 4 == 0, "the state is moved four floats of one row at a time");
 #pragma unroll 2
@@ -449,9 +455,9 @@ struct ApplyDma {
         if (e < D * DV / 4) {
           const int ch = (4 * e) / DV, col = (4 * e) % DV;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) st[(col + i) * D + ch] = x[i];
+          for (int i = 0; i < 4; ++i) st[(col + i) * SS + ch] = x[i];
         } else {
-          reinterpret_cast<f32x4*>(st)[e] = x;
+          reinterpret_cast<f32x4*>(stz)[e - D * DV / 4] = x;
         }
       }
       const float m4 = fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])));
@@ -490,9 +496,9 @@ struct ApplyDma {
           const int ch0 = (chunk < CPR ? chunk : 0) * 8;
           if constexpr (STAGED) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) raw[s][j] = isS ? st[(ch0 + j) * DV + col] : st[D * DV + ch0 + j];
+            for (int j = 0; j < 8; ++j) raw[s][j] = isS ? st[(ch0 + j) * DV + col] : stz[ch0 + j];
           } else {
-            const float* src = isS ? st + col * D + ch0 : st + D * DV + ch0;
+            const float* src = isS ? st + col * SS + ch0 : stz + ch0;
             const f32x4 lo4 = *reinterpret_cast<const f32x4*>(src);
             const f32x4 hi4 = *reinterpret_cast<const f32x4*>(src + 4);
 #pragma unroll
