@@ -21,6 +21,28 @@ int num_cu();
 int check_strides(const long long s[3], int B, int H, long long N, int d, size_t esz, bool written);
 size_t span_bytes(const long long s[3], int B, int H, long long N, int d, size_t esz);
 
+// How a head's tiles are dealt to workgroups of `waves` waves, each of which takes a tile per round: `most` workgroups at
+// most, as few as keep the longest at the number of rounds that `most` of them need (every workgroup leaves a partial state
+// or stages one), and blocks of up to `blk` consecutive tiles, halved until the longest workgroup's whole blocks are within
+// a thirty-second of that number (blocks of 16 tiles, 512 tiles, 25 workgroups: 8 rounds where 6 do).
+// us per call, blocks of 16 or 8 tiles whatever the number -> these: bf16 2 x 10 x 16384 x 64 54.0 -> 48.0, fp16 8 x 100000 x
+// 40 60.1 -> 55.8, 20 x 65536 x 64 130.2 -> 124.2, fp32 forward and backward 12 x 8 x 4096 x 40 192.4 -> 183.1; fewest
+// workgroups: fp16 2 x 5 x 9216 x 64 24.0 -> 23.2, fp32 2 x 10 x 16384 x 64 83.9 -> 82.7.
+struct Share { int wgs, blk; };   // blk: in tiles, whole rounds
+inline Share even_share(long long n_tiles, long long most, int waves, int blk) {
+  const long long rounds = (n_tiles + waves - 1) / waves;
+  long long s = most < rounds ? most : rounds;
+  if (s < 1) s = 1;
+  const long long longest = (rounds + s - 1) / s;
+  s = (rounds + longest - 1) / longest;
+  long long b = blk / waves;   // rounds per block
+  if (b > longest) b = longest;
+  if (b < 1) b = 1;
+  while (b > 1 && ((rounds + b - 1) / b + s - 1) / s * b * 32 > longest * 33) b /= 2;
+  if (b * waves > 1 << 28) b = (1 << 28) / waves;
+  return Share{(int)s, (int)(b * waves)};
+}
+
 // true when the byte ranges [a, a + na) and [b, b + nb) share a byte
 inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;

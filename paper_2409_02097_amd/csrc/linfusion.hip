@@ -101,14 +101,7 @@ int env_int(const char* name, int dflt) {
   return v > 0 ? v : dflt;
 }
 
-// tiles per contiguous block of a workgroup, at most its whole share, rounded up to a multiple of
-// the waves per workgroup; the environment override is a tuning aid
-int block_tiles(long long share, const char* env, int dflt, int multiple = lf::kWavesPerWG) {
-  long long b = env_int(env, dflt);
-  if (b > share) b = share;
-  if (b > (1 << 28)) b = 1 << 28;
-  return (int)((b + multiple - 1) / multiple * multiple);
-}
+using lfh::even_share;
 
 // head widths up to 64 in steps of 8 for every dtype; for the 16-bit types also 80 (same kernels) and the
 // wide kernels' widths
@@ -162,12 +155,10 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   if (is_wide(d)) {
     // wide kernels: every wave of a workgroup visits every tile of its blocks; three-kernel path only
     auto per_head = [&](int want_total, int blk_dflt, const char* env_blk, int* blk) {
-      long long s = want_total / BH;   // rounded down: one workgroup too many costs a whole extra round
-      if (s > p->n_tiles) s = p->n_tiles;
-      if (s < 1) s = 1;
-      const long long t = (p->n_tiles + s - 1) / s;
-      *blk = block_tiles(t, env_blk, blk_dflt, 1);
-      return (int)((p->n_tiles + t - 1) / t);
+      // (rounded down: one workgroup too many costs a whole extra round)
+      const lfh::Share sh = even_share(p->n_tiles, want_total / BH, 1, env_int(env_blk, blk_dflt));
+      *blk = sh.blk;
+      return sh.wgs;
     };
     // reduction workgroups per CU: two; from 768 MB of tensor traffic on, what fits below d = 160 measured faster
     // (d = 128: three, 3-5 %; d = 96: three for fp16, four for bf16, 6-15 %), while smaller problems lose to the
@@ -193,16 +184,13 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     // per CU, long-lived: its prologue loads the (d + 2) x d operands), else the workgroup-shared tiles
     p->wave_apply = lfw::wave_apply_supported(d, dtype) && env_int("LINFUSION_WIDE_WAVE_APPLY", 1) == 1;   // 2: never
     if (p->wave_apply) {
-      const long long max_a = (p->n_tiles + lf::kWavesPerWG - 1) / lf::kWavesPerWG;   // every wave gets a tile
       // (d = 96 leaves room for a second workgroup per CU: at 2^18 tokens of 8 heads apply 166 -> 157 us; measured
       // slower at d = 128 and 160)
       const bool two_per_cu = d <= 96 && 4.0 * (double)BH * (double)N * d * 2.0 >= 768.0 * 1048576.0;
-      long long s = env_int("LINFUSION_WIDE_APPLY_WGS", (two_per_cu ? 2 : 1) * num_cu()) / BH;
-      if (s > max_a) s = max_a;
-      if (s < 1) s = 1;
-      const long long t = (p->n_tiles + s - 1) / s;
-      p->apply_wgs = (int)((p->n_tiles + t - 1) / t);
-      p->blk_apply = block_tiles(t, "LINFUSION_WIDE_APPLY_BLK", lf::kWavesPerWG);
+      const lfh::Share sh = even_share(p->n_tiles, env_int("LINFUSION_WIDE_APPLY_WGS", (two_per_cu ? 2 : 1) * num_cu()) / BH,
+                                       lf::kWavesPerWG, env_int("LINFUSION_WIDE_APPLY_BLK", lf::kWavesPerWG));
+      p->apply_wgs = sh.wgs;
+      p->blk_apply = sh.blk;
     } else {
       p->apply_wgs = per_head(env_int("LINFUSION_WIDE_APPLY_WGS", 2 * num_cu()), 1, "LINFUSION_WIDE_APPLY_BLK", &p->blk_apply);
     }
@@ -226,16 +214,12 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     p->ws_total = p->ws_partials + p->ws_state + p->ws_sync;
     return LINFUSION_OK;
   }
-  const long long max_s = (p->n_tiles + lf::kWavesPerWG - 1) / lf::kWavesPerWG;   // >= one tile per wave
-  auto per_head = [&](int want_total, long long* share) {
-    long long s = want_total / BH;   // rounded down: one workgroup too many costs a whole extra round
-    if (s > max_s) s = max_s;
-    if (s < 1) s = 1;
-    long long t = (p->n_tiles + s - 1) / s;
-    *share = t;
-    return (int)((p->n_tiles + t - 1) / t);
+  auto per_head = [&](int want_total, const char* env_blk, int blk_dflt, int* blk, int waves = lf::kWavesPerWG) {
+    // (rounded down: one workgroup too many costs a whole extra round)
+    const lfh::Share sh = even_share(p->n_tiles, want_total / BH, waves, env_int(env_blk, blk_dflt));
+    *blk = sh.blk;
+    return sh.wgs;
   };
-  long long share = 0;
   // state reduction (read-only stream): two workgroups per CU measured best -- fewer, longer
   // streams keep DRAM pages open
   const size_t esz = dtype == LINFUSION_DTYPE_F32 ? 4 : 2;
@@ -250,8 +234,17 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     if (dtype == LINFUSION_DTYPE_F32) reduce_per_cu = d <= 8 ? 4 : 2;
     else if (d <= 24 || (dtype == LINFUSION_DTYPE_BF16 && d <= 40)) reduce_per_cu = 8;
   }
-  p->splits = per_head(env_int("LINFUSION_REDUCE_WGS", reduce_per_cu * num_cu()), &share);
-  p->blk_reduce = block_tiles(share, "LINFUSION_REDUCE_BLK", 16);
+  p->splits = per_head(env_int("LINFUSION_REDUCE_WGS", reduce_per_cu * num_cu()), "LINFUSION_REDUCE_BLK", 16, &p->blk_reduce);
+  // (the entry point with the fixed scratch array asks for a partial per workgroup of equal shares, so that it takes and
+  // refuses the shapes that it always did)
+  int room = p->splits;
+  if (compact) {
+    const long long most = (p->n_tiles + lf::kWavesPerWG - 1) / lf::kWavesPerWG;
+    long long s = reduce_per_cu * num_cu() / BH;
+    s = s > most ? most : (s < 1 ? 1 : s);
+    const long long t = (p->n_tiles + s - 1) / s, parts = (p->n_tiles + t - 1) / t;
+    if (parts > room) room = (int)parts;
+  }
   // apply (read + write streams): more, smaller workgroups that sweep memory in one moving window.
   // Up to a few hundred MB of tensor traffic one resident round measured best (a second, partly filled
   // round costs more than its finer balance gains); beyond that eight workgroups per CU.
@@ -277,44 +270,32 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     if (!one_round && !resident && by_tiles > apply_want) apply_want = by_tiles > (1 << 24) ? (1 << 24) : (int)by_tiles;
     blk_dflt = p->apply_waves;                                           // one tile per wave and round
   }
-  {
-    // every wave gets at least one tile
-    const long long max_a = (p->n_tiles + p->apply_waves - 1) / p->apply_waves;
-    long long s = env_int("LINFUSION_APPLY_WGS", apply_want) / BH;
-    if (s > max_a) s = max_a;
-    if (s < 1) s = 1;
-    share = (p->n_tiles + s - 1) / s;
-    p->apply_wgs = (int)((p->n_tiles + share - 1) / share);
-  }
-  p->blk_apply = block_tiles(share, "LINFUSION_APPLY_BLK", blk_dflt, p->apply_waves);
+  p->apply_wgs = per_head(env_int("LINFUSION_APPLY_WGS", apply_want), "LINFUSION_APPLY_BLK", blk_dflt, &p->blk_apply,
+                          p->apply_waves);
   // fused single launch: every workgroup must be resident at once
   const long long cap = (long long)fused_wgs_per_cu(d, dtype) * num_cu();
   p->fsplits = 0;
   if (BH <= cap && !compact) {
-    p->fsplits = per_head((int)(cap / BH * BH), &share);
+    p->fsplits = per_head((int)(cap / BH * BH), "LINFUSION_REDUCE_BLK", 16, &p->fblk_reduce);
+    p->fsplits = per_head((int)(cap / BH * BH), "LINFUSION_APPLY_BLK", 8, &p->fblk_apply);
     if ((long long)p->fsplits * BH > cap) p->fsplits = 0;
-    p->fblk_reduce = block_tiles(share, "LINFUSION_REDUCE_BLK", 16);
-    p->fblk_apply = block_tiles(share, "LINFUSION_APPLY_BLK", 8);
   }
   // row-piece kernels: a workgroup covers a whole group of four heads, every wave walks all of its tiles
   p->gwaves = (H % 8 == 0 && d <= 64 && env_int("LINFUSION_GROUP_WAVES", 8) == 8) ? 8 : 4;   // d = 80: registers
   p->groups = compact ? 0 : B * (H / p->gwaves);   // (compact: contiguous tensors only, whose heads are never neighbours)
   if (p->groups > 0) {
-    auto per_group = [&](int want_total, long long* sh) {
-      long long s = want_total / p->groups;
-      if (s > p->n_tiles) s = p->n_tiles;
-      if (s < 1) s = 1;
-      long long t = (p->n_tiles + s - 1) / s;
-      *sh = t;
-      return (int)((p->n_tiles + t - 1) / t);
+    auto per_group = [&](int want_total, const char* env_blk, int blk_dflt, int* blk) {
+      const lfh::Share sh = even_share(p->n_tiles, want_total / p->groups, 1, env_int(env_blk, blk_dflt));
+      *blk = sh.blk;
+      return sh.wgs;
     };
     // (the defaults are in 256-thread units: a workgroup of eight waves counts twice)
     const int unit = p->gwaves / lf::kWavesPerWG;
     // (the widths and sizes that take more reduction workgroups per CU above do here as well: four, eight at d = 8;
     // token-major bf16 8 x 40 at 2 M tokens 0.999 -> 0.971 ms, d = 24 0.616 -> 0.556, fp16 d = 8 0.577 -> 0.407)
     const int greduce_per_cu = reduce_per_cu == 8 ? (d <= 8 ? 8 : 4) : 2;
-    p->gsplits = per_group(env_int("LINFUSION_GROUP_REDUCE_WGS", greduce_per_cu * num_cu()) / unit, &share);
-    p->gblk_reduce = block_tiles(share, "LINFUSION_GROUP_REDUCE_BLK", 2, 1);
+    p->gsplits = per_group(env_int("LINFUSION_GROUP_REDUCE_WGS", greduce_per_cu * num_cu()) / unit,
+                           "LINFUSION_GROUP_REDUCE_BLK", 2, &p->gblk_reduce);
     // up to a few hundred MB one workgroup of eight waves (two of four) per CU; large problems as many short-lived
     // workgroups of about `kGroupTilesPerWG` tiles each (the hardware deals them out in order: one narrow moving
     // window of memory, as for the per-head apply; 2 M tokens of 8 x 40: 472 -> 445 us); tiles dealt out one at
@@ -325,8 +306,8 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       gwant = p->groups * p->n_tiles / kGroupTilesPerWG * unit;
     p->gapply_packed = gwant > 2 * num_cu();
     if (gwant > (1 << 24)) gwant = 1 << 24;
-    p->gapply_wgs = per_group(env_int("LINFUSION_GROUP_APPLY_WGS", (int)gwant) / unit, &share);
-    p->gblk_apply = block_tiles(share, "LINFUSION_GROUP_APPLY_BLK", p->gwaves == 8 ? 1 : 2, 1);
+    p->gapply_wgs = per_group(env_int("LINFUSION_GROUP_APPLY_WGS", (int)gwant) / unit, "LINFUSION_GROUP_APPLY_BLK",
+                              p->gwaves == 8 ? 1 : 2, &p->gblk_apply);
   } else {
     p->gsplits = p->gapply_wgs = 0;
     p->gblk_reduce = p->gblk_apply = lf::kWavesPerWG;
@@ -369,7 +350,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   if ((flags & LINFUSION_FLAG_FORCE_SOLO) && p->path != 2) return LINFUSION_ERR_UNSUPPORTED;
   p->state_floats = (size_t)d * d + d;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  int smax = p->splits > p->fsplits ? p->splits : p->fsplits;
+  int smax = room > p->fsplits ? room : p->fsplits;
   if (dtype != LINFUSION_DTYPE_F32 && p->gsplits > smax) smax = p->gsplits;
   p->ws_partials = up((size_t)BH * smax * p->state_floats * sizeof(float));
   p->ws_state = up((size_t)BH * p->state_floats * sizeof(float));

@@ -54,15 +54,11 @@ int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   }
   const long long BH = (long long)B * H;
   const long long n_tiles = (N + lf::kTile - 1) / lf::kTile;
-  const long long max_s = (n_tiles + lf::kWavesPerWG - 1) / lf::kWavesPerWG;
   auto per_head = [&](int want_total, int blk_dflt, int* blk) {
-    long long s = want_total / BH;   // rounded down: one workgroup too many costs a whole extra round
-    if (s > max_s) s = max_s;
-    if (s < 1) s = 1;
-    long long t = (n_tiles + s - 1) / s;
-    long long b = blk_dflt < t ? blk_dflt : t;
-    *blk = (int)((b + lf::kWavesPerWG - 1) / lf::kWavesPerWG * lf::kWavesPerWG);
-    return (int)((n_tiles + t - 1) / t);
+    // (rounded down: one workgroup too many costs a whole extra round)
+    const lfh::Share sh = lfh::even_share(n_tiles, want_total / BH, lf::kWavesPerWG, blk_dflt);
+    *blk = sh.blk;
+    return sh.wgs;
   };
   // Launch sizes measured on MI355X: up to a few hundred MB of tensor traffic two workgroups per CU (one resident
   // round) are best for the gradient kernels too; at GB sizes four (dQ, dK/dV) and eight (state gradient) per CU.
@@ -144,13 +140,9 @@ int launch_kv_rows(const BwdArgs& a, const float* stateD) {
   const long long n_tiles = (a.N + kTile - 1) / kTile;
   const int resident = 160 * 1024 / lds > 0 ? 160 * 1024 / lds : 1;
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
-  if (wgs > n_tiles) wgs = n_tiles;
-  if (wgs < 1) wgs = 1;
-  long long blk = lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1);
-  const long long share = (n_tiles + wgs - 1) / wgs;
-  if (blk > share) blk = share;
-  bwd_kv16_rows<T, D, FM, W><<<dim3((unsigned)wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (u32x4*)a.dk, (u32x4*)a.dv, a.ldkv, gpb, stateD, a.N, (int)blk);
+  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1));
+  bwd_kv16_rows<T, D, FM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
+      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (u32x4*)a.dk, (u32x4*)a.dv, a.ldkv, gpb, stateD, a.N, sh.blk);
   return LINFUSION_OK;
 }
 
@@ -168,15 +160,11 @@ int launch_qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* 
   const int resident = 160 * 1024 / lds > 0 ? 160 * 1024 / lds : 1;
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
   if (wgs > a.p->most) wgs = a.p->most;   // room for the partial states
-  if (wgs > n_tiles) wgs = n_tiles;
-  if (wgs < 1) wgs = 1;
-  long long blk = lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1);
-  const long long share = (n_tiles + wgs - 1) / wgs;
-  if (blk > share) blk = share;
-  bwd_qs16_rows<T, D, FM, NORM, W><<<dim3((unsigned)wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
+  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1));
+  bwd_qs16_rows<T, D, FM, NORM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
       (const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, (u32x4*)a.dq, a.ldq, gpb, stateS, partials, a.eps, a.N,
-      (int)blk);
-  *wgs_used = (int)wgs;
+      sh.blk);
+  *wgs_used = sh.wgs;
   return LINFUSION_OK;
 }
 
@@ -192,13 +180,9 @@ int launch_q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal) {
   const long long n_tiles = (a.N + kTile - 1) / kTile;
   const int resident = 160 * 1024 / lds > 0 ? 160 * 1024 / lds : 1;
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
-  if (wgs > n_tiles) wgs = n_tiles;
-  if (wgs < 1) wgs = 1;
-  long long blk = lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1);
-  const long long share = (n_tiles + wgs - 1) / wgs;
-  if (blk > share) blk = share;
-  bwd_q16_rows<T, D, FM, NORM, W><<<dim3((unsigned)wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, (u32x4*)a.dq, a.ldq, gpb, stateS, scal, a.eps, a.N, (int)blk);
+  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1));
+  bwd_q16_rows<T, D, FM, NORM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
+      (const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, (u32x4*)a.dq, a.ldq, gpb, stateS, scal, a.eps, a.N, sh.blk);
   return LINFUSION_OK;
 }
 
@@ -269,14 +253,10 @@ int launch_state_rows(const BwdArgs& a, float* partials, int* nparts) {
   const long long n_tiles = (a.N + kTile - 1) / kTile;
   long long s = lfh::env_int("LINFUSION_GROUP_REDUCE_WGS", 2 * lfh::num_cu()) / (W / kWavesPerWG) / groups;
   if (s > a.p->most) s = a.p->most;   // room for the partial states
-  if (s > n_tiles) s = n_tiles;
-  if (s < 1) s = 1;
-  long long blk = lfh::env_int("LINFUSION_GROUP_REDUCE_BLK", 2);
-  const long long share = (n_tiles + s - 1) / s;
-  if (blk > share) blk = share;
-  state_reduce16_rows<T, D, FM, W><<<dim3((unsigned)s, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, gpb, partials, a.N, (int)blk);
-  *nparts = (int)s;
+  const lfh::Share sh = lfh::even_share(n_tiles, s, 1, lfh::env_int("LINFUSION_GROUP_REDUCE_BLK", 2));
+  state_reduce16_rows<T, D, FM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
+      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, gpb, partials, a.N, sh.blk);
+  *nparts = sh.wgs;
   return LINFUSION_OK;
 }
 

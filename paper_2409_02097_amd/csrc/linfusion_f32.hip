@@ -36,9 +36,10 @@ int launch_reduce(const void* k, lf::Layout lk, const void* v, lf::Layout lv, fl
   constexpr int lds = Sum32<D>::kBytes;
   // the plan counts 16-token tiles; this kernel's are 32 or 64 tokens
   constexpr int per = Reduce32s<D>::kTokens / kTile32;
-  const int blk32 = ((p.blk_reduce / per + kWavesPerWG - 1) / kWavesPerWG) * kWavesPerWG;
+  const lfh::Share sh = lfh::even_share((N + Reduce32s<D>::kTokens - 1) / Reduce32s<D>::kTokens, p.splits, kWavesPerWG,
+                                        p.blk_reduce / per);
   state_reduce32s<D, FM><<<dim3(p.splits, (unsigned)BH), dim3(kThreads), lds, st>>>(
-      (const float*)k, lk, (const float*)v, lv, partials, N, blk32 < kWavesPerWG ? kWavesPerWG : blk32);
+      (const float*)k, lk, (const float*)v, lv, partials, N, sh.blk);
   return LINFUSION_OK;
 }
 

@@ -57,12 +57,9 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     p->n_pad = n_tiles * lf::kTile;
     const long long units = (long long)B * (H / 4);
     auto per_group = [&](int want_total, int blk_dflt, int* blk) {
-      long long s = want_total / units;
-      if (s > n_tiles) s = n_tiles;
-      if (s < 1) s = 1;
-      long long t = (n_tiles + s - 1) / s;
-      *blk = (int)(blk_dflt < t ? blk_dflt : t);
-      return (int)((n_tiles + t - 1) / t);
+      const lfh::Share sh = lfh::even_share(n_tiles, want_total / units, 1, blk_dflt);
+      *blk = sh.blk;
+      return sh.wgs;
     };
     const int slot = (lf::kTile * d * 2 + 1023) / 1024 * 1024;
     const int lds_apply = 2 * 3 * slot * 4 + 3 * 1024;
@@ -88,16 +85,9 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     const long long units = (long long)B * H;
     const bool wide = lfm::heads_wide(d);   // there every wave of a workgroup visits every tile of its blocks
     auto per_head = [&](int want_total, int blk_dflt, int* blk) {
-      long long s = want_total / units;
-      const long long most = wide ? n_tiles : (n_tiles + 3) / 4;  // four waves, a tile each at least
-      if (s > most) s = most;
-      if (s < 1) s = 1;
-      long long t = (n_tiles + s - 1) / s;
-      t = blk_dflt < t ? blk_dflt : t;
-      if (!wide) t = (t + 3) / 4 * 4;                             // a block is whole rounds of the four waves
-      *blk = (int)t;
-      const long long g = (n_tiles + t - 1) / t;                  // blocks are dealt round-robin to the workgroups
-      return (int)(g < s ? g : s);
+      const lfh::Share sh = lfh::even_share(n_tiles, want_total / units, wide ? 1 : lf::kWavesPerWG, blk_dflt);
+      *blk = sh.blk;
+      return sh.wgs;
     };
     // apply: one resident round (two rings of three slots and the statistics deposits per wave decide how many
     // workgroups a CU holds); measured at 1 M tokens, 10 heads of 64: 0.725 ms with 256 workgroups, 0.77 with 2048
@@ -125,12 +115,9 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
   p->stats_wgs = 0;
   p->ws_stats = 0;
   auto per_batch = [&](int want_total, int blk_dflt, int* blk) {
-    long long s = want_total / B;
-    if (s > n_tiles) s = n_tiles;
-    if (s < 1) s = 1;
-    long long t = (n_tiles + s - 1) / s;
-    *blk = (int)(blk_dflt < t ? blk_dflt : t);
-    return (int)((n_tiles + t - 1) / t);
+    const lfh::Share sh = lfh::even_share(n_tiles, want_total / B, 1, blk_dflt);
+    *blk = sh.blk;
+    return sh.wgs;
   };
   // (defaults in 256-thread units, as for the row-piece kernels: a workgroup of eight waves counts twice)
   const int unit = H / lf::kWavesPerWG;

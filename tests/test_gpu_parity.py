@@ -423,3 +423,19 @@ def test_narrow_heads_at_large_n_with_more_reduction_workgroups(B, H, N, d, dtyp
     out = _run(q.cuda(), k.cuda(), v.cuda())
     worst = parity.check_all(out, q, k, v, dtype, 0, 1e-6, True, f"narrow heads at large N d={d} {dtype}")
     print(f"  worst max-norm ratio {worst[0]:.2e}, rel L2 {worst[1]:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("wgs,blk", [(6, 16), (10, 16), (14, 8), (2, 4)])
+@pytest.mark.parametrize("N", [32 * 4 * 8, 32 * 4 * 7 + 37])
+def test_blocks_of_tiles_that_do_not_divide(N, wgs, blk, dtype, monkeypatch, tuning):
+    """Three, five, seven workgroups or one per head over eight rounds of tiles, with blocks larger than a share: the
+    blocks are halved until the workgroups are even, the last ones get less or nothing."""
+    B, H, d = 1, 2, 40
+    print(f"blocks N={N} wgs={wgs} blk={blk} {dtype}", flush=True)
+    for name in ("REDUCE", "APPLY"):
+        monkeypatch.setenv(f"LINFUSION_{name}_WGS", str(wgs))
+        monkeypatch.setenv(f"LINFUSION_{name}_BLK", str(blk))
+    q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=95, device="cpu")
+    out = _run(q.cuda(), k.cuda(), v.cuda(), flags=lf.FLAG_FORCE_SPLIT)
+    parity.check_all(out, q, k, v, dtype, 0, 1e-6, True, f"blocks N={N} wgs={wgs} blk={blk} {dtype}")
