@@ -98,6 +98,9 @@ extern "C" {
  * path).  Its barrier waits are bounded: if a wait ever expires (which needs another workload
  * to hold the device's compute units for seconds) the kernel ends early, `out` is incomplete,
  * and linfusion_attn_last_error reports LINFUSION_ERR_TIMEOUT.
+ * At head widths above 80 calls of up to 512 tokens (fewer for many heads) are one kernel without any exchange, unless
+ * out == q or LINFUSION_FLAG_FORCE_SPLIT: workgroups that split a head's value channels.  It leaves the same state in the
+ * workspace and may be captured; its sums run in another order than the split path's.
  *
  *   dtype            LINFUSION_DTYPE_*; accumulation is fp32 for every dtype.
  *   feature_map      LINFUSION_PHI_*.
@@ -457,8 +460,8 @@ int linfusion_attn_plan(int B, int H, long long N, int d, int dtype, unsigned fl
 /*
  * Name of the kernel that will run the apply step for this shape on contiguous tensors ("apply16_dma",
  * "apply16_packed", "apply32", "apply32s", "apply16_wide", "apply16_wave", or "fused16" / "fused32" / "solo16" / "solo32" when a single
- * launch is chosen);
- * an empty string for rejected arguments.  Static storage.  For benchmarks and profile summaries.
+ * launch is chosen); an empty string for rejected arguments.  (A short call at a width above 80 that runs as one launch has
+ * no apply kernel: the name is that of its split path.)  Static storage.  For benchmarks and profile summaries.
  */
 const char* linfusion_attn_apply_kernel(int B, int H, long long N, int d, int dtype, unsigned flags);
 

@@ -381,7 +381,7 @@ struct ApplyWaveMlp {
     __builtin_amdgcn_sched_barrier(0);
     // ---- q = a + LeakyReLU(gamma (t rstd + cn) + beta), phi, fp16: the B operands ------------------------
     const float* aff = reinterpret_cast<const float*>(smem + Sm::kAffOffset);
-    constexpr bool kScaled = !__is_same(T, TA);   // bf16 tensors: see ApplyWave::make_operands
+    constexpr bool kScaled = !__is_same(T, TA);   // bf16 tensors: see wave_operands
     float x[kScaled ? 8 * KS : 2];
     float eps_tok = eps_s, post = 1.0f;
 #pragma unroll

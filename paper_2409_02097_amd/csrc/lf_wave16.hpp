@@ -207,6 +207,58 @@ inline void launch_pack_wave(const float* part, int parts, float* state, unsigne
   }
 }
 
+  // `B`: this lane's 8 KS stored channels of its token (lanes l, l + 16, l + 32, l + 48 hold one token between them)
+  // -> the fp16 operands phi~ = phi(q) 2^c 2^-e, where 2^c = exp(-m) if the row's largest channel m is negative
+  // under elu + 1 (else 1) and 2^e is the power of two at or below the row's largest phi 2^c, so the row's largest
+  // operand lies in [1, 2) whatever the inputs' magnitude.  eps_tok = eps' 2^c 2^-e is what eps becomes in that
+  // row's units (the factor cancels in Eq. 5's ratio), post = its inverse for the un-normalized form.  A row without
+  // a positive phi (relu of non-positive channels) keeps operands 0 and gives 0, as the definition does; a NaN stays
+  // in its own token's outputs (the row maximum skips it).
+  template <typename T, int FM, int KS>
+LF_DEV void wave_operands(u32x4 (&B)[KS], float eps_s, float& eps_tok, float& post) {
+    constexpr float kLog2e = 1.44269504088896340736f;
+    // (the channels are unpacked twice, for the maximum and for phi, rather than kept: 8 KS more live registers
+    //  would not fit beside the head's operands at d = 160)
+    float m = -__builtin_inff();
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        float a, b;
+        unpack2<T>(B[s][w], a, b);
+        m = fmaxf(m, fmaxf(FM == kPhiIdentity ? fabsf(a) : a, FM == kPhiIdentity ? fabsf(b) : b));
+      }
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32));
+    float c = 0.0f, top;   // top: the row's largest |phi 2^c|
+    if constexpr (FM == kPhiEluPlusOne) {
+      c = m < 0.0f ? fminf(-m * kLog2e, 3.0e38f) : 0.0f;   // (finite: a row of -inf gives phi = 0, not inf - inf)
+      top = m < 0.0f ? 1.0f : m + 1.0f;
+    } else if constexpr (FM == kPhiRelu) {
+      top = fmaxf(m, 0.0f);
+    } else {
+      top = m;
+    }
+    // 2^-e from top's exponent field f: (254 - f) as the field of the factor; f is kept inside [1, 253] so that the
+    // factor is a normal number (top = 0: the operands are 0 whatever it is)
+    uint32_t f = (__builtin_bit_cast(uint32_t, top) >> 23) & 0xffu;
+    f = f < 1u ? 1u : (f > 253u ? 253u : f);
+    const float mult = __builtin_bit_cast(float, (254u - f) << 23);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        float a, b;
+        unpack2<T>(B[s][w], a, b);
+        B[s][w] = pack2<F16>(phi_scaled<FM>(a, c) * mult, phi_scaled<FM>(b, c) * mult);
+      }
+    // eps' 2^c 2^-e in two finite factors (2^c alone leaves fp32's range from m = -88.7 on; the clamp only keeps
+    // 0 * 2^c = 0 for eps = 0: beyond it the product is infinite anyway and the row's outputs are 0, as their true
+    // size, below e^-131 / eps of the values', rounds to)
+    eps_tok = __builtin_amdgcn_exp2f(fminf(c, 190.0f) - 64.0f) * (eps_s * mult * 0x1p64f);
+    post = __builtin_amdgcn_exp2f(-c) * __builtin_bit_cast(float, f << 23);   // 2^-c 2^e
+  }
+
 // One wave's apply work on one head: construct, prefetch(), load_packed(), stream().  T: the tensors' storage type.
 template <typename T, int D, int FM, bool NORM>
 struct ApplyWave {
@@ -333,57 +385,6 @@ struct ApplyWave {
     for (int s = 0; s < KS; ++s) B[s] = *reinterpret_cast<const u32x4*>(sl + chunk_off(tb, 4 * s + g));
   }
 
-  // `B`: this lane's 8 KS stored channels of its token (lanes l, l + 16, l + 32, l + 48 hold one token between them)
-  // -> the fp16 operands phi~ = phi(q) 2^c 2^-e, where 2^c = exp(-m) if the row's largest channel m is negative
-  // under elu + 1 (else 1) and 2^e is the power of two at or below the row's largest phi 2^c, so the row's largest
-  // operand lies in [1, 2) whatever the inputs' magnitude.  eps_tok = eps' 2^c 2^-e is what eps becomes in that
-  // row's units (the factor cancels in Eq. 5's ratio), post = its inverse for the un-normalized form.  A row without
-  // a positive phi (relu of non-positive channels) keeps operands 0 and gives 0, as the definition does; a NaN stays
-  // in its own token's outputs (the row maximum skips it).
-  LF_DEV void make_operands(u32x4 (&B)[KS], float& eps_tok, float& post) {
-    constexpr float kLog2e = 1.44269504088896340736f;
-    // (the channels are unpacked twice, for the maximum and for phi, rather than kept: 8 KS more live registers
-    //  would not fit beside the head's operands at d = 160)
-    float m = -__builtin_inff();
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        float a, b;
-        unpack2<T>(B[s][w], a, b);
-        m = fmaxf(m, fmaxf(FM == kPhiIdentity ? fabsf(a) : a, FM == kPhiIdentity ? fabsf(b) : b));
-      }
-    m = fmaxf(m, __shfl_xor(m, 16));
-    m = fmaxf(m, __shfl_xor(m, 32));
-    float c = 0.0f, top;   // top: the row's largest |phi 2^c|
-    if constexpr (FM == kPhiEluPlusOne) {
-      c = m < 0.0f ? fminf(-m * kLog2e, 3.0e38f) : 0.0f;   // (finite: a row of -inf gives phi = 0, not inf - inf)
-      top = m < 0.0f ? 1.0f : m + 1.0f;
-    } else if constexpr (FM == kPhiRelu) {
-      top = fmaxf(m, 0.0f);
-    } else {
-      top = m;
-    }
-    // 2^-e from top's exponent field f: (254 - f) as the field of the factor; f is kept inside [1, 253] so that the
-    // factor is a normal number (top = 0: the operands are 0 whatever it is)
-    uint32_t f = (__builtin_bit_cast(uint32_t, top) >> 23) & 0xffu;
-    f = f < 1u ? 1u : (f > 253u ? 253u : f);
-    const float mult = __builtin_bit_cast(float, (254u - f) << 23);
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        float a, b;
-        unpack2<T>(B[s][w], a, b);
-        B[s][w] = pack2<TA>(phi_scaled<FM>(a, c) * mult, phi_scaled<FM>(b, c) * mult);
-      }
-    // eps' 2^c 2^-e in two finite factors (2^c alone leaves fp32's range from m = -88.7 on; the clamp only keeps
-    // 0 * 2^c = 0 for eps = 0: beyond it the product is infinite anyway and the row's outputs are 0, as their true
-    // size, below e^-131 / eps of the values', rounds to)
-    eps_tok = __builtin_amdgcn_exp2f(fminf(c, 190.0f) - 64.0f) * (eps_s * mult * 0x1p64f);
-    post = __builtin_amdgcn_exp2f(-c) * __builtin_bit_cast(float, f << 23);   // 2^-c 2^e
-  }
-
   // multiply one block of 16 tokens and write its outputs over its rows of the tile at `sl`; `eps_tok`: eps in the
   // units of this lane's token's denominator, `post`: the row's scale taken out of its un-normalized outputs
   LF_DEV void multiply_block(unsigned char* sl, int tb, const u32x4 (&B)[KS], float eps_tok, float post) {
@@ -421,9 +422,9 @@ struct ApplyWave {
     read_block(sl, 1, B1);   // block 0's outputs land in other rows
     __builtin_amdgcn_sched_barrier(0);
     float eps_tok, post;
-    make_operands(B0, eps_tok, post);
+    wave_operands<T, FM>(B0, eps_s, eps_tok, post);
     multiply_block(sl, 0, B0, eps_tok, post);
-    make_operands(B1, eps_tok, post);
+    wave_operands<T, FM>(B1, eps_s, eps_tok, post);
     multiply_block(sl, 1, B1, eps_tok, post);
   }
 

@@ -86,6 +86,8 @@ struct Plan {
   int gwaves, groups, gsplits, gblk_reduce, gapply_wgs, gblk_apply;
   int apply_waves;      // waves per workgroup of the packed per-head apply (1, 2 or 4)
   bool wave_apply;      // widths above 80: apply16_wave (a wave per tile) instead of apply16_wide
+  int short_parts;      // widths above 80: > 0, one launch of so many workgroups per 32 value channels of a head (short16),
+  bool short_half;      //   or per half of the channels
   bool gapply_packed;   // row-piece apply from operands prepared by pack_state16 (many short-lived workgroups)
   bool apply_packed;    // per-head apply from operands prepared by pack_state16 (many short-lived workgroups)
   long long n_tiles;
@@ -131,7 +133,7 @@ int apply_wgs_per_cu(int d, int dtype) {
 lfw::WidePlan wide_plan_of(const Plan& p, int dtype) {
   return lfw::WidePlan{p.splits, p.blk_reduce, p.apply_wgs, p.blk_apply,
                        env_int("LINFUSION_WIDE_APPLY_WAVES", dtype == LINFUSION_DTYPE_BF16 ? 8 : 4) == 8 ? 8 : 4,
-                       p.wave_apply};
+                       p.wave_apply, p.short_parts, p.short_half};
 }
 
 // `compact`: size the scratch for the three-kernel path alone (no room for the single launch's partials and
@@ -175,7 +177,8 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     p->splits = per_head(env_int("LINFUSION_WIDE_REDUCE_WGS", want), 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce);
     // a head of one or two tiles: one workgroup sums them and writes the state itself (no partials, no combine
     // launch; from four tiles on a workgroup's tiles in sequence cost more than the launch saved)
-    if (p->n_tiles <= env_int("LINFUSION_WIDE_ONE_SPLIT_TILES", 2)) {
+    const int one_split = env_int("LINFUSION_WIDE_ONE_SPLIT_TILES", 0);
+    if (p->n_tiles <= (one_split ? one_split : 2)) {
       p->splits = 1;
       p->blk_reduce = (int)p->n_tiles;
       room = 0;
@@ -193,6 +196,26 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       p->blk_apply = sh.blk;
     } else {
       p->apply_wgs = per_head(env_int("LINFUSION_WIDE_APPLY_WGS", 2 * num_cu()), 1, "LINFUSION_WIDE_APPLY_BLK", &p->blk_apply);
+    }
+    // One launch for short streams (not where a switch of the three launches is set: those are asked for then).  A workgroup
+    // walks all of a head's tokens, about 0.6 us per 32 of them, so up to 512 tokens as long as all workgroups run at once
+    // and proportionally fewer beyond (us per call, three launches -> one, d = 160: fp16 2 x 8 heads at 64 / 256 / 512 / 1024
+    // tokens 20.9 -> 9.0, 22.6 -> 13.2, 24.6 -> 18.5, 26.4 -> 27.7, bf16 21.2 -> 7.6, 23.6 -> 13.4, 26.3 -> 20.7, 28.7 -> 35.7; 20 x
+    // 10 heads fp16 27.6 -> 21.5, 40.3 -> 39.9, 56.9 -> 65.1).  Half of the value channels per workgroup where 32 would take
+    // more than a round, or most of one and many tokens (fp16 12 x 8 x 256 28.9 -> 20.0, 4 x 8 x 512 24.5 -> 21.4, but 2 x 8 x
+    // 256 13.2 -> 15.6 and 4 x 8 x 256 15.5 -> 16.0).
+    p->short_parts = 0;
+    p->short_half = false;
+    if (!compact && !(flags & LINFUSION_FLAG_FORCE_SPLIT) && p->wave_apply && !one_split) {
+      const int half = env_int("LINFUSION_WIDE_SHORT_HALF", 0);   // 1: always, 2: never
+      const long long by32 = BH * (d / 32);
+      p->short_half = half ? half == 1 : by32 > num_cu() || (2 * by32 > num_cu() && N > 320);
+      const long long groups = BH * (p->short_half ? 2 : d / 32), blocks = (N + 15) / 16, waves = d / 16;
+      const long long rounds = (groups + num_cu() - 1) / num_cu();
+      if (N * rounds <= env_int("LINFUSION_WIDE_SHORT_TOKENS", 512)) {
+        const long long useful = (blocks + waves - 1) / waves, fit = num_cu() / groups;
+        p->short_parts = (int)(useful < fit ? useful : (fit > 1 ? fit : 1));
+      }
     }
     p->fsplits = 0;
     p->fblk_reduce = p->fblk_apply = 1;
@@ -258,6 +281,8 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   p->apply_packed = dtype != LINFUSION_DTYPE_F32 && (packed_mode == 3 || (packed_mode == 1 && !one_round));
   p->apply_waves = lf::kWavesPerWG;
   p->wave_apply = false;
+  p->short_parts = 0;
+  p->short_half = false;
   int apply_want = apply_dflt, blk_dflt = 8;
   if (p->apply_packed) {
     const int w = env_int("LINFUSION_APPLY_WAVES", lf::kWavesPerWG);

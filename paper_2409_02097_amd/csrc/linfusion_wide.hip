@@ -2,6 +2,7 @@
 // (lf_wide16.hpp).  Kept apart from linfusion.hip so that the two compile side by side.
 #include "../../include/linfusion.h"
 
+#include "lf_short16.hpp"
 #include "lf_wave16.hpp"
 #include "lf_host_api.hpp"
 #include "lf_wide_api.hpp"
@@ -99,8 +100,35 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
 
+// the whole call in one launch
+template <typename T, int D, int CB>
+int run_short(const WideArgs& a) {
+  using namespace lf;
+  using C = Short16Cfg<T, D, CB>;
+  const dim3 grid((unsigned)((long long)a.B * a.H * C::kGroups * a.plan.short_parts));
+  if (a.ev) (void)hipEventRecord(a.ev[0], a.st);
+#define LFW_SHORT(FM, NORM)                                                                                       \
+  {                                                                                                               \
+    if (!allow_lds(short16<T, D, CB, FM, NORM>, C::kLdsBytes)) return LINFUSION_ERR_HIP;                              \
+    short16<T, D, CB, FM, NORM><<<grid, dim3(C::kThreads), C::kLdsBytes, a.st>>>(                                     \
+        (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (const u32x4*)a.q, a.lq, (u32x4*)a.out, a.lo, a.state, a.eps, \
+        (int)a.N, a.plan.short_parts);                                                                            \
+  }
+  switch (a.fm) {
+    case 0: if (a.unnorm) LFW_SHORT(0, false) else LFW_SHORT(0, true) break;
+    case 1: if (a.unnorm) LFW_SHORT(1, false) else LFW_SHORT(1, true) break;
+    default: if (a.unnorm) LFW_SHORT(2, false) else LFW_SHORT(2, true) break;
+  }
+#undef LFW_SHORT
+  if (a.ev) { (void)hipEventRecord(a.ev[1], a.st); (void)hipEventRecord(a.ev[2], a.st); (void)hipEventRecord(a.ev[3], a.st); }
+  return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
+}
+
 template <typename T, int D>
 int run(const WideArgs& a) {
+  // (a workgroup reads whole query rows and writes a part of their channels: not where out is q)
+  if (a.plan.short_parts > 0 && a.out && a.out != a.q)
+    return a.plan.short_half ? run_short<T, D, D / 32>(a) : run_short<T, D, 2>(a);
   const WideReduceArgs r{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.lkv, a.lkv, a.partials, a.state, a.plan, a.st};
   const bool fuse = a.out && a.plan.wave_apply;   // the partials are summed where the operands are packed
   int rc = reduce<T, D>(r, a.ev, !fuse);

@@ -1,0 +1,57 @@
+"""GPU parity of the one-launch forward call for short token streams at head widths above 80 (lf_short16.hpp)."""
+import pytest
+import torch
+
+import paper_2409_02097_amd as lf
+from paper_2409_02097_amd import workloads as wl
+from tests import parity
+from tests.test_gpu_partial_counts import _launches
+
+pytestmark = pytest.mark.gpu
+
+
+# rounds of 64 tokens (four on their way), query blocks of 16; 32 value channels per workgroup ("2") or half of them ("1")
+@pytest.mark.parametrize("half", ["1", "2"])
+@pytest.mark.parametrize("d,dtype", [(96, "f16"), (128, "bf16"), (160, "f16"), (160, "bf16")])
+@pytest.mark.parametrize("N", [1, 16, 17, 64, 65, 255, 257, 512])
+def test_short_streams_in_one_launch(N, d, dtype, half, monkeypatch, tuning):
+    B, H = 2, 3
+    print(f"short N={N} d={d} {dtype} half={half}", flush=True)
+    monkeypatch.setenv("LINFUSION_WIDE_SHORT_HALF", half)
+    code = wl.DTYPE_CODE[dtype]
+    q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=150, device="cpu")
+    tm = lambda t: t.permute(0, 2, 1, 3).contiguous().cuda().permute(0, 2, 1, 3)
+    need = lf.linfusion_attn_workspace_bytes(B, H, N, d, code)
+    off = lf.linfusion_attn_workspace_state_offset(B, H, N, d, code)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    got = []
+    for place in (lambda t: t.cuda(), tm):           # contiguous, and the token-major view of the same values
+        qd, kd, vd = place(q), place(k), place(v)
+        out = place(torch.full_like(q, float("nan")))
+        call = lambda: lf.linfusion_attn_fwd_strided(qd, kd, vd, out, 0, 1e-6, 0, ws)
+        call()
+        torch.cuda.synchronize()
+        got.append(out.contiguous())
+    assert _launches(call) == 1
+    parity.check_all(got[0], q, k, v, dtype, 0, 1e-6, True, f"short N={N} d={d} {dtype}")
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16)), "token-major differs from contiguous"
+    # the state it leaves is the split path's up to the order of the sums
+    state = ws[off:off + 4 * B * H * (d * d + d)].clone().view(torch.float32)
+    lf.linfusion_attn_state(k.cuda(), v.cuda(), split := torch.empty_like(state), 0, ws)
+    torch.cuda.synchronize()
+    assert ((state - split).norm() <= 1e-6 * split.norm()).item()     # (random signs: 2^-24 sqrt(N) of the sums' terms)
+    # in place the query rows are read before they are written: the split path, within the same bound
+    qd = q.cuda()
+    lf.linfusion_attn_fwd_strided(qd, k.cuda(), v.cuda(), qd, 0, 1e-6, 0, ws)
+    torch.cuda.synchronize()
+    parity.check_all(qd, q, k, v, dtype, 0, 1e-6, True, f"short, in place, N={N} d={d} {dtype}")
+
+
+@pytest.mark.parametrize("B,H,N,d,launches", [(2, 8, 256, 160, 1), (2, 8, 513, 160, 3), (50, 8, 256, 96, 3), (50, 8, 128, 96, 1)])
+def test_which_calls_are_short(B, H, N, d, launches):
+    """512 tokens while all workgroups run at once, fewer for more heads; the forced split path is never short."""
+    x = torch.zeros(B, H, N, d, dtype=torch.float16, device="cuda")
+    out = torch.empty_like(x)
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(B, H, N, d, lf.DTYPE_F16), dtype=torch.uint8, device="cuda")
+    assert _launches(lambda: lf.linfusion_attn_fwd_ex(x, x, x, out, 0, 1e-6, 0, ws)) == launches
+    assert _launches(lambda: lf.linfusion_attn_fwd_ex(x, x, x, out, 0, 1e-6, lf.FLAG_FORCE_SPLIT, ws)) >= 2
