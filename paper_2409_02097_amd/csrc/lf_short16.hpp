@@ -42,7 +42,8 @@ template <typename T, int D, int CB> struct Short16Cfg {
   static constexpr int kAhead = 4;                   // rounds on their way
 };
 
-// keep: null, or where the heads' states go ([B*H][D*D + D]).  parts: workgroups that share a head's query tokens.
+// keep: null, or where the heads' states go ([B*H][D*D + D]); O = null: nothing else is wanted (Q is not read).
+// parts: workgroups that share a head's query tokens.
 template <typename T, int D, int CB, int FM, bool NORM>
 __global__ void __launch_bounds__((Short16Cfg<T, D, CB>::kThreads))
 short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, const u32x4* __restrict__ Q, Layout lq,
@@ -69,7 +70,7 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
 #pragma unroll
     for (int s = 0; s < KS; ++s) B[s] = p[4 * s];
   };
-  const int blocks = (N + 15) / 16;
+  const int blocks = O ? (N + 15) / 16 : 0;
   int t = part * W + wave;
   u32x4 B[KS];
 
@@ -223,6 +224,7 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
       if (grp == 0 && j16 == 0) dst[D * D + row] = accz[i];
     }
   }
+  if (!O) return;
   float m[CB + 1];
 #pragma unroll
   for (int b = 0; b <= CB; ++b) {

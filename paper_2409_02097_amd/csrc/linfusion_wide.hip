@@ -105,14 +105,15 @@ template <typename T, int D, int CB>
 int run_short(const WideArgs& a) {
   using namespace lf;
   using C = Short16Cfg<T, D, CB>;
-  const dim3 grid((unsigned)((long long)a.B * a.H * C::kGroups * a.plan.short_parts));
+  const int parts = a.out ? a.plan.short_parts : 1;
+  const dim3 grid((unsigned)((long long)a.B * a.H * C::kGroups * parts));
   if (a.ev) (void)hipEventRecord(a.ev[0], a.st);
 #define LFW_SHORT(FM, NORM)                                                                                       \
   {                                                                                                               \
     if (!allow_lds(short16<T, D, CB, FM, NORM>, C::kLdsBytes)) return LINFUSION_ERR_HIP;                              \
     short16<T, D, CB, FM, NORM><<<grid, dim3(C::kThreads), C::kLdsBytes, a.st>>>(                                     \
         (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (const u32x4*)a.q, a.lq, (u32x4*)a.out, a.lo, a.state, a.eps, \
-        (int)a.N, a.plan.short_parts);                                                                            \
+        (int)a.N, parts);                                                                                          \
   }
   switch (a.fm) {
     case 0: if (a.unnorm) LFW_SHORT(0, false) else LFW_SHORT(0, true) break;
@@ -126,8 +127,9 @@ int run_short(const WideArgs& a) {
 
 template <typename T, int D>
 int run(const WideArgs& a) {
-  // (a workgroup reads whole query rows and writes a part of their channels: not where out is q)
-  if (a.plan.short_parts > 0 && a.out && a.out != a.q)
+  // (A workgroup reads whole query rows and writes a part of their channels: not where out is q.  The state alone is summed
+  // the same way, so that it has the bits of the state that a call leaves behind.)
+  if (a.plan.short_parts > 0 && (!a.out || a.out != a.q))
     return a.plan.short_half ? run_short<T, D, D / 32>(a) : run_short<T, D, 2>(a);
   const WideReduceArgs r{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.lkv, a.lkv, a.partials, a.state, a.plan, a.st};
   const bool fuse = a.out && a.plan.wave_apply;   // the partials are summed where the operands are packed
