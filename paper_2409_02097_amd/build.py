@@ -19,6 +19,8 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "--offload-compress",   # the device images are stored compressed (the library shrinks about five-fold)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first fourteen 32-bit words of a kernel's arguments are in scalar registers when it starts
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -809,15 +809,16 @@ struct ApplyDma {
 // state: [B*H][parts][D*D + D]; the sum of more than one partial goes to keep ([B*H][D*D + D]) as well.
 template <typename T, int D, int FM, bool NORM>
 __global__ void __launch_bounds__(kThreads)
-apply16_dma(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, HeadSubset hs,
-            const float* __restrict__ state, int parts, float* __restrict__ keep, float eps, long long N,
-            int tiles_per_block) {
+apply16_dma(const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, unsigned heads, int tiles_per_block,
+            long long N, const float* __restrict__ state, int parts, float eps, float* __restrict__ keep,
+            u32x4* __restrict__ O, long long obatch, long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const long long bh = hs.bh(blockIdx.y, lq.H);
-  ApplyDma<T, D, FM, NORM> ap(Q + lq.slice(bh), lq.row, O + lo.slice(bh), lo.row, N, tiles_per_block, blockIdx.x,
-                              gridDim.x, smem);
+  const HeadAt at(blockIdx.y, heads);
+  ApplyDma<T, D, FM, NORM> ap(Q + at.slice(qbatch, qhead), qrow, O + at.slice(obatch, ohead), orow, N, tiles_per_block,
+                              blockIdx.x, gridDim.x, smem);
   ap.prefetch();
   constexpr int NE = D * D + D;
+  const long long bh = at.index;
   ap.run(state + bh * parts * NE, eps, parts, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr);
 }
 
@@ -827,14 +828,15 @@ apply16_dma(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layou
 // moving window of memory, which the write stream in particular rewards.
 template <typename T, int D, int FM, bool NORM, int WPW>
 __global__ void __launch_bounds__(64 * WPW)
-apply16_packed(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, HeadSubset hs,
-               const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
+apply16_packed(const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, unsigned heads, int tiles_per_block,
+               long long N, const unsigned char* __restrict__ packed, float eps, u32x4* __restrict__ O, long long obatch,
+               long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const long long bh = hs.bh(blockIdx.y, lq.H);
-  ApplyDma<T, D, FM, NORM, 0, false, D, false, WPW> ap(Q + lq.slice(bh), lq.row, O + lo.slice(bh), lo.row, N,
-                                                       tiles_per_block, blockIdx.x, gridDim.x, smem);
+  const HeadAt at(blockIdx.y, heads);
+  ApplyDma<T, D, FM, NORM, 0, false, D, false, WPW> ap(Q + at.slice(qbatch, qhead), qrow, O + at.slice(obatch, ohead), orow,
+                                                       N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   ap.prefetch();
-  ap.load_packed(packed + bh * Pack16<T, D>::kHeadBytes, eps);
+  ap.load_packed(packed + (long long)at.index * Pack16<T, D>::kHeadBytes, eps);
   ap.stream();
 }
 
@@ -844,17 +846,16 @@ apply16_packed(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, La
 // whole group are left to apply16_dma.
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
-apply16_rows(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, int groups_per_batch,
-             const unsigned char* __restrict__ packed, const float* __restrict__ state, float eps, long long N,
-             int tiles_per_block) {
+apply16_rows(const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, int groups_per_batch,
+             int tiles_per_block, long long N, const float* __restrict__ state, const unsigned char* __restrict__ packed,
+             float eps, int H, u32x4* __restrict__ O, long long obatch, long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const long long b = blockIdx.y / groups_per_batch;
-  const long long h0 = (long long)(blockIdx.y % groups_per_batch) * W;
-  ApplyDma<T, D, FM, NORM, W> ap(Q + (b * lq.batch + h0 * lq.head), lq.row, O + (b * lo.batch + h0 * lo.head), lo.row,
-                                 N, tiles_per_block, blockIdx.x, gridDim.x, smem);
+  const HeadAt group(blockIdx.y, groups_per_batch);
+  const long long b = group.b, h0 = group.h * W;
+  ApplyDma<T, D, FM, NORM, W> ap(Q + (b * qbatch + h0 * qhead), qrow, O + (b * obatch + h0 * ohead), orow, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   ap.prefetch();
-  const long long bh = b * lq.H + h0 + wave;
+  const long long bh = b * H + h0 + wave;
   if (packed) ap.load_packed(packed + bh * Pack16<T, D>::kHeadBytes, eps);
   else ap.load_direct(state + bh * (D * D + D), eps);
   ap.stream();

@@ -324,13 +324,13 @@ LF_DEV void reduce16_phase(const u32x4* __restrict__ Kh, const u32x4* __restrict
 
 template <typename T, int D, int FM>
 __global__ void __launch_bounds__(kThreads)
-state_reduce16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout kv, HeadSubset hs,
-               float* __restrict__ partials, long long N, int tiles_per_block) {
+state_reduce16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long batch, long long head, int row,
+               unsigned heads, int tiles_per_block, long long N, float* __restrict__ partials) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const long long bh = hs.bh(blockIdx.y, kv.H);
-  float* dst = partials + (bh * gridDim.x + blockIdx.x) * (long long)(D * D + D);
-  const long long off = kv.slice(bh);
-  reduce16_phase<T, D, FM>(K + off, V + off, kv.row, dst, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
+  const HeadAt at(blockIdx.y, heads);
+  const long long off = at.slice(batch, head);
+  float* dst = partials + ((long long)at.index * gridDim.x + blockIdx.x) * (D * D + D);
+  reduce16_phase<T, D, FM>(K + off, V + off, row, dst, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
 }
 
 // ==========================================================================================
@@ -360,8 +360,8 @@ template <typename T, int D, int W> struct ReduceRowsCfg {
 
 template <typename T, int D, int FM, int W>
 __global__ void __launch_bounds__(64 * W)
-state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout kv, int groups_per_batch,
-                    float* __restrict__ partials, long long N, int tiles_per_block) {
+state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long batch, long long head, int row,
+                    int groups_per_batch, int tiles_per_block, long long N, int H, float* __restrict__ partials) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using Sh = Shape16<D>;
   using RC = Reduce16Cfg<D>;
@@ -372,11 +372,11 @@ state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, La
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const long long b = blockIdx.y / groups_per_batch;
-  const long long h0 = (long long)(blockIdx.y % groups_per_batch) * W;
-  const u32x4* Kg = K + (b * kv.batch + h0 * kv.head);
-  const u32x4* Vg = V + (b * kv.batch + h0 * kv.head);
-  const int rs = kv.row;
+  const HeadAt group(blockIdx.y, groups_per_batch);
+  const long long b = group.b, h0 = group.h * W;
+  const u32x4* Kg = K + (b * batch + h0 * head);
+  const u32x4* Vg = V + (b * batch + h0 * head);
+  const int rs = row;
   uint16_t* lds = reinterpret_cast<uint16_t*>(smem);
 
   // per-thread constants: chunk p = 64 W u + tid of a tile is chunk p % PC of token row p / PC; it
@@ -592,7 +592,7 @@ state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, La
 
   // ---- each wave owns a whole partial: straight from the accumulator layout (lane: rows 4 (l / 16) + i,
   //      column l % 16 of each 16 x 16 block) to memory ----------------------------------------------
-  float* dst = partials + (((b * kv.H + h0 + wave) * gridDim.x) + blockIdx.x) * (long long)(D * D + D);
+  float* dst = partials + (((b * H + h0 + wave) * gridDim.x) + blockIdx.x) * (long long)(D * D + D);
 #pragma unroll
   for (int a = 0; a < MT; ++a) {
 #pragma unroll

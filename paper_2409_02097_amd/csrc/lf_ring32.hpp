@@ -486,8 +486,8 @@ template <int D> struct Reduce32s {
 };
 template <int D, int FM>
 __global__ void __launch_bounds__(kThreads, 2)
-state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict__ V, Layout vl,
-                float* __restrict__ partials, long long N, int tiles_per_block) {
+state_reduce32s(const float* __restrict__ K, const float* __restrict__ V, long long batch, long long head, int row,
+                unsigned heads, int tiles_per_block, long long N, float* __restrict__ partials) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using C = Reduce32s<D>;
   constexpr int CPL = C::kCPL, TOK = C::kTokens;
@@ -499,9 +499,9 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
   // rows apart every 128-byte line would be fetched by several instructions: 8 x 40 at 2^20 tokens 609 us, d = 8 173 us)
   constexpr int kStep = 4 * C::kGroups;
   const int t0 = kq + (C::kGroups == 2 ? (m >> 3) * 4 : 0);
-  const float* Kh = K + kl.slice(bh) * 4;
-  const float* Vh = V + vl.slice(bh) * 4;
-  const int rsk = kl.row * 4, rsv = vl.row * 4;
+  const long long off = HeadAt(blockIdx.y, heads).slice(batch, head) * 4;
+  const float *Kh = K + off, *Vh = V + off;
+  const int rs = row * 4;
   TileIter it(blockIdx.x, gridDim.x, wave, tiles_per_block, (N + TOK - 1) / TOK);
 
   float kr[8][CPL], vr[8][CPL];   // this lane's channels of its eight tokens: the next tile's
@@ -521,13 +521,13 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
   // (an offset is 63 rows of floats at most: unsigned, since it may exceed an int)
   static_assert((TOK - 1) * 4 * (kMaxRowStride - 1) + D <= 0xffffffffLL, "row offsets of a tile fit 32 bits");
   auto issue_loads = [&](long long tile, int lim) {   // rows past N: the tile's first row instead
-    const float* kp = Kh + tile * TOK * rsk;
-    const float* vp = Vh + tile * TOK * rsv;
+    const float* kp = Kh + tile * TOK * rs;
+    const float* vp = Vh + tile * TOK * rs;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const unsigned r = t0 + kStep * j < lim ? t0 + kStep * j : 0;
-      load_row(kp + (r * (unsigned)rsk + c0), kr[j]);
-      load_row(vp + (r * (unsigned)rsv + c0), vr[j]);
+      load_row(kp + (r * (unsigned)rs + c0), kr[j]);
+      load_row(vp + (r * (unsigned)rs + c0), vr[j]);
     }
   };
 
@@ -700,16 +700,18 @@ state_reduce32s(const float* __restrict__ K, Layout kl, const float* __restrict_
 // state: [B*H][parts][D*D + D]; with `keep` the summed state goes there too ([B*H][D*D + D]).
 template <int D, int FM, bool NORM>
 __global__ void __launch_bounds__(kThreads, 2)
-apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout lo, const float* __restrict__ state,
-         int parts, float* __restrict__ keep, float eps, long long N, int tiles_per_block) {
+apply32s(const f32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, unsigned heads, int tiles_per_block,
+         long long N, const float* __restrict__ state, int parts, float eps, float* __restrict__ keep, f32x4* __restrict__ O,
+         long long obatch, long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RG = Ring32For<D, 1>;
   constexpr int MT = RG::MT, R = RG::R, NE = RG::NE;
   const long long bh = blockIdx.y;
-  const f32x4* const src[1] = {Q + lq.slice(bh)};
-  const int rs[1] = {lq.row};
+  const HeadAt at(blockIdx.y, heads);
+  const f32x4* const src[1] = {Q + at.slice(qbatch, qhead)};
+  const int rs[1] = {qrow};
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
-  f32x4* Oh = O + lo.slice(bh);
+  f32x4* Oh = O + at.slice(obatch, ohead);
   rg.prefetch();
   bool raw;
   const float* st = rg.stage_state(state + bh * parts * (long long)NE, parts, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr, raw);
@@ -761,7 +763,7 @@ apply32s(const f32x4* __restrict__ Q, Layout lq, f32x4* __restrict__ O, Layout l
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     rg.write_rows(slot, 0, acc);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    rg.store_tile(tile, slot, 0, Oh, lo.row);
+    rg.store_tile(tile, slot, 0, Oh, orow);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     rg.it.next();
     rg.ahead.next();

@@ -46,8 +46,9 @@ template <typename T, int D, int CB> struct Short16Cfg {
 // parts: workgroups that share a head's query tokens.
 template <typename T, int D, int CB, int FM, bool NORM>
 __global__ void __launch_bounds__((Short16Cfg<T, D, CB>::kThreads))
-short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, const u32x4* __restrict__ Q, Layout lq,
-        u32x4* __restrict__ O, Layout lo, float* __restrict__ keep, float eps, int N, int parts) {
+short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long kbatch, long long khead, int rs, unsigned heads,
+        int N, int parts, const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, float eps,
+        float* __restrict__ keep, u32x4* __restrict__ O, long long obatch, long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using C = Short16Cfg<T, D, CB>;
   constexpr int W = C::kWaves, NT = C::kThreads, NS = C::kNS, NL = C::kNL, KS = C::kKS, CPR = C::kCPR;
@@ -58,15 +59,16 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
   const int unit = solo_unit((int)blockIdx.x, (int)gridDim.x);   // a head's workgroups share an XCD's L2
   const int per_head = C::kGroups * parts;
   const int bh = unit / per_head, rem = unit - bh * per_head;
+  const HeadAt head((unsigned)bh, heads);
   const int part = rem / C::kGroups, grp = rem - part * C::kGroups;
   uint16_t* lds = reinterpret_cast<uint16_t*>(smem);
   uint16_t* ops = reinterpret_cast<uint16_t*>(smem + C::kTileBytes);
 
   // ---- query tokens: block t of 16 ---------------------------------------------------------------------------
-  const u32x4* Qh = Q + lq.slice(bh);
+  const u32x4* Qh = Q + head.slice(qbatch, qhead);
   auto load_q = [&](int t, u32x4 (&B)[KS]) {
     const int tok = 16 * t + j16;
-    const u32x4* p = Qh + (long long)(tok < N ? tok : 0) * lq.row + g4;   // (rows past the end are never stored)
+    const u32x4* p = Qh + (long long)(tok < N ? tok : 0) * qrow + g4;   // (rows past the end are never stored)
 #pragma unroll
     for (int s = 0; s < KS; ++s) B[s] = p[4 * s];
   };
@@ -75,8 +77,8 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
   u32x4 B[KS];
 
   // ---- state columns -------------------------------------------------------------------------------------------
-  const u32x4* Kh = K + lkv.slice(bh);
-  const u32x4* Vh = V + lkv.slice(bh) + grp * (C::kCols / 8);
+  const u32x4* Kh = K + head.slice(kbatch, khead);
+  const u32x4* Vh = V + head.slice(kbatch, khead) + grp * (C::kCols / 8);
   const int rounds = (N + TOK - 1) / TOK;
   int krow[NL], kcol[NL];
 #pragma unroll
@@ -92,11 +94,11 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
   u32x4 kr[AH][NL], vr[AH];
   auto issue = [&](int rd, u32x4 (&k)[NL], u32x4& v) {
     const int lim = N - rd * TOK;      // (rows past it: the round's first, replaced below)
-    const u32x4* kp = Kh + (long long)rd * TOK * lkv.row;
-    const u32x4* vp = Vh + (long long)rd * TOK * lkv.row;
+    const u32x4* kp = Kh + (long long)rd * TOK * rs;
+    const u32x4* vp = Vh + (long long)rd * TOK * rs;
 #pragma unroll
-    for (int u = 0; u < NL; ++u) k[u] = kp[(krow[u] < lim ? krow[u] : 0) * lkv.row + kcol[u]];
-    if (has_v) v = vp[(vrow < lim ? vrow : 0) * lkv.row + vcol];
+    for (int u = 0; u < NL; ++u) k[u] = kp[(krow[u] < lim ? krow[u] : 0) * rs + kcol[u]];
+    if (has_v) v = vp[(vrow < lim ? vrow : 0) * rs + vcol];
     if (lim < TOK) {
 #pragma unroll
       for (int u = 0; u < NL; ++u)
@@ -198,7 +200,7 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
       if (!(zm < (float)N * 0x1p-11f)) break;                // ordinary data, NaNs
       f16x2 kmax2 = __builtin_bit_cast(f16x2, LowestBits<F16>::value);
       for (int p = tid; p < N * CPR; p += NT) {
-        const u32x4 k = Kh[(long long)(p / CPR) * lkv.row + p % CPR];
+        const u32x4 k = Kh[(long long)(p / CPR) * rs + p % CPR];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
           const uint32_t word = k[w];
@@ -275,7 +277,7 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
   for (int b = 0; b < CB; ++b) c1[b] = scale[CB] / scale[b];
 
   // ---- out^T = S'^T phi(q)^T, 16 tokens at a time ------------------------------------------------------------------
-  u32x2* Oh = reinterpret_cast<u32x2*>(O + lo.slice(bh)) + grp * (C::kCols / 4);
+  u32x2* Oh = reinterpret_cast<u32x2*>(O + head.slice(obatch, ohead)) + grp * (C::kCols / 4);
   while (t < blocks) {
     const int next = t + parts * W;
     u32x4 Bn[KS];
@@ -295,7 +297,7 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, co
     if constexpr (NORM) inv = __builtin_amdgcn_rcpf(__shfl(o[CB][0] + o[CB][1], j16) + eps_tok);
     const int tok = 16 * t + j16;
     if (tok < N) {
-      u32x2* p = Oh + 2LL * tok * lo.row;
+      u32x2* p = Oh + 2LL * tok * orow;
 #pragma unroll
       for (int b = 0; b < CB; ++b) {
         const f32x4 x = o[b] * (c1[b] * inv);

@@ -463,14 +463,15 @@ struct ApplyWave {
 // grid = (wgs, heads), block = 256 (four waves that share nothing but the workgroup); `packed` from combine_pack_wave<D>
 template <typename T, int D, int FM, bool NORM>
 __global__ void __launch_bounds__(kThreads)
-apply16_wave(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, HeadSubset hs,
-             const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
+apply16_wave(const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, unsigned heads, int tiles_per_block,
+             long long N, const unsigned char* __restrict__ packed, float eps, u32x4* __restrict__ O, long long obatch,
+             long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const long long bh = hs.bh(blockIdx.y, lq.H);
-  ApplyWave<T, D, FM, NORM> ap(Q + lq.slice(bh), lq.row, O + lo.slice(bh), lo.row, N, tiles_per_block, blockIdx.x,
-                               gridDim.x, smem);
+  const HeadAt at(blockIdx.y, heads);
+  ApplyWave<T, D, FM, NORM> ap(Q + at.slice(qbatch, qhead), qrow, O + at.slice(obatch, ohead), orow, N, tiles_per_block,
+                               blockIdx.x, gridDim.x, smem);
   ap.prefetch();
-  ap.load_packed(packed + bh * PackWave<D>::kHeadBytes, eps);
+  ap.load_packed(packed + (long long)at.index * PackWave<D>::kHeadBytes, eps);
   ap.stream();
 }
 

@@ -69,7 +69,7 @@ constexpr int apply16_wide_lds_bytes() {
 // ==========================================================================================
 template <typename T, int D, int FM>
 __global__ void __launch_bounds__(kThreads, 2)   // two workgroups per CU: one multiplies while the other loads
-state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restrict__ V, Layout vl, HeadSubset hs,
+state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restrict__ V, Layout vl,
                     float* __restrict__ partials, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using Sw = ShapeWide<D>;
@@ -81,7 +81,7 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave & 1, a0 = (wave >> 1) * MH, b0 = wc * MH;
-  const long long bh = hs.bh(blockIdx.y, kl.H);
+  const long long bh = blockIdx.y;
   const u32x4* Kh = K + kl.slice(bh);
   const u32x4* Vh = V + vl.slice(bh);
   const int rs = kl.row, rsv = vl.row;   // the two tensors may be laid out differently (the backward pass pairs q with a dense temporary)
@@ -720,10 +720,10 @@ struct ApplyWide {
 
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
-apply16_wide(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo, HeadSubset hs,
+apply16_wide(const u32x4* __restrict__ Q, Layout lq, u32x4* __restrict__ O, Layout lo,
              const unsigned char* __restrict__ packed, float eps, long long N, int tiles_per_block) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const long long bh = hs.bh(blockIdx.y, lq.H);
+  const long long bh = blockIdx.y;
   ApplyWide<T, D, FM, NORM, W> ap(Q + lq.slice(bh), lq.row, O + lo.slice(bh), lo.row, N, tiles_per_block, blockIdx.x,
                                gridDim.x, smem);
   ap.prefetch();

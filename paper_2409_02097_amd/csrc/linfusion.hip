@@ -237,6 +237,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     p->ws_total = p->ws_partials + p->ws_state + p->ws_sync;
     return LINFUSION_OK;
   }
+  const size_t esz = dtype == LINFUSION_DTYPE_F32 ? 4 : 2;
   auto per_head = [&](int want_total, const char* env_blk, int blk_dflt, int* blk, int waves = lf::kWavesPerWG) {
     // (rounded down: one workgroup too many costs a whole extra round)
     const lfh::Share sh = even_share(p->n_tiles, want_total / BH, waves, env_int(env_blk, blk_dflt));
@@ -245,7 +246,6 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   };
   // state reduction (read-only stream): two workgroups per CU measured best -- fewer, longer
   // streams keep DRAM pages open
-  const size_t esz = dtype == LINFUSION_DTYPE_F32 ? 4 : 2;
   const double bytes = 4.0 * (double)BH * (double)N * d * (double)esz;
   // From 768 MB of tensor traffic on, the narrow heads whose tiles carry more vector work than bytes run faster with
   // more, shorter streams (sweeps at 2-4 M tokens of 8 heads: bf16 d = 8 / 16 / 24 / 32 / 40 -30 / -13 / -9 / -3.5 /
@@ -524,15 +524,17 @@ int run16(const Args& a) {
   if (a.ev) (void)hipEventRecord(a.ev[0], st);
   const int H = a.lkv.H, B = (int)(a.BH / H);
   const int gpb = H / p.gwaves, rest = H % p.gwaves;   // whole groups of heads, heads left over
-  const HeadSubset all{0, H}, tail{H - rest, rest > 0 ? rest : 1};
+  const unsigned all = (unsigned)H | (unsigned)H << 16, tail = (unsigned)rest | (unsigned)H << 16;   // HeadAt
+  const long long first = H - rest;
   if (a.group_reduce) {
     const dim3 g1(p.gsplits, (unsigned)p.groups);
 #define LF_REDUCE_W(FM, WW)                                                                              \
   {                                                                                                      \
     constexpr int ldsr = ReduceRowsCfg<T, D, WW>::kLdsBytes;                                             \
     if (!allow_lds(state_reduce16_rows<T, D, FM, WW>, ldsr)) return LINFUSION_ERR_HIP;                   \
-    state_reduce16_rows<T, D, FM, WW><<<g1, dim3(64 * WW), ldsr, st>>>(K, V, a.lkv, gpb, partials, a.N,  \
-                                                                       p.gblk_reduce);                   \
+    state_reduce16_rows<T, D, FM, WW><<<g1, dim3(64 * WW), ldsr, st>>>(K, V, a.lkv.batch, a.lkv.head,    \
+                                                                       a.lkv.row, gpb, p.gblk_reduce, a.N, H, \
+                                                                       partials);                        \
   }
 #define LF_REDUCE(FM)                                   \
   if constexpr (D <= 64) {                              \
@@ -545,7 +547,9 @@ int run16(const Args& a) {
       const dim3 g1t(p.gsplits, (unsigned)(B * rest));
 #define LF_REDUCE(FM)                                                                    \
   if (!allow_lds(state_reduce16<T, D, FM>, (int)lds1)) return LINFUSION_ERR_HIP;         \
-  state_reduce16<T, D, FM><<<g1t, blk, lds1, st>>>(K, V, a.lkv, tail, partials, a.N, p.blk_reduce);
+  state_reduce16<T, D, FM><<<g1t, blk, lds1, st>>>(K + first * a.lkv.head, V + first * a.lkv.head, a.lkv.batch,       \
+                                                   a.lkv.head, a.lkv.row, tail, p.blk_reduce, a.N,            \
+                                                   partials + first * p.gsplits * NE);
       LF_SWITCH_FM(LF_REDUCE)
 #undef LF_REDUCE
     }
@@ -553,7 +557,7 @@ int run16(const Args& a) {
     const dim3 g1(p.splits, (unsigned)a.BH);
 #define LF_REDUCE(FM)                                                                    \
   if (!allow_lds(state_reduce16<T, D, FM>, (int)lds1)) return LINFUSION_ERR_HIP;         \
-  state_reduce16<T, D, FM><<<g1, blk, lds1, st>>>(K, V, a.lkv, all, partials, a.N, p.blk_reduce);
+  state_reduce16<T, D, FM><<<g1, blk, lds1, st>>>(K, V, a.lkv.batch, a.lkv.head, a.lkv.row, all, p.blk_reduce, a.N, partials);
     LF_SWITCH_FM(LF_REDUCE)
 #undef LF_REDUCE
   }
@@ -589,8 +593,9 @@ int run16(const Args& a) {
   {                                                                                                       \
     constexpr int ldsa = apply16_dma_lds_bytes<T, D>(WW);                                                 \
     if (!allow_lds(apply16_rows<T, D, FM, NORM, WW>, ldsa)) return LINFUSION_ERR_HIP;                     \
-    apply16_rows<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), ldsa, st>>>(Q, a.lq, O, a.lo, gpb, packed, state, \
-                                                                      a.eps, a.N, p.gblk_apply);                 \
+    apply16_rows<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), ldsa, st>>>(Q, a.lq.batch, a.lq.head, a.lq.row, gpb, \
+                                                                      p.gblk_apply, a.N, state, packed, a.eps, H, \
+                                                                      O, a.lo.batch, a.lo.head, a.lo.row);        \
   }
 #define LF_APPLY(FM, NORM)                                          \
   if constexpr (D <= 64) {                                          \
@@ -603,7 +608,9 @@ int run16(const Args& a) {
         const dim3 g2t(p.apply_wgs, (unsigned)(B * rest));
 #define LF_APPLY(FM, NORM)                                                               \
   if (!allow_lds(apply16_dma<T, D, FM, NORM>, (int)lds2)) return LINFUSION_ERR_HIP;      \
-  apply16_dma<T, D, FM, NORM><<<g2t, blk, lds2, st>>>(Q, a.lq, O, a.lo, tail, state, 1, nullptr, a.eps, a.N, p.blk_apply);
+  apply16_dma<T, D, FM, NORM><<<g2t, blk, lds2, st>>>(Q + first * a.lq.head, a.lq.batch, a.lq.head, a.lq.row, tail,    \
+                                                     p.blk_apply, a.N, state + first * NE, 1, a.eps, nullptr,   \
+                                                     O + first * a.lo.head, a.lo.batch, a.lo.head, a.lo.row);
         LF_SWITCH_FM_NORM(LF_APPLY)
 #undef LF_APPLY
       }
@@ -619,8 +626,9 @@ int run16(const Args& a) {
   {                                                                                                       \
     constexpr size_t lds3 = (size_t)ApplyDmaCfg<D>::kRing * ApplyDmaCfg<D>::kSlotBytes * WW;              \
     if (!allow_lds(apply16_packed<T, D, FM, NORM, WW>, (int)lds3)) return LINFUSION_ERR_HIP;             \
-    apply16_packed<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), lds3, st>>>(Q, a.lq, O, a.lo, all, packed, a.eps, a.N, \
-                                                                        p.blk_apply);                    \
+    apply16_packed<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), lds3, st>>>(Q, a.lq.batch, a.lq.head, a.lq.row, all, \
+                                                                        p.blk_apply, a.N, packed, a.eps, \
+                                                                        O, a.lo.batch, a.lo.head, a.lo.row); \
   }
 #define LF_APPLY(FM, NORM)                                                        \
   if (p.apply_waves == 1) LF_APPLY_W(FM, NORM, 1) else if (p.apply_waves == 2) LF_APPLY_W(FM, NORM, 2) else LF_APPLY_W(FM, NORM, 4)
@@ -631,8 +639,9 @@ int run16(const Args& a) {
       const dim3 g2(p.apply_wgs, (unsigned)a.BH);
 #define LF_APPLY(FM, NORM)                                                               \
   if (!allow_lds(apply16_dma<T, D, FM, NORM>, (int)lds2)) return LINFUSION_ERR_HIP;      \
-  apply16_dma<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq, O, a.lo, all, fold ? partials : state, fold ? parts : 1, \
-                                                      fold ? state : nullptr, a.eps, a.N, p.blk_apply);
+  apply16_dma<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq.batch, a.lq.head, a.lq.row, all, p.blk_apply, a.N,         \
+                                                    fold ? partials : state, fold ? parts : 1, a.eps,            \
+                                                    fold ? state : nullptr, O, a.lo.batch, a.lo.head, a.lo.row);
       LF_SWITCH_FM_NORM(LF_APPLY)
 #undef LF_APPLY
     }

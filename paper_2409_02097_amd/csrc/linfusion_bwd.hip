@@ -255,7 +255,7 @@ int launch_state_rows(const BwdArgs& a, float* partials, int* nparts) {
   if (s > a.p->most) s = a.p->most;   // room for the partial states
   const lfh::Share sh = lfh::even_share(n_tiles, s, 1, lfh::env_int("LINFUSION_GROUP_REDUCE_BLK", 2));
   state_reduce16_rows<T, D, FM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, gpb, partials, a.N, sh.blk);
+      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv.batch, a.lkv.head, a.lkv.row, gpb, sh.blk, a.N, a.H, partials);
   *nparts = sh.wgs;
   return LINFUSION_OK;
 }
@@ -338,7 +338,7 @@ int run_bwd(const BwdArgs& a) {
   const u32x4* G = (const u32x4*)a.g;
   const dim3 blk(kThreads);
   hipStream_t st = a.st;
-  const HeadSubset all{0, a.H};
+  const unsigned all = (unsigned)a.H | (unsigned)a.H << 16;   // HeadAt
   const dim3 gr(p.splits, (unsigned)BH), ga(p.apply_wgs, (unsigned)BH);
   const dim3 gc((NE + kCombineElems - 1) / kCombineElems, (unsigned)BH);
 
@@ -354,7 +354,7 @@ int run_bwd(const BwdArgs& a) {
   } else {
     int nparts = p.splits, rcs = LINFUSION_OK;
     if (!state_rows<T, D, FM>(a, partials, &nparts, &rcs))
-      state_reduce16<T, D, FM><<<gr, blk, lds_r, st>>>(K, V, a.lkv, all, partials, a.N, p.blk_reduce);
+      state_reduce16<T, D, FM><<<gr, blk, lds_r, st>>>(K, V, a.lkv.batch, a.lkv.head, a.lkv.row, all, p.blk_reduce, a.N, partials);
     if (rcs != LINFUSION_OK) return rcs;
     combine_state<0><<<gc, dim3(kCombineThreads), 0, st>>>(partials, nparts, NE, stateS);
   }

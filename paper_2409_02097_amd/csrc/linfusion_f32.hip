@@ -29,8 +29,10 @@ bool fold(int parts, int d) {
 // every result) has the same bits whether it is handed over or computed again
 bool fold_fwd(int parts, int d) { return !narrow_apply(d) && fold(parts, d); }
 
+unsigned heads_of(const lf::Layout& l) { return (unsigned)l.H | (unsigned)l.H << 16; }   // lf::HeadAt
+
 template <int D, int FM>
-int launch_reduce(const void* k, lf::Layout lk, const void* v, lf::Layout lv, float* partials, long long N,
+int launch_reduce(const void* k, const void* v, lf::Layout l, float* partials, long long N,
                   const Plan32& p, long long BH, hipStream_t st) {
   using namespace lf;
   constexpr int lds = Sum32<D>::kBytes;
@@ -39,7 +41,7 @@ int launch_reduce(const void* k, lf::Layout lk, const void* v, lf::Layout lv, fl
   const lfh::Share sh = lfh::even_share((N + Reduce32s<D>::kTokens - 1) / Reduce32s<D>::kTokens, p.splits, kWavesPerWG,
                                         p.blk_reduce / per);
   state_reduce32s<D, FM><<<dim3(p.splits, (unsigned)BH), dim3(kThreads), lds, st>>>(
-      (const float*)k, lk, (const float*)v, lv, partials, N, sh.blk);
+      (const float*)k, (const float*)v, l.batch, l.head, l.row, heads_of(l), sh.blk, N, partials);
   return LINFUSION_OK;
 }
 
@@ -54,7 +56,7 @@ int fwd(const Fwd32Args& a) {
   using namespace lf;
   const Plan32& p = a.plan;
   if (a.ev) (void)hipEventRecord(a.ev[0], a.st);
-  if (int rc = launch_reduce<D, FM>(a.k, a.lkv, a.v, a.lkv, a.partials, a.N, p, a.BH, a.st)) return rc;
+  if (int rc = launch_reduce<D, FM>(a.k, a.v, a.lkv, a.partials, a.N, p, a.BH, a.st)) return rc;
   if (a.ev) (void)hipEventRecord(a.ev[1], a.st);
   const bool folded = a.out && fold_fwd(p.splits, D);
   if (!folded) launch_combine(a.partials, p.splits, D, a.state, a.BH, a.st);
@@ -66,8 +68,8 @@ int fwd(const Fwd32Args& a) {
     constexpr int lds = consume32_lds_bytes<D, 1>();
     if (!lfh::allow_lds(apply32s<D, FM, NORM>, lds)) return LINFUSION_ERR_HIP;
     apply32s<D, FM, NORM><<<dim3(p.apply_wgs, (unsigned)a.BH), dim3(kThreads), lds, a.st>>>(
-        (const f32x4*)a.q, a.lq, (f32x4*)a.out, a.lo, folded ? a.partials : a.state, folded ? p.splits : 1,
-        folded ? a.state : nullptr, a.eps, a.N, p.blk_apply);
+        (const f32x4*)a.q, a.lq.batch, a.lq.head, a.lq.row, heads_of(a.lq), p.blk_apply, a.N, folded ? a.partials : a.state,
+        folded ? p.splits : 1, a.eps, folded ? a.state : nullptr, (f32x4*)a.out, a.lo.batch, a.lo.head, a.lo.row);
   }
   if (a.ev) (void)hipEventRecord(a.ev[3], a.st);
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
@@ -104,7 +106,7 @@ int bwd(const Bwd32Args& a, const Regions& r) {
   int parts = 1;
   if (!state) {
     float* fpart = reinterpret_cast<float*>(a.ws + r.fpart);
-    if (int rc = launch_reduce<D, FM>(a.k, a.lkv, a.v, a.lkv, fpart, a.N, p, BH, a.st)) return rc;
+    if (int rc = launch_reduce<D, FM>(a.k, a.v, a.lkv, fpart, a.N, p, BH, a.st)) return rc;
     if (fold_fwd(p.splits, D)) {
       state = fpart;
       parts = p.splits;

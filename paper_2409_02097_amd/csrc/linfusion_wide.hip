@@ -27,7 +27,6 @@ int reduce(const WideReduceArgs& a, hipEvent_t* ev, bool combine) {
   const dim3 blk(kThreads);
   const u32x4* K = (const u32x4*)a.k;
   const u32x4* V = (const u32x4*)a.v;
-  const HeadSubset all{0, a.H};
   hipStream_t st = a.st;
   constexpr int lds1 = reduce16_wide_lds_bytes<T, D>();
   const dim3 g1(a.plan.splits, (unsigned)BH);
@@ -38,7 +37,7 @@ int reduce(const WideReduceArgs& a, hipEvent_t* ev, bool combine) {
 #define LFW_REDUCE(FM)                                                                       \
   {                                                                                          \
     if (!allow_lds(state_reduce16_wide<T, D, FM>, lds1)) return LINFUSION_ERR_HIP;           \
-    state_reduce16_wide<T, D, FM><<<g1, blk, lds1, st>>>(K, a.lk, V, a.lv, all, part, a.N, a.plan.blk_reduce); \
+    state_reduce16_wide<T, D, FM><<<g1, blk, lds1, st>>>(K, a.lk, V, a.lv, part, a.N, a.plan.blk_reduce); \
   }
   switch (a.fm) {
     case 0: LFW_REDUCE(0) break;
@@ -63,7 +62,7 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
   const dim3 blk(kThreads);
   const u32x4* Q = (const u32x4*)a.q;
   u32x4* O = (u32x4*)a.out;
-  const HeadSubset all{0, a.H};
+  const unsigned all = (unsigned)a.H | (unsigned)a.H << 16;   // HeadAt
   hipStream_t st = a.st;
   const dim3 g2(a.plan.apply_wgs, (unsigned)BH);
 #define LFW_APPLY_W(FM, NORM, WW)                                                                            \
@@ -72,7 +71,7 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
     if (!allow_lds(apply16_wide<T, D, FM, NORM, WW>, lds2)) return LINFUSION_ERR_HIP;                        \
     pack_state_wide<T, D, WW><<<dim3(ApplyWideShape<D, WW>::kKS, (unsigned)BH), dim3(64 * WW), 0, st>>>(     \
         a.state, a.packed, NORM ? 1 : 0);                                                                    \
-    apply16_wide<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), lds2, st>>>(Q, a.lq, O, a.lo, all, a.packed, a.eps, \
+    apply16_wide<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), lds2, st>>>(Q, a.lq, O, a.lo, a.packed, a.eps, \
                                                                       a.N, a.plan.blk_apply);                \
   }
 #define LFW_APPLY_WAVE(FM, NORM)                                                                             \
@@ -81,8 +80,9 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
     if (!allow_lds(apply16_wave<T, D, FM, NORM>, lds2)) return LINFUSION_ERR_HIP;                            \
     if (parts > 0) launch_pack_wave<D>(a.state, parts, keep, a.packed, NORM, (unsigned)BH, st);              \
     if (ev) (void)hipEventRecord(*ev, st);                                                                   \
-    apply16_wave<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq, O, a.lo, all, a.packed, a.eps, a.N,         \
-                                                        a.plan.blk_apply);                                   \
+    apply16_wave<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq.batch, a.lq.head, a.lq.row, all,              \
+                                                        a.plan.blk_apply, a.N, a.packed, a.eps, O, a.lo.batch, \
+                                                        a.lo.head, a.lo.row);                                \
   } else {                                                                                                   \
     return LINFUSION_ERR_UNSUPPORTED;                                                                        \
   }
@@ -112,8 +112,9 @@ int run_short(const WideArgs& a) {
   {                                                                                                               \
     if (!allow_lds(short16<T, D, CB, FM, NORM>, C::kLdsBytes)) return LINFUSION_ERR_HIP;                              \
     short16<T, D, CB, FM, NORM><<<grid, dim3(C::kThreads), C::kLdsBytes, a.st>>>(                                     \
-        (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (const u32x4*)a.q, a.lq, (u32x4*)a.out, a.lo, a.state, a.eps, \
-        (int)a.N, parts);                                                                                          \
+        (const u32x4*)a.k, (const u32x4*)a.v, a.lkv.batch, a.lkv.head, a.lkv.row,                                 \
+        (unsigned)a.H | (unsigned)a.H << 16, (int)a.N, parts, (const u32x4*)a.q, a.lq.batch, a.lq.head, \
+        a.lq.row, a.eps, a.state, (u32x4*)a.out, a.lo.batch, a.lo.head, a.lo.row);                                \
   }
   switch (a.fm) {
     case 0: if (a.unnorm) LFW_SHORT(0, false) else LFW_SHORT(0, true) break;
