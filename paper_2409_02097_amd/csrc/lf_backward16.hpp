@@ -32,6 +32,65 @@ LF_DEV float phi_prime_from(float x, float phi_x) {   // d phi / dx given x and 
   else return 1.0f;
 }
 
+// A head's fp32 state in LDS, for operands in both orientations: the matrix in rows of kRow floats (the padding spreads the
+// lanes of an operand read, one row each, over the bank groups), then the vector, then a word per wave.
+template <int D> struct StageBwd {
+  static constexpr int kRow = D + 4, kVec = D * kRow;
+  static constexpr int kBytes = (kVec + D) * 4 + 64;
+  // element group e (of four) of the state as it lies in memory
+  static __device__ __forceinline__ int place(int e) {
+    return e < D * D / 4 ? (4 * e) / D * kRow + (4 * e) % D : kVec + 4 * e - D * D;
+  }
+};
+// A operands of the staged matrix M scaled by aS, for products  out[o] = sum_c M'[.][.] b[c]  over the contraction index c =
+// input channel of the B operand and o = this lane-half's output channels:
+//   TRANSPOSED = false: element M[o][c]   (out = M b);   TRANSPOSED = true: element M[c][o]  (out = M^T b)
+// A tile's values are read before the first is used, from clamped and valid places: with a test around every read they were
+// some hundred LDS round trips one after the other (forward and backward of bf16 12 x 8 x 4096 x 40 token-major 128.0 -> 125.1
+// us).
+template <typename T, int D, bool TRANSPOSED, int NS, int MTB, int KS>
+LF_DEV void operands_bwd(const float* st, int lane, float aS, u32x4 (&A)[NS][MTB][KS]) {
+  constexpr int HALF = D / 2, CPR = D / 8, SS = StageBwd<D>::kRow;
+  const int m = lane & 31, kg = lane >> 5, hv = (m >> 2) & 1;
+#pragma unroll
+  for (int t = 0; t < MTB; ++t) {
+    const int slot = 16 * t + 4 * (m >> 3) + (m & 3);
+    const int o = hv * HALF + (slot < HALF ? slot : 0);
+    float raw[KS][8];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int c0 = (kg * KS + s < CPR ? kg * KS + s : 0) * 8;
+      if constexpr (TRANSPOSED) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) raw[s][j] = st[(c0 + j) * SS + o];
+      } else {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(st + o * SS + c0);
+        const f32x4 b = *reinterpret_cast<const f32x4*>(st + o * SS + c0 + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { raw[s][j] = a[j]; raw[s][4 + j] = b[j]; }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bool used = kg * KS + s < CPR && slot < HALF;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        float hi2[2], lo2[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float x = used ? raw[s][2 * w + q] * aS : 0.0f;
+          float r0, r1;
+          unpack2<T>(pack2<T>(x, 0.0f), r0, r1);
+          hi2[q] = x;
+          lo2[q] = x - r0;
+        }
+        A[0][t][s][w] = pack2<T>(hi2[0], hi2[1]);
+        if constexpr (NS == 2) A[1][t][s][w] = pack2<T>(lo2[0], lo2[1]);
+      }
+    }
+  }
+}
+
 // RING: slots of the per-wave ring (RING - 1 tiles in flight); three where two workgroups share a CU
 template <int D, int RING = 3> struct BwdCfg {
   using Sh = Shape16<D>;
@@ -41,7 +100,7 @@ template <int D, int RING = 3> struct BwdCfg {
   static constexpr int kSlotBytes = 2 * kTileBytes;              // two tensors per ring slot
   static constexpr int kRing = RING;
   static constexpr int kStageOffset = (kRing - 1) * kWavesPerWG * kSlotBytes;
-  static constexpr int kStageBytes = (D * D + D) * 4 + 64;
+  static constexpr int kStageBytes = StageBwd<D>::kBytes;
   static constexpr int kMTB = (Sh::kHalf + 15) / 16;            // 32-row output tiles (no normalizer rows)
   static constexpr int lds_bytes() {
     int ring = kRing * kWavesPerWG * kSlotBytes, st = kStageOffset + kStageBytes;
@@ -163,11 +222,11 @@ struct Ring2 {
   // for the matrix.  The staging area starts at the third slot block (free before the stream loop).
   LF_DEV float stage_state(const float* state) {
     float* st = reinterpret_cast<float*>(smem + BC::kStageOffset);
-    float* redmax = st + NE;
+    float* redmax = st + StageBwd<D>::kVec + D;
     float mS = 0.0f;
     for (int e = threadIdx.x; e < NE / 4; e += kThreads) {
       const f32x4 x = reinterpret_cast<const f32x4*>(state)[e];
-      reinterpret_cast<f32x4*>(st)[e] = x;
+      *reinterpret_cast<f32x4*>(st + StageBwd<D>::place(e)) = x;
       if (e < D * D / 4) mS = fmaxf(mS, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
     }
 #pragma unroll
@@ -179,43 +238,13 @@ struct Ring2 {
     for (int w = 0; w < kWavesPerWG; ++w) mS = fmaxf(mS, redmax[w]);
     return pow2_scale_for(mS);
   }
-  // A operands of the staged matrix M scaled by aS, for products  out[o] = sum_c M'[.][.] b[c]  over the
-  // contraction index c = input channel of the B operand and o = this lane-half's output channels:
-  //   TRANSPOSED = false: element M[o][c]   (out = M b);   TRANSPOSED = true: element M[c][o]  (out = M^T b)
   template <bool TRANSPOSED>
   LF_DEV void build_A(float aS, u32x4 (&A)[NS][MTB][KS]) const {
-    const float* st = reinterpret_cast<const float*>(smem + BC::kStageOffset);
-    const int m = lane & 31;
-    const int hv = (m >> 2) & 1;
-#pragma unroll
-    for (int t = 0; t < MTB; ++t) {
-      const int slot = 16 * t + 4 * (m >> 3) + (m & 3);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const int chunk = kg * KS + s;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          float hi2[2], lo2[2];
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int c = chunk * 8 + 2 * w + q;
-            const int o = hv * HALF + slot;
-            float x = 0.0f;
-            if (chunk < CPR && slot < HALF) x = (TRANSPOSED ? st[c * D + o] : st[o * D + c]) * aS;
-            float r0, r1;
-            unpack2<T>(pack2<T>(x, 0.0f), r0, r1);
-            hi2[q] = x;
-            lo2[q] = x - r0;
-          }
-          A[0][t][s][w] = pack2<T>(hi2[0], hi2[1]);
-          if constexpr (NS == 2) A[1][t][s][w] = pack2<T>(lo2[0], lo2[1]);
-        }
-      }
-    }
+    operands_bwd<T, D, TRANSPOSED>(reinterpret_cast<const float*>(smem + BC::kStageOffset), lane, aS, A);
   }
   // the staged vector at this lane-half's output channels
   LF_DEV void load_vec(float (&v)[HALF]) const {
-    const float* st = reinterpret_cast<const float*>(smem + BC::kStageOffset) + D * D;
+    const float* st = reinterpret_cast<const float*>(smem + BC::kStageOffset) + StageBwd<D>::kVec;
 #pragma unroll
     for (int i = 0; i < HALF; ++i) v[i] = st[kg * HALF + i];
   }
@@ -412,7 +441,7 @@ bwd_qs16(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G, La
   if constexpr (NS == 1) {
     rg.load_vec(zo);
   } else {
-    const float* z = reinterpret_cast<const float*>(smem + BC::kStageOffset) + D * D;
+    const float* z = reinterpret_cast<const float*>(smem + BC::kStageOffset) + StageBwd<D>::kVec;
     for (int i = threadIdx.x; i < D; i += kThreads) zlds[i] = z[i];
   }
   auto zv = [&](int i) -> float {
@@ -422,7 +451,7 @@ bwd_qs16(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G, La
   const float inv_aS = 1.0f / aS;
   float beta = 1.0f, inv_beta = 1.0f;
   if constexpr (NORM) {   // power of two near the typical denominator (see bwd_state16)
-    const float* z = reinterpret_cast<const float*>(smem + BC::kStageOffset) + D * D;
+    const float* z = reinterpret_cast<const float*>(smem + BC::kStageOffset) + StageBwd<D>::kVec;
     float zs = 0.0f;
     for (int i = 0; i < D; ++i) zs += z[i];
     if (zs > 0.0f && zs < 3.0e38f) {
@@ -794,7 +823,7 @@ bwd_pack_kv16(const float* __restrict__ dstate, unsigned char* __restrict__ pack
           frag[((l * MTB + t) * KS + s) * 64 + rg.lane] = A1[l][t][s];
           frag[(PK::kFrags + (l * MTB + t) * KS + s) * 64 + rg.lane] = A2[l][t][s];
         }
-    const float* st = reinterpret_cast<const float*>(smem + BwdCfg<D>::kStageOffset) + D * D;
+    const float* st = reinterpret_cast<const float*>(smem + BwdCfg<D>::kStageOffset) + StageBwd<D>::kVec;
     float* dz = reinterpret_cast<float*>(dst + PK::kDzOffset);
     for (int i = rg.lane; i < D; i += 64) dz[i] = st[i];
     if (rg.lane == 0) *reinterpret_cast<float*>(dst) = 1.0f / aS;

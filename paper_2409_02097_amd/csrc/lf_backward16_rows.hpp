@@ -25,7 +25,7 @@ template <int D, int W, int RING = 3> struct BwdRowsCfg {
   static constexpr int kSlotBytes = 2 * kTileBytes;
   static constexpr int kRing = RING;
   static constexpr int kStageOffset = (kRing - 1) * kSlotBytes; // last slot: free before the stream loop
-  static constexpr int kStageBytes = (D * D + D) * 4 + 64;
+  static constexpr int kStageBytes = StageBwd<D>::kBytes;
   static constexpr int kG = (kPC % 16 == 0) ? 16 : ((kPC % 8 == 0) ? 8 : 4);
   static_assert(kTile % W == 0 && kPC % 4 == 0 && kRPR * kG >= 16, "rotation classes must fit a region");
   static_assert(kRegionChunks % 32 == 0, "a region is whole half-waves of chunks");
@@ -152,9 +152,18 @@ struct Ring2Rows {
   LF_DEV float stage_state_own(const float* state) {
     float* st = reinterpret_cast<float*>(smem + C::kSlotBytes + wave * C::kOwnBytes);
     float mS = 0.0f;
-    for (int e = lane; e < NE / 4; e += 64) {
-      const f32x4 x = reinterpret_cast<const f32x4*>(state)[e];
-      reinterpret_cast<f32x4*>(st)[e] = x;
+    constexpr int PER = (NE / 4 + 63) / 64;
+    f32x4 v[PER];   // (all loads are issued before the first is used)
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = lane + 64 * i;
+      v[i] = reinterpret_cast<const f32x4*>(state)[e < NE / 4 ? e : 0];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = lane + 64 * i;
+      const f32x4 x = v[i];
+      if (e < NE / 4) *reinterpret_cast<f32x4*>(st + StageBwd<D>::place(e)) = x;
       if (e < D * D / 4) mS = fmaxf(mS, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
     }
 #pragma unroll
@@ -183,11 +192,11 @@ struct Ring2Rows {
   // the power-of-two scale for the matrix.
   LF_DEV float stage_state(const float* state) {
     float* st = reinterpret_cast<float*>(smem + C::kStageOffset);
-    float* redmax = st + NE;
+    float* redmax = st + StageBwd<D>::kVec + D;
     float mS = 0.0f;
     for (int e = threadIdx.x; e < NE / 4; e += 64 * W) {
       const f32x4 x = reinterpret_cast<const f32x4*>(state)[e];
-      reinterpret_cast<f32x4*>(st)[e] = x;
+      *reinterpret_cast<f32x4*>(st + StageBwd<D>::place(e)) = x;
       if (e < D * D / 4) mS = fmaxf(mS, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
     }
 #pragma unroll
@@ -199,40 +208,12 @@ struct Ring2Rows {
     for (int w = 0; w < W; ++w) mS = fmaxf(mS, redmax[w]);
     return pow2_scale_for(mS);
   }
-  // A operands of the staged matrix (see Ring2::build_A)
   template <bool TRANSPOSED>
   LF_DEV void build_A(float aS, u32x4 (&A)[NS][MTB][KS]) const {
-    const float* st = stage;
-    const int m = lane & 31;
-    const int hv = (m >> 2) & 1;
-#pragma unroll
-    for (int t = 0; t < MTB; ++t) {
-      const int slot = 16 * t + 4 * (m >> 3) + (m & 3);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const int chunk = kg * KS + s;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          float hi2[2], lo2[2];
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int c = chunk * 8 + 2 * w + q;
-            const int o = hv * HALF + slot;
-            float x = 0.0f;
-            if (chunk < CPR && slot < HALF) x = (TRANSPOSED ? st[c * D + o] : st[o * D + c]) * aS;
-            float r0, r1;
-            unpack2<T>(pack2<T>(x, 0.0f), r0, r1);
-            hi2[q] = x;
-            lo2[q] = x - r0;
-          }
-          A[0][t][s][w] = pack2<T>(hi2[0], hi2[1]);
-          if constexpr (NS == 2) A[1][t][s][w] = pack2<T>(lo2[0], lo2[1]);
-        }
-      }
-    }
+    operands_bwd<T, D, TRANSPOSED>(stage, lane, aS, A);
   }
   LF_DEV void load_vec(float (&v)[HALF]) const {
-    const float* st = stage + D * D;
+    const float* st = stage + StageBwd<D>::kVec;
 #pragma unroll
     for (int i = 0; i < HALF; ++i) v[i] = st[kg * HALF + i];
   }
@@ -519,11 +500,11 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
     if constexpr (NS == 1) {
       rg.load_vec(zo);
     } else {
-      for (int i = rg.lane; i < D; i += 64) zlds[i] = rg.stage[D * D + i];
+      for (int i = rg.lane; i < D; i += 64) zlds[i] = rg.stage[StageBwd<D>::kVec + i];
     }
     inv_aS = 1.0f / aS;
     if constexpr (NORM) {   // power of two near the typical denominator (see bwd_state16)
-      const float* z = rg.stage + D * D;
+      const float* z = rg.stage + StageBwd<D>::kVec;
       float zs = 0.0f;
       for (int i = 0; i < D; ++i) zs += z[i];
       if (zs > 0.0f && zs < 3.0e38f) {
