@@ -28,13 +28,23 @@ size_t span_bytes(const long long s[3], int B, int H, long long N, int d, size_t
 // us per call, blocks of 16 or 8 tiles whatever the number -> these: bf16 2 x 10 x 16384 x 64 54.0 -> 48.0, fp16 8 x 100000 x
 // 40 60.1 -> 55.8, 20 x 65536 x 64 130.2 -> 124.2, fp32 forward and backward 12 x 8 x 4096 x 40 192.4 -> 183.1; fewest
 // workgroups: fp16 2 x 5 x 9216 x 64 24.0 -> 23.2, fp32 2 x 10 x 16384 x 64 83.9 -> 82.7.
+// `shared_lines`: a head's rows (of a group of heads: its pieces of a row) are no whole 128-byte lines, so that in a
+// token-major tensor neighbouring heads share lines.  Workgroups are dealt to the eight XCDs in turn; with 1, 2, 4 or a multiple of eight
+// workgroups per head, where the same rounds allow it, the workgroups that walk the same tokens of all, every fourth or every
+// second head share an XCD and its L2 (forward and backward of fp16 2 x 10 x 13056 x 16 token-major: 24 workgroups 73 us, 21
+// 80 us; of bf16 12 x 10 x 1094 x 8: 4 workgroups 41.5 us, 3 45.5 us).
 struct Share { int wgs, blk; };   // blk: in tiles, whole rounds
-inline Share even_share(long long n_tiles, long long most, int waves, int blk) {
+inline Share even_share(long long n_tiles, long long most, int waves, int blk, bool shared_lines = false) {
   const long long rounds = (n_tiles + waves - 1) / waves;
   long long s = most < rounds ? most : rounds;
   if (s < 1) s = 1;
   const long long longest = (rounds + s - 1) / s;
+  const long long room = s;
   s = (rounds + longest - 1) / longest;
+  if (shared_lines) {
+    const long long even = s <= 2 ? s : (s <= 4 ? 4 : (s + 7) / 8 * 8);
+    if (even <= room) s = even;
+  }
   long long b = blk / waves;   // rounds per block
   if (b > longest) b = longest;
   if (b < 1) b = 1;

@@ -240,7 +240,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   const size_t esz = dtype == LINFUSION_DTYPE_F32 ? 4 : 2;
   auto per_head = [&](int want_total, const char* env_blk, int blk_dflt, int* blk, int waves = lf::kWavesPerWG) {
     // (rounded down: one workgroup too many costs a whole extra round)
-    const lfh::Share sh = even_share(p->n_tiles, want_total / BH, waves, env_int(env_blk, blk_dflt));
+    const lfh::Share sh = even_share(p->n_tiles, want_total / BH, waves, env_int(env_blk, blk_dflt), d * esz % 128 != 0);
     *blk = sh.blk;
     return sh.wgs;
   };
@@ -310,7 +310,8 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   p->groups = compact ? 0 : B * (H / p->gwaves);   // (compact: contiguous tensors only, whose heads are never neighbours)
   if (p->groups > 0) {
     auto per_group = [&](int want_total, const char* env_blk, int blk_dflt, int* blk) {
-      const lfh::Share sh = even_share(p->n_tiles, want_total / p->groups, 1, env_int(env_blk, blk_dflt));
+      const lfh::Share sh = even_share(p->n_tiles, want_total / p->groups, 1, env_int(env_blk, blk_dflt),
+                                       p->gwaves * d * esz % 128 != 0);
       *blk = sh.blk;
       return sh.wgs;
     };

@@ -369,10 +369,14 @@ def test_strided_backward_validates_on_the_host():
 @pytest.mark.parametrize("BH,N,d,dtype", [((2, 10), 16384, 64, 2), ((2, 5), 9216, 64, 1), ((1, 8), 100000, 40, 1),
                                           ((12, 8), 4096, 40, 0), ((1, 3), 33, 40, 1), ((1, 1), 127 * 32, 64, 1)])
 def test_as_few_workgroups_as_keep_the_longest_wave(BH, N, d, dtype):
-    """A head's tiles in rounds of four: no more workgroups than the number of rounds of the longest one calls for, and
-    no more rounds than two workgroups per CU need (256 while no device is visible)."""
+    """A head's tiles in rounds of four: no more workgroups than the number of rounds of the longest one calls for (or the
+    next of 1, 2, 4, 8, 16, 24 and so on, where head rows are no whole cache lines), and no more rounds than two workgroups per CU need
+    (256 while no device is visible)."""
     B, H = BH
     plan = lf.linfusion_attn_plan(B, H, N, d, dtype, lf.FLAG_FORCE_SPLIT)
     rounds = -(-N // (4 * plan["tile_tokens"]))
     most = max(1, min(512 // (B * H), rounds))
-    assert plan["reduce_wgs_per_head"] == -(-rounds // -(-rounds // most))
+    least = -(-rounds // -(-rounds // most))
+    even = least if least <= 2 else 4 if least <= 4 else -(-least // 8) * 8
+    lines = d * (4 if dtype == 0 else 2) % 128 == 0
+    assert plan["reduce_wgs_per_head"] == (least if lines or even > most else even)
