@@ -1,7 +1,7 @@
 // Apply + normalize for fp16 / bf16 with asynchronous global->LDS tile loads.
 //   out_i = phi(q_i) S / (phi(q_i).z + eps)                     (Eq. 5 normalizer on Prop. 2's form)
 //
-// grid = (wgs_per_head, B*H), block = 256, dynamic LDS.
+// grid = (wgs_per_head, B*H), block = 256 or 512, dynamic LDS.
 //
 // Prologue (once per workgroup): the head's fp32 state is staged in LDS, rescaled by powers of
 // two so that 16-bit storage neither overflows nor loses small entries (S' = alpha_S S,
@@ -807,15 +807,16 @@ struct ApplyDma {
 };
 
 // state: [B*H][parts][D*D + D]; the sum of more than one partial goes to keep ([B*H][D*D + D]) as well.
-template <typename T, int D, int FM, bool NORM>
-__global__ void __launch_bounds__(kThreads)
+// WPW: waves per workgroup, 4 or 8 (a state is staged half as often; see the plan's apply_waves).
+template <typename T, int D, int FM, bool NORM, int WPW>
+__global__ void __launch_bounds__(64 * WPW)
 apply16_dma(const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, unsigned heads, int tiles_per_block,
             long long N, const float* __restrict__ state, int parts, float eps, float* __restrict__ keep,
             u32x4* __restrict__ O, long long obatch, long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const HeadAt at(blockIdx.y, heads);
-  ApplyDma<T, D, FM, NORM> ap(Q + at.slice(qbatch, qhead), qrow, O + at.slice(obatch, ohead), orow, N, tiles_per_block,
-                              blockIdx.x, gridDim.x, smem);
+  ApplyDma<T, D, FM, NORM, 0, false, D, false, WPW> ap(Q + at.slice(qbatch, qhead), qrow, O + at.slice(obatch, ohead), orow,
+                                                       N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   ap.prefetch();
   constexpr int NE = D * D + D;
   const long long bh = at.index;

@@ -84,7 +84,7 @@ struct Plan {
   // row-piece kernels (heads adjacent in memory): whole groups of gwaves (8 if H % 8 == 0, else 4)
   // heads, one wave per head; workgroups per group
   int gwaves, groups, gsplits, gblk_reduce, gapply_wgs, gblk_apply;
-  int apply_waves;      // waves per workgroup of the packed per-head apply (1, 2 or 4)
+  int apply_waves;      // waves per workgroup of the per-head apply (packed: 1, 2 or 4; else 4 or 8)
   bool wave_apply;      // widths above 80: apply16_wave (a wave per tile) instead of apply16_wide
   int short_parts;      // widths above 80: > 0, one launch of so many workgroups per 32 value channels of a head (short16),
   bool short_half;      //   or per half of the channels
@@ -297,6 +297,24 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   }
   p->apply_wgs = per_head(env_int("LINFUSION_APPLY_WGS", apply_want), "LINFUSION_APPLY_BLK", blk_dflt, &p->blk_apply,
                           p->apply_waves);
+  // Where a CU has two workgroups of four waves or more, workgroups of eight: the state is staged, and made into operands, half
+  // as often (us per call, four waves -> eight: fp16 2 x 8 x 16384 x 40 24.7 -> 24.1, bf16 29.5 -> 27.7, 1 x 8 x 100000 x 40 54.5 ->
+  // 53.2, 6 x 16 x 2500 x 48 28.1 -> 25.9), unless that leaves some CU with more tiles, as it does where eight waves are one
+  // and a half workgroups per CU (4 x 8 x 9000 x 48 29.6 -> 32.1, bf16 1 x 10 x 50000 x 48 47.3 -> 51.3).
+  const int waves8 = env_int("LINFUSION_APPLY_WAVES", 0);   // under tuning: 4 or 8, whatever the rule
+  if (dtype != LINFUSION_DTYPE_F32 && one_round && !p->apply_packed && (waves8 == 0 || waves8 == 8)) {
+    int blk8 = 8;
+    const int wgs8 = per_head(env_int("LINFUSION_APPLY_WGS", apply_want / 2), "LINFUSION_APPLY_BLK", blk_dflt, &blk8, 8);
+    auto tiles_of_a_cu = [&](int wgs, int waves) {
+      const long long rounds = (p->n_tiles + (long long)wgs * waves - 1) / ((long long)wgs * waves);
+      return ((long long)wgs * BH + num_cu() - 1) / num_cu() * rounds * waves;
+    };
+    if (waves8 == 8 || (p->apply_wgs * BH > num_cu() && tiles_of_a_cu(wgs8, 8) <= tiles_of_a_cu(p->apply_wgs, 4))) {
+      p->apply_waves = 8;
+      p->apply_wgs = wgs8;
+      p->blk_apply = blk8;
+    }
+  }
   // fused single launch: every workgroup must be resident at once
   const long long cap = (long long)fused_wgs_per_cu(d, dtype) * num_cu();
   p->fsplits = 0;
@@ -607,13 +625,18 @@ int run16(const Args& a) {
 #undef LF_APPLY_W
       if (rest > 0) {
         const dim3 g2t(p.apply_wgs, (unsigned)(B * rest));
-#define LF_APPLY(FM, NORM)                                                               \
-  if (!allow_lds(apply16_dma<T, D, FM, NORM>, (int)lds2)) return LINFUSION_ERR_HIP;      \
-  apply16_dma<T, D, FM, NORM><<<g2t, blk, lds2, st>>>(Q + first * a.lq.head, a.lq.batch, a.lq.head, a.lq.row, tail,    \
-                                                     p.blk_apply, a.N, state + first * NE, 1, a.eps, nullptr,   \
-                                                     O + first * a.lo.head, a.lo.batch, a.lo.head, a.lo.row);
+#define LF_APPLY_W(FM, NORM, WW)                                                                  \
+  {                                                                                               \
+    constexpr int lds3 = apply16_dma_lds_bytes<T, D>(WW);                                         \
+    if (!allow_lds(apply16_dma<T, D, FM, NORM, WW>, lds3)) return LINFUSION_ERR_HIP;              \
+    apply16_dma<T, D, FM, NORM, WW><<<g2t, dim3(64 * WW), lds3, st>>>(                            \
+        Q + first * a.lq.head, a.lq.batch, a.lq.head, a.lq.row, tail, p.blk_apply, a.N, state + first * NE, 1, a.eps, \
+        nullptr, O + first * a.lo.head, a.lo.batch, a.lo.head, a.lo.row);                         \
+  }
+#define LF_APPLY(FM, NORM) if (p.apply_waves == 8) LF_APPLY_W(FM, NORM, 8) else LF_APPLY_W(FM, NORM, 4)
         LF_SWITCH_FM_NORM(LF_APPLY)
 #undef LF_APPLY
+#undef LF_APPLY_W
       }
     } else if (p.apply_packed) {
       const dim3 g2(p.apply_wgs, (unsigned)a.BH);
@@ -638,13 +661,18 @@ int run16(const Args& a) {
 #undef LF_APPLY_W
     } else {
       const dim3 g2(p.apply_wgs, (unsigned)a.BH);
-#define LF_APPLY(FM, NORM)                                                               \
-  if (!allow_lds(apply16_dma<T, D, FM, NORM>, (int)lds2)) return LINFUSION_ERR_HIP;      \
-  apply16_dma<T, D, FM, NORM><<<g2, blk, lds2, st>>>(Q, a.lq.batch, a.lq.head, a.lq.row, all, p.blk_apply, a.N,         \
-                                                    fold ? partials : state, fold ? parts : 1, a.eps,            \
-                                                    fold ? state : nullptr, O, a.lo.batch, a.lo.head, a.lo.row);
+#define LF_APPLY_W(FM, NORM, WW)                                                                  \
+  {                                                                                               \
+    constexpr int lds3 = apply16_dma_lds_bytes<T, D>(WW);                                         \
+    if (!allow_lds(apply16_dma<T, D, FM, NORM, WW>, lds3)) return LINFUSION_ERR_HIP;              \
+    apply16_dma<T, D, FM, NORM, WW><<<g2, dim3(64 * WW), lds3, st>>>(                             \
+        Q, a.lq.batch, a.lq.head, a.lq.row, all, p.blk_apply, a.N, fold ? partials : state, fold ? parts : 1, a.eps, \
+        fold ? state : nullptr, O, a.lo.batch, a.lo.head, a.lo.row);                              \
+  }
+#define LF_APPLY(FM, NORM) if (p.apply_waves == 8) LF_APPLY_W(FM, NORM, 8) else LF_APPLY_W(FM, NORM, 4)
       LF_SWITCH_FM_NORM(LF_APPLY)
 #undef LF_APPLY
+#undef LF_APPLY_W
     }
   }
   if (a.ev) (void)hipEventRecord(a.ev[3], st);

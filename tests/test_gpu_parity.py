@@ -439,3 +439,18 @@ def test_blocks_of_tiles_that_do_not_divide(N, wgs, blk, dtype, monkeypatch, tun
     q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=95, device="cpu")
     out = _run(q.cuda(), k.cuda(), v.cuda(), flags=lf.FLAG_FORCE_SPLIT)
     parity.check_all(out, q, k, v, dtype, 0, 1e-6, True, f"blocks N={N} wgs={wgs} blk={blk} {dtype}")
+
+
+@pytest.mark.parametrize("d,dtype", [(8, "f16"), (24, "bf16"), (40, "bf16"), (48, "f16"), (64, "f16"), (64, "bf16"), (80, "f16")])
+@pytest.mark.parametrize("N", [1, 33, 256, 257, 2500])
+def test_apply_in_workgroups_of_eight_waves(N, d, dtype, monkeypatch, tuning):
+    """Fewer, larger workgroups stage a head's state less often: the same bits, and the oracle's values."""
+    B, H = 1, 3
+    print(f"eight waves N={N} d={d} {dtype}", flush=True)
+    q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=96, device="cpu")
+    got = []
+    for waves in ("4", "8"):
+        monkeypatch.setenv("LINFUSION_APPLY_WAVES", waves)
+        got.append(_run(q.cuda(), k.cuda(), v.cuda(), flags=lf.FLAG_FORCE_SPLIT))
+    assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16))
+    parity.check_all(got[1], q, k, v, dtype, 0, 1e-6, True, f"eight waves N={N} d={d} {dtype}")
