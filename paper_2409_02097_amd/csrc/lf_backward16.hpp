@@ -971,7 +971,7 @@ bwd_state16(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G,
 
   int lim = 0;
   if (it.valid()) lim = issue_loads(it.t);
-  for (int i = lane; i < 2 * NS * TE; i += 64) wbase[i] = 0;   // pad columns and the unused part of the extra block
+  lds_zero(wbase, 2 * NS * TE, lane, 64);   // pad columns and the unused part of the extra block
 
   while (it.valid()) {
 #pragma unroll

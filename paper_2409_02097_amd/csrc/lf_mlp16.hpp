@@ -135,12 +135,16 @@ state_reduce16_mlp(const u32x4* __restrict__ Ak, const u32x4* __restrict__ Tk, c
   if (it.valid()) lim = issue_loads(it.t);
 
   // one-time fill: pad columns zero, ones column (index D, where a spare column exists) in the V tiles
-  for (int i = tid; i < (Cfg::kDouble ? 2 : 1) * Cfg::kBufElems; i += NT) {
-    const int tile_idx = i / TE, within = i % TE;
-    const bool is_v = tile_idx % (NS + 1) == NS;
-    lds[i] = (is_v && Sh::kSpareCol && within % RS == D) ? OneBits<T>::value : (uint16_t)0;
+  constexpr int BUFS = Cfg::kDouble ? 2 : 1;
+  static_assert(Cfg::kBufElems % 8 == 0, "whole 16-byte pieces");
+  lds_zero(lds, BUFS * Cfg::kBufElems, tid, NT);
+  lds_barrier();   // (and whatever else was staged in LDS is in place)
+  if constexpr (Sh::kSpareCol) {
+    for (int i = tid; i < BUFS * W * kTile; i += NT) {
+      const int row = i % kTile, head = i / kTile % W, buf = i / (kTile * W);
+      lds[buf * Cfg::kBufElems + head * Cfg::kHeadElems + NS * TE + row * RS + D] = OneBits<T>::value;
+    }
   }
-  __syncthreads();
 
   int buf = 0;
   while (it.valid()) {

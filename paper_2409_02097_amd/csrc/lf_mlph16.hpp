@@ -160,12 +160,13 @@ state_reduce16_mlph(const u32x4* __restrict__ Ak, const u32x4* __restrict__ Tk, 
 
   int lim = 0;
   if (it.valid()) lim = issue_loads(it.t);
-  for (int i = lane; i < Cfg::kTileElems; i += 64) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) ldsP[s][i] = 0;
-    ldsV[i] = (Sh::kSpareCol && (i % RS) == D) ? OneBits<T>::value : (uint16_t)0;
+  for (int s = 0; s < NS; ++s) lds_zero(ldsP[s], Cfg::kTileElems, lane, 64);
+  lds_zero(ldsV, Cfg::kTileElems, lane, 64);
+  if constexpr (Sh::kSpareCol) {   // (a wave's LDS operations complete in order: the ones land on the zeros)
+    if (lane < kTile) ldsV[lane * RS + D] = OneBits<T>::value;
   }
-  __syncthreads();   // the head's affine is in place
+  lds_barrier();   // the head's affine is in place
 
   while (it.valid()) {
 #pragma unroll

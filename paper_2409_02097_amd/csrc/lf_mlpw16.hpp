@@ -89,7 +89,7 @@ state_reduce16_wide_mlp(const u32x4* __restrict__ Ak, const u32x4* __restrict__ 
 
   int lim = 0;
   if (it.valid()) lim = issue_loads(it.t);
-  for (int i = tid; i < 2 * BUF; i += kThreads) lds[i] = 0;   // pad columns stay zero
+  lds_zero(lds, 2 * BUF, tid, kThreads);   // pad columns stay zero
   for (int i = tid; i < 2 * D; i += kThreads) aff[i] = i < D ? gamma[h * D + i] : beta[h * D + i - D];
   __syncthreads();
 

@@ -95,12 +95,12 @@ state_reduce16_qv(const u32x4* __restrict__ K, const u32x4* __restrict__ V, floa
   if (it.valid()) lim = issue_loads(it.t);
 
   // one-time fill: pad columns zero; the ones column at index DV of the V tile (when a spare column exists)
-  for (int i = lane; i < CK::kTileElems; i += 64) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) ldsP[s][i] = 0;
+  for (int s = 0; s < NS; ++s) lds_zero(ldsP[s], CK::kTileElems, lane, 64);
+  lds_zero(ldsV, CV::kTileElems, lane, 64);
+  if constexpr (ShV::kSpareCol) {   // (a wave's LDS operations complete in order: the ones land on the zeros)
+    if (lane < kTile) ldsV[lane * RSV + DV] = OneBits<T>::value;
   }
-  for (int i = lane; i < CV::kTileElems; i += 64)
-    ldsV[i] = (ShV::kSpareCol && (i % RSV) == DV) ? OneBits<T>::value : (uint16_t)0;
 
   while (it.valid()) {
 #pragma unroll

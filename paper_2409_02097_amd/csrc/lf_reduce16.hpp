@@ -420,13 +420,20 @@ state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, lo
     return lim;
   };
 
-  // one-time fill: pad columns zero, ones column (index D, where a spare column exists) in the V tiles
-  for (int i = tid; i < (Cfg::kDouble ? 2 : 1) * Cfg::kBufElems; i += NT) {
-    const int tile_idx = i / TE, within = i % TE;
-    const bool is_v = tile_idx % (NS + 1) == NS;
-    lds[i] = (is_v && Sh::kSpareCol && within % RS == D) ? OneBits<T>::value : (uint16_t)0;
-  }
-  __syncthreads();
+  // One-time fill, under the latency of the first loads: pad columns zero, ones column (index D, where a spare column exists)
+  // in the V tiles.
+  auto fill_tiles = [&]() {
+    constexpr int BUFS = Cfg::kDouble ? 2 : 1;
+    static_assert(Cfg::kBufElems % 8 == 0, "whole 16-byte pieces");
+    lds_zero(lds, BUFS * Cfg::kBufElems, tid, NT);
+    lds_barrier();
+    if constexpr (Sh::kSpareCol) {
+      for (int i = tid; i < BUFS * W * kTile; i += NT) {
+        const int row = i % kTile, head = i / kTile % W, buf = i / (kTile * W);
+        lds[buf * Cfg::kBufElems + head * Cfg::kHeadElems + NS * TE + row * RS + D] = OneBits<T>::value;
+      }
+    }
+  };
 
   // fp16 with elu+1: a head whose keys are all far below zero is summed a second time relative to its largest
   // key (see reduce16_phase).  Here the waves of a workgroup move in step, so the workgroup decides together;
@@ -454,6 +461,7 @@ state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, lo
     int lim = 0;
     long long tokens = 0;
     if (it.valid()) lim = issue_loads(it.t);
+    if (!shifted) fill_tiles();
     int buf = 0;
     while (it.valid()) {
       tokens += lim;
