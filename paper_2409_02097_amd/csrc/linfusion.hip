@@ -834,6 +834,23 @@ lf::Layout device_layout(const Strides& s, int H, size_t esz) {
   return lf::Layout{s.b / vec, s.h / vec, (int)(s.n / vec), H};
 }
 
+// MB of tensor traffic (q, k, v and out together) from which the row-piece kernels are picked.  A lone head's rows
+// leave part of every 128-byte line to its neighbours, which the L2 makes good while a token's heads run side by side;
+// the row pieces need no such luck, but start later (a group's prologue) and at d = 56 and 80 move four heads per
+// workgroup.  Measured on token-major tensors, per-head time over row-piece time at MB per tensor:
+//   d = 8, 16, 24         5.5 MB 0.93 to 1.03, 10 MB 1.17 to 1.31
+//   d = 32 (half lines)   7 MB 0.83, 15 MB 0.87 to 0.89, 30 MB 1.03 to 1.08
+//   d = 40, 48            eight heads and more: 7 MB 0.97 to 1.09, 15 MB 1.01 to 1.17, 30 MB 1.3 to 1.5;
+//                         four heads: 7 MB 0.94 to 0.96, 15 MB 0.93 to 1.03, 30 MB 1.02 to 1.18
+//   d = 56                7 MB 0.73 to 0.76, 15 MB 0.89 to 0.99, 30 MB 1.06 to 1.15
+//   d = 80                7 MB 0.77 to 0.90, 15 MB 0.75 to 0.88, 30 MB 0.77 to 1.01, 60 MB 0.96 to 1.24,
+//                         120 MB 1.16 to 1.18
+constexpr int group_min_mb(int d, int heads) {
+  if (d <= 24) return 24;
+  if (d == 40 || d == 48) return heads >= 8 ? 24 : 80;
+  return d <= 56 ? 80 : 240;
+}
+
 // `sq`, `skv`, `so`: strides of q, of k and v, and of out; null = contiguous [B, H, N, d]
 int fwd_impl(const void* q, const void* k, const void* v, void* out, int B, int H, long long N, int d, int dtype,
              int feature_map, float eps, unsigned flags, void* workspace, size_t workspace_bytes, void* stream,
@@ -872,11 +889,9 @@ int fwd_impl(const void* q, const void* k, const void* v, void* out, int B, int 
   // single heads would touch as scattered fragments.  (Not used by the single-launch kernel, so a
   // forced single launch keeps the one-head-per-workgroup mapping.)
   auto heads_adjacent = [&](const Strides& s) { return p.groups > 0 && s.h == d && s.n > d; };
-  // Measured (token-major, d = 40): from about 40 MB of tensor traffic up the row-piece kernels match the
-  // contiguous layout's speed and the per-head kernels fall behind (2x at 170 MB, 3x at 2.7 GB); below
-  // about 20 MB the per-head kernels' shorter start wins.
+  // From which size on depends on how much of a line a lone head wastes (see group_min_mb).
   const double tensor_bytes = 4.0 * (double)B * H * (double)N * d * (double)esz;
-  const bool big = tensor_bytes >= (double)env_int("LINFUSION_GROUP_MIN_MB", 24) * 1048576.0;
+  const bool big = tensor_bytes >= (double)env_int("LINFUSION_GROUP_MIN_MB", group_min_mb(d, H)) * 1048576.0;
   const int group_mode = env_int("LINFUSION_HEAD_GROUPS", 1);   // 1 = by size, 2 = never, 3 = whenever possible
   const bool frag = (group_mode == 3 || (group_mode == 1 && big)) && dtype != LINFUSION_DTYPE_F32 &&
                     (d * esz) % 128 != 0 && !(flags & LINFUSION_FLAG_FORCE_FUSED);

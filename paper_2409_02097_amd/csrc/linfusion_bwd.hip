@@ -121,10 +121,29 @@ struct BwdArgs {
 };
 
 // The row-piece kernels run one workgroup of W waves per group and tile, with a longer prologue than the per-head
-// kernels: measured token-major, fp16 8 x 40, per-head / row-piece: 5 MB per tensor 43 / 50 us, 21 MB 106 / 102 us,
-// 84 MB 408 / 322 us, 1.3 GB 7.0 / 2.6 ms.  They are picked from 24 MB up.
-inline bool rows_pay(const BwdArgs& a, int d) {
-  return (double)a.B * a.H * (double)a.N * d * 2.0 >= (double)lfh::env_int("LINFUSION_BWD_ROWS_MIN_MB", 24) * 1048576.0;
+// kernels, and pay once the lines that a lone head's rows leave half used no longer meet in the L2.  MB per tensor from
+// which they are picked; measured on token-major tensors, a gradient call with the per-head kernels over one with the
+// row pieces:
+//   d = 8 .. 32          3 MB 1.05, 5 MB 1.05 to 1.24, 8 MB 1.27 to 1.70 (d = 32, 15 MB: 1.12)
+//   d = 40, 48 (fp16)    by eight heads 3 MB 1.05, 5 MB 0.99 to 1.01, 8 MB 1.05 to 1.11, 15 MB 1.2 to 1.33;
+//                        by four 5 MB 0.91 to 0.96, 8 MB 0.97 to 1.05, 15 MB 1.07 to 1.24
+//   d = 48 (bf16)        two kernels for dQ and its state: 5 MB 0.89, 15 MB 1.0, 30 MB 1.17
+//   d = 56               fp16 15 MB 0.97, 30 MB 1.06; bf16 15 MB 0.85, 30 MB 0.91, 60 MB 1.02
+//   d = 80               fp16 15 to 30 MB 0.74, 60 MB 0.84, 120 MB 0.93 to 1.0; bf16 30 MB 0.96 to 1.07, 60 MB 1.02
+template <typename T>
+constexpr int rows_min_mb(int d, int heads) {
+  constexpr bool bf16 = lf::NSplit<T>::value != 1;
+  if (d <= 32) return 4;
+  if (d <= 40 || (d <= 48 && !bf16)) return heads % 8 == 0 ? 7 : 12;
+  if (d <= 48) return 20;
+  if (d <= 56) return bf16 ? 60 : 24;
+  return bf16 ? 48 : 160;
+}
+
+template <typename T>
+bool rows_pay(const BwdArgs& a, int d) {
+  return (double)a.B * a.H * (double)a.N * d * 2.0 >=
+         (double)lfh::env_int("LINFUSION_BWD_ROWS_MIN_MB", rows_min_mb<T>(d, a.H)) * 1048576.0;
 }
 
 // dK, dV: the row-piece kernel on groups of W heads where the heads of a token are neighbours in memory (k, v and
@@ -188,7 +207,7 @@ int launch_q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal) {
 
 // whether q_rows below would take the dQ launch (the widths at which the merged kernel has no row-piece form, see
 // qs_rows_fits, keep the separate row-piece kernels wherever they would be picked)
-template <int D>
+template <typename T, int D>
 bool q_rows_wanted(const BwdArgs& a) {
   constexpr int CPR = D / 8;
   if constexpr ((D * 2) % 128 == 0) {
@@ -196,7 +215,7 @@ bool q_rows_wanted(const BwdArgs& a) {
   } else {
     if (a.lq.head != CPR || a.lg.head != CPR || a.ldq.head != CPR) return false;
     const int mode = lfh::env_int("LINFUSION_BWD_ROWS", 1);
-    if (mode == 2 || (mode != 3 && !rows_pay(a, D))) return false;
+    if (mode == 2 || (mode != 3 && !rows_pay<T>(a, D))) return false;
     if constexpr (D <= 48) {
       if (a.H % 8 == 0) return true;
     }
@@ -215,7 +234,7 @@ bool q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal, int* rc) {
   } else {
     if (a.lq.head != CPR || a.lg.head != CPR || a.ldq.head != CPR) return false;
     const int mode = lfh::env_int("LINFUSION_BWD_ROWS", 1);   // 1: by size, 2: never, 3: always (a test aid)
-    if (mode == 2 || (mode != 3 && !rows_pay(a, D))) return false;
+    if (mode == 2 || (mode != 3 && !rows_pay<T>(a, D))) return false;
     if constexpr (D <= 48) {
       if (a.H % 8 == 0) { *rc = launch_q_rows<T, D, FM, NORM, 8>(a, stateS, scal); return true; }
     }
@@ -234,7 +253,7 @@ bool qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* wgs_us
   } else {
     if (a.lq.head != CPR || a.lg.head != CPR || a.ldq.head != CPR) return false;
     const int mode = lfh::env_int("LINFUSION_BWD_ROWS", 1);   // 1: by size, 2: never, 3: always (a test aid)
-    if (mode == 2 || (mode != 3 && !rows_pay(a, D))) return false;
+    if (mode == 2 || (mode != 3 && !rows_pay<T>(a, D))) return false;
     if (a.H % 8 == 0) { *rc = launch_qs_rows<T, D, FM, NORM, 8>(a, stateS, partials, wgs_used); return true; }
     if (a.H % 4 == 0) { *rc = launch_qs_rows<T, D, FM, NORM, 4>(a, stateS, partials, wgs_used); return true; }
     return false;
@@ -266,7 +285,7 @@ bool state_rows(const BwdArgs& a, float* partials, int* nparts, int* rc) {
   if constexpr ((D * 2) % 128 == 0) return false;
   if (a.lkv.head != CPR) return false;
   const int mode = lfh::env_int("LINFUSION_BWD_ROWS", 1);   // 1: by size, 2: never, 3: always (a test aid)
-  if (mode == 2 || (mode != 3 && !rows_pay(a, D))) return false;
+  if (mode == 2 || (mode != 3 && !rows_pay<T>(a, D))) return false;
   if constexpr (D <= 64) {
     if (a.H % 8 == 0) { *rc = launch_state_rows<T, D, FM, 8>(a, partials, nparts); return true; }
   }
@@ -284,7 +303,7 @@ bool kv_rows(const BwdArgs& a, const float* stateD, int* rc) {
   if constexpr ((D * 2) % 128 == 0) return false;
   if (a.lkv.head != CPR || a.ldkv.head != CPR) return false;
   const int mode = lfh::env_int("LINFUSION_BWD_ROWS", 1);   // 1: by size, 2: never, 3: always (a test aid)
-  if (mode == 2 || (mode != 3 && !rows_pay(a, D))) return false;
+  if (mode == 2 || (mode != 3 && !rows_pay<T>(a, D))) return false;
   if constexpr (kRowsW8<D>) {
     if (a.H % 8 == 0) { *rc = launch_kv_rows<T, D, FM, 8>(a, stateD); return true; }
   }
@@ -364,7 +383,7 @@ int run_bwd(const BwdArgs& a) {
   constexpr bool kQsRows = lf::qs_rows_fits<T, D>();
   if constexpr (kMerged) {
     bool merged = lfh::env_int("LINFUSION_BWD_MERGED", 1) == 1;
-    if (!kQsRows && q_rows_wanted<D>(a)) merged = false;
+    if (!kQsRows && q_rows_wanted<T, D>(a)) merged = false;
     if (merged) {
       constexpr int lds_qs = qs_lds_bytes<T, D>();
       static_assert(lds_qs <= 160 * 1024, "workgroup LDS limit of the device");

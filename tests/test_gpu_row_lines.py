@@ -1,0 +1,67 @@
+"""Which token-major calls go to the row-piece kernels: the line of every width, from both sides."""
+import pytest
+import torch
+
+import paper_2409_02097_amd as lf
+from paper_2409_02097_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+MB = 1 << 20
+
+
+def _token_major(B, H, N, d, dtype, fill=None):
+    t = torch.empty((B, N, H, d), dtype=wl.TORCH_DTYPE[dtype], device="cuda")
+    t = t.normal_() if fill is None else t.fill_(fill)
+    return t.permute(0, 2, 1, 3)
+
+
+def _knob(monkeypatch, name, value):
+    if value is None:
+        monkeypatch.delenv(name, raising=False)
+    else:
+        monkeypatch.setenv(name, value)
+
+
+# (H, d, type, MB of one tensor from which the row pieces are due: forward, backward)
+LINES = [(8, 16, "f16", 6, 4), (8, 32, "bf16", 20, 4), (8, 40, "f16", 6, 7), (4, 40, "bf16", 20, 12), (8, 48, "f16", 6, 7),
+         (8, 48, "bf16", 6, 20), (8, 56, "f16", 20, 24), (4, 56, "bf16", 20, 60), (4, 80, "bf16", 60, 48)]
+
+
+@pytest.mark.parametrize("above", [False, True])
+@pytest.mark.parametrize("H,d,dtype,fwd_mb,bwd_mb", LINES)
+def test_row_pieces_from_their_line_up(H, d, dtype, fwd_mb, bwd_mb, above, monkeypatch, tuning):
+    """Just below its line a call gives the bits of the per-head kernels, from the line on those of the row pieces; where
+    the two differ they do so by the order of the sums, and the forward result is the oracle's."""
+    torch.manual_seed(d)
+    code = wl.DTYPE_CODE[dtype]
+    forced = "3" if above else "2"
+    # forward
+    N = -(-fwd_mb * MB // (2 * H * d)) - (0 if above else 1)
+    print(f"line H={H} d={d} {dtype} N={N} above={above}", flush=True)
+    q, k, v = (_token_major(1, H, N, d, dtype) for _ in range(3))
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(1, H, N, d, code), dtype=torch.uint8, device="cuda")
+    outs = []
+    for mode in (None, forced):
+        _knob(monkeypatch, "LINFUSION_HEAD_GROUPS", mode)
+        outs.append(_token_major(1, H, N, d, dtype, float("nan")))
+        lf.linfusion_attn_fwd_strided(q, k, v, outs[-1], 0, 1e-6, 0, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    parity.check_all(outs[0][:, :1].contiguous().cpu(), *(t[:, :1].contiguous().cpu() for t in (q, k, v)), dtype, 0, 1e-6, True,
+                     f"line d={d}")
+    # backward
+    N = -(-bwd_mb * MB // (2 * H * d)) - (0 if above else 1)
+    q, k, v, g = (_token_major(1, H, N, d, dtype) for _ in range(4))
+    ws = torch.empty(lf.linfusion_attn_bwd_workspace_bytes(1, H, N, d, code), dtype=torch.uint8, device="cuda")
+    got = []
+    for mode in (None, forced, "2"):
+        _knob(monkeypatch, "LINFUSION_BWD_ROWS", mode)
+        got.append([_token_major(1, H, N, d, dtype, float("nan")) for _ in range(3)])
+        lf.linfusion_attn_bwd_strided(q, k, v, g, *got[-1], 0, 1e-6, 0, ws)
+    torch.cuda.synchronize()
+    ulp2 = 2.0 ** -7 if dtype == "bf16" else 2.0 ** -10      # two units in the last place of the 16-bit results
+    for a, b, c in zip(*got):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        assert (a.float() - c.float()).abs().max().item() <= ulp2 * c.float().abs().max().item()
