@@ -147,22 +147,29 @@ struct Ring2Rows {
     if (ahead.valid()) issue_copy(ahead.t, 1);
     ahead.next();
   }
-  // This wave alone: stages its head's fp32 state in its own piece of LDS (kOwnStage) and returns the power-of-two
-  // scale for the matrix.  A workgroup barrier must follow before prefetch_second().
-  LF_DEV float stage_state_own(const float* state) {
+  // This wave alone: loads its head's fp32 state and (kOwnStage) stages it in its own piece of LDS; returns the
+  // power-of-two scale for the matrix.  A workgroup barrier must follow before prefetch_second().  The kernels load before
+  // anything else: behind the loads lie the two hundred instructions of the ring's addresses (the prologue of the dQ kernel
+  // of bf16 12 x 8 x 4096 x 40 5.5 -> 4.4 us).
+  struct OwnState {
+    static constexpr int PER = (NE / 4 + 63) / 64;
+    f32x4 v[PER];
+    LF_DEV explicit OwnState(const float* state) {
+      const int lane = threadIdx.x & 63;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int e = lane + 64 * i;
+        v[i] = reinterpret_cast<const f32x4*>(state)[e < NE / 4 ? e : 0];
+      }
+    }
+  };
+  LF_DEV float stage_state_own(const OwnState& s) {
     float* st = reinterpret_cast<float*>(smem + C::kSlotBytes + wave * C::kOwnBytes);
     float mS = 0.0f;
-    constexpr int PER = (NE / 4 + 63) / 64;
-    f32x4 v[PER];   // (all loads are issued before the first is used)
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
+    for (int i = 0; i < OwnState::PER; ++i) {
       const int e = lane + 64 * i;
-      v[i] = reinterpret_cast<const f32x4*>(state)[e < NE / 4 ? e : 0];
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = lane + 64 * i;
-      const f32x4 x = v[i];
+      const f32x4 x = s.v[i];
       if (e < NE / 4) *reinterpret_cast<f32x4*>(st + StageBwd<D>::place(e)) = x;
       if (e < D * D / 4) mS = fmaxf(mS, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
     }
@@ -315,12 +322,13 @@ struct Ring2Rows {
 // ==========================================================================================
 template <typename T, int D, int FM, int W>
 __global__ void __launch_bounds__(64 * W)
-bwd_kv16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout lkv, u32x4* __restrict__ dK,
-              u32x4* __restrict__ dV, Layout ldkv, int gpb, const float* __restrict__ dstate, long long N,
-              int tiles_per_block) {
+bwd_kv16_rows(const float* __restrict__ dstate, const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long N, int gpb,
+              int tiles_per_block, u32x4* __restrict__ dK, u32x4* __restrict__ dV, Layout lkv, Layout ldkv) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RG = Ring2Rows<T, D, W>;
   constexpr int NS = RG::NS, KS = RG::KS, MTB = RG::MTB, HALF = RG::HALF, NL = RG::NL, R = RG::R, CPR = RG::CPR;
+  const typename RG::OwnState own(dstate + ((long long)blockIdx.y * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) *
+                                           (D * D + D));
   const long long b = blockIdx.y / gpb;
   const long long h0 = (long long)(blockIdx.y % gpb) * W;
   const long long in_off = b * lkv.batch + h0 * lkv.head, out_off = b * ldkv.batch + h0 * ldkv.head;
@@ -334,7 +342,7 @@ bwd_kv16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout l
   float dzo[HALF];
   float inv_aS = 1.0f;
   if constexpr (BwdRowsCfg<D, W>::kOwnStage) {
-    const float aS = rg.stage_state_own(dstate + (b * lkv.H + h0 + rg.wave) * (D * D + D));
+    const float aS = rg.stage_state_own(own);
     rg.template build_A<true>(aS, A1);    // dv = dS^T p
     rg.template build_A<false>(aS, A2);   // dp = dS v (+ dz)
     rg.load_vec(dzo);
@@ -367,12 +375,18 @@ bwd_kv16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout l
   while (rg.it.valid()) {
     const long long tile = rg.it.t;
     const bool have_prev = prev_tile >= 0;
-    if (have_prev) {
-      rg.store_tile(prev_tile, prev_slot, 0, dKg, ldkv.row);
-      rg.store_tile(prev_tile, prev_slot, 1, dVg, ldkv.row);
-    }
     const bool copied = rg.ahead.valid();
-    if (copied) rg.issue_copy(rg.ahead.t, have_prev ? prev_slot : R - 1);
+    // Tile j - 1 out, tile j + 2 in, by half of the waves here and by the other half after its products: a CU takes about
+    // 1 KB of these accesses per 100 cycles, three of a tile's six microseconds, and the two waves of a SIMD, in step by the
+    // barrier, would both stand still for them (bf16 12 x 8 x 4096 x 40: a tile 6.3 -> 5.5 us, fp16 5.4 -> 4.8).
+    auto move = [&]() {
+      if (have_prev) {
+        rg.store_tile(prev_tile, prev_slot, 0, dKg, ldkv.row);
+        rg.store_tile(prev_tile, prev_slot, 1, dVg, ldkv.row);
+      }
+      if (copied) rg.issue_copy(rg.ahead.t, have_prev ? prev_slot : R - 1);
+    };
+    if (rg.wave < W / 2) move();
 
     // phi(k) of this lane's input chunks -> B operands (hi [, lo]); v raw
     u32x4 Bp[KS], Bpl[NS == 2 ? KS : 1], Bv[KS];
@@ -399,6 +413,7 @@ bwd_kv16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, Layout l
     f32x16 acc1[MTB], acc2[MTB];
     rg.products(A1, Bp, NS == 2 ? Bpl : nullptr, acc1);
     rg.products(A2, Bv, nullptr, acc2);
+    if (rg.wave >= W / 2) move();
     float x[HALF], o[HALF];
     rg.read_half_row(slot, 0, x);             // k at this lane's output channels
 #pragma unroll
@@ -459,9 +474,9 @@ template <typename T, int D, int W> struct QsRowsLds {
 template <typename T, int D, int W> constexpr int qs_rows_lds_bytes() { return QsRowsLds<T, D, W>::kEnd; }
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
-bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G, Layout lg, u32x4* __restrict__ dQ,
-              Layout ldq, int gpb, const float* __restrict__ state, float* __restrict__ partials, float eps,
-              long long N, int tiles_per_block) {
+bwd_qs16_rows(const float* __restrict__ state, const u32x4* __restrict__ Q, const u32x4* __restrict__ G, long long N, int gpb,
+              int tiles_per_block, u32x4* __restrict__ dQ, float* __restrict__ partials, float eps, Layout lq, Layout lg,
+              Layout ldq) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RG = Ring2Rows<T, D, W, qs_rows_ring<T>()>;
   using Sh = Shape16<D>;
@@ -469,6 +484,8 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
   constexpr int NS = NSplit<T>::value, KS = RG::KS, MTB = RG::MTB, HALF = RG::HALF, NL = RG::NL, R = RG::R, CPR = RG::CPR;
   constexpr int MT = Sh::kMT, NE = D * D + D;
   constexpr bool kECol = NS == 2 && Sh::kSpareCol;
+  const typename RG::OwnState own(state + ((long long)blockIdx.y * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) *
+                                           (D * D + D));
   const long long b = blockIdx.y / gpb;
   const long long h0 = (long long)(blockIdx.y % gpb) * W;
   RG rg(Q + (b * lq.batch + h0 * lq.head), lq.row, G + (b * lg.batch + h0 * lg.head), lg.row, N, tiles_per_block,
@@ -517,7 +534,7 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
     }
   };
   if constexpr (L::kOwnStage) {
-    build(rg.stage_state_own(state + (b * lq.H + h0 + rg.wave) * NE));
+    build(rg.stage_state_own(own));
     __syncthreads();   // the staged states are dead: the second slot may be filled
     if constexpr (R == 3) rg.prefetch_second();
   } else {
@@ -792,14 +809,15 @@ bwd_qs16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ 
 // ==========================================================================================
 template <typename T, int D, int FM, bool NORM, int W>
 __global__ void __launch_bounds__(64 * W)
-bwd_q16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G, Layout lg, u32x4* __restrict__ dQ,
-             Layout ldq, int gpb, const float* __restrict__ state, f32x2* __restrict__ scal, float eps, long long N,
-             int tiles_per_block) {
+bwd_q16_rows(const float* __restrict__ state, const u32x4* __restrict__ Q, const u32x4* __restrict__ G, long long N, int gpb,
+             int tiles_per_block, u32x4* __restrict__ dQ, f32x2* __restrict__ scal, float eps, Layout lq, Layout lg, Layout ldq) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RG = Ring2Rows<T, D, W>;
   using C = BwdRowsCfg<D, W>;
   constexpr int NS = RG::NS, KS = RG::KS, MTB = RG::MTB, HALF = RG::HALF, NL = RG::NL, R = RG::R;
   constexpr int NE = D * D + D;
+  const typename RG::OwnState own(state + ((long long)blockIdx.y * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) *
+                                           (D * D + D));
   const long long b = blockIdx.y / gpb;
   const long long h0 = (long long)(blockIdx.y % gpb) * W;
   RG rg(Q + (b * lq.batch + h0 * lq.head), lq.row, G + (b * lg.batch + h0 * lg.head), lg.row, N, tiles_per_block,
@@ -812,7 +830,7 @@ bwd_q16_rows(const u32x4* __restrict__ Q, Layout lq, const u32x4* __restrict__ G
   float zo[HALF];
   float inv_aS = 1.0f;
   if constexpr (C::kOwnStage) {
-    const float aS = rg.stage_state_own(state + (b * lq.H + h0 + rg.wave) * NE);
+    const float aS = rg.stage_state_own(own);
     rg.template build_A<false>(aS, A);       // u = S g
     rg.load_vec(zo);
     inv_aS = 1.0f / aS;

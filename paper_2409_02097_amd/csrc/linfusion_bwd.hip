@@ -161,7 +161,7 @@ int launch_kv_rows(const BwdArgs& a, const float* stateD) {
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
   const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), W * D % 64 != 0);
   bwd_kv16_rows<T, D, FM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.k, (const u32x4*)a.v, a.lkv, (u32x4*)a.dk, (u32x4*)a.dv, a.ldkv, gpb, stateD, a.N, sh.blk);
+      stateD, (const u32x4*)a.k, (const u32x4*)a.v, a.N, gpb, sh.blk, (u32x4*)a.dk, (u32x4*)a.dv, a.lkv, a.ldkv);
   return LINFUSION_OK;
 }
 
@@ -181,8 +181,7 @@ int launch_qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* 
   if (wgs > a.p->most) wgs = a.p->most;   // room for the partial states
   const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), W * D % 64 != 0);
   bwd_qs16_rows<T, D, FM, NORM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, (u32x4*)a.dq, a.ldq, gpb, stateS, partials, a.eps, a.N,
-      sh.blk);
+      stateS, (const u32x4*)a.q, (const u32x4*)a.g, a.N, gpb, sh.blk, (u32x4*)a.dq, partials, a.eps, a.lq, a.lg, a.ldq);
   *wgs_used = sh.wgs;
   return LINFUSION_OK;
 }
@@ -201,7 +200,7 @@ int launch_q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal) {
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
   const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), W * D % 64 != 0);
   bwd_q16_rows<T, D, FM, NORM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
-      (const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, (u32x4*)a.dq, a.ldq, gpb, stateS, scal, a.eps, a.N, sh.blk);
+      stateS, (const u32x4*)a.q, (const u32x4*)a.g, a.N, gpb, sh.blk, (u32x4*)a.dq, scal, a.eps, a.lq, a.lg, a.ldq);
   return LINFUSION_OK;
 }
 
