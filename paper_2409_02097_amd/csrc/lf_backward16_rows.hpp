@@ -378,7 +378,9 @@ bwd_kv16_rows(const float* __restrict__ dstate, const u32x4* __restrict__ K, con
     const bool copied = rg.ahead.valid();
     // Tile j - 1 out, tile j + 2 in, by half of the waves here and by the other half after its products: a CU takes about
     // 1 KB of these accesses per 100 cycles, three of a tile's six microseconds, and the two waves of a SIMD, in step by the
-    // barrier, would both stand still for them (bf16 12 x 8 x 4096 x 40: a tile 6.3 -> 5.5 us, fp16 5.4 -> 4.8).
+    // barrier, would both stand still for them (bf16 12 x 8 x 4096 x 40: a tile 6.3 -> 5.5 us, fp16 5.4 -> 4.8).  Groups of four
+    // have one wave per SIMD and the wider heads: the second copy of this code would only cost them registers (30 to 50, with
+    // spills at d = 80: 8 x 131072 x 80 bf16 684 -> 862 us).
     auto move = [&]() {
       if (have_prev) {
         rg.store_tile(prev_tile, prev_slot, 0, dKg, ldkv.row);
@@ -386,7 +388,7 @@ bwd_kv16_rows(const float* __restrict__ dstate, const u32x4* __restrict__ K, con
       }
       if (copied) rg.issue_copy(rg.ahead.t, have_prev ? prev_slot : R - 1);
     };
-    if (rg.wave < W / 2) move();
+    if (W == 4 || rg.wave < W / 2) move();
 
     // phi(k) of this lane's input chunks -> B operands (hi [, lo]); v raw
     u32x4 Bp[KS], Bpl[NS == 2 ? KS : 1], Bv[KS];
@@ -413,7 +415,7 @@ bwd_kv16_rows(const float* __restrict__ dstate, const u32x4* __restrict__ K, con
     f32x16 acc1[MTB], acc2[MTB];
     rg.products(A1, Bp, NS == 2 ? Bpl : nullptr, acc1);
     rg.products(A2, Bv, nullptr, acc2);
-    if (rg.wave >= W / 2) move();
+    if (W == 8 && rg.wave >= W / 2) move();
     float x[HALF], o[HALF];
     rg.read_half_row(slot, 0, x);             // k at this lane's output channels
 #pragma unroll
