@@ -380,7 +380,7 @@ bwd_kv16_rows(const float* __restrict__ dstate, const u32x4* __restrict__ K, con
     // 1 KB of these accesses per 100 cycles, three of a tile's six microseconds, and the two waves of a SIMD, in step by the
     // barrier, would both stand still for them (bf16 12 x 8 x 4096 x 40: a tile 6.3 -> 5.5 us, fp16 5.4 -> 4.8).  Groups of four
     // have one wave per SIMD and the wider heads: the second copy of this code would only cost them registers (30 to 50, with
-    // spills at d = 80: 8 x 131072 x 80 bf16 684 -> 862 us).
+    // spills at d = 80: 8 x 131072 x 80 bf16 633 -> 862 us).
     auto move = [&]() {
       if (have_prev) {
         rg.store_tile(prev_tile, prev_slot, 0, dKg, ldkv.row);
