@@ -93,9 +93,11 @@ int run_wide(const WideArgs& a);
 // the forward plan's launch shape for a wide width (linfusion.hip), and the bytes its partial states take;
 // LINFUSION_ERR_UNSUPPORTED for other widths
 int wide_launch_plan(int B, int H, long long N, int d, int dtype, WidePlan* wp, size_t* partial_bytes);
-// For the backward pass of these widths: the reduction by itself -- the summed state in a.state, or the partials as they
-// are (a single one is the state, in a.state) -- and the apply kernel of one wave per tile on operands that lie packed
+// For the backward pass of these widths: the forward state of k and v (one layout) in a.state, with the bits that the forward
+// call of these tensors leaves in its workspace; the reduction by itself -- the summed state in a.state, or the partials as
+// they are (a single one is the state, in a.state) -- and the apply kernel of one wave per tile on operands that lie packed
 // (PackWave's layout) already; a.state is not read.
+int run_wide_state(const WideReduceArgs& a);
 int run_wide_reduce(const WideReduceArgs& a);
 int run_wide_reduce_partials(const WideReduceArgs& a);
 int run_wide_apply_packed(const WideApplyArgs& a);

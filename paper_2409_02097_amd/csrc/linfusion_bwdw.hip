@@ -70,7 +70,7 @@ int run(const BwdWideArgs& a, const Regions& r) {
   const float* state = a.saved_state;
   if (!state) {
     const lfw::WideReduceArgs x{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, FM, a.lkv, a.lkv, partials, whole, r.plan, st};
-    if ((rc = lfw::run_wide_reduce(x)) != LINFUSION_OK) return rc;
+    if ((rc = lfw::run_wide_state(x)) != LINFUSION_OK) return rc;
     state = whole;
   }
   const float* z = NORM ? state + D * D : nullptr;

@@ -102,7 +102,7 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
 
 // the whole call in one launch
 template <typename T, int D, int CB>
-int run_short(const WideArgs& a) {
+int launch_short(const WideArgs& a) {
   using namespace lf;
   using C = Short16Cfg<T, D, CB>;
   const int parts = a.out ? a.plan.short_parts : 1;
@@ -127,12 +127,24 @@ int run_short(const WideArgs& a) {
 }
 
 template <typename T, int D>
+int run_short(const WideArgs& a) {
+  return a.plan.short_half ? launch_short<T, D, D / 32>(a) : launch_short<T, D, 2>(a);
+}
+
+// The state of a problem whose call is one launch, with the bits that this launch leaves: summed by the same kernel.
+template <typename T, int D>
+int state_of_short(const WideReduceArgs& a, hipEvent_t* ev) {
+  return run_short<T, D>(WideArgs{nullptr, a.k, a.v, nullptr, a.B, a.H, a.N, a.d, a.dtype, a.fm, 0.0f, true, a.lk, a.lk, a.lk,
+                                  a.partials, a.state, nullptr, a.plan, a.st, ev});
+}
+
+template <typename T, int D>
 int run(const WideArgs& a) {
-  // (A workgroup reads whole query rows and writes a part of their channels: not where out is q.  The state alone is summed
-  // the same way, so that it has the bits of the state that a call leaves behind.)
-  if (a.plan.short_parts > 0 && (!a.out || a.out != a.q))
-    return a.plan.short_half ? run_short<T, D, D / 32>(a) : run_short<T, D, 2>(a);
   const WideReduceArgs r{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.lkv, a.lkv, a.partials, a.state, a.plan, a.st};
+  if (a.plan.short_parts > 0) {
+    if (!a.out) return state_of_short<T, D>(r, a.ev);
+    if (a.out != a.q) return run_short<T, D>(a);
+  }
   const bool fuse = a.out && a.plan.wave_apply;   // the partials are summed where the operands are packed
   int rc = reduce<T, D>(r, a.ev, !fuse);
   if (rc != LINFUSION_OK) return rc;
@@ -193,6 +205,17 @@ int run_wide_reduce(const WideReduceArgs& a) {
   switch (a.d) {
 #define X(DD) \
   case DD: return a.dtype == LINFUSION_DTYPE_F16 ? reduce<lf::F16, DD>(a, nullptr, true) : reduce<lf::BF16, DD>(a, nullptr, true);
+    LFW_FOR_D(X)
+#undef X
+  }
+  return LINFUSION_ERR_UNSUPPORTED;
+}
+
+int run_wide_state(const WideReduceArgs& a) {
+  if (a.plan.short_parts == 0) return run_wide_reduce(a);
+  switch (a.d) {
+#define X(DD) \
+  case DD: return a.dtype == LINFUSION_DTYPE_F16 ? state_of_short<lf::F16, DD>(a, nullptr) : state_of_short<lf::BF16, DD>(a, nullptr);
     LFW_FOR_D(X)
 #undef X
   }
