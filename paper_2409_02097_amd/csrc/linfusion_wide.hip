@@ -131,9 +131,16 @@ int run_short(const WideArgs& a) {
   return a.plan.short_half ? launch_short<T, D, D / 32>(a) : launch_short<T, D, 2>(a);
 }
 
-// The state of a problem whose call is one launch, with the bits that this launch leaves: summed by the same kernel.
+// The state of a problem whose call is one launch, with the bits that this launch leaves: summed by the same kernel, or
+// by the state reduction where one workgroup of it sums a whole head -- the same products in the same order -- and the
+// one-launch kernel's workgroups, which repeat phi(K), would be more than run at once, or in fp16 a head is one tile (us per
+// state-only call, that kernel / the reduction, fp16: 128 heads of 128 x 160 8.7 / 9.5, 160 heads 14.3 / 9.7, 512 heads
+// 30.4 / 15.9, 160 heads of 128 x 128 11.3 / 8.0; 128 heads of 32 x 160 7.9 / 6.3, in bf16 6.9 / 6.7 and 8 heads 6.1 / 6.4).
 template <typename T, int D>
 int state_of_short(const WideReduceArgs& a, hipEvent_t* ev) {
+  const long long wgs = (long long)a.B * a.H * (a.plan.short_half ? 2 : D / 32);
+  const bool one_tile = lf::NSplit<T>::value == 1 && a.N <= lf::kTile;
+  if (a.plan.splits == 1 && (wgs > lfh::num_cu() || one_tile)) return reduce<T, D>(a, ev, true);
   return run_short<T, D>(WideArgs{nullptr, a.k, a.v, nullptr, a.B, a.H, a.N, a.d, a.dtype, a.fm, 0.0f, true, a.lk, a.lk, a.lk,
                                   a.partials, a.state, nullptr, a.plan, a.st, ev});
 }

@@ -48,6 +48,29 @@ def test_short_streams_in_one_launch(N, d, dtype, half, monkeypatch, tuning):
     parity.check_all(qd, q, k, v, dtype, 0, 1e-6, True, f"short, in place, N={N} d={d} {dtype}")
 
 
+# one workgroup of the state reduction per head, or several; few heads, and more than the one launch's workgroups run at once
+@pytest.mark.parametrize("keys", [0.0, -20.0])
+@pytest.mark.parametrize("B,H,N,d,dtype", [(2, 8, 64, 160, "f16"), (6, 8, 65, 160, "bf16"), (20, 8, 128, 160, "f16"),
+                                           (20, 8, 200, 128, "bf16"), (25, 8, 33, 96, "f16"), (40, 8, 100, 160, "bf16"),
+                                           (2, 8, 400, 96, "f16")])
+def test_the_state_alone_has_the_bits_of_the_calls(B, H, N, d, dtype, keys):
+    """Also where keys far below zero make either kernel sum them a second time."""
+    print(f"state alone {B}x{H}x{N}x{d} {dtype} keys {keys}", flush=True)
+    code = wl.DTYPE_CODE[dtype]
+    q, k, v = (t.cuda() for t in wl.make_qkv(B, H, N, d, dtype, idx=151))
+    k = k + keys
+    need = lf.linfusion_attn_workspace_bytes(B, H, N, d, code)
+    off = lf.linfusion_attn_workspace_state_offset(B, H, N, d, code)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    call = lambda: lf.linfusion_attn_fwd_ex(q, k, v, torch.empty_like(q), 0, 1e-6, 0, ws)
+    assert _launches(call) == 1
+    call()
+    left = ws[off:off + 4 * B * H * (d * d + d)].clone().view(torch.float32)
+    lf.linfusion_attn_state(k, v, alone := torch.full_like(left, float("nan")), 0, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(left, alone)
+
+
 @pytest.mark.parametrize("B,H,N,d,launches", [(2, 8, 256, 160, 1), (2, 8, 513, 160, 3), (50, 8, 256, 96, 3), (50, 8, 128, 96, 1)])
 def test_which_calls_are_short(B, H, N, d, launches):
     """512 tokens while all workgroups run at once, fewer for more heads; the forced split path is never short."""
