@@ -149,8 +149,16 @@ template <typename T, int D>
 int run(const WideArgs& a) {
   const WideReduceArgs r{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.lkv, a.lkv, a.partials, a.state, a.plan, a.st};
   if (a.plan.short_parts > 0) {
-    if (!a.out) return state_of_short<T, D>(r, a.ev);
-    if (a.out != a.q) return run_short<T, D>(a);
+    if (a.out && a.out != a.q) return run_short<T, D>(a);
+    int rc = state_of_short<T, D>(r, a.ev);
+    if (rc != LINFUSION_OK || !a.out) return rc;
+    // In place a workgroup of the one launch would read query rows that others have written a part of: the same state, then
+    // the apply of a wave per tile, whose arithmetic is the same.
+    const WideApplyArgs p{a.q, a.out, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.eps, a.unnorm, a.lq, a.lo, a.state, a.packed,
+                          a.plan, a.st};
+    rc = apply<T, D>(p, 1, nullptr, a.ev ? a.ev + 2 : nullptr);
+    if (a.ev) (void)hipEventRecord(a.ev[3], a.st);
+    return rc;
   }
   const bool fuse = a.out && a.plan.wave_apply;   // the partials are summed where the operands are packed
   int rc = reduce<T, D>(r, a.ev, !fuse);

@@ -35,17 +35,22 @@ def test_short_streams_in_one_launch(N, d, dtype, half, monkeypatch, tuning):
     assert _launches(call) == 1
     parity.check_all(got[0], q, k, v, dtype, 0, 1e-6, True, f"short N={N} d={d} {dtype}")
     assert torch.equal(got[0].view(torch.int16), got[1].view(torch.int16)), "token-major differs from contiguous"
-    # the state it leaves is the state-only call's, and the split path's up to the order of the sums; in place the query rows
-    # must be read before they are written: the split path, within the same bound
-    state = ws[off:off + 4 * B * H * (d * d + d)].clone().view(torch.float32)
+    # the state it leaves is the state-only call's, and the split path's up to the order of the sums
+    left = lambda: ws[off:off + 4 * B * H * (d * d + d)].clone().view(torch.float32)
+    state = left()
     lf.linfusion_attn_state(k.cuda(), v.cuda(), alone := torch.empty_like(state), 0, ws)
+    # in place the query rows must be read before they are written: other launches, the same bits in output and state
     qd = q.cuda()
     lf.linfusion_attn_fwd_strided(qd, k.cuda(), v.cuda(), qd, 0, 1e-6, 0, ws)
     torch.cuda.synchronize()
-    assert torch.equal(state, alone)
-    split = ws[off:off + 4 * B * H * (d * d + d)].view(torch.float32)
+    assert torch.equal(state, alone) and torch.equal(state, left())
+    assert torch.equal(got[0].view(torch.int16), qd.view(torch.int16)), "in place differs from out of place"
+    out = torch.full_like(qd, float("nan"))
+    lf.linfusion_attn_fwd_strided(q.cuda(), k.cuda(), v.cuda(), out, 0, 1e-6, lf.FLAG_FORCE_SPLIT, ws)
+    torch.cuda.synchronize()
+    split = left()
     assert ((state - split).norm() <= 1e-6 * split.norm()).item()     # (random signs: 2^-24 sqrt(N) of the sums' terms)
-    parity.check_all(qd, q, k, v, dtype, 0, 1e-6, True, f"short, in place, N={N} d={d} {dtype}")
+    parity.check_all(out, q, k, v, dtype, 0, 1e-6, True, f"short, split path, N={N} d={d} {dtype}")
 
 
 # one workgroup of the state reduction per head, or several; few heads, and more than the one launch's workgroups run at once

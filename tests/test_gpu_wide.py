@@ -226,8 +226,10 @@ def test_wide_nan_stays_where_it_belongs(d, dtype):
 
 
 @pytest.mark.parametrize("d,dtype", [(80, "f16"), (160, "f16"), (80, "bf16"), (160, "bf16"), (96, "f16"), (128, "bf16")])
-def test_wide_heads_token_major_and_in_place(d, dtype):
-    B, H, N = 2, 4, 700
+@pytest.mark.parametrize("N", [700, 256, 33])     # above width 80: three launches; short streams
+def test_wide_heads_token_major_and_in_place(N, d, dtype):
+    B, H = 2, 4
+    print(f"wide token-major and in place N={N} d={d} {dtype}", flush=True)
     q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=71, device="cpu")
     tm = lambda t: t.permute(0, 2, 1, 3).contiguous().cuda()
     qt, kt, vt = tm(q), tm(k), tm(v)
