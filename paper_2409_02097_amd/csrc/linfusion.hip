@@ -203,7 +203,11 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     // tokens 20.9 -> 9.0, 22.6 -> 13.2, 24.6 -> 18.5, 26.4 -> 27.7, bf16 21.2 -> 7.6, 23.6 -> 13.4, 26.3 -> 20.7, 28.7 -> 35.7; 20 x
     // 10 heads fp16 27.6 -> 21.5, 40.3 -> 39.9, 56.9 -> 65.1).  Half of the value channels per workgroup where 32 would take
     // more than a round, or most of one and many tokens (fp16 12 x 8 x 256 28.9 -> 20.0, 4 x 8 x 512 24.5 -> 21.4, but 2 x 8 x
-    // 256 13.2 -> 15.6 and 4 x 8 x 256 15.5 -> 16.0).
+    // 256 13.2 -> 15.6 and 4 x 8 x 256 15.5 -> 16.0).  Three launches over one where a second round has begun, inputs from
+    // memory, 136 / 160 / 200 heads: 256 tokens, d = 160 fp16 0.97, 0.98, 1.01, bf16 1.08 to 1.12, d = 128 1.10 to 1.23, d =
+    // 96 1.05 to 1.42; 200 tokens 1.04 to 1.42.  fp16 of 96 channels, whose three launches are the shortest, loses from a
+    // fourth round on (448 to 640 heads: 64 tokens 1.10 to 1.13, 100 and 128 tokens 0.84; 768 heads 0.95 to 1.03, 1024 and
+    // more 0.83 to 0.94), the others at no number of heads (256 to 2048, 1 to 256 tokens: 1.02 to 2.5).
     p->short_parts = 0;
     p->short_half = false;
     if (!compact && !(flags & LINFUSION_FLAG_FORCE_SPLIT) && p->wave_apply && !one_split) {
@@ -212,7 +216,8 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       p->short_half = half ? half == 1 : by32 > num_cu() || (2 * by32 > num_cu() && N > 320);
       const long long groups = BH * (p->short_half ? 2 : d / 32), blocks = (N + 15) / 16, waves = d / 16;
       const long long rounds = (groups + num_cu() - 1) / num_cu();
-      if (N * rounds <= env_int("LINFUSION_WIDE_SHORT_TOKENS", 512)) {
+      const bool pays = d != 96 || dtype != LINFUSION_DTYPE_F16 || rounds <= 3 || (rounds <= 5 && N <= 64);
+      if (pays && N * rounds <= env_int("LINFUSION_WIDE_SHORT_TOKENS", 512)) {
         const long long useful = (blocks + waves - 1) / waves, fit = num_cu() / groups;
         p->short_parts = (int)(useful < fit ? useful : (fit > 1 ? fit : 1));
       }

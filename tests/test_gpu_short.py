@@ -76,9 +76,12 @@ def test_the_state_alone_has_the_bits_of_the_calls(B, H, N, d, dtype, keys):
     assert torch.equal(left, alone)
 
 
-@pytest.mark.parametrize("B,H,N,d,launches", [(2, 8, 256, 160, 1), (2, 8, 513, 160, 3), (50, 8, 256, 96, 3), (50, 8, 128, 96, 1)])
+@pytest.mark.parametrize("B,H,N,d,launches", [(2, 8, 256, 160, 1), (2, 8, 513, 160, 3), (50, 8, 128, 128, 1), (50, 8, 129, 128, 3),
+                                                (50, 8, 256, 96, 3), (48, 8, 128, 96, 1), (50, 8, 128, 96, 3),
+                                                (50, 8, 64, 96, 1), (50, 8, 65, 96, 3), (80, 8, 64, 96, 1), (81, 8, 64, 96, 3)])
 def test_which_calls_are_short(B, H, N, d, launches):
-    """512 tokens while all workgroups run at once, fewer for more heads; the forced split path is never short."""
+    """512 tokens while all workgroups run at once, fewer for more heads (96 fp16 channels: no more than three rounds of
+    them, or five of 64 tokens); the forced split path is never short."""
     x = torch.zeros(B, H, N, d, dtype=torch.float16, device="cuda")
     out = torch.empty_like(x)
     ws = torch.empty(lf.linfusion_attn_workspace_bytes(B, H, N, d, lf.DTYPE_F16), dtype=torch.uint8, device="cuda")
