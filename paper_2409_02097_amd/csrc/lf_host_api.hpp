@@ -53,6 +53,13 @@ inline Share even_share(long long n_tiles, long long most, int waves, int blk, b
   return Share{(int)s, (int)(b * waves)};
 }
 
+// Whether per-head kernels of that many heads keep nearly all of two workgroups per CU busy with a multiple of eight of them
+// per head, so that the heads' workgroups which share cache lines of a token-major tensor share an XCD too.
+inline bool heads_fill(long long heads) {
+  const long long all = 2 * num_cu(), even = all / heads / 8 * 8;
+  return 20 * even * heads >= 17 * all;
+}
+
 // true when the byte ranges [a, a + na) and [b, b + nb) share a byte
 inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;

@@ -839,21 +839,33 @@ lf::Layout device_layout(const Strides& s, int H, size_t esz) {
   return lf::Layout{s.b / vec, s.h / vec, (int)(s.n / vec), H};
 }
 
-// MB of tensor traffic (q, k, v and out together) from which the row-piece kernels are picked.  A lone head's rows
-// leave part of every 128-byte line to its neighbours, which the L2 makes good while a token's heads run side by side;
-// the row pieces need no such luck, but start later (a group's prologue) and at d = 56 and 80 move four heads per
-// workgroup.  Measured on token-major tensors, per-head time over row-piece time at MB per tensor:
-//   d = 8, 16, 24         5.5 MB 0.93 to 1.03, 10 MB 1.17 to 1.31
-//   d = 32 (half lines)   7 MB 0.83, 15 MB 0.87 to 0.89, 30 MB 1.03 to 1.08
-//   d = 40, 48            eight heads and more: 7 MB 0.97 to 1.09, 15 MB 1.01 to 1.17, 30 MB 1.3 to 1.5;
-//                         four heads: 7 MB 0.94 to 0.96, 15 MB 0.93 to 1.03, 30 MB 1.02 to 1.18
-//   d = 56                7 MB 0.73 to 0.76, 15 MB 0.89 to 0.99, 30 MB 1.06 to 1.15
-//   d = 80                7 MB 0.77 to 0.90, 15 MB 0.75 to 0.88, 30 MB 0.77 to 1.01, 60 MB 0.96 to 1.24,
-//                         120 MB 1.16 to 1.18
-constexpr int group_min_mb(int d, int heads) {
-  if (d <= 24) return 24;
-  if (d == 40 || d == 48) return heads >= 8 ? 24 : 80;
-  return d <= 56 ? 80 : 240;
+// MB of one tensor from which the row-piece kernels are picked.  A lone head's rows leave part of every 128-byte line to its
+// neighbours, which the L2 makes good while a token's heads run side by side; the row pieces need no such luck, but start
+// later (a group's prologue), move four heads per workgroup where H is no multiple of eight or d = 80, and leave the heads
+// beyond whole groups to a second launch each of reduction and apply.  Measured on token-major tensors, one to sixteen
+// batches of 4 to 32 heads, both types, inputs from memory: per-head time over row-piece time at MB per tensor, where the
+// per-head kernels fill the chip (lfh::heads_fill; 4 heads set apart) -- and where they do not:
+//   d = 8, 16, 24   6 MB 0.89 to 1.30, 9 MB 0.95 to 1.36; 4 heads 8 MB 0.88 to 1.19, 10 MB 0.90 to 1.22 -- 6 MB 0.91 to 2.1
+//   d = 32          22 MB 0.87 to 1.02, 30 MB 0.95 to 1.12; 4 heads 30 MB 0.91 to 0.93, 42 MB 1.00 to 1.34 -- 12 MB 0.88 to
+//                   1.14, 15 MB 1.00 to 1.26
+//   d = 40          groups of eight 11 MB 0.97 to 1.15, 13 MB 0.98 to 1.07, of four 15 MB 0.90 to 1.02, 18 MB 0.95 to 1.06 --
+//                   9 MB 0.95 to 1.04, 11 MB 0.96 to 1.16
+//   d = 48          18 MB 0.86 to 1.10, 21 MB 0.98 to 1.12 -- 15 MB 0.98 to 1.18, 18 MB 0.96 to 1.22
+//   d = 56          22 MB 0.86 to 1.17, 26 MB 0.95 to 1.27 -- 18 MB 0.96 to 1.13, 20 MB 0.95 to 1.21
+//   d = 80          60 MB 0.94 to 1.15, 70 MB 0.99 to 1.21 -- 35 MB 0.98 to 1.08, 42 MB 1.04 to 1.11
+// and with heads left over (5 to 18 of them): d = 8 9 MB 0.72 to 1.65, 13 MB 0.83 to 1.45, d = 16 18 MB 0.82 to 1.53, d = 24
+// 13 MB 0.67 to 1.15, 45 MB 0.98 to 1.64, d = 32 70 MB 0.79 to 1.21, d = 40 45 MB 0.84 to 1.32, 70 MB 0.96 to 1.45, d = 48 45
+// MB 0.77 to 1.11, 70 MB 0.91 to 1.30, d = 56 70 MB 0.83 to 1.10, 110 MB 0.91 to 1.34, d = 80 110 MB 0.74 to 0.96, 170 MB
+// 0.87 to 1.13.
+int group_min_mb(int d, int B, int H) {
+  const bool fill = lfh::heads_fill((long long)B * H);
+  if (H % 4 != 0) return d <= 8 ? 12 : d <= 16 ? 20 : d <= 24 ? 30 : d <= 32 ? 75 : d <= 48 ? 55 : d <= 56 ? 90 : 150;
+  if (d <= 24) return fill && H == 4 ? 10 : 6;
+  if (d <= 32) return fill ? (H == 4 ? 40 : 28) : 14;
+  if (d <= 40) return fill ? (H % 8 == 0 ? 13 : 18) : 11;
+  if (d <= 48) return fill ? 21 : 17;
+  if (d <= 56) return fill ? 25 : 19;
+  return fill ? 62 : 40;
 }
 
 // `sq`, `skv`, `so`: strides of q, of k and v, and of out; null = contiguous [B, H, N, d]
@@ -894,9 +906,8 @@ int fwd_impl(const void* q, const void* k, const void* v, void* out, int B, int 
   // single heads would touch as scattered fragments.  (Not used by the single-launch kernel, so a
   // forced single launch keeps the one-head-per-workgroup mapping.)
   auto heads_adjacent = [&](const Strides& s) { return p.groups > 0 && s.h == d && s.n > d; };
-  // From which size on depends on how much of a line a lone head wastes (see group_min_mb).
-  const double tensor_bytes = 4.0 * (double)B * H * (double)N * d * (double)esz;
-  const bool big = tensor_bytes >= (double)env_int("LINFUSION_GROUP_MIN_MB", group_min_mb(d, H)) * 1048576.0;
+  const double tensor_bytes = (double)B * H * (double)N * d * (double)esz;
+  const bool big = tensor_bytes >= (double)env_int("LINFUSION_GROUP_MIN_MB", group_min_mb(d, B, H)) * 1048576.0;
   const int group_mode = env_int("LINFUSION_HEAD_GROUPS", 1);   // 1 = by size, 2 = never, 3 = whenever possible
   const bool frag = (group_mode == 3 || (group_mode == 1 && big)) && dtype != LINFUSION_DTYPE_F32 &&
                     (d * esz) % 128 != 0 && !(flags & LINFUSION_FLAG_FORCE_FUSED);

@@ -40,8 +40,9 @@ def test_wide_partials(B, H, N, d, dtype):
 @pytest.mark.parametrize("B,H,N,d,dtype", [(1, 8, 20001, 40, "f16"), (2, 8, 9000, 48, "bf16"), (1, 4, 33333, 80, "bf16"),
                                            (1, 12, 20000, 24, "f16"), (1, 16, 70000, 8, "f16")])
 @pytest.mark.parametrize("normalize", [True, False])
-def test_row_pieces_build_their_operands(B, H, N, d, dtype, normalize):
+def test_row_pieces_build_their_operands(B, H, N, d, dtype, normalize, monkeypatch, tuning):
     print(f"rows direct B={B} H={H} N={N} d={d} {dtype}", flush=True)
+    monkeypatch.setenv("LINFUSION_HEAD_GROUPS", "3")     # row pieces at every size
     q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=131, device="cpu")
     if not normalize:
         v = v * 0.02            # keeps the un-normalized sums inside fp16's range
