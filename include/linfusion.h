@@ -146,8 +146,9 @@ int linfusion_attn_fwd_ex(const void* q, const void* k, const void* v, void* out
  * Speed: 16-bit tensors whose heads are neighbours in memory (head stride == d) and whose head rows are
  * not whole 128-byte lines (d = 40, say) are moved in groups of 4 or 8 heads as whole contiguous row
  * pieces once the problem is large enough for that to pay (6 to 62 MB per tensor, by width and heads;
- * up to 150 MB where H is no multiple of 4); they then run as fast as the contiguous layout.  Results there may differ from the
- * contiguous call's in the last bits (another summation order); they stay run-to-run identical.
+ * up to 150 MB where H is no multiple of 4); they then run as fast as the contiguous layout.  Results
+ * there may differ from the contiguous call's in the last bits (another summation order); they stay
+ * run-to-run identical.
  */
 int linfusion_attn_fwd_strided(const void* q, const void* k, const void* v, void* out,
                                int B, int H, long long N, int d,
@@ -214,9 +215,9 @@ int linfusion_attn_bwd(const void* q, const void* k, const void* v, const void* 
  * accepted).  Same arithmetic and order as the contiguous call: dense strides give bit-identical results.
  * Speed: where the heads of a token are neighbours in memory (head stride == d, the UNet's [B, N, H*d]), a head's
  * row is no whole number of 128-byte lines (d * 2 % 128 != 0: d = 40, 80, ...), H is a multiple of 4 and a tensor
- * is large enough (from 4 MB up to d = 32, 7 or 12 MB at d = 40, more above), the gradients come from kernels that
- * move whole row pieces of four or eight neighbouring heads: the forward state (when not handed in), dQ, dK and dV for every width up to 56 and 80, the state gradient
- * in the same kernel as dQ for fp16 up to d = 48 and bf16 up to d = 40 (forward and backward of 12 x 8 x 4096 x 40
+ * is large enough (from 4 to 18 MB up to d = 48, 20 to 340 MB above, by width, type and heads), the gradients come
+ * from kernels that move whole row pieces of four or eight neighbouring heads: the forward state (when not handed in),
+ * dQ, dK and dV for every width up to 56 and 80, the state gradient in the same kernel as dQ for fp16 up to d = 48 and bf16 up to d = 40 (forward and backward of 12 x 8 x 4096 x 40
  * token-major: bf16 167 us with a state-gradient kernel of its own, 133 so).  These kernels sum the state and its gradient over the tiles in another order
  * than the per-head kernels, so the gradients may differ from the contiguous call's in the last bit; they stay
  * run-to-run identical.  Head counts that are no multiple of 4 run the per-head kernels on partial lines, at a

@@ -122,28 +122,43 @@ struct BwdArgs {
 
 // The row-piece kernels run one workgroup of W waves per group and tile, with a longer prologue than the per-head
 // kernels, and pay once the lines that a lone head's rows leave half used no longer meet in the L2.  MB per tensor from
-// which they are picked; measured on token-major tensors, a gradient call with the per-head kernels over one with the
-// row pieces:
-//   d = 8 .. 32          3 MB 1.05, 5 MB 1.05 to 1.24, 8 MB 1.27 to 1.70 (d = 32, 15 MB: 1.12)
-//   d = 40, 48 (fp16)    by eight heads 3 MB 1.05, 5 MB 0.99 to 1.01, 8 MB 1.05 to 1.11, 15 MB 1.2 to 1.33;
-//                        by four 5 MB 0.91 to 0.96, 8 MB 0.97 to 1.05, 15 MB 1.07 to 1.24
-//   d = 48 (bf16)        two kernels for dQ and its state: 5 MB 0.89, 15 MB 1.0, 30 MB 1.17
-//   d = 56               fp16 15 MB 0.97, 30 MB 1.06; bf16 15 MB 0.85, 30 MB 0.91, 60 MB 1.02
-//   d = 80               fp16 15 to 30 MB 0.74, 60 MB 0.84, 120 MB 0.93 to 1.0; bf16 30 MB 0.96 to 1.07, 60 MB 1.02
+// which they are picked.  Measured on token-major tensors, one to sixteen batches of 4 to 32 heads, inputs from memory: a
+// gradient call with the per-head kernels over one with the row pieces at MB per tensor, where the per-head kernels fill the
+// chip (lfh::heads_fill) -- and where they do not:
+//   d = 8, 16, 24   4 MB 0.92 to 1.49 (eight heads of 16 channels 0.80, 6 MB 0.91), 4 heads 6 MB 0.81 to 1.26, 8 MB 0.84 to
+//                   1.54 -- 4 MB 1.03 to 2.1
+//   d = 32          groups of eight 12 MB 0.88 to 1.15, 15 MB 0.96 to 1.19, of four 9 MB 0.98 to 1.07, 4 heads 16 MB 0.83 to
+//                   0.86, 18 MB 1.00 to 1.28, 22 MB 0.95 -- 5 MB 0.94 to 1.16, 6 MB 0.99 to 1.06
+//   d = 40          groups of eight 9 MB 0.95 to 1.05, 11 MB 1.09 to 1.23, of four 13 MB 0.92 to 1.03, 16 MB 0.96 to 1.10 --
+//                   eight 7 MB 0.96 to 1.12, four 10 MB 0.90 to 1.11, 13 MB 1.10 to 1.20
+//   d = 48 fp16     groups of eight 12 MB 0.96 to 1.03, of four 14 MB 1.02 to 1.05, 4 heads 16 MB 0.92 to 17 MB 1.24 -- eight 9
+//                   MB 0.94 to 1.08, four 12 MB 1.00
+//   d = 48 bf16     (two kernels for dQ and its state) 14 MB 0.94 to 1.05, 16 MB 0.94 to 1.04 -- 13 MB 0.96 to 1.06
+//   d = 56 fp16     groups of eight 32 MB 0.90 to 1.02, 40 MB 0.98 to 1.09, of four 24 MB 0.96 to 1.07 -- 18 MB 0.95 to 1.02,
+//                   24 MB 1.01 to 1.19
+//   d = 56 bf16     groups of eight 140 MB 0.92 to 1.02, of four 60 MB 1.04 to 1.06, 4 heads 75 MB 0.95 to 1.14 -- eight 75 MB
+//                   0.96 to 1.03, four 55 MB 1.02
+//   d = 80 fp16     300 MB 0.92 to 1.08, 420 MB 1.01 to 1.13 (12, 20, 28 heads 220 MB 0.98 to 1.06) -- 220 MB 0.92 to 1.01, 300
+//                   MB 1.00 to 1.04
+//   d = 80 bf16     110 MB 0.99 to 1.15 (12, 20, 28 heads 80 MB 0.97 to 1.10) -- 48 MB 1.00 to 1.04
 template <typename T>
-constexpr int rows_min_mb(int d, int heads) {
+int rows_min_mb(int d, int B, int H) {
   constexpr bool bf16 = lf::NSplit<T>::value != 1;
-  if (d <= 32) return 4;
-  if (d <= 40 || (d <= 48 && !bf16)) return heads % 8 == 0 ? 7 : 12;
-  if (d <= 48) return 20;
-  if (d <= 56) return bf16 ? 60 : 24;
-  return bf16 ? 48 : 160;
+  const bool fill = lfh::heads_fill((long long)B * H), eight = H % 8 == 0, four = H == 4;
+  if (d <= 24) return fill && four ? 7 : (fill && eight && d == 16 ? 6 : 4);
+  if (d <= 32) return fill ? (four ? 18 : eight ? 15 : 9) : 6;
+  if (d <= 40) return eight ? (fill ? 10 : 7) : (fill ? 15 : 11);
+  if (d <= 48) return bf16 ? (fill ? 16 : 13) : eight ? (fill ? 12 : 9) : (fill ? 15 : 12);
+  if (d <= 56 && !bf16) return fill ? (eight ? 36 : 24) : 20;
+  if (d <= 56) return fill ? (eight ? 150 : four ? 75 : 60) : (eight ? 85 : 55);
+  if (!bf16) return fill ? (eight || four ? 340 : 200) : 250;
+  return fill ? (eight || four ? 110 : 80) : 46;
 }
 
 template <typename T>
 bool rows_pay(const BwdArgs& a, int d) {
   return (double)a.B * a.H * (double)a.N * d * 2.0 >=
-         (double)lfh::env_int("LINFUSION_BWD_ROWS_MIN_MB", rows_min_mb<T>(d, a.H)) * 1048576.0;
+         (double)lfh::env_int("LINFUSION_BWD_ROWS_MIN_MB", rows_min_mb<T>(d, a.B, a.H)) * 1048576.0;
 }
 
 // dK, dV: the row-piece kernel on groups of W heads where the heads of a token are neighbours in memory (k, v and

@@ -26,11 +26,11 @@ def _knob(monkeypatch, name, value):
 
 # (H, d, type, MB of one tensor from which the row pieces are due: forward, backward)
 # (one batch; groups of eight and of four heads, heads left over (forward only); 24 heads do not fill the chip one by one)
-LINES = [(8, 16, "f16", 6, 4), (8, 32, "bf16", 28, 4), (8, 40, "f16", 13, 7), (4, 40, "bf16", 18, 12), (8, 48, "f16", 21, 7),
-         (8, 48, "bf16", 21, 20), (8, 56, "f16", 25, 24), (4, 56, "bf16", 25, 60), (4, 80, "bf16", 62, 48),
-         (4, 24, "f16", 10, None), (24, 32, "f16", 14, None), (12, 40, "bf16", 18, None), (24, 40, "f16", 11, None),
-         (24, 48, "bf16", 17, None), (24, 56, "f16", 19, None), (24, 80, "f16", 40, None), (5, 16, "bf16", 20, None),
-         (10, 40, "f16", 55, None), (10, 48, "bf16", 55, None)]
+LINES = [(8, 16, "f16", 6, 6), (8, 32, "bf16", 28, 15), (8, 40, "f16", 13, 10), (4, 40, "bf16", 18, 15), (8, 48, "f16", 21, 12),
+         (8, 48, "bf16", 21, 16), (8, 56, "f16", 25, 36), (4, 56, "bf16", 25, 75), (4, 80, "bf16", 62, 110),
+         (4, 24, "f16", 10, 7), (24, 32, "f16", 14, 6), (12, 40, "bf16", 18, 15), (24, 40, "f16", 11, 7),
+         (24, 48, "bf16", 17, 13), (24, 56, "f16", 19, 20), (24, 80, "f16", 40, 250), (8, 80, "f16", 62, 340),
+         (5, 16, "bf16", 20, None), (10, 40, "f16", 55, None), (10, 48, "bf16", 55, None)]
 
 
 @pytest.mark.parametrize("above", [False, True])
