@@ -166,7 +166,8 @@ def launch_floor(reps=200):
     return res
 
 
-PATH_NAMES = {0: "three kernels", 1: "single launch with barriers", 2: "replicated-state single launch"}
+PATH_NAMES = {0: "three kernels", 1: "single launch with barriers", 2: "replicated-state single launch",
+              3: "one launch for short streams"}
 PAPER_CONFIGS = ["sd15_256_f32", "sd15_512_f16", "sd21_768_f16", "sd21_768_f16_peaky", "sdxl_2048_A_bf16",
                  "sdxl_2048_B_bf16"]
 
@@ -356,7 +357,9 @@ def main():
     rname = ("state_reduce32s" if dtype == "f32" else "state_reduce16") + tag
     aname = lf.linfusion_attn_apply_kernel(B, H, N, d, code, args.flags) + tag
     mid = "combine_state + pack_state16" if aname.startswith("apply16_packed") else "combine_state"
-    if d > 80:
+    if aname.startswith("short16"):
+        rname, mid, aname = aname, "(one launch)", "(one launch)"
+    elif d > 80:
         rname = rname.replace("state_reduce16<", "state_reduce16_wide<")
         if (N + 31) // 32 <= 2:
             mid = "(no combine: one workgroup per head wrote the state)"
@@ -367,9 +370,9 @@ def main():
         mid = "combine_state + pack_state16"
     half = alg_bytes / 2      # K+V read by the reduction; Q read + out written by apply
     kernels = [
-        {"name": rname, "ms": kms[0], "alg_bytes": half},
+        {"name": rname, "ms": kms[0], "alg_bytes": alg_bytes if plan["path"] == 3 else half},
         {"name": mid, "ms": kms[1], "alg_bytes": 0},
-        {"name": aname, "ms": kms[2], "alg_bytes": half},
+        {"name": aname, "ms": kms[2], "alg_bytes": 0 if plan["path"] == 3 else half},
     ]
     for kk in kernels:
         kk["gbps"] = kk["alg_bytes"] / (kk["ms"] * 1e-3) / 1e9 if kk["ms"] > 0 else None

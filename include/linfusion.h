@@ -453,17 +453,18 @@ void linfusion_set_tuning(int on);
 /*
  * Introspection for benchmarks and tests (host only, no device work): the launch plan the
  * forward call will use for this shape.  plan[0] = path (0 = split-N three-kernel path,
- * 1 = single launch with barriers, 2 = replicated-state launch), plan[1] = state-reduction workgroups per
- * head, plan[2] = apply workgroups per head (on the single-launch paths both are its workgroups per head),
- * plan[3] = tokens per tile.  Returns LINFUSION_OK or an error code.
+ * 1 = single launch with barriers, 2 = replicated-state launch, 3 = one launch for short streams at widths
+ * above 80), plan[1] = state-reduction workgroups per head, plan[2] = apply workgroups per head (on the
+ * single-launch paths both are its workgroups per head), plan[3] = tokens per tile.  Returns LINFUSION_OK or
+ * an error code.
  */
 int linfusion_attn_plan(int B, int H, long long N, int d, int dtype, unsigned flags, int plan[4]);
 
 /*
- * Name of the kernel that will run the apply step for this shape on contiguous tensors ("apply16_dma",
- * "apply16_packed", "apply32", "apply32s", "apply16_wide", "apply16_wave", or "fused16" / "fused32" / "solo16" / "solo32" when a single
- * launch is chosen); an empty string for rejected arguments.  (A short call at a width above 80 that runs as one launch has
- * no apply kernel: the name is that of its split path.)  Static storage.  For benchmarks and profile summaries.
+ * Name of the kernel that will run the apply step for this shape on contiguous tensors, not in place ("apply16_dma",
+ * "apply16_packed", "apply32", "apply32s", "apply16_wide", "apply16_wave", or "fused16" / "fused32" / "solo16" / "solo32" /
+ * "short16" when a single launch is chosen); an empty string for rejected arguments.  Static storage.  For benchmarks and
+ * profile summaries.
  */
 const char* linfusion_attn_apply_kernel(int B, int H, long long N, int d, int dtype, unsigned flags);
 

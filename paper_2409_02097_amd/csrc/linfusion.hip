@@ -1166,6 +1166,7 @@ void linfusion_set_tuning(int on) { g_tuning.store(on ? 1 : 0, std::memory_order
 const char* linfusion_attn_apply_kernel(int B, int H, long long N, int d, int dtype, unsigned flags) {
   Plan p;
   if (make_plan(B, H, N, d, dtype, flags, &p) != LINFUSION_OK) return "";
+  if (p.short_parts > 0) return "short16";
   if (is_wide(d)) return p.wave_apply ? "apply16_wave" : "apply16_wide";
   if (p.path == 2) return dtype == LINFUSION_DTYPE_F32 ? "solo32" : "solo16";
   if (p.path == 1) return dtype == LINFUSION_DTYPE_F32 ? "fused32" : "fused16";
@@ -1178,6 +1179,12 @@ int linfusion_attn_plan(int B, int H, long long N, int d, int dtype, unsigned fl
   Plan p;
   int rc = make_plan(B, H, N, d, dtype, flags, &p);
   if (rc != LINFUSION_OK) return rc;
+  if (p.short_parts > 0) {
+    plan[0] = 3;
+    plan[1] = plan[2] = p.short_parts * (p.short_half ? 2 : d / 32);
+    plan[3] = 64;   // Short16Cfg::kTokens
+    return LINFUSION_OK;
+  }
   plan[0] = p.path;
   plan[1] = p.path == 2 ? p.solo_g : (p.path == 1 ? p.fsplits : p.splits);
   plan[2] = p.path == 2 ? p.solo_g : (p.path == 1 ? p.fsplits : p.apply_wgs);

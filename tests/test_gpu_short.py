@@ -86,4 +86,9 @@ def test_which_calls_are_short(B, H, N, d, launches):
     out = torch.empty_like(x)
     ws = torch.empty(lf.linfusion_attn_workspace_bytes(B, H, N, d, lf.DTYPE_F16), dtype=torch.uint8, device="cuda")
     assert _launches(lambda: lf.linfusion_attn_fwd_ex(x, x, x, out, 0, 1e-6, 0, ws)) == launches
+    # ... and what the library says it runs
+    plan = lf.linfusion_attn_plan(B, H, N, d, lf.DTYPE_F16)
+    assert (plan["path"] == 3) == (launches == 1)
+    assert lf.linfusion_attn_apply_kernel(B, H, N, d, lf.DTYPE_F16) == ("short16" if launches == 1 else "apply16_wave")
+    assert lf.linfusion_attn_plan(B, H, N, d, lf.DTYPE_F16, lf.FLAG_FORCE_SPLIT)["path"] == 0
     assert _launches(lambda: lf.linfusion_attn_fwd_ex(x, x, x, out, 0, 1e-6, lf.FLAG_FORCE_SPLIT, ws)) >= 2

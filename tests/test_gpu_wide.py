@@ -46,11 +46,11 @@ def test_wide_heads_match_oracle(B, H, N, d, dtype):
                                            (1, 3, 1030, 128, "bf16"), (1, 2, 700, 96, "f16"), (1, 2, 65, 96, "bf16"),
                                            (2, 2, 515, 160, "bf16")])
 def test_workgroup_shared_apply_where_the_wave_apply_is_the_default(B, H, N, d, dtype, waves, monkeypatch, tuning):
-    """These shapes run apply16_wave (a wave per tile) by default; the workgroup-shared apply16_wide, which the
+    """These shapes run apply16_wave (a wave per tile) on the split path; the workgroup-shared apply16_wide, which the
     MLP-fed call at these widths is built on, is checked on them as well."""
     print(f"shared-tile apply B={B} H={H} N={N} d={d} {dtype} waves={waves}", flush=True)
     code = wl.DTYPE_CODE[dtype]
-    assert lf.linfusion_attn_apply_kernel(B, H, N, d, code) == "apply16_wave"
+    assert lf.linfusion_attn_apply_kernel(B, H, N, d, code, lf.FLAG_FORCE_SPLIT) == "apply16_wave"
     monkeypatch.setenv("LINFUSION_WIDE_WAVE_APPLY", "2")
     monkeypatch.setenv("LINFUSION_WIDE_APPLY_WAVES", str(waves))
     assert lf.linfusion_attn_apply_kernel(B, H, N, d, code) == "apply16_wide"
