@@ -11,13 +11,18 @@ from tests import parity
 pytestmark = pytest.mark.gpu
 
 
-# partials per head with 256 compute units: 1, 1, 2, 4, 5, 11, 18
+# partials per head with 256 compute units: 1, 1, 2, 4, 5, 11, 18 (the first four shapes are one launch without partials
+# unless that is switched off, for the call and for the state alone)
+@pytest.mark.parametrize("short", [True, False])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("B,H,N,d", [(2, 8, 64, 160), (12, 16, 70, 160), (8, 16, 200, 96), (4, 16, 300, 128),
                                      (4, 10, 777, 96), (1, 16, 2001, 160), (1, 4, 1100, 128)])
-def test_wide_partials(B, H, N, d, dtype):
-    print(f"wide partials B={B} H={H} N={N} d={d} {dtype}", flush=True)
+def test_wide_partials(B, H, N, d, dtype, short, monkeypatch, tuning):
+    print(f"wide partials B={B} H={H} N={N} d={d} {dtype} short={short}", flush=True)
     code = wl.DTYPE_CODE[dtype]
+    if not short:
+        monkeypatch.setenv("LINFUSION_WIDE_SHORT_TOKENS", "1")
+        assert lf.linfusion_attn_plan(B, H, N, d, code)["path"] == 0
     q, k, v = (t.cuda() for t in wl.make_qkv(B, H, N, d, dtype, idx=130))
     size = lf.linfusion_attn_workspace_bytes(B, H, N, d, code)
     ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")

@@ -25,18 +25,20 @@ SHAPES = [
 ]
 
 
+# (above width 80 up to 512 tokens are one launch, unless the split path is asked for)
+@pytest.mark.parametrize("flags", [0, lf.FLAG_FORCE_SPLIT])
 @pytest.mark.parametrize("B,H,N,d,dtype", SHAPES)
-def test_wide_heads_match_oracle(B, H, N, d, dtype):
-    print(f"wide B={B} H={H} N={N} d={d} {dtype}", flush=True)
+def test_wide_heads_match_oracle(B, H, N, d, dtype, flags):
+    print(f"wide B={B} H={H} N={N} d={d} {dtype} flags={flags}", flush=True)
     q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=70, device="cpu")
     qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
     out = torch.full_like(qd, float("nan"))
-    lf.linfusion_attn_fwd_ex(qd, kd, vd, out, 0, 1e-6, 0, _ws(B, H, N, d, dtype))
+    lf.linfusion_attn_fwd_ex(qd, kd, vd, out, 0, 1e-6, flags, _ws(B, H, N, d, dtype))
     torch.cuda.synchronize()
     worst = parity.check_all(out, q, k, v, dtype, 0, 1e-6, True, f"wide N={N} d={d} {dtype}")
     print(f"  worst max-norm ratio {worst[0]:.2e}, rel L2 {worst[1]:.2e}", flush=True)
     out2 = torch.full_like(qd, float("nan"))
-    lf.linfusion_attn_fwd_ex(qd, kd, vd, out2, 0, 1e-6, 0, _ws(B, H, N, d, dtype))
+    lf.linfusion_attn_fwd_ex(qd, kd, vd, out2, 0, 1e-6, flags, _ws(B, H, N, d, dtype))
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.uint8), out2.view(torch.uint8)), "not run-to-run identical"
 
@@ -198,8 +200,9 @@ def test_wide_fp16_keys_far_below_zero(case, d):
         print(f"{case} d={d} eps={eps}: worst max-norm ratio {worst[0]:.2e}, rel L2 {worst[1]:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("flags", [0, lf.FLAG_FORCE_SPLIT])
 @pytest.mark.parametrize("d,dtype", [(160, "f16"), (160, "bf16"), (96, "bf16")])
-def test_wide_nan_stays_where_it_belongs(d, dtype):
+def test_wide_nan_stays_where_it_belongs(d, dtype, flags):
     """A NaN in one query row reaches that token's outputs only (the row's maximum, which scales the row, skips it and
     the other rows are bit-identical to a clean run); a NaN in a key poisons its own head and no other."""
     B, H, N = 1, 3, 333
@@ -207,11 +210,11 @@ def test_wide_nan_stays_where_it_belongs(d, dtype):
     qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
     ws = _ws(B, H, N, d, dtype)
     clean = torch.full_like(qd, float("nan"))
-    lf.linfusion_attn_fwd_ex(qd, kd, vd, clean, 0, 1e-6, 0, ws)
+    lf.linfusion_attn_fwd_ex(qd, kd, vd, clean, 0, 1e-6, flags, ws)
     qn = qd.clone()
     qn[0, 1, 200, 17] = float("nan")
     out = torch.full_like(qd, float("nan"))
-    lf.linfusion_attn_fwd_ex(qn, kd, vd, out, 0, 1e-6, 0, ws)
+    lf.linfusion_attn_fwd_ex(qn, kd, vd, out, 0, 1e-6, flags, ws)
     torch.cuda.synchronize()
     assert bool(torch.isnan(out[0, 1, 200]).all()), "the poisoned token must not produce numbers"
     keep = torch.ones(B, H, N, dtype=torch.bool, device="cuda")
@@ -219,7 +222,7 @@ def test_wide_nan_stays_where_it_belongs(d, dtype):
     assert torch.equal(out[keep].view(torch.uint8), clean[keep].view(torch.uint8)), "other tokens changed"
     kn = kd.clone()
     kn[0, 2, 100, 5] = float("nan")
-    lf.linfusion_attn_fwd_ex(qd, kn, vd, out, 0, 1e-6, 0, ws)
+    lf.linfusion_attn_fwd_ex(qd, kn, vd, out, 0, 1e-6, flags, ws)
     torch.cuda.synchronize()
     assert bool(torch.isnan(out[0, 2]).all()), "the poisoned head must not produce numbers"
     assert torch.equal(out[0, :2].view(torch.uint8), clean[0, :2].view(torch.uint8)), "other heads changed"
@@ -245,7 +248,8 @@ def test_wide_heads_token_major_and_in_place(N, d, dtype):
 
 @pytest.mark.parametrize("d,dtype", [(80, "f16"), (160, "f16"), (160, "bf16"), (96, "bf16")])
 @pytest.mark.parametrize("fm,normalize", [(1, True), (2, True), (0, False)])
-def test_wide_heads_other_feature_maps_and_unnormalized(d, dtype, fm, normalize):
+@pytest.mark.parametrize("flags", [0, lf.FLAG_FORCE_SPLIT])
+def test_wide_heads_other_feature_maps_and_unnormalized(d, dtype, fm, normalize, flags):
     B, H, N = 1, 2, 300
     q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=72, device="cpu")
     if fm == 2:
@@ -254,7 +258,7 @@ def test_wide_heads_other_feature_maps_and_unnormalized(d, dtype, fm, normalize)
         v = v * 0.01          # keeps the un-normalized sums inside fp16's range
     qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
     out = torch.full_like(qd, float("nan"))
-    lf.linfusion_attn_fwd_ex(qd, kd, vd, out, fm, 1e-6, 0 if normalize else lf.FLAG_UNNORMALIZED, _ws(B, H, N, d, dtype))
+    lf.linfusion_attn_fwd_ex(qd, kd, vd, out, fm, 1e-6, flags | (0 if normalize else lf.FLAG_UNNORMALIZED), _ws(B, H, N, d, dtype))
     torch.cuda.synchronize()
     parity.check_all(out, q, k, v, dtype, fm, 1e-6, normalize, f"wide d={d} fm={fm} norm={normalize}")
 
