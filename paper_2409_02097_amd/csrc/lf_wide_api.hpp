@@ -12,8 +12,8 @@ struct WidePlan {
   int splits, blk_reduce, apply_wgs, blk_apply;
   int apply_waves;            // waves per apply workgroup: 4 or 8 (apply16_wide)
   bool wave_apply;            // apply16_wave (a wave per tile, the whole state in its registers) instead
-  int short_parts;            // > 0: the whole forward call in one launch (lf_short16.hpp), that many workgroups per 32
-  bool short_half;            // value channels of a head, or per half of them
+  int short_parts;            // > 0: the whole forward call in one launch (lf_short16.hpp), that many workgroups per group of
+  bool short_half;            // value channels: 32 of a head, or half of the head's
 };
 
 // state reduction + combine:  state[bh] = {S = sum_t phi(k_t)^T v_t, z = sum_t phi(k_t)}, fp32 [d*d + d]

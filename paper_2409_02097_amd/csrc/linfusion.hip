@@ -86,8 +86,8 @@ struct Plan {
   int gwaves, groups, gsplits, gblk_reduce, gapply_wgs, gblk_apply;
   int apply_waves;      // waves per workgroup of the per-head apply (packed: 1, 2 or 4; else 4 or 8)
   bool wave_apply;      // widths above 80: apply16_wave (a wave per tile) instead of apply16_wide
-  int short_parts;      // widths above 80: > 0, one launch of so many workgroups per 32 value channels of a head (short16),
-  bool short_half;      //   or per half of the channels
+  int short_parts;      // widths above 80: > 0, one launch (short16) of so many workgroups per group of value channels: 32
+  bool short_half;      //   of a head, or half of the head's
   bool gapply_packed;   // row-piece apply from operands prepared by pack_state16 (many short-lived workgroups)
   bool apply_packed;    // per-head apply from operands prepared by pack_state16 (many short-lived workgroups)
   long long n_tiles;
@@ -152,6 +152,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   if (!supported_d(d, dtype)) return LINFUSION_ERR_UNSUPPORTED;
   if (N > (1LL << 40) / d) return LINFUSION_ERR_INVALID;
   const long long BH = (long long)B * H;
+  const int cus = num_cu();   // (asks the runtime for the current device: once per plan)
   const int tile = dtype == LINFUSION_DTYPE_F32 ? lf::kTile32 : lf::kTile;
   p->n_tiles = (N + tile - 1) / tile;
   if (is_wide(d)) {
@@ -170,7 +171,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       const double bytes = 4.0 * (double)BH * (double)N * d * 2.0;
       if (d <= 128 && bytes >= 768.0 * 1048576.0) reduce_per_cu = (d <= 96 && dtype == LINFUSION_DTYPE_BF16) ? 4 : 3;
     }
-    const int fill = reduce_per_cu * num_cu(), want = lfw::wide_reduce_wgs(BH, p->n_tiles, d, fill, num_cu());
+    const int fill = reduce_per_cu * cus, want = lfw::wide_reduce_wgs(BH, p->n_tiles, d, fill, cus);
     // (the entry point with the fixed scratch array keeps asking for what the chip-filling launch needs, so that it
     // takes and refuses the shapes that it always did)
     int room = want < fill && compact ? per_head(fill, 4, "LINFUSION_WIDE_REDUCE_BLK", &p->blk_reduce) : 0;
@@ -190,12 +191,12 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
       // (d = 96 leaves room for a second workgroup per CU: at 2^18 tokens of 8 heads apply 166 -> 157 us; measured
       // slower at d = 128 and 160)
       const bool two_per_cu = d <= 96 && 4.0 * (double)BH * (double)N * d * 2.0 >= 768.0 * 1048576.0;
-      const lfh::Share sh = even_share(p->n_tiles, env_int("LINFUSION_WIDE_APPLY_WGS", (two_per_cu ? 2 : 1) * num_cu()) / BH,
+      const lfh::Share sh = even_share(p->n_tiles, env_int("LINFUSION_WIDE_APPLY_WGS", (two_per_cu ? 2 : 1) * cus) / BH,
                                        lf::kWavesPerWG, env_int("LINFUSION_WIDE_APPLY_BLK", lf::kWavesPerWG));
       p->apply_wgs = sh.wgs;
       p->blk_apply = sh.blk;
     } else {
-      p->apply_wgs = per_head(env_int("LINFUSION_WIDE_APPLY_WGS", 2 * num_cu()), 1, "LINFUSION_WIDE_APPLY_BLK", &p->blk_apply);
+      p->apply_wgs = per_head(env_int("LINFUSION_WIDE_APPLY_WGS", 2 * cus), 1, "LINFUSION_WIDE_APPLY_BLK", &p->blk_apply);
     }
     // One launch for short streams (not where a switch of the three launches is set: those are asked for then).  A workgroup
     // walks all of a head's tokens, about 0.6 us per 32 of them, so up to 512 tokens as long as all workgroups run at once
@@ -213,12 +214,12 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     if (!compact && !(flags & LINFUSION_FLAG_FORCE_SPLIT) && p->wave_apply && !one_split) {
       const int half = env_int("LINFUSION_WIDE_SHORT_HALF", 0);   // 1: always, 2: never
       const long long by32 = BH * (d / 32);
-      p->short_half = half ? half == 1 : by32 > num_cu() || (2 * by32 > num_cu() && N > 320);
+      p->short_half = half ? half == 1 : by32 > cus || (2 * by32 > cus && N > 320);
       const long long groups = BH * (p->short_half ? 2 : d / 32), blocks = (N + 15) / 16, waves = d / 16;
-      const long long rounds = (groups + num_cu() - 1) / num_cu();
+      const long long rounds = (groups + cus - 1) / cus;
       const bool pays = d != 96 || dtype != LINFUSION_DTYPE_F16 || rounds <= 3 || (rounds <= 5 && N <= 64);
       if (pays && N * rounds <= env_int("LINFUSION_WIDE_SHORT_TOKENS", 512)) {
-        const long long useful = (blocks + waves - 1) / waves, fit = num_cu() / groups;
+        const long long useful = (blocks + waves - 1) / waves, fit = cus / groups;
         p->short_parts = (int)(useful < fit ? useful : (fit > 1 ? fit : 1));
       }
     }
@@ -262,13 +263,13 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     if (dtype == LINFUSION_DTYPE_F32) reduce_per_cu = d <= 8 ? 4 : 2;
     else if (d <= 24 || (dtype == LINFUSION_DTYPE_BF16 && d <= 40)) reduce_per_cu = 8;
   }
-  p->splits = per_head(env_int("LINFUSION_REDUCE_WGS", reduce_per_cu * num_cu()), "LINFUSION_REDUCE_BLK", 16, &p->blk_reduce);
+  p->splits = per_head(env_int("LINFUSION_REDUCE_WGS", reduce_per_cu * cus), "LINFUSION_REDUCE_BLK", 16, &p->blk_reduce);
   // (the entry point with the fixed scratch array asks for a partial per workgroup of equal shares, so that it takes and
   // refuses the shapes that it always did)
   int room = p->splits;
   if (compact) {
     const long long most = (p->n_tiles + lf::kWavesPerWG - 1) / lf::kWavesPerWG;
-    long long s = reduce_per_cu * num_cu() / BH;
+    long long s = reduce_per_cu * cus / BH;
     s = s > most ? most : (s < 1 ? 1 : s);
     const long long t = (p->n_tiles + s - 1) / s, parts = (p->n_tiles + t - 1) / t;
     if (parts > room) room = (int)parts;
@@ -277,7 +278,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   // Up to a few hundred MB of tensor traffic one resident round measured best (a second, partly filled
   // round costs more than its finer balance gains); beyond that eight workgroups per CU.
   const bool one_round = bytes < (double)env_int("LINFUSION_APPLY_ONE_ROUND_MB", 768) * 1048576.0;
-  const int apply_dflt = (one_round ? apply_wgs_per_cu(d, dtype) : 8) * num_cu();
+  const int apply_dflt = (one_round ? apply_wgs_per_cu(d, dtype) : 8) * cus;
   // Large 16-bit problems: the head's operands are packed once (pack_state16) and apply runs as many short-lived
   // workgroups of about 16 tiles each, dealt out by the hardware in order, so that the chip reads and writes one
   // narrow moving window (measured on the 2 M-token workload: 443 us against 488 us for 2048 long-lived
@@ -312,16 +313,16 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     const int wgs8 = per_head(env_int("LINFUSION_APPLY_WGS", apply_want / 2), "LINFUSION_APPLY_BLK", blk_dflt, &blk8, 8);
     auto tiles_of_a_cu = [&](int wgs, int waves) {
       const long long rounds = (p->n_tiles + (long long)wgs * waves - 1) / ((long long)wgs * waves);
-      return ((long long)wgs * BH + num_cu() - 1) / num_cu() * rounds * waves;
+      return ((long long)wgs * BH + cus - 1) / cus * rounds * waves;
     };
-    if (waves8 == 8 || (p->apply_wgs * BH > num_cu() && tiles_of_a_cu(wgs8, 8) <= tiles_of_a_cu(p->apply_wgs, 4))) {
+    if (waves8 == 8 || (p->apply_wgs * BH > cus && tiles_of_a_cu(wgs8, 8) <= tiles_of_a_cu(p->apply_wgs, 4))) {
       p->apply_waves = 8;
       p->apply_wgs = wgs8;
       p->blk_apply = blk8;
     }
   }
   // fused single launch: every workgroup must be resident at once
-  const long long cap = (long long)fused_wgs_per_cu(d, dtype) * num_cu();
+  const long long cap = (long long)fused_wgs_per_cu(d, dtype) * cus;
   p->fsplits = 0;
   if (BH <= cap && !compact) {
     p->fsplits = per_head((int)(cap / BH * BH), "LINFUSION_REDUCE_BLK", 16, &p->fblk_reduce);
@@ -343,17 +344,17 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     // (the widths and sizes that take more reduction workgroups per CU above do here as well: four, eight at d = 8;
     // token-major bf16 8 x 40 at 2 M tokens 0.999 -> 0.971 ms, d = 24 0.616 -> 0.556, fp16 d = 8 0.577 -> 0.407)
     const int greduce_per_cu = reduce_per_cu == 8 ? (d <= 8 ? 8 : 4) : 2;
-    p->gsplits = per_group(env_int("LINFUSION_GROUP_REDUCE_WGS", greduce_per_cu * num_cu()) / unit,
+    p->gsplits = per_group(env_int("LINFUSION_GROUP_REDUCE_WGS", greduce_per_cu * cus) / unit,
                            "LINFUSION_GROUP_REDUCE_BLK", 2, &p->gblk_reduce);
     // up to a few hundred MB one workgroup of eight waves (two of four) per CU; large problems as many short-lived
     // workgroups of about `kGroupTilesPerWG` tiles each (the hardware deals them out in order: one narrow moving
     // window of memory, as for the per-head apply; 2 M tokens of 8 x 40: 472 -> 445 us); tiles dealt out one at
     // a time
     constexpr long long kGroupTilesPerWG = 8;
-    long long gwant = 2 * num_cu();
+    long long gwant = 2 * cus;
     if (!one_round && p->groups * p->n_tiles / kGroupTilesPerWG * unit > gwant)
       gwant = p->groups * p->n_tiles / kGroupTilesPerWG * unit;
-    p->gapply_packed = gwant > 2 * num_cu();
+    p->gapply_packed = gwant > 2 * cus;
     if (gwant > (1 << 24)) gwant = 1 << 24;
     p->gapply_wgs = per_group(env_int("LINFUSION_GROUP_APPLY_WGS", (int)gwant) / unit, "LINFUSION_GROUP_APPLY_BLK",
                               p->gwaves == 8 ? 1 : 2, &p->gblk_apply);
@@ -378,7 +379,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   p->solo_g = 0;
   if (d <= 64 && !compact && BH <= 32768) {
     const int waves = lfs::solo_waves(d, dtype);
-    long long g = num_cu() / BH;
+    long long g = cus / BH;
     const long long blocks = (p->n_tiles + waves - 1) / waves;
     if (g > blocks) g = blocks;
     if (g < 1) g = 1;
@@ -390,7 +391,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     // (LINFUSION_FLAG_FORCE_SOLO; LINFUSION_SOLO_MAX_KB under the tuning switch): a launch that needs no workspace
     // content, no barrier and no ticket, e.g. for capture into a graph of very small layers.
     const double kv_head = 2.0 * (double)N * d * (double)esz;
-    const bool solo_pays = kv_head <= (double)env_int("LINFUSION_SOLO_MAX_KB", 0) * 1024.0 && BH <= num_cu() &&
+    const bool solo_pays = kv_head <= (double)env_int("LINFUSION_SOLO_MAX_KB", 0) * 1024.0 && BH <= cus &&
                            env_int("LINFUSION_SOLO_MAX_KB", 0) > 0;
     if (p->solo_g > 0 && !(flags & (LINFUSION_FLAG_FORCE_SPLIT | LINFUSION_FLAG_FORCE_FUSED)) &&
         ((flags & LINFUSION_FLAG_FORCE_SOLO) || solo_pays))
@@ -906,13 +907,16 @@ int fwd_impl(const void* q, const void* k, const void* v, void* out, int B, int 
   // single heads would touch as scattered fragments.  (Not used by the single-launch kernel, so a
   // forced single launch keeps the one-head-per-workgroup mapping.)
   auto heads_adjacent = [&](const Strides& s) { return p.groups > 0 && s.h == d && s.n > d; };
-  const double tensor_bytes = (double)B * H * (double)N * d * (double)esz;
-  const bool big = tensor_bytes >= (double)env_int("LINFUSION_GROUP_MIN_MB", group_min_mb(d, B, H)) * 1048576.0;
-  const int group_mode = env_int("LINFUSION_HEAD_GROUPS", 1);   // 1 = by size, 2 = never, 3 = whenever possible
-  const bool frag = (group_mode == 3 || (group_mode == 1 && big)) && dtype != LINFUSION_DTYPE_F32 &&
-                    (d * esz) % 128 != 0 && !(flags & LINFUSION_FLAG_FORCE_FUSED);
-  const bool group_reduce = frag && heads_adjacent(lkv);
-  const bool group_apply = frag && heads_adjacent(lo) && heads_adjacent(lq);
+  bool group_reduce = heads_adjacent(lkv), group_apply = heads_adjacent(lo) && heads_adjacent(lq);
+  if (group_reduce || group_apply) {
+    const double tensor_bytes = (double)B * H * (double)N * d * (double)esz;
+    const bool big = tensor_bytes >= (double)env_int("LINFUSION_GROUP_MIN_MB", group_min_mb(d, B, H)) * 1048576.0;
+    const int group_mode = env_int("LINFUSION_HEAD_GROUPS", 1);   // 1 = by size, 2 = never, 3 = whenever possible
+    const bool frag = (group_mode == 3 || (group_mode == 1 && big)) && dtype != LINFUSION_DTYPE_F32 &&
+                      (d * esz) % 128 != 0 && !(flags & LINFUSION_FLAG_FORCE_FUSED);
+    group_reduce = group_reduce && frag;
+    group_apply = group_apply && frag;
+  }
   // (where the row-piece kernels are due -- large token-major tensors -- they go before the replicated-state launch,
   // whose per-head accesses would touch the rows as fragments)
   if (p.path == 2 && (group_reduce || group_apply) && !(flags & LINFUSION_FLAG_FORCE_SOLO)) p.path = 0;

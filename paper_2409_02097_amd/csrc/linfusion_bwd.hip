@@ -54,6 +54,7 @@ int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   }
   const long long BH = (long long)B * H;
   const long long n_tiles = (N + lf::kTile - 1) / lf::kTile;
+  const int cus = lfh::num_cu();   // (asks the runtime for the current device)
   auto per_head = [&](int want_total, int blk_dflt, int* blk) {
     // (rounded down: one workgroup too many costs a whole extra round)
     const lfh::Share sh = lfh::even_share(n_tiles, want_total / BH, lf::kWavesPerWG, blk_dflt, d % 64 != 0);
@@ -63,13 +64,13 @@ int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   // Launch sizes measured on MI355X: up to a few hundred MB of tensor traffic two workgroups per CU (one resident
   // round) are best for the gradient kernels too; at GB sizes four (dQ, dK/dV) and eight (state gradient) per CU.
   const bool mid = 4.0 * (double)BH * (double)N * d * 2.0 < (double)lfh::env_int("LINFUSION_APPLY_ONE_ROUND_MB", 768) * 1048576.0;
-  p->splits = per_head(lfh::env_int("LINFUSION_REDUCE_WGS", 2 * lfh::num_cu()), lfh::env_int("LINFUSION_REDUCE_BLK", 16),
+  p->splits = per_head(lfh::env_int("LINFUSION_REDUCE_WGS", 2 * cus), lfh::env_int("LINFUSION_REDUCE_BLK", 16),
                        &p->blk_reduce);
-  p->gsplits = per_head(lfh::env_int("LINFUSION_BWD_REDUCE_WGS", (mid ? 2 : 8) * lfh::num_cu()),
+  p->gsplits = per_head(lfh::env_int("LINFUSION_BWD_REDUCE_WGS", (mid ? 2 : 8) * cus),
                         lfh::env_int("LINFUSION_BWD_REDUCE_BLK", 16), &p->gblk_reduce);
-  p->apply_wgs = per_head(lfh::env_int("LINFUSION_BWD_APPLY_WGS", (mid ? 2 : 4) * lfh::num_cu()),
+  p->apply_wgs = per_head(lfh::env_int("LINFUSION_BWD_APPLY_WGS", (mid ? 2 : 4) * cus),
                           lfh::env_int("LINFUSION_BWD_APPLY_BLK", 8), &p->blk_apply);
-  p->apply1_wgs = per_head(lfh::env_int("LINFUSION_BWD_APPLY1_WGS", lfh::num_cu()),
+  p->apply1_wgs = per_head(lfh::env_int("LINFUSION_BWD_APPLY1_WGS", cus),
                            lfh::env_int("LINFUSION_BWD_APPLY1_BLK", 8), &p->blk_apply1);
   p->ne = (size_t)d * d + d;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -81,7 +82,7 @@ int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   // workgroups: 81 us at 4096 tokens of 40 fp16 channels, 33 us with all of the chip.)
   if (H % 4 == 0 && d <= 48 && (d * 2) % 128 != 0) {
     const int w = H % 8 == 0 ? 8 : 4;
-    const long long rows = (long long)lfh::num_cu() * (d <= 16 ? 2 : 1) * (8 / w) / ((long long)B * (H / w));
+    const long long rows = (long long)cus * (d <= 16 ? 2 : 1) * (8 / w) / ((long long)B * (H / w));
     if (rows > most) most = (int)(rows < n_tiles ? rows : n_tiles);
   }
   p->most = most;
