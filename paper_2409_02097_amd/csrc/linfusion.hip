@@ -85,6 +85,7 @@ struct Plan {
   // heads, one wave per head; workgroups per group
   int gwaves, groups, gsplits, gblk_reduce, gapply_wgs, gblk_apply;
   int apply_waves;      // waves per workgroup of the per-head apply (packed: 1, 2 or 4; else 4 or 8)
+  int apply_wgs4, blk_apply4;   // where that is 8: the launch shape with four (see waves_of_a_token_major_apply)
   bool wave_apply;      // widths above 80: apply16_wave (a wave per tile) instead of apply16_wide
   int short_parts;      // widths above 80: > 0, one launch (short16) of so many workgroups per group of value channels: 32
   bool short_half;      //   of a head, or half of the head's
@@ -303,6 +304,8 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   }
   p->apply_wgs = per_head(env_int("LINFUSION_APPLY_WGS", apply_want), "LINFUSION_APPLY_BLK", blk_dflt, &p->blk_apply,
                           p->apply_waves);
+  p->apply_wgs4 = p->apply_wgs;
+  p->blk_apply4 = p->blk_apply;
   // Where a CU has two workgroups of four waves or more, workgroups of eight: the state is staged, and made into operands, half
   // as often (us per call, four waves -> eight: fp16 2 x 8 x 16384 x 40 24.7 -> 24.1, bf16 29.5 -> 27.7, 1 x 8 x 100000 x 40 54.5 ->
   // 53.2, 6 x 16 x 2500 x 48 28.1 -> 25.9), unless that leaves some CU with more tiles, as it does where eight waves are one
@@ -869,6 +872,22 @@ int group_min_mb(int d, int B, int H) {
   return fill ? 62 : 40;
 }
 
+// Workgroups of eight waves are half as many per head.  Where that gives up a multiple of eight, the workgroups that walk the
+// same tokens of neighbouring heads no longer share an XCD, whose L2 made one fetch of the lines that the heads of a
+// token-major tensor share: four waves then (us per call, eight waves / four: 2 x 20 x 6072 x 8, 12 or 24 workgroups per
+// head, 20.8 / 17.7; 12 x 10 x 6488 x 8, 4 or 8, 48.8 / 43.1; 8 x 5 x 5509 x 24, 11 or 24, 31.8 / 27.5; 3 x 20 x 3542 x 56, 4 or
+// 8, 50.1 / 43.7; 3 x 8 x 8476 x 48, 17 or 40, 38.7 / 36.7; but 3 x 16 x 975 x 32, 4 or 8, 12.2 / 13.3 and 3 x 12 x 4766 x 40, 10
+// or 24, 34.7 / 36.0).  On contiguous tensors eight waves stay.  The results have the same bits.
+void waves_of_a_token_major_apply(Plan& p, const Strides& lq, const Strides& lo, int d, size_t esz) {
+  const bool shared = ((lq.h == d && lq.n > d) || (lo.h == d && lo.n > d)) && d * esz % 128 != 0;
+  if (p.apply_waves != 8 || !shared || p.apply_wgs4 % 8 != 0 || p.apply_wgs % 8 == 0 ||
+      env_int("LINFUSION_APPLY_WAVES", 0) != 0)
+    return;
+  p.apply_waves = 4;
+  p.apply_wgs = p.apply_wgs4;
+  p.blk_apply = p.blk_apply4;
+}
+
 // `sq`, `skv`, `so`: strides of q, of k and v, and of out; null = contiguous [B, H, N, d]
 int fwd_impl(const void* q, const void* k, const void* v, void* out, int B, int H, long long N, int d, int dtype,
              int feature_map, float eps, unsigned flags, void* workspace, size_t workspace_bytes, void* stream,
@@ -920,6 +939,7 @@ int fwd_impl(const void* q, const void* k, const void* v, void* out, int B, int 
   // (where the row-piece kernels are due -- large token-major tensors -- they go before the replicated-state launch,
   // whose per-head accesses would touch the rows as fragments)
   if (p.path == 2 && (group_reduce || group_apply) && !(flags & LINFUSION_FLAG_FORCE_SOLO)) p.path = 0;
+  waves_of_a_token_major_apply(p, lq, lo, d, esz);
   Args a{q, k, v, out, (long long)B * H, N, feature_map, eps, (flags & LINFUSION_FLAG_UNNORMALIZED) != 0,
          &p, (unsigned char*)workspace, nullptr, (hipStream_t)stream, ev,
          device_layout(lq, H, esz), device_layout(lkv, H, esz), device_layout(lo, H, esz), group_reduce, group_apply};

@@ -1,4 +1,6 @@
 """Which token-major calls go to the row-piece kernels: the line of every width, from both sides."""
+import ctypes
+
 import pytest
 import torch
 
@@ -71,3 +73,47 @@ def test_row_pieces_from_their_line_up(H, d, dtype, fwd_mb, bwd_mb, above, monke
     for a, b, c in zip(*got):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
         assert (a.float() - c.float()).abs().max().item() <= ulp2 * c.float().abs().max().item()
+
+
+class _KernelNode(ctypes.Structure):      # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def _block_sizes(call):
+    """Threads per workgroup of every kernel that the call records into a graph."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)   # the one torch runs on
+    hip = ctypes.CDLL(path)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    sizes = []
+    for node in nodes:
+        p = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        sizes.append(p.block[0])
+    return sizes
+
+
+# workgroups per head with four waves and with eight on 256 compute units: 24 and 12, 8 and 4, 24 and 11; 16 and 8, 20 and 10, 32 and 16
+@pytest.mark.parametrize("B,H,N,d,waves", [(2, 20, 6072, 8, 4), (3, 20, 3542, 56, 4), (8, 5, 5509, 24, 4), (4, 8, 2000, 24, 8),
+                                           (3, 16, 2500, 40, 8), (4, 8, 4000, 40, 8)])
+def test_waves_of_the_token_major_apply(B, H, N, d, waves):
+    """Eight where the workgroups of neighbouring heads then still share an XCD, and always on contiguous tensors; the
+    results have the same bits."""
+    print(f"apply waves {B}x{H}x{N}x{d}", flush=True)
+    tm = [_token_major(B, H, N, d, "f16") for _ in range(3)]
+    dense = [t.contiguous() for t in tm]
+    ws = torch.empty(lf.linfusion_attn_workspace_bytes(B, H, N, d, lf.DTYPE_F16), dtype=torch.uint8, device="cuda")
+    outs = []
+    for ins, expect in ((tm, waves), (dense, 8)):
+        outs.append(torch.full_like(ins[0], float("nan")))
+        sizes = _block_sizes(lambda: lf.linfusion_attn_fwd_strided(*ins, outs[-1], 0, 1e-6, 0, ws))
+        assert sizes[-1] == 64 * expect, sizes
+        lf.linfusion_attn_fwd_strided(*ins, outs[-1], 0, 1e-6, 0, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].contiguous().view(torch.int16), outs[1].view(torch.int16))
