@@ -146,7 +146,7 @@ int linfusion_attn_fwd_ex(const void* q, const void* k, const void* v, void* out
  * Speed: 16-bit tensors whose heads are neighbours in memory (head stride == d) and whose head rows are
  * not whole 128-byte lines (d = 40, say) are moved in groups of 4 or 8 heads as whole contiguous row
  * pieces once the problem is large enough for that to pay (6 to 62 MB per tensor, by width and heads;
- * up to 150 MB where H is no multiple of 4); they then run as fast as the contiguous layout.  Results
+ * up to 170 MB where H is no multiple of 4); they then run as fast as the contiguous layout.  Results
  * there may differ from the contiguous call's in the last bits (another summation order); they stay
  * run-to-run identical.
  */

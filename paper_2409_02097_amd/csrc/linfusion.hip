@@ -857,13 +857,17 @@ lf::Layout device_layout(const Strides& s, int H, size_t esz) {
 //   d = 48          18 MB 0.86 to 1.10, 21 MB 0.98 to 1.12 -- 15 MB 0.98 to 1.18, 18 MB 0.96 to 1.22
 //   d = 56          22 MB 0.86 to 1.17, 26 MB 0.95 to 1.27 -- 18 MB 0.96 to 1.13, 20 MB 0.95 to 1.21
 //   d = 80          60 MB 0.94 to 1.15, 70 MB 0.99 to 1.21 -- 35 MB 0.98 to 1.08, 42 MB 1.04 to 1.11
-// and with heads left over (5 to 18 of them): d = 8 9 MB 0.72 to 1.65, 13 MB 0.83 to 1.45, d = 16 18 MB 0.82 to 1.53, d = 24
-// 13 MB 0.67 to 1.15, 45 MB 0.98 to 1.64, d = 32 70 MB 0.79 to 1.21, d = 40 45 MB 0.84 to 1.32, 70 MB 0.96 to 1.45, d = 48 45
-// MB 0.77 to 1.11, 70 MB 0.91 to 1.30, d = 56 70 MB 0.83 to 1.10, 110 MB 0.91 to 1.34, d = 80 110 MB 0.74 to 0.96, 170 MB
-// 0.87 to 1.13.
+// and with heads left over (5 to 18 of them), in the same order:
+//   d = 8           13 MB 0.83 to 0.98, 15 MB 1.04 -- 9 MB 0.90 to 1.65
+//   d = 16, 24      22 MB 0.89 to 0.94, 45 MB 0.97 to 1.57 -- 13 MB 0.83 to 1.15, d = 16 18 MB 1.07 to 1.53, d = 24 45 MB 1.15
+//   d = 32          45 MB 0.69 to 0.84, 70 MB 0.79 to 1.16 -- 45 MB 0.87 to 1.02, 70 MB 0.99 to 1.21
+//   d = 40, 48      45 MB 0.77 to 0.99, 60 MB 1.00 to 1.19 -- d = 40 24 MB 0.81 to 1.01, 45 MB 1.04, d = 48 45 MB 0.91 to 1.11
+//   d = 56          70 MB 0.83 to 0.94, 110 MB 0.91 to 1.34 -- 45 MB 0.82 to 0.98, 70 MB 0.95 to 1.10
+//   d = 80          120 MB 0.78, 170 MB 0.87 to 1.13 -- 110 MB 0.87 to 0.96, 170 MB 0.95 to 1.06
 int group_min_mb(int d, int B, int H) {
   const bool fill = lfh::heads_fill((long long)B * H);
-  if (H % 4 != 0) return d <= 8 ? 12 : d <= 16 ? 20 : d <= 24 ? 30 : d <= 32 ? 75 : d <= 48 ? 55 : d <= 56 ? 90 : 150;
+  if (H % 4 != 0 && fill) return d <= 8 ? 15 : d <= 16 ? 26 : d <= 24 ? 34 : d <= 32 ? 70 : d <= 48 ? 60 : d <= 56 ? 95 : 170;
+  if (H % 4 != 0) return d <= 8 ? 8 : d <= 16 ? 13 : d <= 24 ? 20 : d <= 32 ? 55 : d <= 40 ? 36 : d <= 48 ? 50 : d <= 56 ? 70 : 160;
   if (d <= 24) return fill && H == 4 ? 10 : 6;
   if (d <= 32) return fill ? (H == 4 ? 40 : 28) : 14;
   if (d <= 40) return fill ? (H % 8 == 0 ? 13 : 18) : 11;

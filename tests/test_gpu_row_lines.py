@@ -32,7 +32,8 @@ LINES = [(8, 16, "f16", 6, 6), (8, 32, "bf16", 28, 15), (8, 40, "f16", 13, 10), 
          (8, 48, "bf16", 21, 16), (8, 56, "f16", 25, 36), (4, 56, "bf16", 25, 75), (4, 80, "bf16", 62, 110),
          (4, 24, "f16", 10, 7), (24, 32, "f16", 14, 6), (12, 40, "bf16", 18, 15), (24, 40, "f16", 11, 7),
          (24, 48, "bf16", 17, 13), (24, 56, "f16", 19, 20), (24, 80, "f16", 40, 250), (8, 80, "f16", 62, 340),
-         (5, 16, "bf16", 20, None), (10, 40, "f16", 55, None), (10, 48, "bf16", 55, None)]
+         (5, 16, "bf16", 26, None), (10, 40, "f16", 60, None), (10, 48, "bf16", 60, None), (18, 8, "f16", 8, None),
+         (18, 40, "bf16", 36, None)]
 
 
 @pytest.mark.parametrize("above", [False, True])
