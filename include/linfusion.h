@@ -101,7 +101,7 @@ extern "C" {
  * At head widths above 80 calls of up to 512 tokens (fewer for many heads) are one kernel without any exchange, unless
  * LINFUSION_FLAG_FORCE_SPLIT: workgroups that split a head's value channels.  It leaves the state in the workspace like
  * the other paths and may be captured; its sums run in another order than the split path's, so that output and state differ
- * from the forced split path's in the last bits.  In place (out == q) such a call is three kernels with the bits of the one.
+ * from the forced split path's in the last bits.  In place (out == q) such a call is two or three kernels with the bits of the one.
  *
  *   dtype            LINFUSION_DTYPE_*; accumulation is fp32 for every dtype.
  *   feature_map      LINFUSION_PHI_*.

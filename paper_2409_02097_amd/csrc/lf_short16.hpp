@@ -310,4 +310,16 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long kbat
   }
 }
 
+// Rows of CPR 16-byte chunks of every head, one after the other.  grid = (whole rows / 256 chunks, heads), block = 256;
+// `chunks`: of one head.
+template <int CPR>
+__global__ void __launch_bounds__(kThreads)
+copy_rows(const u32x4* __restrict__ X, long long batch, long long head, int row, unsigned heads, unsigned chunks,
+          u32x4* __restrict__ Y) {
+  const unsigned c = blockIdx.x * kThreads + threadIdx.x;
+  if (c >= chunks) return;
+  const HeadAt at(blockIdx.y, heads);
+  Y[(long long)at.index * chunks + c] = X[at.slice(batch, head) + (long long)(c / CPR) * row + c % CPR];
+}
+
 }  // namespace lf

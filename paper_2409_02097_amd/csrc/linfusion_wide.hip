@@ -150,10 +150,32 @@ int run(const WideArgs& a) {
   const WideReduceArgs r{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.lkv, a.lkv, a.partials, a.state, a.plan, a.st};
   if (a.plan.short_parts > 0) {
     if (a.out && a.out != a.q) return run_short<T, D>(a);
+    if (!a.out) return state_of_short<T, D>(r, a.ev);
+    // In place a workgroup of the one launch would read query rows that others have written a part of.  Where the room for
+    // partial states, which this launch does not use, holds the queries, it reads a copy of them, unless heads of more than
+    // 128 tokens take it a second round (us per call, the split path / the same state, then the apply kernel / a copy:
+    // bf16 1 x 5 x 439 x 96 15.9 / 19.1 / 15.3, fp16 2 x 8 x 256 x 160 22.9 / 20.5 / 15.1, 12 x 8 x 256 x 160 31.4 / 28.3 / 28.2,
+    // 25 x 8 x 100 x 160 31.8 / 32.0 / 29.8, 20 x 8 x 200 x 160 38.2 / 38.2 / 42.8).
+    constexpr int CPR = D / 8;
+    const bool rounds = (long long)a.B * a.H * (a.plan.short_half ? 2 : D / 32) > lfh::num_cu();
+    if ((!rounds || a.N <= 128) && (long long)a.plan.splits * (D * D + D) * 4 >= a.N * D * 2) {
+      if (a.ev) (void)hipEventRecord(a.ev[0], a.st);
+      lf::u32x4* copy = (lf::u32x4*)a.partials;
+      const unsigned chunks = (unsigned)(a.N * CPR);
+      lf::copy_rows<CPR><<<dim3((chunks + lf::kThreads - 1) / lf::kThreads, (unsigned)((long long)a.B * a.H)), dim3(lf::kThreads),
+                           0, a.st>>>((const lf::u32x4*)a.q, a.lq.batch, a.lq.head, a.lq.row,
+                                      (unsigned)a.H | (unsigned)a.H << 16, chunks, copy);
+      WideArgs b = a;
+      b.q = copy;
+      b.lq = lf::Layout{(long long)a.H * chunks, (long long)chunks, CPR, a.H};
+      b.ev = nullptr;
+      const int rc = run_short<T, D>(b);
+      if (a.ev) { (void)hipEventRecord(a.ev[1], a.st); (void)hipEventRecord(a.ev[2], a.st); (void)hipEventRecord(a.ev[3], a.st); }
+      return rc;
+    }
+    // Else the same state, then the apply of a wave per tile, whose arithmetic is the same.
     int rc = state_of_short<T, D>(r, a.ev);
-    if (rc != LINFUSION_OK || !a.out) return rc;
-    // In place a workgroup of the one launch would read query rows that others have written a part of: the same state, then
-    // the apply of a wave per tile, whose arithmetic is the same.
+    if (rc != LINFUSION_OK) return rc;
     const WideApplyArgs p{a.q, a.out, a.B, a.H, a.N, a.d, a.dtype, a.fm, a.eps, a.unnorm, a.lq, a.lo, a.state, a.packed,
                           a.plan, a.st};
     rc = apply<T, D>(p, 1, nullptr, a.ev ? a.ev + 2 : nullptr);
