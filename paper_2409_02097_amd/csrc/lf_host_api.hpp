@@ -28,22 +28,26 @@ size_t span_bytes(const long long s[3], int B, int H, long long N, int d, size_t
 // us per call, blocks of 16 or 8 tiles whatever the number -> these: bf16 2 x 10 x 16384 x 64 54.0 -> 48.0, fp16 8 x 100000 x
 // 40 60.1 -> 55.8, 20 x 65536 x 64 130.2 -> 124.2, fp32 forward and backward 12 x 8 x 4096 x 40 192.4 -> 183.1; fewest
 // workgroups: fp16 2 x 5 x 9216 x 64 24.0 -> 23.2, fp32 2 x 10 x 16384 x 64 83.9 -> 82.7.
-// `shared_lines`: a head's rows (of a group of heads: its pieces of a row) are no whole 128-byte lines, so that in a
-// token-major tensor neighbouring heads share lines.  Workgroups are dealt to the eight XCDs in turn; with 1, 2, 4 or a multiple of eight
-// workgroups per head, where the same rounds allow it, the workgroups that walk the same tokens of all, every fourth or every
-// second head share an XCD and its L2 (forward and backward of fp16 2 x 10 x 13056 x 16 token-major: 24 workgroups 73 us, 21
-// 80 us; of bf16 12 x 10 x 1094 x 8: 4 workgroups 41.5 us, 3 45.5 us).
+// `row_bytes`: of a head's rows (of a group of heads: its pieces of a row).  Where they are no whole 128-byte lines,
+// neighbouring heads of a token-major tensor share lines.  Workgroups are dealt to the eight XCDs in turn; with 1, 2, 4 or a
+// multiple of eight workgroups per head, where the same rounds allow it, the workgroups that walk the same tokens of all,
+// every fourth or every second head share an XCD and its L2 (forward and backward of fp16 2 x 10 x 13056 x 16 token-major: 24
+// workgroups 73 us, 21 80 us; of bf16 12 x 10 x 1094 x 8: 4 workgroups 41.5 us, 3 45.5 us).  Where eight are too many, rows of
+// up to 48 bytes take a multiple of four, with which every second head shares (forward token-major, bf16: 4 x 10 x 9626 x 16
+// 10 workgroups 32.3 us, 12 28.2; 2 x 12 x 9443 x 8 22.2, 17.8; 1 x 5 x 135255 x 16 56.9, 48.5; wider rows 0.97 to 1.07,
+// contiguous tensors 0.97 to 1.06 either way).
 struct Share { int wgs, blk; };   // blk: in tiles, whole rounds
-inline Share even_share(long long n_tiles, long long most, int waves, int blk, bool shared_lines = false) {
+inline Share even_share(long long n_tiles, long long most, int waves, int blk, long long row_bytes = 0) {
   const long long rounds = (n_tiles + waves - 1) / waves;
   long long s = most < rounds ? most : rounds;
   if (s < 1) s = 1;
   const long long longest = (rounds + s - 1) / s;
   const long long room = s;
   s = (rounds + longest - 1) / longest;
-  if (shared_lines) {
-    const long long even = s <= 2 ? s : (s <= 4 ? 4 : (s + 7) / 8 * 8);
+  if (row_bytes % 128 != 0) {
+    const long long even = s <= 2 ? s : (s <= 4 ? 4 : (s + 7) / 8 * 8), half = (s + 3) / 4 * 4;
     if (even <= room) s = even;
+    else if (row_bytes <= 48 && s > 4 && half <= room) s = half;
   }
   long long b = blk / waves;   // rounds per block
   if (b > longest) b = longest;

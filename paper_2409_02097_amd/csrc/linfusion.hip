@@ -247,7 +247,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   const size_t esz = dtype == LINFUSION_DTYPE_F32 ? 4 : 2;
   auto per_head = [&](int want_total, const char* env_blk, int blk_dflt, int* blk, int waves = lf::kWavesPerWG) {
     // (rounded down: one workgroup too many costs a whole extra round)
-    const lfh::Share sh = even_share(p->n_tiles, want_total / BH, waves, env_int(env_blk, blk_dflt), d * esz % 128 != 0);
+    const lfh::Share sh = even_share(p->n_tiles, want_total / BH, waves, env_int(env_blk, blk_dflt), (long long)(d * esz));
     *blk = sh.blk;
     return sh.wgs;
   };
@@ -338,7 +338,7 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
   if (p->groups > 0) {
     auto per_group = [&](int want_total, const char* env_blk, int blk_dflt, int* blk) {
       const lfh::Share sh = even_share(p->n_tiles, want_total / p->groups, 1, env_int(env_blk, blk_dflt),
-                                       p->gwaves * d * esz % 128 != 0);
+                                       (long long)(p->gwaves * d * esz));
       *blk = sh.blk;
       return sh.wgs;
     };

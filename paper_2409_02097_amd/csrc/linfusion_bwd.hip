@@ -57,7 +57,7 @@ int make_bwd_plan(int B, int H, long long N, int d, int dtype, BwdPlan* p) {
   const int cus = lfh::num_cu();   // (asks the runtime for the current device)
   auto per_head = [&](int want_total, int blk_dflt, int* blk) {
     // (rounded down: one workgroup too many costs a whole extra round)
-    const lfh::Share sh = lfh::even_share(n_tiles, want_total / BH, lf::kWavesPerWG, blk_dflt, d % 64 != 0);
+    const lfh::Share sh = lfh::even_share(n_tiles, want_total / BH, lf::kWavesPerWG, blk_dflt, 2 * d);
     *blk = sh.blk;
     return sh.wgs;
   };
@@ -175,7 +175,7 @@ int launch_kv_rows(const BwdArgs& a, const float* stateD) {
   const long long n_tiles = (a.N + kTile - 1) / kTile;
   const int resident = 160 * 1024 / lds > 0 ? 160 * 1024 / lds : 1;
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
-  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), W * D % 64 != 0);
+  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), 2 * W * D);
   bwd_kv16_rows<T, D, FM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
       stateD, (const u32x4*)a.k, (const u32x4*)a.v, a.N, gpb, sh.blk, (u32x4*)a.dk, (u32x4*)a.dv, a.lkv, a.ldkv);
   return LINFUSION_OK;
@@ -195,7 +195,7 @@ int launch_qs_rows(const BwdArgs& a, const float* stateS, float* partials, int* 
   const int resident = 160 * 1024 / lds > 0 ? 160 * 1024 / lds : 1;
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
   if (wgs > a.p->most) wgs = a.p->most;   // room for the partial states
-  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), W * D % 64 != 0);
+  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), 2 * W * D);
   bwd_qs16_rows<T, D, FM, NORM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
       stateS, (const u32x4*)a.q, (const u32x4*)a.g, a.N, gpb, sh.blk, (u32x4*)a.dq, partials, a.eps, a.lq, a.lg, a.ldq);
   *wgs_used = sh.wgs;
@@ -214,7 +214,7 @@ int launch_q_rows(const BwdArgs& a, const float* stateS, lf::f32x2* scal) {
   const long long n_tiles = (a.N + kTile - 1) / kTile;
   const int resident = 160 * 1024 / lds > 0 ? 160 * 1024 / lds : 1;
   long long wgs = lfh::env_int("LINFUSION_BWD_ROWS_WGS", resident * lfh::num_cu()) / groups;
-  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), W * D % 64 != 0);
+  const lfh::Share sh = lfh::even_share(n_tiles, wgs, 1, lfh::env_int("LINFUSION_BWD_ROWS_BLK", 1), 2 * W * D);
   bwd_q16_rows<T, D, FM, NORM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
       stateS, (const u32x4*)a.q, (const u32x4*)a.g, a.N, gpb, sh.blk, (u32x4*)a.dq, scal, a.eps, a.lq, a.lg, a.ldq);
   return LINFUSION_OK;
@@ -287,7 +287,7 @@ int launch_state_rows(const BwdArgs& a, float* partials, int* nparts) {
   const long long n_tiles = (a.N + kTile - 1) / kTile;
   long long s = lfh::env_int("LINFUSION_GROUP_REDUCE_WGS", 2 * lfh::num_cu()) / (W / kWavesPerWG) / groups;
   if (s > a.p->most) s = a.p->most;   // room for the partial states
-  const lfh::Share sh = lfh::even_share(n_tiles, s, 1, lfh::env_int("LINFUSION_GROUP_REDUCE_BLK", 2), W * D % 64 != 0);
+  const lfh::Share sh = lfh::even_share(n_tiles, s, 1, lfh::env_int("LINFUSION_GROUP_REDUCE_BLK", 2), 2 * W * D);
   state_reduce16_rows<T, D, FM, W><<<dim3((unsigned)sh.wgs, (unsigned)groups), dim3(64 * W), lds, a.st>>>(
       (const u32x4*)a.k, (const u32x4*)a.v, a.lkv.batch, a.lkv.head, a.lkv.row, gpb, sh.blk, a.N, a.H, partials);
   *nparts = sh.wgs;

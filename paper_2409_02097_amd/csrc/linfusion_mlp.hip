@@ -57,7 +57,7 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     p->n_pad = n_tiles * lf::kTile;
     const long long units = (long long)B * (H / 4);
     auto per_group = [&](int want_total, int blk_dflt, int* blk) {
-      const lfh::Share sh = lfh::even_share(n_tiles, want_total / units, 1, blk_dflt, 4 * d % 64 != 0);
+      const lfh::Share sh = lfh::even_share(n_tiles, want_total / units, 1, blk_dflt, 8 * d);
       *blk = sh.blk;
       return sh.wgs;
     };
@@ -85,7 +85,8 @@ int make_mlp_plan(int B, int H, long long N, int d, int dtype, MlpPlan* p) {
     const long long units = (long long)B * H;
     const bool wide = lfm::heads_wide(d);   // there every wave of a workgroup visits every tile of its blocks
     auto per_head = [&](int want_total, int blk_dflt, int* blk) {
-      const lfh::Share sh = lfh::even_share(n_tiles, want_total / units, wide ? 1 : lf::kWavesPerWG, blk_dflt, !wide && d % 64 != 0);
+      const lfh::Share sh = lfh::even_share(n_tiles, want_total / units, wide ? 1 : lf::kWavesPerWG, blk_dflt,
+                                            wide ? 0 : 2 * d);
       *blk = sh.blk;
       return sh.wgs;
     };

@@ -367,10 +367,12 @@ def test_strided_backward_validates_on_the_host():
 
 
 @pytest.mark.parametrize("BH,N,d,dtype", [((2, 10), 16384, 64, 2), ((2, 5), 9216, 64, 1), ((1, 8), 100000, 40, 1),
-                                          ((12, 8), 4096, 40, 0), ((1, 3), 33, 40, 1), ((1, 1), 127 * 32, 64, 1)])
+                                          ((12, 8), 4096, 40, 0), ((1, 3), 33, 40, 1), ((1, 1), 127 * 32, 64, 1), ((4, 10), 9626, 16, 2),
+                                          ((2, 12), 9443, 8, 2), ((8, 5), 5496, 8, 0), ((4, 10), 9626, 40, 2)])
 def test_as_few_workgroups_as_keep_the_longest_wave(BH, N, d, dtype):
     """A head's tiles in rounds of four: no more workgroups than the number of rounds of the longest one calls for (or the
-    next of 1, 2, 4, 8, 16, 24 and so on, where head rows are no whole cache lines), and no more rounds than two workgroups per CU need
+    next of 1, 2, 4, 8, 16, 24 and so on, where head rows are no whole cache lines; of 4, 8, 12 and so on where that is too
+    many and rows are 48 bytes or fewer), and no more rounds than two workgroups per CU need
     (256 while no device is visible)."""
     B, H = BH
     plan = lf.linfusion_attn_plan(B, H, N, d, dtype, lf.FLAG_FORCE_SPLIT)
@@ -378,5 +380,8 @@ def test_as_few_workgroups_as_keep_the_longest_wave(BH, N, d, dtype):
     most = max(1, min(512 // (B * H), rounds))
     least = -(-rounds // -(-rounds // most))
     even = least if least <= 2 else 4 if least <= 4 else -(-least // 8) * 8
-    lines = d * (4 if dtype == 0 else 2) % 128 == 0
-    assert plan["reduce_wgs_per_head"] == (least if lines or even > most else even)
+    row = d * (4 if dtype == 0 else 2)
+    half = -(-least // 4) * 4
+    if even > most:
+        even = half if row <= 48 and half <= most else least
+    assert plan["reduce_wgs_per_head"] == (least if row % 128 == 0 else even)
