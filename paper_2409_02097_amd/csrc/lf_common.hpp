@@ -224,7 +224,8 @@ struct Layout {
 // The head of grid row y, in kernels whose arguments come first to last in the order in which a workgroup needs them, all as
 // plain numbers: the library is built so that the first fourteen 32-bit words of a kernel's arguments are in scalar registers
 // when it starts (a structure would end that), and a workgroup's first loads need not wait for the arguments to be read from
-// memory (us per call: fp16 2 x 8 x 4096 x 40 14.8 -> 14.1, 2 x 5 x 9216 x 64 22.9 -> 21.9, 2 x 8 x 256 x 160 12.7 -> 12.2).
+// memory (500 calls drawn from 0.25 to 3 MB per tensor, with the words preloaded against the same kernels without: forward calls of
+// less than 16 us 2.2 %, in place 2 to 3 %, the state alone 1.2 %, backward 1.5 %).
 // `heads`: heads per batch of this launch, and << 16 those of the arrays that are indexed by head (a launch on some of a
 // batch's heads is given their first one's addresses).
 struct HeadAt {

@@ -1,14 +1,16 @@
 // One launch for short token streams at head widths above 80: no partial states, no exchange between workgroups.
 //   grid = heads x (d / (16 CB)) x parts, block = 4 d threads (one wave per 16 feature channels); CB = 2 or d / 32.
-// A workgroup owns 16 CB value channels of one head.  It computes the columns of the state that belong to them from all of
-// the head's tokens, S[:, cols] = phi(K)^T V[:, cols], and z (Prop. 2, Eq. 5's normalizer), lays them out in LDS as
-// matrix-core operands, and applies them to its part of the head's query tokens, out[:, cols].  Nothing a workgroup needs is
-// computed by another; what is repeated is phi(K), once per group of value channels and part.
+// A workgroup takes 16 CB value channels of one head and a part of its query tokens.  It computes the columns of the state
+// that belong to the channels from all of the head's tokens, S[:, cols] = phi(K)^T V[:, cols], and z (Prop. 2, Eq. 5's
+// normalizer), lays them out in LDS as matrix-core operands, and applies them to its query tokens, out[:, cols].  No workgroup
+// waits for another; what is repeated for that is phi(K) and z, once per group of value channels and part, and the columns of
+// the state once per part.
 //
 // What bounds such a call otherwise is three dependent launches, each with its fill, its round trips to memory and its drain
-// (fp16 2 x 8 x 256 x 160: 8.4 + 6.3 + 8.7 us; one launch 22.6 -> 13.2 us per call).  Here K and V come to LDS through
+// (fp16 2 x 8 x 256 x 160: 8.4 + 6.3 + 8.7 us; per call 22.1 us, one launch 12.4).  Here K and V come to LDS through
 // registers, four rounds of 64 tokens on their way, so that up to 256 tokens are one round trip, and a wave's first query
-// tokens behind them; what bounds it is a round's phi(K), LDS round trip and barrier, 1.3 us, and the launch, 7 us per call.
+// tokens behind them; what bounds it is the chain of rounds, phi(K), LDS round trip and barrier, 1.3 us each, between the
+// launch and the operands (a graph of such calls takes as long as calls one by one, whose host part is 7.1 us).
 //
 // Reduction: a round's phi(K) and V rows are written to LDS by all threads; after a barrier wave w multiplies feature block w
 // with all column blocks (transposing LDS reads, 16x16x32 products, bf16: phi(K) in two terms) and with ones for z.  A wave

@@ -201,11 +201,11 @@ int make_plan(int B, int H, long long N, int d, int dtype, unsigned flags, Plan*
     }
     // One launch for short streams (not where a switch of the three launches is set: those are asked for then).  A workgroup
     // walks all of a head's tokens, about 0.6 us per 32 of them, so up to 512 tokens as long as all workgroups run at once
-    // and proportionally fewer beyond (us per call, three launches -> one, d = 160: fp16 2 x 8 heads at 64 / 256 / 512 / 1024
-    // tokens 20.9 -> 9.0, 22.6 -> 13.2, 24.6 -> 18.5, 26.4 -> 27.7, bf16 21.2 -> 7.6, 23.6 -> 13.4, 26.3 -> 20.7, 28.7 -> 35.7; 20 x
-    // 10 heads fp16 27.6 -> 21.5, 40.3 -> 39.9, 56.9 -> 65.1).  Half of the value channels per workgroup where 32 would take
-    // more than a round, or most of one and many tokens (fp16 12 x 8 x 256 28.9 -> 20.0, 4 x 8 x 512 24.5 -> 21.4, but 2 x 8 x
-    // 256 13.2 -> 15.6 and 4 x 8 x 256 15.5 -> 16.0).  Three launches over one where a second round has begun, inputs from
+    // and proportionally fewer beyond (us per call, three launches -> one, d = 160: fp16 16 heads at 64 / 256 / 512 / 640
+    // tokens 19.6 -> 8.1, 22.8 -> 12.5, 25.2 -> 17.7, 26.9 -> 21.0, bf16 20.6 -> 7.4, 23.9 -> 12.7, 27.6 -> 20.2, 29.4 -> 24.6; 192
+    // heads fp16 at 128 / 256 / 320 tokens 31.6 -> 24.9, 40.2 -> 36.4, 45.8 -> 42.2).  Half of the value channels per workgroup
+    // where 32 would take more than a round, or most of one and many tokens (fp16 96 heads of 256 tokens 28.0 -> 19.0, 32 of 512
+    // 23.6 -> 20.5, but 16 of 256 12.5 -> 15.1 and 32 of 256 14.8 -> 15.5).  Three launches over one where a second round has begun, inputs from
     // memory, 136 / 160 / 200 heads: 256 tokens, d = 160 fp16 0.97, 0.98, 1.01, bf16 1.08 to 1.12, d = 128 1.10 to 1.23, d =
     // 96 1.05 to 1.42; 200 tokens 1.04 to 1.42.  fp16 of 96 channels, whose three launches are the shortest, loses from a
     // fourth round on (448 to 640 heads: 64 tokens 1.10 to 1.13, 100 and 128 tokens 0.84; 768 heads 0.95 to 1.03, 1024 and

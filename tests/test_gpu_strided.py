@@ -16,7 +16,7 @@ SENTINEL = 12345.0
 
 @pytest.fixture(autouse=True)
 def _row_piece_kernels_at_every_size(monkeypatch, tuning):
-    """By default the library keeps the per-head kernels below ~24 MB of tensor traffic; these tests want the
+    """By default the library keeps the per-head kernels for small tensors; these tests want the
     row-piece kernels wherever the layout allows them (the library reads the variable at every call)."""
     monkeypatch.setenv("LINFUSION_HEAD_GROUPS", "3")
 
