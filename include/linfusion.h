@@ -198,7 +198,7 @@ int linfusion_attn_fwd_profile(const void* q, const void* k, const void* v, void
  *   flags           LINFUSION_FLAG_NONE or LINFUSION_FLAG_UNNORMALIZED (anything else -> ERR_INVALID).
  *   workspace       DEVICE scratch of at least linfusion_attn_bwd_workspace_bytes(...) bytes, 16-byte
  *                   aligned, caller-owned, contents undefined before and after.
- * Enqueues up to six kernels (four when `state` is given; fp16 above 80 up to nine, seven) on `stream`; never allocates, never synchronises.  Results are run-to-run identical.
+ * Enqueues up to six kernels (four when `state` is given; fp16 above 80 up to nine, seven, of short streams two, one) on `stream`; never allocates, never synchronises.  Results are run-to-run identical.
  */
 int linfusion_attn_bwd(const void* q, const void* k, const void* v, const void* dout, const float* state,
                        void* dq, void* dk, void* dv,

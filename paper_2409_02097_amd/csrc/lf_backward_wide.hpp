@@ -15,6 +15,7 @@
 //   bwdw_pack (dS, both ways)     summed partials as operands of the next two
 //   the forward's wide apply      dv = dS^T phi(k)
 //   bwdw_k                        reads k, v: writes dk
+// Short streams go another way (lf_bwd_short16.hpp).
 // bwdw_q and bwdw_k are apply16_wave with a second tensor in every ring slot: a wave holds the whole operand-ready state of
 // its head in registers (200 of the 512 a lone wave per SIMD has, at d = 160) and streams 16-token tiles through a ring of
 // its own; a product's results lie channels-of-my-token, so everything elementwise happens where they land, in fp32.

@@ -3,6 +3,7 @@
 #include "../../include/linfusion.h"
 
 #include "lf_backward_wide.hpp"
+#include "lf_bwd_short16.hpp"
 #include "lf_bwdw_api.hpp"
 #include "lf_host_api.hpp"
 #include "lf_wide_api.hpp"
@@ -47,6 +48,20 @@ int make_regions(int B, int H, long long N, int d, int dtype, Regions* r) {
   return LINFUSION_OK;
 }
 
+// Longest stream that the one launch (lf_bwd_short16.hpp) takes.  It costs 4 to 5.5 us per 64 tokens whatever the heads up to
+// 128, where its workgroups fill the chip; the launches below cost a chain of 30 to 45 us, and what their packed states and
+// partials move, which grows with the heads.  us per call with the state given, these launches / that one, fp16:
+//   4 heads of 160:   64 tokens 39.8 / 12.1, 256 42.8 / 28.2, 448 45.1 / 44.3, 512 44.6 / 49.7
+//   16 heads of 96:   64 29.6 / 9.5, 256 32.0 / 20.1, 512 35.0 / 35.1, 640 37.8 / 42.8
+//   40 heads of 128:  640 55.3 / 48.9, 768 58.1 / 57.5, 896 66.6 / 66.0
+//   96 heads of 160:  64 51.6 / 13.1, 256 68.9 / 31.0, 640 107.5 / 65.3
+//   128 heads of 160: 1024 152 / 106;  of 96: 1024 92.7 / 70.0
+//   192 heads of 96 (two rounds): 512 89.3 / 70.2, 1024 143 / 134, 1536 196 / 200
+int bwd_short_tokens(long long heads) {
+  const int line = 400 + 7 * (heads > 100 ? 100 : (int)heads);
+  return lfh::env_int("LINFUSION_BWDW_SHORT_TOKENS", line);
+}
+
 template <int D, int FM, bool NORM>
 int run(const BwdWideArgs& a, const Regions& r) {
   using namespace lf;
@@ -72,6 +87,16 @@ int run(const BwdWideArgs& a, const Regions& r) {
     const lfw::WideReduceArgs x{a.k, a.v, a.B, a.H, a.N, a.d, a.dtype, FM, a.lkv, a.lkv, partials, whole, r.plan, st};
     if ((rc = lfw::run_wide_state(x)) != LINFUSION_OK) return rc;
     state = whole;
+  }
+  if constexpr (NORM) {   // (the un-normalized form has no ratio in which the scale of a query row cancels)
+    if (a.N <= bwd_short_tokens(BH)) {
+      using C = BwdShortCfg<D>;
+      if (!lfh::allow_lds(bwd_short16<D, FM>, C::kLdsBytes)) return LINFUSION_ERR_HIP;
+      bwd_short16<D, FM><<<dim3((unsigned)(2 * BH)), dim3(C::kThreads), C::kLdsBytes, st>>>(
+          (const u32x4*)a.q, a.lq, (const u32x4*)a.g, a.lg, state, (int)a.N, a.eps, (const u32x4*)a.k, (const u32x4*)a.v, a.lkv,
+          (u32x4*)a.dq, a.ldq, (u32x4*)a.dk, (u32x4*)a.dv, a.ldkv);
+      return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
+    }
   }
   const float* z = NORM ? state + D * D : nullptr;
   bwdw_pack<D><<<dim3(D / 16, (unsigned)BH, 1), blk, 0, st>>>(state, 1, z, packed, packed_t, 1);
