@@ -267,6 +267,32 @@ struct TileIter {
   }
 };
 
+// A wave's priority on its SIMD, by how far it has come: 3 for the first half of its tiles, 2 for the next quarter, 1 for
+// the next eighth, then 0.  A SIMD serves its waves oldest first, so that of two workgroups on a CU the one that came
+// first runs ahead and the other one ends alone, with nobody to hide its waits behind (96 heads of 40 fp32 channels and 4096
+// tokens, time in the loop over tiles, first and second workgroup of a CU: state_reduce32s 19 and 27 us, apply32s 26 and 31,
+// bwd_qs32 53 and 65, bwd_kv32 40 and 45; with this 22 and 24, 27 and 27, 52 and 55, 42 and 42).
+struct Pace {
+  int left, next, level;   // tiles left, how many are left when the priority falls next, the priority
+  // a wave takes one of `per_round` tiles, n_tiles in all
+  LF_DEV Pace(long long n_tiles, long long per_round) {
+    const unsigned n = n_tiles < 0x7fffffff ? (unsigned)n_tiles : 0x7fffffffu;
+    const unsigned r = per_round < 0x7fffffff ? (unsigned)per_round : 0x7fffffffu;
+    left = __builtin_amdgcn_readfirstlane((int)((n + r - 1) / r));
+    next = left / 2;
+    level = 3;
+    __builtin_amdgcn_s_setprio(3);
+  }
+  LF_DEV void tile_done() {
+    if (--left == next) {
+      next = --level > 0 ? left / 2 : -1;
+      if (level == 2) __builtin_amdgcn_s_setprio(2);
+      else if (level == 1) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
+    }
+  }
+};
+
 template <typename T> struct NSplit;                 // operand levels needed to hold an fp32 value
 template <> struct NSplit<F16> { static constexpr int value = 1; };
 template <> struct NSplit<BF16> { static constexpr int value = 2; };

@@ -662,23 +662,25 @@ LF_DEV void combine_slice(const float* __restrict__ head_partials, int splits, i
 // before the first addition, from clamped, valid places (as loops over the quarters, one dependent round trip each, two or
 // more partials cost more than the launch they saved).
 constexpr int kFoldParts = 8;
-LF_DEV f32x4 sum_partials(const f32x4* __restrict__ src, int parts, int stride) {
-  if (parts == 1) return *src;
+template <int MOST>   // 4 or 8 partials at most
+LF_DEV f32x4 sum_up_to(const f32x4* __restrict__ src, int parts, int stride) {
   const f32x4 none = f32x4{0, 0, 0, 0};
-  if (parts <= 4) {
-    f32x4 v[4];
+  f32x4 v[MOST];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) v[p] = src[(p < parts ? p : 0) * stride];
+  for (int p = 0; p < MOST; ++p) v[p] = src[(p < parts ? p : 0) * stride];
+  if constexpr (MOST == 4) {
 #pragma unroll
     for (int p = 1; p < 4; ++p) v[0] += p < parts ? v[p] : none;
     return v[0];
+  } else {
+#pragma unroll
+    for (int p = 4; p < MOST; ++p) v[p] = p < parts ? v[p] : none;
+    return (((v[0] + v[1]) + (v[2] + v[3])) + (v[4] + v[5])) + (v[6] + v[7]);
   }
-  f32x4 v[kFoldParts];
-#pragma unroll
-  for (int p = 0; p < kFoldParts; ++p) v[p] = src[(p < parts ? p : 0) * stride];
-#pragma unroll
-  for (int p = 4; p < kFoldParts; ++p) v[p] = p < parts ? v[p] : none;
-  return (((v[0] + v[1]) + (v[2] + v[3])) + (v[4] + v[5])) + (v[6] + v[7]);
+}
+LF_DEV f32x4 sum_partials(const f32x4* __restrict__ src, int parts, int stride) {
+  if (parts == 1) return *src;
+  return parts <= 4 ? sum_up_to<4>(src, parts, stride) : sum_up_to<kFoldParts>(src, parts, stride);
 }
 
 // grid = (ceil(NE / 64), B*H), block = 256, NE = d*d + d.  (A template only so that the two translation
