@@ -716,8 +716,8 @@ struct ApplyDma {
             Bh[s][w] = ok ? r : 0u;
             continue;
           }
-          float r0 = ok ? (shift ? phi_scaled<FM>(x0, qc) : phi<FM>(x0)) : 0.0f;
-          float r1 = ok ? (shift ? phi_scaled<FM>(x1, qc) : phi<FM>(x1)) : 0.0f;
+          float r0 = ok ? (shift ? phi_scaled<FM>(x0, qc) : phi_by_sign<FM>(x0)) : 0.0f;
+          float r1 = ok ? (shift ? phi_scaled<FM>(x1, qc) : phi_by_sign<FM>(x1)) : 0.0f;
           if constexpr (NS == 1) {
             Bh[s][w] = pack2<T>(r0, r1);
           } else {

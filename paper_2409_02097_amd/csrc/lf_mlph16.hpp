@@ -190,7 +190,7 @@ state_reduce16_mlph(const u32x4* __restrict__ Ak, const u32x4* __restrict__ Tk, 
           const float y1 = __builtin_fmaf(gg[2 * w + 1], __builtin_fmaf(t1, rstd, cn), bb[2 * w + 1]);
           x0 += fmaxf(y0, slope * y0);   // LeakyReLU for slopes up to one
           x1 += fmaxf(y1, slope * y1);
-          float p0 = phi<FM>(x0), p1 = phi<FM>(x1);
+          float p0 = phi_by_sign<FM>(x0), p1 = phi_by_sign<FM>(x1);
           if constexpr (!kPhiKillsLowest<FM>) {
             p0 = ok ? p0 : 0.0f;
             p1 = ok ? p1 : 0.0f;

@@ -170,8 +170,8 @@ LF_DEV void reduce16_phase(const u32x4* __restrict__ Kh, const u32x4* __restrict
             }
             float x0, x1;
             unpack2<T>(kr[u][w], x0, x1);
-            float p0 = kRescan ? phi_scaled<FM>(x0, kc) : phi<FM>(x0);
-            float p1 = kRescan ? phi_scaled<FM>(x1, kc) : phi<FM>(x1);
+            float p0 = kRescan ? phi_scaled<FM>(x0, kc) : phi_by_sign<FM>(x0);
+            float p1 = kRescan ? phi_scaled<FM>(x1, kc) : phi_by_sign<FM>(x1);
             if constexpr (!kPhiKillsLowest<FM>) {
               p0 = ok ? p0 : 0.0f;
               p1 = ok ? p1 : 0.0f;
@@ -480,8 +480,8 @@ state_reduce16_rows(const u32x4* __restrict__ K, const u32x4* __restrict__ V, lo
             }
             float x0, x1;
             unpack2<T>(kr[u][w], x0, x1);
-            float p0 = (kRescan && shifted) ? phi_scaled<FM>(x0, kcu[u]) : phi<FM>(x0);
-            float p1 = (kRescan && shifted) ? phi_scaled<FM>(x1, kcu[u]) : phi<FM>(x1);
+            float p0 = (kRescan && shifted) ? phi_scaled<FM>(x0, kcu[u]) : phi_by_sign<FM>(x0);
+            float p1 = (kRescan && shifted) ? phi_scaled<FM>(x1, kcu[u]) : phi_by_sign<FM>(x1);
             if constexpr (!kPhiKillsLowest<FM>) {
               p0 = ok ? p0 : 0.0f;
               p1 = ok ? p1 : 0.0f;
