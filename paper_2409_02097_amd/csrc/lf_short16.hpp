@@ -9,8 +9,10 @@
 // What bounds such a call otherwise is three dependent launches, each with its fill, its round trips to memory and its drain
 // (fp16 2 x 8 x 256 x 160: 8.4 + 6.3 + 8.7 us; per call 22.1 us, one launch 12.4).  Here K and V come to LDS through
 // registers, four rounds of 64 tokens on their way, so that up to 256 tokens are one round trip, and a wave's first query
-// tokens behind them; what bounds it is the chain of rounds, phi(K), LDS round trip and barrier, 1.3 us each, between the
-// launch and the operands (a graph of such calls takes as long as calls one by one, whose host part is 7.1 us).
+// tokens behind them; what bounds it is the chain of phi(K), LDS round trip and barrier between the launch and the operands
+// (a graph of such calls takes as long as calls one by one, whose host part is 7.1 us).  1.3 us a round while each had a
+// barrier of its own; a CU's only workgroup now takes four rounds (bf16 above 96 channels: two) in one (that call 12.4 -> 12.0
+// us, in bf16 12.9 -> 12.3).
 //
 // Reduction: a round's phi(K) and V rows are written to LDS by all threads; after a barrier wave w multiplies feature block w
 // with all column blocks (transposing LDS reads, 16x16x32 products, bf16: phi(K) in two terms) and with ones for z.  A wave
@@ -23,8 +25,8 @@
 
 namespace lf {
 
-// CB: blocks of 16 value channels per workgroup
-template <typename T, int D, int CB> struct Short16Cfg {
+// CB: blocks of 16 value channels per workgroup; DEEP: the only workgroup of its CU
+template <typename T, int D, int CB, bool DEEP> struct Short16Cfg {
   static constexpr int kWaves = D / 16, kThreads = 64 * kWaves;
   static constexpr int kCols = 16 * CB, kGroups = D / kCols;
   static_assert(D % kCols == 0, "whole groups of value channels");
@@ -36,23 +38,29 @@ template <typename T, int D, int CB> struct Short16Cfg {
   // row strides in elements that spread the four rows of a transposing read over the banks
   static constexpr int kRS = D + 16, kVS = kCols + (kCols % 64 == 48 ? 8 : 16);
   static constexpr int kLevel = kTokens * kRS, kBuf = kNS * kLevel + kTokens * kVS;
-  static constexpr int kBuffers = kNS == 1 ? 2 : 1;  // (two of bf16 would leave one workgroup per CU)
+  static constexpr int kAhead = 4;                   // rounds on their way
+  // A CU's only workgroup takes as many rounds between two barriers as its LDS holds (4 or 2); where a CU has two workgroups,
+  // they are each other's company: one round at a time, two buffers (fp16) or one (two of bf16 would leave one workgroup per CU).
+  static constexpr int kTogether = !DEEP ? 1 : (kAhead * kBuf * 2 <= 156 * 1024 ? kAhead : 2);
+  static constexpr int kBuffers = DEEP ? kTogether : (kNS == 1 ? 2 : 1);
   static constexpr int kOS = D + 8;                  // operand rows: [32 value channels, z', its remainder][d]
   static constexpr int kTileBytes = kBuffers * kBuf * 2;
   static constexpr int kOperandBytes = (kCols + 2) * kOS * 2;
-  static constexpr int kLdsBytes = kTileBytes + kOperandBytes;
-  static constexpr int kAhead = 4;                   // rounds on their way
+  // (DEEP: the operands take the place of the tiles, which every wave has left by then)
+  static constexpr int kOperandsAt = DEEP ? 0 : kTileBytes;
+  static constexpr int kLdsBytes = DEEP ? (kTileBytes > kOperandBytes ? kTileBytes : kOperandBytes) : kTileBytes + kOperandBytes;
+  static_assert(kLdsBytes <= 159 * 1024 && kAhead % kTogether == 0, "workgroup LDS limit of the device");
 };
 
 // keep: null, or where the heads' states go ([B*H][D*D + D]); O = null: nothing else is wanted (Q is not read).
 // parts: workgroups that share a head's query tokens.
-template <typename T, int D, int CB, int FM, bool NORM>
-__global__ void __launch_bounds__((Short16Cfg<T, D, CB>::kThreads))
+template <typename T, int D, int CB, int FM, bool NORM, bool DEEP>
+__global__ void __launch_bounds__((Short16Cfg<T, D, CB, DEEP>::kThreads))
 short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long kbatch, long long khead, int rs, unsigned heads,
         int N, int parts, const u32x4* __restrict__ Q, long long qbatch, long long qhead, int qrow, float eps,
         float* __restrict__ keep, u32x4* __restrict__ O, long long obatch, long long ohead, int orow) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  using C = Short16Cfg<T, D, CB>;
+  using C = Short16Cfg<T, D, CB, DEEP>;
   constexpr int W = C::kWaves, NT = C::kThreads, NS = C::kNS, NL = C::kNL, KS = C::kKS, CPR = C::kCPR;
   constexpr int RS = C::kRS, VS = C::kVS, OS = C::kOS, TOK = C::kTokens, AH = C::kAhead;
   __shared__ float red[CB + 1][W];
@@ -64,7 +72,7 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long kbat
   const HeadAt head((unsigned)bh, heads);
   const int part = rem / C::kGroups, grp = rem - part * C::kGroups;
   uint16_t* lds = reinterpret_cast<uint16_t*>(smem);
-  uint16_t* ops = reinterpret_cast<uint16_t*>(smem + C::kTileBytes);
+  uint16_t* ops = reinterpret_cast<uint16_t*>(smem + C::kOperandsAt);
 
   // ---- query tokens: block t of 16 ---------------------------------------------------------------------------
   const u32x4* Qh = Q + head.slice(qbatch, qhead);
@@ -138,54 +146,75 @@ short16(const u32x4* __restrict__ K, const u32x4* __restrict__ V, long long kbat
 #pragma unroll
     for (int s = 0; s < AH; ++s)
       if (s < rounds) issue(s, kr[s], vr[s]);
+    // round base + s, from the registers to a buffer; its registers take the round four ahead
+    auto convert = [&](int base, int s, uint16_t* buf) {
+#pragma unroll
+      for (int u = 0; u < NL; ++u) {
+        u32x4 ph, pl;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          if constexpr (NS == 1) {
+            ph[w] = kRescan ? phi_pack2_scaled<T, FM>(kr[s][u][w], kc) : phi_pack2<T, FM>(kr[s][u][w]);
+          } else {
+            float x0, x1;
+            unpack2<T>(kr[s][u][w], x0, x1);
+            uint32_t h, l;
+            pack2_split<T>(phi<FM>(x0), phi<FM>(x1), h, l);
+            ph[w] = h;
+            pl[w] = l;
+          }
+        }
+        *reinterpret_cast<u32x4*>(buf + krow[u] * RS + kcol[u] * 8) = ph;
+        if constexpr (NS == 2) *reinterpret_cast<u32x4*>(buf + C::kLevel + krow[u] * RS + kcol[u] * 8) = pl;
+      }
+      if (has_v) *reinterpret_cast<u32x4*>(buf + NS * C::kLevel + vrow * VS + vcol * 8) = vr[s];
+      if (base + s + AH < rounds) issue(base + s + AH, kr[s], vr[s]);
+      if (base + s == (rounds > 1 ? 1 : 0) && pass == 0 && t < blocks) load_q(t, B);   // the wave's first block
+    };
+    auto multiply = [&](const uint16_t* buf) {
+#pragma unroll
+      for (int ks = 0; ks < TOK / 32; ++ks) {
+        u32x4 bv[CB];
+#pragma unroll
+        for (int b = 0; b < CB; ++b) {
+          const uint16_t* p = buf + NS * C::kLevel + v_at + 32 * ks * VS + 16 * b;
+          const u32x2 r0 = lds_read_tr16(p), r1 = lds_read_tr16(p + 4 * VS);
+          bv[b] = u32x4{r0[0], r0[1], r1[0], r1[1]};
+        }
+#pragma unroll
+        for (int l = 0; l < NS; ++l) {
+          const uint16_t* p = buf + l * C::kLevel + a_at + 32 * ks * RS;
+          const u32x2 r0 = lds_read_tr16(p), r1 = lds_read_tr16(p + 4 * RS);
+          const u32x4 a = u32x4{r0[0], r0[1], r1[0], r1[1]};
+#pragma unroll
+          for (int b = 0; b < CB; ++b) acc[b] = mfma_16x16x32<T>(a, bv[b], acc[b]);
+          accz = mfma_16x16x32<T>(a, ones, accz);
+        }
+      }
+    };
+    constexpr int G = C::kTogether;
     for (int base = 0; base < rounds; base += AH) {
 #pragma unroll
-      for (int s = 0; s < AH; ++s) {
-        if (base + s >= rounds) break;
-        uint16_t* buf = lds + (C::kBuffers == 2 ? (s & 1) : 0) * C::kBuf;
+      for (int first = 0; first < AH; first += G) {
+        if (base + first >= rounds) break;
+        uint16_t* bufs = lds + (G == 1 && C::kBuffers == 2 ? (first & 1) : 0) * C::kBuf;
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-          u32x4 ph, pl;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            if constexpr (NS == 1) {
-              ph[w] = kRescan ? phi_pack2_scaled<T, FM>(kr[s][u][w], kc) : phi_pack2<T, FM>(kr[s][u][w]);
-            } else {
-              float x0, x1;
-              unpack2<T>(kr[s][u][w], x0, x1);
-              uint32_t h, l;
-              pack2_split<T>(phi<FM>(x0), phi<FM>(x1), h, l);
-              ph[w] = h;
-              pl[w] = l;
-            }
-          }
-          *reinterpret_cast<u32x4*>(buf + krow[u] * RS + kcol[u] * 8) = ph;
-          if constexpr (NS == 2) *reinterpret_cast<u32x4*>(buf + C::kLevel + krow[u] * RS + kcol[u] * 8) = pl;
+        for (int i = 0; i < G; ++i) {
+          if (base + first + i >= rounds) break;
+          convert(base, first + i, bufs + i * C::kBuf);
         }
-        if (has_v) *reinterpret_cast<u32x4*>(buf + NS * C::kLevel + vrow * VS + vcol * 8) = vr[s];
-        if (base + s + AH < rounds) issue(base + s + AH, kr[s], vr[s]);
-        if (base + s == (rounds > 1 ? 1 : 0) && pass == 0 && t < blocks) load_q(t, B);   // the wave's first block
-        lds_barrier();   // the round is complete in LDS; with two buffers the other one is free to be rewritten
+        lds_barrier();   // the rounds are complete in LDS; with two buffers of one the other one is free to be rewritten
+        if (base + first + G <= rounds) {   // (all of them without a branch between: operands are read ahead)
 #pragma unroll
-        for (int ks = 0; ks < TOK / 32; ++ks) {
-          u32x4 bv[CB];
+          for (int i = 0; i < G; ++i) multiply(bufs + i * C::kBuf);
+        } else {
 #pragma unroll
-          for (int b = 0; b < CB; ++b) {
-            const uint16_t* p = buf + NS * C::kLevel + v_at + 32 * ks * VS + 16 * b;
-            const u32x2 r0 = lds_read_tr16(p), r1 = lds_read_tr16(p + 4 * VS);
-            bv[b] = u32x4{r0[0], r0[1], r1[0], r1[1]};
-          }
-#pragma unroll
-          for (int l = 0; l < NS; ++l) {
-            const uint16_t* p = buf + l * C::kLevel + a_at + 32 * ks * RS;
-            const u32x2 r0 = lds_read_tr16(p), r1 = lds_read_tr16(p + 4 * RS);
-            const u32x4 a = u32x4{r0[0], r0[1], r1[0], r1[1]};
-#pragma unroll
-            for (int b = 0; b < CB; ++b) acc[b] = mfma_16x16x32<T>(a, bv[b], acc[b]);
-            accz = mfma_16x16x32<T>(a, ones, accz);
+          for (int i = 0; i < G - 1; ++i) {
+            if (base + first + i >= rounds) break;
+            multiply(bufs + i * C::kBuf);
           }
         }
-        if constexpr (C::kBuffers == 1) lds_barrier();
+        if (G == 1 ? C::kBuffers == 1 : base + first + G < rounds) lds_barrier();
       }
     }
     if constexpr (!kRescan) {

@@ -101,17 +101,15 @@ int apply(const WideApplyArgs& a, int parts = 1, float* keep = nullptr, hipEvent
 }
 
 // the whole call in one launch
-template <typename T, int D, int CB>
-int launch_short(const WideArgs& a) {
+template <typename T, int D, int CB, bool DEEP>
+int launch_short_as(const WideArgs& a, dim3 grid, int parts) {
   using namespace lf;
-  using C = Short16Cfg<T, D, CB>;
-  const int parts = a.out ? a.plan.short_parts : 1;
-  const dim3 grid((unsigned)((long long)a.B * a.H * C::kGroups * parts));
+  using C = Short16Cfg<T, D, CB, DEEP>;
   if (a.ev) (void)hipEventRecord(a.ev[0], a.st);
 #define LFW_SHORT(FM, NORM)                                                                                       \
   {                                                                                                               \
-    if (!allow_lds(short16<T, D, CB, FM, NORM>, C::kLdsBytes)) return LINFUSION_ERR_HIP;                              \
-    short16<T, D, CB, FM, NORM><<<grid, dim3(C::kThreads), C::kLdsBytes, a.st>>>(                                     \
+    if (!allow_lds(short16<T, D, CB, FM, NORM, DEEP>, C::kLdsBytes)) return LINFUSION_ERR_HIP;                              \
+    short16<T, D, CB, FM, NORM, DEEP><<<grid, dim3(C::kThreads), C::kLdsBytes, a.st>>>(                                     \
         (const u32x4*)a.k, (const u32x4*)a.v, a.lkv.batch, a.lkv.head, a.lkv.row,                                 \
         (unsigned)a.H | (unsigned)a.H << 16, (int)a.N, parts, (const u32x4*)a.q, a.lq.batch, a.lq.head, \
         a.lq.row, a.eps, a.state, (u32x4*)a.out, a.lo.batch, a.lo.head, a.lo.row);                                \
@@ -124,6 +122,21 @@ int launch_short(const WideArgs& a) {
 #undef LFW_SHORT
   if (a.ev) { (void)hipEventRecord(a.ev[1], a.st); (void)hipEventRecord(a.ev[2], a.st); (void)hipEventRecord(a.ev[3], a.st); }
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
+}
+
+// Where every workgroup has a CU to itself, several rounds of tokens between two barriers (DEEP) rather than one: us per call,
+// bf16 2 x 8 x 500 x 128 15.2 -> 14.1, 1 x 8 x 512 x 160 18.7 -> 17.6, 2 x 8 x 256 x 160 12.9 -> 12.3, the same in fp16 12.4 -> 12.0; fp16
+// of 96 and 128 channels the same either way.  Not with half of a head's channels, whose sums leave no registers for it: fp16
+// 12 x 8 x 256 x 160 forward and backward 50.4 -> 54.6 (58 spilled; two rounds 54.0, 27), bf16 forward 19.5 -> 20.6.
+template <typename T, int D, int CB>
+int launch_short(const WideArgs& a) {
+  const int parts = a.out ? a.plan.short_parts : 1;
+  const long long wgs = (long long)a.B * a.H * (D / (16 * CB)) * parts;
+  const dim3 grid((unsigned)wgs);
+  if constexpr (CB == 2) {
+    if (wgs <= lfh::num_cu()) return launch_short_as<T, D, CB, true>(a, grid, parts);
+  }
+  return launch_short_as<T, D, CB, false>(a, grid, parts);
 }
 
 template <typename T, int D>
