@@ -11,8 +11,12 @@
 //   dq                 leaves from registers;  dz' is summed in registers
 //   r, gp              phi(q) and g / den' replace q and g in LDS
 //   dS'^T = gp^T r     (a wave: 32 feature channels x half of the value channels) in fp32 registers
-// As the outer product r_i gp_i^T does not change when a row of one is scaled up and that of the other down, phi(q) is scaled
-// into fp16's range row by row, as the apply kernels do (lf_wave16.hpp: wave_operands): rows far below zero keep their bits.
+// As the outer product r_i gp_i^T does not change when a row of one is scaled up and that of the other down, rows of phi(q) whose
+// largest value is below one are scaled up to it, as the apply kernels do (lf_wave16.hpp: wave_operands): rows far below zero keep
+// their bits, and gp = g / den' loses no headroom, since den' is below one with them.  Rows of large values are scaled down only
+// as far as den' is above one (by all of their largest phi, gp would be up to phi_max / den' times g: for one query channel of 300
+// among ordinary ones and dout of 1000 that is beyond fp16, and with it all of the head's dk and dv).  So |gp| is at most the larger
+// of |g| and |g / den'|, and phi(q) at most itself.
 // Then dS' turns into operands through LDS, with a scale per 16 output channels, and the keys follow, a round after the other:
 // dk = (dS v + dz) phi'(k) or dv = dS^T phi(k).
 //
@@ -20,7 +24,7 @@
 // four SIMDs, of which the fuller ones issue vector instructions 58 % of the time (conversions, phi, the elementwise part), LDS
 // busy 40 %, matrix units 13 %; a wave alone on its part of the chain waits for LDS.  12 x 8 x 256 x 160 with the state given: 33
 // us, against 68 of the seven launches before (lf_backward_wide.hpp), two of which only pack states; the training step 88.7 -> 50.0
-// us.
+// us.  At d = 160 a few registers go to scratch before the query rounds and come back behind them.
 #pragma once
 #include "lf_backward_wide.hpp"
 #include "lf_solo.hpp"   // solo_unit
@@ -152,28 +156,24 @@ LF_DEV void bwd_short_head(const u32x4* Qh, int qrow, const u32x4* Gh, int grow,
   float* maxe = maxc + 4 * CB;           // [value group of 16][feature block]
   uint16_t* M = reinterpret_cast<uint16_t*>(smem + C::kMatrixOffset);   // [feature channel][value channel]
 
-  // ---- copies of a round: chunk u * NT + tid of either tensor ----
-  int crow[NL], cat[NL];
-#pragma unroll
-  for (int u = 0; u < NL; ++u) {
-    const int p = u * NT + tid;
-    crow[u] = p / CPR;
-    cat[u] = p % CPR;
-  }
+  // ---- copies of a round: chunk u * NT + tid of either tensor, column ccol of row crow + u * kStep ----
+  constexpr int kStep = NT / CPR;
+  static_assert(NT % CPR == 0, "a thread's chunks lie in one column");
+  const int crow = tid / CPR, ccol = tid % CPR;
   auto issue = [&](const u32x4* X, int rx, const u32x4* Y, int ry, int rd, u32x4 (&x)[NL], u32x4 (&y)[NL]) {
     const int lim = N - rd * TOK;      // (rows past it: the round's first; they add nothing and are never stored)
     const u32x4 *xp = X + (long long)rd * TOK * rx, *yp = Y + (long long)rd * TOK * ry;
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
-      const int r = crow[u] < lim ? crow[u] : 0;
-      x[u] = xp[r * rx + cat[u]];
-      y[u] = yp[r * ry + cat[u]];
+      const int r = crow + u * kStep < lim ? crow + u * kStep : 0;
+      x[u] = xp[r * rx + ccol];
+      y[u] = yp[r * ry + ccol];
     }
   };
   auto deposit = [&](unsigned char* slot, const u32x4 (&x)[NL], const u32x4 (&y)[NL]) {
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
-      unsigned char* p = slot + (crow[u] * RS + cat[u] * 8) * 2;
+      unsigned char* p = slot + ((crow + u * kStep) * RS + ccol * 8) * 2;
       *reinterpret_cast<u32x4*>(p) = x[u];
       *reinterpret_cast<u32x4*>(p + C::kTensorBytes) = y[u];
     }
@@ -283,21 +283,22 @@ LF_DEV void bwd_short_head(const u32x4* Qh, int qrow, const u32x4* Gh, int grow,
 
   // The power of two (or, for a row of negative channels under elu + 1, exp of minus the largest) that brings the row's largest
   // operand into [1, 2), from its largest channel (wave_operands, there on phi's argument: here phi itself is in fp32 first,
-  // so that the factor ends where that has underflowed), and its inverse
-  auto row_scale = [&](float m, float& mult, float& post) {
-    float top, c = 0.0f;
+  // so that the factor ends where that has underflowed), and its inverse.  The inverse exceeds 2^most only where it is below one.
+  auto row_scale = [&](float m, int most, float& mult, float& post) {
     if constexpr (FM == kPhiEluPlusOne) {
-      c = m < 0.0f ? fminf(-m * kLog2e, 120.0f) : 0.0f;
-      top = m < 0.0f ? 1.0f : m + 1.0f;
-    } else if constexpr (FM == kPhiRelu) {
-      top = fmaxf(m, 0.0f);
+      int ex = __builtin_amdgcn_frexp_expf(m + 1.0f) - 1;
+      ex = ex < most ? ex : most;
+      const float c = m < 0.0f ? fminf(-m * kLog2e, 120.0f) : (float)-ex;
+      mult = __builtin_amdgcn_exp2f(c);
+      post = __builtin_amdgcn_exp2f(-c);
     } else {
-      top = m;
+      const float top = FM == kPhiRelu ? fmaxf(m, 0.0f) : m;
+      int f = (int)(__builtin_bit_cast(uint32_t, top) >> 23) & 0xff;
+      f = f < 127 + most ? f : 127 + most;
+      f = f < 1 ? 1 : (f > 253 ? 253 : f);
+      mult = __builtin_bit_cast(float, (uint32_t)(254 - f) << 23);
+      post = __builtin_bit_cast(float, (uint32_t)f << 23);
     }
-    uint32_t f = (__builtin_bit_cast(uint32_t, top) >> 23) & 0xffu;
-    f = f < 1u ? 1u : (f > 253u ? 253u : f);
-    mult = __builtin_amdgcn_exp2f(c) * __builtin_bit_cast(float, (254u - f) << 23);
-    post = __builtin_amdgcn_exp2f(-c) * __builtin_bit_cast(float, f << 23);
   };
   auto row_max = [&](const u32x2 (&raw)[4]) {   // of the wave's 32 channels
     f16x2 m = __builtin_bit_cast(f16x2, FM == kPhiIdentity ? 0u : 0xfc00fc00u);
@@ -371,7 +372,8 @@ LF_DEV void bwd_short_head(const u32x4* Qh, int qrow, const u32x4* Gh, int grow,
     const float invden = 1.0f / (den + eps_b);
     const bool in = rd * TOK + tok < N;      // rows past the end add nothing
     float mult, post;
-    row_scale(m, mult, post);
+    const int above = -__builtin_amdgcn_frexp_expf(invden);   // den' is 2^above and some, at most twice that
+    row_scale(m, above > 0 ? above : 0, mult, post);
     const float gs = invden * post;
     write_phi(qt, r, mult);
     u32x2 gx[4];
@@ -516,7 +518,7 @@ LF_DEV void bwd_short_head(const u32x4* Qh, int qrow, const u32x4* Gh, int grow,
 #pragma unroll
       for (int b = 1; b < CB; ++b) m = fmaxf(m, red[b * TOK + tok][0]);
       float mult, post;
-      row_scale(m, mult, post);
+      row_scale(m, 127, mult, post);   // (dv takes the inverse in fp32: no bound)
       write_phi(kt, r, mult);
       if (rd + 1 < rounds) deposit(slot_of(rounds + rd + 1), x, y);
       issue_round(rounds + rd + 2);

@@ -54,6 +54,41 @@ def test_short_backward_over_the_range_of_its_operands(case, d):
     _check(_run(q, k, v, g, fm, eps), q, k, v, g, fm, eps, True, f"short bwd, {case}, d={d}")
 
 
+# large gradients, and query rows whose largest phi lies far above the row's normalizer: the same inputs to the launches of longer streams
+@pytest.mark.parametrize("short_tokens", ["256", "1"])
+@pytest.mark.parametrize("d", [96, 160])
+@pytest.mark.parametrize("case", ["dout 1e-4", "dout 1e3", "dout 4e3", "dout 4e3, wide queries", "one channel of 300", "one channel of 1000",
+                                  "one channel of 100 above small ones", "relu, a channel without keys"])
+def test_backward_stays_finite(case, d, short_tokens, monkeypatch, tuning):
+    """Query row and g / den' are rounded to fp16 each: neither may leave its range where the gradients do not."""
+    B, H, N = 1, 2, 256
+    print(f"bwd stays finite, {case}, d={d} short_tokens={short_tokens}", flush=True)
+    monkeypatch.setenv("LINFUSION_BWDW_SHORT_TOKENS", short_tokens)
+    q, k, v, g = _inputs(B, H, N, d, 194)
+    fm, eps = 0, 1e-6
+    if case.startswith("dout"):
+        g *= float(case.split()[1].rstrip(","))
+        if "wide" in case:
+            q *= 2.0
+    elif case == "one channel of 300":
+        q[:, :, ::7, 3] = 300.0
+        g *= 256.0
+    elif case == "one channel of 1000":
+        q[:, :, ::7, 3] = 1000.0
+        g *= 1024.0
+    elif case == "one channel of 100 above small ones":
+        q[:] = q * 0.25 - 14.0
+        q[..., 0] = 100.0
+        k[..., 0] = -9.0
+        g *= 0.05
+    else:
+        fm = 1
+        q[:, :, ::7, 3] = 500.0
+        k[..., 3] = -1.0
+        g *= 100.0
+    _check(_run(q, k, v, g, fm, eps), q, k, v, g, fm, eps, True, f"bwd stays finite, {case}, d={d}")
+
+
 @pytest.mark.parametrize("N", [64, 200])
 def test_short_backward_beside_the_launches_it_replaces(N, monkeypatch, tuning):
     """Contiguous and token-major, the same values: bit for bit alike; the other launches round phi(q) unscaled and sum in
