@@ -51,14 +51,20 @@ int make_regions(int B, int H, long long N, int d, int dtype, Regions* r) {
 // Longest stream that the one launch (lf_bwd_short16.hpp) takes.  It costs 4 to 5.5 us per 64 tokens whatever the heads up to
 // 128, where its workgroups fill the chip; the launches below cost a chain of 30 to 45 us, and what their packed states and
 // partials move, which grows with the heads.  us per call with the state given, these launches / that one, fp16:
-//   4 heads of 160:   64 tokens 39.8 / 12.1, 256 42.8 / 28.2, 448 45.1 / 44.3, 512 44.6 / 49.7
-//   16 heads of 96:   64 29.6 / 9.5, 256 32.0 / 20.1, 512 35.0 / 35.1, 640 37.8 / 42.8
-//   40 heads of 128:  640 55.3 / 48.9, 768 58.1 / 57.5, 896 66.6 / 66.0
-//   96 heads of 160:  64 51.6 / 13.1, 256 68.9 / 31.0, 640 107.5 / 65.3
-//   128 heads of 160: 1024 152 / 106;  of 96: 1024 92.7 / 70.0
-//   192 heads of 96 (two rounds): 512 89.3 / 70.2, 1024 143 / 134, 1536 196 / 200
-int bwd_short_tokens(long long heads) {
-  const int line = 400 + 7 * (heads > 100 ? 100 : (int)heads);
+//   4 heads of 160:   64 tokens 40.0 / 13.4, 256 42.8 / 28.2, 448 44.9 / 44.2, 512 44.7 / 49.7
+//   16 heads of 96:   64 28.7 / 10.7, 192 30.9 / 17.1, 512 34.2 / 34.7, 640 37.0 / 42.3
+//   100 heads of 128: 512 74.4 / 42.6, 1100 123 / 86.9
+//   128 heads of 160: 1100 164 / 119;  of 96: 1100 100 / 77.2
+// More heads: it runs a round of workgroups per 128 heads, these a round per 256, and both step where one begins.
+//   129 heads, 1100 tokens: of 160 244 / 223, of 128 186 / 171, of 96 146 / 145;  385 of 160 468 / 462, 4096 of 160 3992 / 3720
+// At 96 channels these are the faster ones from a length on that depends on the rounds:
+//   3 rounds: 257 heads 1000 tokens 202 / 196, 1100 214 / 216      4: 385 heads 384 108 / 107, 448 121 / 122, 1100 238 / 288
+//   5: 513 heads 512 184 / 174, 800 264 / 265                      6: 641 heads 320 145 / 141, 384 160 / 163
+//   8: 1024 heads 320 195 / 188, 384 216 / 219                     16: 2048 heads 192 272 / 258, 256 314 / 316
+int bwd_short_tokens(int d, long long heads) {
+  int line = 400 + 7 * (heads > 100 ? 100 : (int)heads);
+  const long long cus = lfh::num_cu(), rounds = (2 * heads + cus - 1) / cus;
+  if (d == 96 && rounds > 2) line = rounds == 3 ? 1024 : rounds == 4 ? 384 : rounds == 5 ? 768 : rounds <= 8 ? 320 : 192;
   return lfh::env_int("LINFUSION_BWDW_SHORT_TOKENS", line);
 }
 
@@ -89,7 +95,7 @@ int run(const BwdWideArgs& a, const Regions& r) {
     state = whole;
   }
   if constexpr (NORM) {   // (the un-normalized form has no ratio in which the scale of a query row cancels)
-    if (a.N <= bwd_short_tokens(BH)) {
+    if (a.N <= bwd_short_tokens(D, BH)) {
       using C = BwdShortCfg<D>;
       if (!lfh::allow_lds(bwd_short16<D, FM>, C::kLdsBytes)) return LINFUSION_ERR_HIP;
       bwd_short16<D, FM><<<dim3((unsigned)(2 * BH)), dim3(C::kThreads), C::kLdsBytes, st>>>(

@@ -6,6 +6,7 @@ import torch
 import paper_2409_02097_amd as lf
 from paper_2409_02097_amd import workloads as wl
 from tests.test_gpu_backward_composed import _check, _run
+from tests.test_gpu_partial_counts import _gradients_match, _launches
 
 pytestmark = pytest.mark.gpu
 
@@ -52,6 +53,28 @@ def test_short_backward_over_the_range_of_its_operands(case, d):
         if fm == 2:
             q, k = q.abs(), k.abs()
     _check(_run(q, k, v, g, fm, eps), q, k, v, g, fm, eps, True, f"short bwd, {case}, d={d}")
+
+
+# with 256 compute units: one and two rounds of workgroups, and 96 channels with three, four, five, eight and more, on both sides of the line
+@pytest.mark.parametrize("heads,N,d,launches", [(128, 1100, 96, 1), (128, 1101, 96, 6), (129, 1100, 160, 1), (257, 1024, 96, 1), (257, 1025, 96, 6),
+                                                (385, 384, 96, 1), (400, 385, 96, 6), (513, 768, 96, 1), (640, 769, 96, 6), (641, 320, 96, 1),
+                                                (1024, 321, 96, 6), (1025, 192, 96, 1), (1025, 193, 96, 6), (400, 1100, 128, 1)])
+def test_the_line_between_the_launches(heads, N, d, launches):
+    print(f"short bwd line heads={heads} N={N} d={d}", flush=True)
+    q, k, v, g = _inputs(1, heads, N, d, 195)
+    dev = [t.cuda() for t in (q, k, v, g)]
+    outs = [torch.full_like(dev[0], float("nan")) for _ in range(3)]
+    scratch = lambda n: torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+    state = torch.empty(heads * (d * d + d), dtype=torch.float32, device="cuda")
+    lf.linfusion_attn_state(dev[1], dev[2], state, 0, scratch(lf.linfusion_attn_workspace_bytes(1, heads, N, d, lf.DTYPE_F16)))
+    ws = scratch(lf.linfusion_attn_bwd_workspace_bytes(1, heads, N, d, lf.DTYPE_F16))
+    call = lambda: lf.linfusion_attn_bwd(*dev, *outs, 0, 1e-6, 0, ws, state=state)
+    count = _launches(call)
+    # (six, seven where more partials are summed first)
+    assert (count == 1 if launches == 1 else count >= launches), f"{count} launches"
+    call()
+    torch.cuda.synchronize()
+    _gradients_match(outs, (q, k, v, g), "f16", "short bwd line")
 
 
 # large gradients, and query rows whose largest phi lies far above the row's normalizer: the same inputs to the launches of longer streams
