@@ -682,7 +682,10 @@ struct ApplyDma {
     };
     f32x16 acc[MT2];
     float den = 0.0f;
-    // B operands of the lane's token (each row times 2^c) and the products with the state operands
+    // B operands of the lane's token (each row times 2^c) and the products with the state operands.  elu + 1 by the sign bit and the
+    // remainders from the packed word (phi_by_sign, pack2_split), but not of MLP-fed queries of half a block of 16 channels more: us per
+    // call, without / with, 1 x 10 x 7294 x 40 32.1 / 32.4, x 56 40.9 / 41.2, 2 x 5 x 30000 x 40 72.8 / 73.1 (whole blocks: x 64 38.2 / 37.9).
+    constexpr bool kBySign = !(MLP && D % 16 == 8);
     auto products = [&](const bool shift, const bool only_small) {
       u32x4 qraw[KS];
 #pragma unroll
@@ -716,13 +719,13 @@ struct ApplyDma {
             Bh[s][w] = ok ? r : 0u;
             continue;
           }
-          float r0 = ok ? (shift ? phi_scaled<FM>(x0, qc) : phi_by_sign<FM>(x0)) : 0.0f;
-          float r1 = ok ? (shift ? phi_scaled<FM>(x1, qc) : phi_by_sign<FM>(x1)) : 0.0f;
+          float r0 = ok ? (shift ? phi_scaled<FM>(x0, qc) : (kBySign ? phi_by_sign<FM>(x0) : phi<FM>(x0))) : 0.0f;
+          float r1 = ok ? (shift ? phi_scaled<FM>(x1, qc) : (kBySign ? phi_by_sign<FM>(x1) : phi<FM>(x1))) : 0.0f;
           if constexpr (NS == 1) {
             Bh[s][w] = pack2<T>(r0, r1);
           } else {
             uint32_t h, l;
-            pack2_split<T>(r0, r1, h, l);
+            pack2_split<T, kBySign>(r0, r1, h, l);
             Bh[s][w] = h;
             Bl[s][w] = l;
           }

@@ -61,9 +61,10 @@ LF_DEV float phi(float x) {
 // phi(x) to the same bits with elu(x) + 1 chosen by the sign bit (both branches give 1 at +-0 and keep a NaN one): two vector
 // instructions that write no condition code, where a compare and a select of its result have a wait between them.  For kernels
 // bound by their vector work that do not need the compare again (the gradient kernels take phi'(x) from it, and they are short of
-// registers: with this in the dQ kernel on row pieces 29 registers spilled, 43 -> 62 us).  bf16 12 x 8 x 4096 x 40, token-major, with the
-// remainders of pack2_split: apply16_rows 23.5 -> 21.9 us, state_reduce16_rows 20.2 -> 19.3; 2 x 10 x 16384 x 64: state_reduce16_mlph
-// 35.1 -> 33.7, fused16 51.5 -> 51.0.
+// registers: with this in the dQ kernel on row pieces 29 registers spilled, 43 -> 62 us).  Kernel times in a trace, both sides on one box,
+// with the remainders of pack2_split: bf16 12 x 8 x 4096 x 40 token-major apply16_rows 23.0 -> 21.9 us, state_reduce16_rows 20.3 -> 19.9;
+// 2 x 10 x 16384 x 64 state_reduce16_mlph 35.5 -> 33.3, fused16 50.4 -> 49.3.  Calls gain less (2 x 8 x 36503 x 40 51.1 -> 50.3, the
+// first and the last of those above nothing that can be told from noise).
 template <int FM>
 LF_DEV float phi_by_sign(float x) {
   if constexpr (FM == kPhiEluPlusOne) {
@@ -154,10 +155,14 @@ template <> struct PhiPack2<F16, kPhiEluPlusOne> {
 template <typename T, int FM> LF_DEV uint32_t phi_pack2(uint32_t w) { return PhiPack2<T, FM>::run(w); }
 template <typename T, int FM> LF_DEV uint32_t phi_pack2_scaled(uint32_t w, float c) { return PhiPack2<T, FM>::run_scaled(w, c); }
 
-// value of a packed pair after rounding, back in fp32 (for hi/lo operand splitting)
-template <typename T> LF_DEV void pack2_split(float lo, float hi, uint32_t& w_hi, uint32_t& w_lo) {
+// value of a packed pair after rounding, back in fp32 (for hi/lo operand splitting).  ONCE: the remainders come from the packed
+// word; left to itself the compiler rounds the lower half a second time for its remainder, off the chain through the word.  The same bits
+// either way; us per call, ONCE false / true: bf16 forward 2 x 8 x 36503 x 40 token-major 51.4 / 50.2, forward and backward 4 x 8 x 4096
+// x 64 85.1 / 83.7, 12 x 8 x 2048 x 24 48.9 / 48.2, 4 x 8 x 8192 x 40 token-major 84.4 / 83.6; but the row-piece MLP-fed forward 2 x 8 x
+// 16384 x 40 49.3 / 50.7, 2 x 8 x 4096 x 40 24.8 / 25.1, and forward 2 x 8 x 8000 x 128 54.3 / 55.3 (96 and 160 channels the same).
+template <typename T, bool ONCE = true> LF_DEV void pack2_split(float lo, float hi, uint32_t& w_hi, uint32_t& w_lo) {
   w_hi = pack2<T>(lo, hi);
-  asm("" : "+v"(w_hi));   // (or the compiler rounds the lower half a second time for its remainder)
+  if constexpr (ONCE) asm("" : "+v"(w_hi));
   float rl, rh;
   unpack2<T>(w_hi, rl, rh);
   w_lo = pack2<T>(lo - rl, hi - rh);

@@ -252,7 +252,7 @@ state_reduce16_mlp(const u32x4* __restrict__ Ak, const u32x4* __restrict__ Tk, c
             ph[w] = pack2<T>(p0, p1);
           } else {
             uint32_t h, l;
-            pack2_split<T>(p0, p1, h, l);
+            pack2_split<T, false>(p0, p1, h, l);
             ph[w] = h;
             pl[w] = l;
           }

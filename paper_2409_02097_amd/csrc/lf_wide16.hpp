@@ -188,7 +188,7 @@ state_reduce16_wide(const u32x4* __restrict__ K, Layout kl, const u32x4* __restr
             ph[w] = pack2<T>(p0, p1);
           } else {
             uint32_t h, l;
-            pack2_split<T>(p0, p1, h, l);
+            pack2_split<T, D != 128>(p0, p1, h, l);
             ph[w] = h;
             pl[w] = l;
           }
