@@ -300,7 +300,13 @@ struct TileIter {
 struct Pace {
   int left, next, level;   // tiles left, how many are left when the priority falls next, the priority
   // a wave takes one of `per_round` tiles, n_tiles in all
-  LF_DEV Pace(long long n_tiles, long long per_round) {
+  LF_DEV Pace(long long n_tiles, long long per_round, bool on) {
+    if (!on) {
+      left = 0;
+      next = 1;   // (never reached)
+      level = 0;
+      return;
+    }
     const unsigned n = n_tiles < 0x7fffffff ? (unsigned)n_tiles : 0x7fffffffu;
     const unsigned r = per_round < 0x7fffffff ? (unsigned)per_round : 0x7fffffffu;
     left = __builtin_amdgcn_readfirstlane((int)((n + r - 1) / r));

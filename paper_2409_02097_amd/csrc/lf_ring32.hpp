@@ -34,9 +34,11 @@
 //   column form  lane (m, kq) reads channel 16 i + m of tokens 4 u + kq: the operand whose contraction runs over
 //                tokens (the state's gradient).
 // Chunks of a row are rotated by a row-dependent amount so that both forms are (nearly) free of bank conflicts.
-// The waves' priorities follow their progress (Pace): 96 heads of 40 channels and 4096 tokens, forward 65 -> 62.5 us, forward and
-// backward 182 -> 174; 20 heads of 64 and 16384 tokens 82 -> 79.5.  The state is loaded before the first tiles are requested:
-// 62.5 -> 58.8, 174 -> 170, 79.5 -> 78 us.
+// The waves' priorities follow their progress (Pace; us per call without / with): 96 heads of 40 channels and 4096 tokens, forward and
+// backward 180.3 / 175.0, 700 tokens 60.9 / 59.9, 16 heads, forward, 20.9 / 20.6; 20 heads of 64 and 16384 tokens, forward, 80.4 / 79.2.
+// The state is loaded before the first tiles are requested rather than behind them: 175.1 -> 174.4, 20.8 -> 20.6, 79.3 -> 79.2 us.  Up to
+// 24 channels neither holds for short streams (forward and backward of 96 heads of 24: 300 tokens 29.9 -> 29.4 without, 700 tokens 41.6 ->
+// 41.2, of 16 700 tokens 28.6 -> 28.2): there the state comes behind the tiles, and a wave of few tiles keeps its priority.
 // They take a state as `parts` partial states and sum them while they stage it (parts = 1: a finished
 // state): where the partials are few that is cheaper than a launch of combine_state in between.
 #pragma once
@@ -184,6 +186,9 @@ template <int D> struct Tile32 {
 };
 
 // NT: tensors per slot.  R: slots (R - 1 tiles in flight).
+// Priorities by progress: in narrow heads not below 64 tokens per wave, where what comes behind the loop is as long as the loop.
+template <int D> LF_DEV bool paced(long long N) { return D > 24 || N >= (long long)gridDim.x * (kWavesPerWG * 64); }
+
 template <int D, int NT, int R_>
 struct Ring32 {
   using TC = Tile32<D>;
@@ -303,7 +308,9 @@ struct Ring32 {
   // ---- the head's state ------------------------------------------------------------------------------------
   static constexpr int kStageBytes = NE * 4 + kWavesPerWG * 4;   // the state, and a word per wave
   // The sum of `parts` partial states, this thread's share of it: before the first tiles are requested, since a request that
-  // waits behind the chip's first two tiles comes two microseconds later.
+  // waits behind the chip's first two tiles comes two microseconds later; in narrow heads behind them (kLate), since there the tiles
+  // are small and it is they that wait for the sums.
+  static constexpr bool kLate = D <= 24;
   static constexpr int kPer = (NE / 4 + kThreads - 1) / kThreads;
   static LF_DEV int share(int i) {   // (past the state's end: its last element again)
     const int e = i * kThreads + (int)threadIdx.x;
@@ -330,8 +337,10 @@ struct Ring32 {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int e = share(i);   // (the last element is written by several threads, with one value)
-      st[e] = s[i];
-      if (keep) reinterpret_cast<f32x4*>(keep)[e] = s[i];
+      if (!kLate || i * kThreads + (int)threadIdx.x < NE / 4) {   // (narrow: by one, where most threads would have it)
+        st[e] = s[i];
+        if (keep) reinterpret_cast<f32x4*>(keep)[e] = s[i];
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) ok &= splits_exactly(s[i][k]) | (4 * e >= D * D);
     }
@@ -609,7 +618,7 @@ state_reduce32s(const float* __restrict__ K, const float* __restrict__ V, long l
     lim = lim_of(it.t);
     issue_loads(it.t, lim);
   }
-  Pace pace((N + TOK - 1) / TOK, (long long)gridDim.x * kWavesPerWG);
+  Pace pace((N + TOK - 1) / TOK, (long long)gridDim.x * kWavesPerWG, paced<D>(N));
   while (it.valid()) {
     float k[8][CPL], v[8][CPL];
     const bool passes = take(k, v, lim);
@@ -739,8 +748,9 @@ apply32s(const f32x4* __restrict__ Q, long long qbatch, long long qhead, int qro
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   f32x4* Oh = O + at.slice(obatch, ohead);
   f32x4 whole[RG::kPer];
-  RG::load_state(state + bh * parts * (long long)NE, parts, whole);
+  if constexpr (!RG::kLate) RG::load_state(state + bh * parts * (long long)NE, parts, whole);
   rg.prefetch();
+  if constexpr (RG::kLate) RG::load_state(state + bh * parts * (long long)NE, parts, whole);
   bool raw;
   const float* st = rg.stage_state(whole, keep && blockIdx.x == 0 ? keep + bh * NE : nullptr, raw);
   Split8 A[MT][RG::KS];
@@ -748,7 +758,7 @@ apply32s(const f32x4* __restrict__ Q, long long qbatch, long long qhead, int qro
   f32x4 z[MT];
   if constexpr (NORM) rg.load_vec(st, z);
   __syncthreads();   // the staged state is dead
-  Pace pace((N + kTile32 - 1) / kTile32, (long long)gridDim.x * kWavesPerWG);
+  Pace pace((N + kTile32 - 1) / kTile32, (long long)gridDim.x * kWavesPerWG, paced<D>(N));
   int slot = 0, iter = 0;
   while (rg.it.valid()) {
     const long long tile = rg.it.t;
@@ -817,8 +827,9 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   f32x4* dQh = dQ + ldq.slice(bh);
   f32x4 whole[RG::kPer];
-  RG::load_state(state + bh * parts * (long long)NE, parts, whole);
+  if constexpr (!RG::kLate) RG::load_state(state + bh * parts * (long long)NE, parts, whole);
   rg.prefetch();
+  if constexpr (RG::kLate) RG::load_state(state + bh * parts * (long long)NE, parts, whole);
   bool raw;
   const float* st = rg.stage_state(whole, nullptr, raw);
   Split8 A[MT][RG::KS];
@@ -833,7 +844,7 @@ bwd_qs32(const f32x4* __restrict__ Q, Layout lq, const f32x4* __restrict__ G, La
 #pragma unroll
     for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0, 0, 0, 0};
   }
-  Pace pace((N + kTile32 - 1) / kTile32, (long long)gridDim.x * kWavesPerWG);
+  Pace pace((N + kTile32 - 1) / kTile32, (long long)gridDim.x * kWavesPerWG, paced<D>(N));
   int slot = 0, iter = 0;
   while (rg.it.valid()) {
     const long long tile = rg.it.t;
@@ -979,8 +990,9 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
   RG rg(src, rs, N, tiles_per_block, blockIdx.x, gridDim.x, smem);
   f32x4 *dKh = dK + ldkv.slice(bh), *dVh = dV + ldkv.slice(bh);
   f32x4 whole[RG::kPer];
-  RG::load_state(state + bh * parts * (long long)NE, parts, whole);
+  if constexpr (!RG::kLate) RG::load_state(state + bh * parts * (long long)NE, parts, whole);
   rg.prefetch();
+  if constexpr (RG::kLate) RG::load_state(state + bh * parts * (long long)NE, parts, whole);
   bool raw;
   const float* st = rg.stage_state(whole, nullptr, raw);
   Split8 A[MT][RG::KS], At[MT][RG::KS];
@@ -989,7 +1001,7 @@ bwd_kv32(const f32x4* __restrict__ K, const f32x4* __restrict__ V, Layout lkv, f
   f32x4 dz[MT];
   rg.load_vec(st, dz);
   __syncthreads();                          // the staged state is dead
-  Pace pace((N + kTile32 - 1) / kTile32, (long long)gridDim.x * kWavesPerWG);
+  Pace pace((N + kTile32 - 1) / kTile32, (long long)gridDim.x * kWavesPerWG, paced<D>(N));
   int slot = 0, iter = 0;
   while (rg.it.valid()) {
     const long long tile = rg.it.t;

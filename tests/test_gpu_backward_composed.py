@@ -146,6 +146,20 @@ def test_fp32_backward_other_feature_maps_and_unnormalized(fm, normalize):
     _check(outs, q, k, v, g, fm, 1e-6, normalize, f"fp32 bwd fm={fm} norm={normalize}", "f32")
 
 
+# narrow heads: a wave's one tile and several, one partial state, a few and the finished state
+@pytest.mark.parametrize("d", [8, 16, 24])
+@pytest.mark.parametrize("B,H,N", [(1, 1, 1), (12, 8, 300), (2, 3, 1100), (1, 1, 20011)])
+def test_fp32_backward_of_narrow_heads(B, H, N, d):
+    print(f"fp32 bwd, narrow, B={B} H={H} N={N} d={d}", flush=True)
+    q, k, v = wl.make_qkv(B, H, N, d, "f32", idx=97, device="cpu")
+    g = wl.draw((B, H, N, d), wl.BASE_SEED + 97777, "f32", "cpu")
+    st = torch.full((B, H, d * d + d), float("nan"), dtype=torch.float32, device="cuda")
+    fws = torch.empty(lf.linfusion_attn_workspace_bytes(B, H, N, d, lf.DTYPE_F32), dtype=torch.uint8, device="cuda")
+    lf.linfusion_attn_state(k.cuda(), v.cuda(), st, 0, fws)
+    for state in (None, st):
+        _check(_run(q, k, v, g, state=state), q, k, v, g, 0, 1e-6, True, f"fp32 bwd, narrow, N={N} d={d}", "f32")
+
+
 def test_fp32_backward_token_major_views_and_saved_state():
     B, H, N, d = 2, 4, 300, 40
     q, k, v = wl.make_qkv(B, H, N, d, "f32", idx=96, device="cpu")
