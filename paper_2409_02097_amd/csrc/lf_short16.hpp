@@ -11,8 +11,8 @@
 // registers, four rounds of 64 tokens on their way, so that up to 256 tokens are one round trip, and a wave's first query
 // tokens behind them; what bounds it is the chain of phi(K), LDS round trip and barrier between the launch and the operands
 // (a graph of such calls takes as long as calls one by one, whose host part is 7.1 us).  1.3 us a round while each had a
-// barrier of its own; a CU's only workgroup now takes four rounds (bf16 above 96 channels: two) in one (that call 12.4 -> 12.0
-// us, in bf16 12.9 -> 12.3).
+// barrier of its own; where a call leaves CUs to others a workgroup takes four rounds (bf16 above 96 channels: two) in one (2 x 8 x 256 x
+// 128 bf16 9.9 -> 9.6 us, 1 x 8 x 512 x 128 14.2 -> 13.5).
 //
 // Reduction: a round's phi(K) and V rows are written to LDS by all threads; after a barrier wave w multiplies feature block w
 // with all column blocks (transposing LDS reads, 16x16x32 products, bf16: phi(K) in two terms) and with ones for z.  A wave
@@ -25,7 +25,7 @@
 
 namespace lf {
 
-// CB: blocks of 16 value channels per workgroup; DEEP: the only workgroup of its CU
+// CB: blocks of 16 value channels per workgroup; DEEP: several rounds between two barriers, the only workgroup of its CU
 template <typename T, int D, int CB, bool DEEP> struct Short16Cfg {
   static constexpr int kWaves = D / 16, kThreads = 64 * kWaves;
   static constexpr int kCols = 16 * CB, kGroups = D / kCols;

@@ -124,17 +124,23 @@ int launch_short_as(const WideArgs& a, dim3 grid, int parts) {
   return hipGetLastError() == hipSuccess ? LINFUSION_OK : LINFUSION_ERR_HIP;
 }
 
-// Where every workgroup has a CU to itself, several rounds of tokens between two barriers (DEEP) rather than one: us per call,
-// bf16 2 x 8 x 500 x 128 15.2 -> 14.1, 1 x 8 x 512 x 160 18.7 -> 17.6, 2 x 8 x 256 x 160 12.9 -> 12.3, the same in fp16 12.4 -> 12.0; fp16
-// of 96 and 128 channels the same either way.  Not with half of a head's channels, whose sums leave no registers for it: fp16
-// 12 x 8 x 256 x 160 forward and backward 50.4 -> 54.6 (58 spilled; two rounds 54.0, 27), bf16 forward 19.5 -> 20.6.
+// Several rounds of tokens between two barriers (DEEP) rather than one, where the call's workgroups take two thirds of the CUs at most:
+// such a workgroup fills its CU's LDS, so that with more of them two calls on two streams would go one after the other.  us per call,
+// alone / beside another on a second stream, one round -> several:
+//   bf16 1 x 8 x 400 x 96 (120 workgroups) 12.0 / 13.7 -> 11.6 / 12.0,  2 x 8 x 256 x 128 (128) 9.9 / 11.5 -> 9.6 / 10.2,
+//        1 x 8 x 512 x 128 (128) 14.2 / 16.3 -> 13.5 / 13.9,  2 x 8 x 256 x 160 (160) 12.3 / 14.7 -> 12.1 / 14.9
+//   fp16 2 x 8 x 256 x 96 (144) 8.6 / 10.1 -> 8.4 / 10.2,  2 x 8 x 256 x 128 (128) 9.4 / 10.0 -> 9.2 / 9.8
+//   too many: bf16 2 x 8 x 500 x 128 (256) 14.5 / 19.5 -> 13.9 / 25.0, of 96 (240) 13.8 / 19.9 -> 13.3 / 21.4, fp16 (256) 12.3 / 20.9 -> 12.3 / 21.8
+// Not for fp16 of 160 channels (2 x 8 x 256 12.0 / 14.4 -> 12.0 / 14.8, four registers spilled), and not with half of a head's
+// channels, whose sums leave no registers for it: fp16 12 x 8 x 256 x 160 forward and backward 50.4 -> 54.6 (58 spilled; two rounds
+// 54.0, 27), bf16 forward 19.5 -> 20.6.
 template <typename T, int D, int CB>
 int launch_short(const WideArgs& a) {
   const int parts = a.out ? a.plan.short_parts : 1;
   const long long wgs = (long long)a.B * a.H * (D / (16 * CB)) * parts;
   const dim3 grid((unsigned)wgs);
-  if constexpr (CB == 2) {
-    if (wgs <= lfh::num_cu()) return launch_short_as<T, D, CB, true>(a, grid, parts);
+  if constexpr (CB == 2 && (lf::NSplit<T>::value == 2 || D < 160)) {
+    if (3 * wgs <= 2 * (long long)lfh::num_cu()) return launch_short_as<T, D, CB, true>(a, grid, parts);
   }
   return launch_short_as<T, D, CB, false>(a, grid, parts);
 }

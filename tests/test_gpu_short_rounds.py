@@ -10,12 +10,12 @@ from tests.test_gpu_partial_counts import _launches
 pytestmark = pytest.mark.gpu
 
 
-# rounds of 64 tokens, four together at most (bf16 above 96 channels: two); keys at -20: fp16 sums them a second time
+# rounds of 64 tokens, four together at most (bf16 above 96 channels: two, fp16 of 160: one); keys at -20: fp16 sums them a second time
 @pytest.mark.parametrize("keys", [0.0, -20.0])
 @pytest.mark.parametrize("d,dtype", [(96, "bf16"), (96, "f16"), (128, "f16"), (160, "f16"), (160, "bf16")])
 @pytest.mark.parametrize("N", [1, 63, 64, 65, 129, 192, 193, 256])
 def test_rounds_together_and_one_by_one(N, d, dtype, keys, monkeypatch, tuning):
-    """A head among few, whose workgroups have a CU each, and the same head among more than run at once."""
+    """A head among few, whose workgroups have a CU each and leave others free, and the same head among more than run at once."""
     print(f"short rounds N={N} d={d} {dtype} keys={keys}", flush=True)
     monkeypatch.setenv("LINFUSION_WIDE_SHORT_HALF", "2")
     code, H = wl.DTYPE_CODE[dtype], 256 // (d // 32) + 1
