@@ -20,12 +20,16 @@ def test_values_at_the_edges(N, d, groups, layout, flags, monkeypatch, tuning):
     q, k, v = wl.make_qkv(B, H, N, d, dtype, idx=153, device="cpu")
     inf, nan = float("inf"), float("nan")
     k[..., 0], k[..., 1], k[..., 2] = 0.0, -0.0, -inf
-    k[0, 0, 3, 3], k[0, 0, 5, 4] = -nan, nan               # (of head 0 alone)
+    k[0, 0, 3, 3], k[0, 0, 5, 4] = nan, nan                # (of head 0 alone)
     q[:, 1, 0], q[:, 1, 1] = 0.0, -0.0
-    q[:, 1, 2, 0], q[:, 1, 3, d - 1], q[:, 1, 4, 1] = nan, -nan, -inf
+    q[:, 1, 2, 0], q[:, 1, 3, d - 1], q[:, 1, 4, 1] = nan, nan, -inf
+    for t, at in ((k, (0, 0, 3, 3)), (q, (0, 1, 3, d - 1))):   # (an assignment of -nan loses the sign)
+        t.view(torch.int16)[at] = -64
+        assert t.view(torch.int16)[at] < 0 and t[at].isnan()
     place = (lambda t: t.cuda()) if layout == "heads" else \
         (lambda t: t.permute(0, 2, 1, 3).contiguous().cuda().permute(0, 2, 1, 3))
     qd, kd, vd = place(q), place(k), place(v)
+    assert kd[0, 0, 3, 3].view(torch.int16).item() == qd[0, 1, 3, d - 1].view(torch.int16).item() == -64
     out = place(torch.full_like(q, 7.0))
     ws = torch.full((lf.linfusion_attn_workspace_bytes(B, H, N, d, code),), 0xFF, dtype=torch.uint8, device="cuda")
     off = lf.linfusion_attn_workspace_state_offset(B, H, N, d, code)
