@@ -62,6 +62,7 @@ int make_regions(int B, int H, long long N, int d, int dtype, Regions* r) {
 //   5: 513 heads 512 184 / 174, 800 264 / 265                      6: 641 heads 320 145 / 141, 384 160 / 163
 //   8: 1024 heads 320 195 / 188, 384 216 / 219                     16: 2048 heads 192 272 / 258, 256 314 / 316
 int bwd_short_tokens(int d, long long heads) {
+  if (lfh::env_int("LINFUSION_BWDW_SHORT", 1) == 2) return 0;   // never
   int line = 400 + 7 * (heads > 100 ? 100 : (int)heads);
   const long long cus = lfh::num_cu(), rounds = (2 * heads + cus - 1) / cus;
   if (d == 96 && rounds > 2) line = rounds == 3 ? 1024 : rounds == 4 ? 384 : rounds == 5 ? 768 : rounds <= 8 ? 320 : 192;

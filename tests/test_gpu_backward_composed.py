@@ -48,9 +48,15 @@ SHAPES = [
 ]
 
 
+# short streams in one launch ("1": by length), and all by the launches of longer ones ("2")
+by_both_routes = pytest.mark.parametrize("short", ["1", "2"])
+
+
+@by_both_routes
 @pytest.mark.parametrize("B,H,N,d", SHAPES)
-def test_wide_backward_matches_oracle(B, H, N, d):
-    print(f"wide bwd B={B} H={H} N={N} d={d}", flush=True)
+def test_wide_backward_matches_oracle(B, H, N, d, short, monkeypatch, tuning):
+    print(f"wide bwd B={B} H={H} N={N} d={d} short={short}", flush=True)
+    monkeypatch.setenv("LINFUSION_BWDW_SHORT", short)
     q, k, v = wl.make_qkv(B, H, N, d, "f16", idx=90, device="cpu")
     g = wl.draw((B, H, N, d), wl.BASE_SEED + 90777, "f16", "cpu")
     outs = _run(q, k, v, g)
@@ -61,9 +67,12 @@ def test_wide_backward_matches_oracle(B, H, N, d):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), "not run-to-run identical"
 
 
+@by_both_routes
 @pytest.mark.parametrize("fm,normalize", [(1, True), (2, True), (0, False), (1, False)])
-def test_wide_backward_other_feature_maps_and_unnormalized(fm, normalize):
+def test_wide_backward_other_feature_maps_and_unnormalized(fm, normalize, short, monkeypatch, tuning):
     B, H, N, d = 1, 2, 300, 160
+    print(f"wide bwd fm={fm} normalize={normalize} short={short}", flush=True)
+    monkeypatch.setenv("LINFUSION_BWDW_SHORT", short)
     q, k, v = wl.make_qkv(B, H, N, d, "f16", idx=91, device="cpu")
     g = wl.draw((B, H, N, d), wl.BASE_SEED + 91777, "f16", "cpu")
     if fm == 2:
@@ -74,12 +83,14 @@ def test_wide_backward_other_feature_maps_and_unnormalized(fm, normalize):
     _check(outs, q, k, v, g, fm, 1e-6, normalize, f"wide bwd fm={fm} norm={normalize}")
 
 
+@by_both_routes
 @pytest.mark.parametrize("N,d", [(515, 160), (256, 160), (33, 128), (500, 96)])   # three launches; one, all rounds and a few
-def test_wide_backward_with_the_forward_state_handed_in(N, d):
+def test_wide_backward_with_the_forward_state_handed_in(N, d, short, monkeypatch, tuning):
     """A forward call leaves the fp32 state in its workspace; handing it to the backward call skips the first
     reduction and must not change a bit."""
     B, H = 2, 4
-    print(f"wide bwd, state handed in, N={N} d={d}", flush=True)
+    print(f"wide bwd, state handed in, N={N} d={d} short={short}", flush=True)
+    monkeypatch.setenv("LINFUSION_BWDW_SHORT", short)
     q, k, v = wl.make_qkv(B, H, N, d, "f16", idx=92, device="cpu")
     g = wl.draw((B, H, N, d), wl.BASE_SEED + 92777, "f16", "cpu")
     qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
@@ -95,8 +106,11 @@ def test_wide_backward_with_the_forward_state_handed_in(N, d):
     _check(with_state, q, k, v, g, 0, 1e-6, True, "wide bwd with saved state")
 
 
-def test_wide_backward_token_major_views():
+@by_both_routes
+def test_wide_backward_token_major_views(short, monkeypatch, tuning):
     B, H, N, d = 2, 4, 300, 160
+    print(f"wide bwd token-major short={short}", flush=True)
+    monkeypatch.setenv("LINFUSION_BWDW_SHORT", short)
     q, k, v = wl.make_qkv(B, H, N, d, "f16", idx=93, device="cpu")
     g = wl.draw((B, H, N, d), wl.BASE_SEED + 93777, "f16", "cpu")
     tm = lambda t: t.permute(0, 2, 1, 3).contiguous().cuda().permute(0, 2, 1, 3)   # [B, N, H, d] in memory

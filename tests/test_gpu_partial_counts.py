@@ -67,11 +67,14 @@ def test_narrow_partials_summed_by_the_apply_kernel(N, d, dtype, monkeypatch, tu
     assert torch.equal(res[0][1], res[1][1])
 
 
-# partials per head with 256 compute units: 1, 2, 4, 9, 32
+# partials per head with 256 compute units: 1, 2, 4, 9, 32, as the launches of longer streams take them ("2"; by length the first three
+# are one launch)
+@pytest.mark.parametrize("short", ["1", "2"])
 @pytest.mark.parametrize("B,H,N,d", [(1, 8, 64, 160), (12, 8, 256, 160), (1, 4, 100, 96), (1, 8, 777, 160), (1, 8, 2001, 96)])
 @pytest.mark.parametrize("saved", [False, True])
-def test_wide_backward_partials(B, H, N, d, saved):
-    print(f"wide backward partials B={B} H={H} N={N} d={d} saved={saved}", flush=True)
+def test_wide_backward_partials(B, H, N, d, saved, short, monkeypatch, tuning):
+    print(f"wide backward partials B={B} H={H} N={N} d={d} saved={saved} short={short}", flush=True)
+    monkeypatch.setenv("LINFUSION_BWDW_SHORT", short)
     q, k, v = wl.make_qkv(B, H, N, d, "f16", idx=141, device="cpu")
     g = wl.draw((B, H, N, d), wl.BASE_SEED + 14141, "f16", "cpu")
     dev = [t.cuda() for t in (q, k, v, g)]
