@@ -61,7 +61,9 @@ constexpr int apply16_wide_lds_bytes() {
 // waves still multiply the previous one, one barrier per tile.
 // Partial: S as [D][D] row-major then z, fp32; each wave writes its own quarter.
 // What bounds it is issue: conversion, LDS operands and matrix steps of a tile follow one another in each of a SIMD's two
-// waves (in a form of eight waves, loads two to four tiles ahead changed nothing, and leaving the matrix steps out 0.4 of the time).  Quarters need
+// waves (d = 160 in bf16: the vector unit is busy for 43 % of the time, the matrix unit for 32 %; in a form of eight waves, loads two to four
+// tiles ahead changed nothing, and leaving the matrix steps out 0.4 of the time), in long runs at nine tenths of the clock, which the
+// power limit holds down.  Quarters need
 // 15 operand blocks per 50 matrix steps at d = 160 in bf16, and as many in each wave; all rows of every fourth column
 // needed 23 per 60 in two waves and per 40 in the others.  Whole tiles test no rows.  Together, 8 heads x 131072 tokens on
 // MI355X, us (TB/s): bf16 d = 160 228 (2.9) -> 195 (3.4), fp16 161 (4.2) -> 143 (4.7), bf16 d = 96 140 (2.9) -> 111 (3.6);
