@@ -80,7 +80,7 @@ def test_the_line_between_the_launches(heads, N, d, launches):
 # large gradients, and query rows whose largest phi lies far above the row's normalizer: the same inputs to the launches of longer streams
 @pytest.mark.parametrize("short_tokens", ["256", "1"])
 @pytest.mark.parametrize("d", [96, 160])
-@pytest.mark.parametrize("case", ["dout 1e-4", "dout 1e3", "dout 4e3", "dout 4e3, wide queries", "one channel of 300", "one channel of 1000",
+@pytest.mark.parametrize("case", ["dout 1e-4", "dout 1e3", "dout 4e3", "dout 4e3, wide queries", "largest dout 2e4", "one channel of 300", "one channel of 1000",
                                   "one channel of 100 above small ones", "relu, a channel without keys"])
 def test_backward_stays_finite(case, d, short_tokens, monkeypatch, tuning):
     """Query row and g / den' are rounded to fp16 each: neither may leave its range where the gradients do not."""
@@ -93,6 +93,8 @@ def test_backward_stays_finite(case, d, short_tokens, monkeypatch, tuning):
         g *= float(case.split()[1].rstrip(","))
         if "wide" in case:
             q *= 2.0
+    elif case == "largest dout 2e4":
+        g *= 2e4 / g.abs().max().float()
     elif case == "one channel of 300":
         q[:, :, ::7, 3] = 300.0
         g *= 256.0
